@@ -1,20 +1,20 @@
 // Prefill attention on MFMA: Eq. 1-2 over the whole prompt with the causal mask,
 //   out[t] = sum_{j<=t} softmax_{j<=t}(q_t . k_j * scale) v_j      for every prompt position t.
 // One workgroup (4 waves) per (pair, block of 128 queries); a wave owns 32 queries.  The
-// attention-weight matrix is never stored: key tiles of 32 stream through LDS (double-buffered,
-// loaded to registers one tile ahead), and every wave keeps flash-style running (max, sum,
-// output) state for its queries.
+// attention-weight matrix is never stored: key tiles of 32 stream through LDS and every wave keeps
+// flash-style running (max, sum, output) state for its queries.
 //
 // Both contractions are arranged so that a lane owns ONE query throughout:
 //   S^T = K Q^T     A = key tile (LDS, row-major), B = query fragments (registers)
 //                   -> lane l holds, for query l%32, the logits of 16 of the tile's keys;
-//   O^T = V^T P^T   A = value tile transposed in LDS, B = the lane's own 16 weights, packed
+//   O^T = V^T P^T   A = value tile, transposed, B = the lane's own 16 weights, packed
 //                   -> lane l holds, for query l%32, 16 channels of every 32-channel tile.
 // So the row statistics, the rescaling of the running output and the weights that feed the
 // second product never leave the lane (one exchange with the other half-wave for the maximum).
-// The 16 keys a lane holds are keys 8*(i/4) + 4*(l/32) + (i%4) of the tile; the value tile is
-// written to LDS transposed AND with its keys in that order, so a value fragment is one 16-byte
-// LDS read and the contraction pairs every weight with its own key.
+// The 16 keys a lane holds are keys 8*(i/4) + 4*(l/32) + (i%4) of the tile; the value fragments are
+// read in that order, so the contraction pairs every weight with its own key.
+//
+// Two kernels: 16-bit formats (tuned), and fp32 (there for completeness).
 #include "swa_kernels.hpp"
 
 namespace swa {
@@ -31,13 +31,6 @@ struct FlashArgs {
 };
 
 constexpr int kXcds = 8;   // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
-
-// Half-precision element e (0..7) of a 16-byte vector, in the low 16 bits.
-__device__ __forceinline__ uint32_t half_of(const Vec16& v, int e)
-{
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    return (w[e >> 1] >> ((e & 1) * 16)) & 0xffffu;
-}
 
 // x of lane (l % 32) and x of lane (l % 32) + 32, in every lane: v_permlane32_swap exchanges the
 // upper half of one register with the lower half of another, so two copies of x come back as
@@ -64,16 +57,16 @@ __device__ __forceinline__ uint32_t pack2<BF16>(float f0, float f1)
     return f32x2_to_bf16x2_bits(f0, f1);
 }
 
-// 16-bit formats: three workgroups per CU (one wave of each per SIMD), 168 registers per lane,
-// 38 KB of LDS each.  fp32 (32x32x2 MFMA, four issues per 16-byte fragment) is there for
-// completeness, not speed: two waves per SIMD, and at d = 128 a single LDS buffer.
-template <typename T, int D>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Elem<T>::kBytes == 2 ? 3 : 2)))
-swa_flash_prefill_kernel(FlashArgs a)
+// fp32 (32x32x2 MFMA, four issues per 16-byte fragment): two waves per SIMD, tiles double-buffered through
+// registers (at d = 128 a single LDS buffer), the value tile transposed on its way into LDS.
+template <int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+swa_flash_f32_kernel(FlashArgs a)
 {
+    typedef F32 T;
     constexpr int NT = 256;
-    constexpr int EB = Elem<T>::kBytes;     // 2 or 4
-    constexpr int EPV = Elem<T>::kPerVec;   // elements per 16-byte fragment: 8 or 4
+    constexpr int EB = 4;
+    constexpr int EPV = 4;              // elements per 16-byte fragment
     constexpr int NP = 16 / EPV;            // fragments that hold a lane's 16 weights
     constexpr int ROWB = D * EB;
     constexpr int NV = ROWB / 32;       // 16-byte vectors a lane supplies for a 32-row operand
@@ -84,10 +77,9 @@ swa_flash_prefill_kernel(FlashArgs a)
     constexpr int VSTR = BK * EB + 16;  // LDS row (one channel, 32 keys) of the transposed value tile
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
     constexpr int LD = BK * CPR / NT;   // chunks per thread, per tensor and tile
-    constexpr bool kPaired = EB == 2 && LD == 2;
     constexpr float kSlack = 8.f;       // how far (powers of two) a tile maximum may exceed the reference maximum
     constexpr int PF = 3;               // LDS fragment reads in flight ahead of the product that uses them
-    constexpr int NBUF = (EB == 4 && D == 128) ? 1 : 2;   // LDS buffers (64 KB of static LDS at most)
+    constexpr int NBUF = D == 128 ? 1 : 2;   // LDS buffers (64 KB of static LDS at most)
     static_assert(LD >= 1 && BK * CPR % NT == 0, "tile must split evenly over the workgroup");
 
     __shared__ __align__(16) char s_k[NBUF][BK * KSTR];
@@ -134,19 +126,7 @@ swa_flash_prefill_kernel(FlashArgs a)
     const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
     const int my_last = (w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
 
-    // Which tile rows a thread stages.  With two chunks per thread (d = 128) they are an even key
-    // and its successor, which sit next to each other in a lane's key order, so their values are
-    // stored to the transposed tile as one dword; the four (even key) slots of a wave are chosen
-    // so that, with the 16 channel groups, its 64 stores hit 64 different banks.
-    auto tile_key = [&](int x) {
-        if constexpr (kPaired) {
-            const int q = tid / CPR;                 // 0..15
-            const int pr = (q & 1) + 4 * ((q >> 1) & 1) + 2 * ((q >> 2) & 1) + 8 * (q >> 3);
-            return 2 * pr + x;
-        } else {
-            return (tid + x * NT) / CPR;
-        }
-    };
+    auto tile_key = [&](int x) { return (tid + x * NT) / CPR; };     // tile row of the thread's chunk x
     Vec16 gk[LD], gv[LD];
     auto gload = [&](int kt) {
 #pragma unroll
@@ -160,43 +140,17 @@ swa_flash_prefill_kernel(FlashArgs a)
             gv[x] = load16(Vp + off);
         }
     };
-    // key j is element i16 of half-wave hbk's 16 keys: its place (in elements) in a channel's
-    // row.  16-bit: fragment v of half-wave hbk holds i16 = 8v..8v+7; fp32 fragments hold four
-    // consecutive keys, so there the natural order is already the lanes' order.
-    auto key_slot = [](int j) {
-        if constexpr (EB == 4) return j;
-        const int i16 = 4 * (j / 8) + (j % 4);
-        const int hbk = (j / 4) % 2;
-        return ((i16 / 8) * 2 + hbk) * 8 + (i16 % 8);
-    };
     auto lstore = [&](int buf) {
         const int cc = tid % CPR;
 #pragma unroll
         for (int x = 0; x < LD; ++x) store16(s_k[buf] + tile_key(x) * KSTR + cc * 16, gk[x]);
-        if constexpr (kPaired) {
-            const int posk = key_slot(tile_key(0));      // even, and key_slot(tile_key(1)) == posk + 1
-            const uint32_t w0[4] = {gv[0].x, gv[0].y, gv[0].z, gv[0].w}, w1[4] = {gv[1].x, gv[1].y, gv[1].z, gv[1].w};
+        // fp32 fragments hold four consecutive keys: the natural order is the lanes' order
 #pragma unroll
-            for (int e = 0; e < 8; ++e)      // channel e of the even key below, of its successor above: one byte permute
-                *reinterpret_cast<uint32_t*>(s_vt[buf] + vt_row(cc * 8 + e) + posk * 2) =
-                    __builtin_amdgcn_perm(w1[e >> 1], w0[e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
-        } else if constexpr (EB == 2) {
+        for (int x = 0; x < LD; ++x) {
+            const uint32_t w[4] = {gv[x].x, gv[x].y, gv[x].z, gv[x].w};
 #pragma unroll
-            for (int x = 0; x < LD; ++x) {
-                const int posk = key_slot(tile_key(x));
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    *reinterpret_cast<uint16_t*>(s_vt[buf] + vt_row(cc * 8 + e) + posk * 2) = (uint16_t)half_of(gv[x], e);
-            }
-        } else {
-#pragma unroll
-            for (int x = 0; x < LD; ++x) {
-                const int posk = key_slot(tile_key(x));
-                const uint32_t w[4] = {gv[x].x, gv[x].y, gv[x].z, gv[x].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    *reinterpret_cast<uint32_t*>(s_vt[buf] + vt_row(cc * 4 + e) + posk * 4) = w[e];
-            }
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<uint32_t*>(s_vt[buf] + vt_row(cc * 4 + e) + tile_key(x) * 4) = w[e];
         }
     };
 
@@ -307,18 +261,296 @@ swa_flash_prefill_kernel(FlashArgs a)
             for (int g = 0; g < 4; ++g) {
                 // channels 32 ct + 8 g + 4 hb + 0..3 of query t
                 char* dst = Op + (int64_t)t * ROWB + (32 * ct + 8 * g + 4 * hb) * EB;
-                if constexpr (EB == 4) {
-                    float f[4];
+                float f[4];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) f[r] = o[ct][4 * g + r] * inv;
-                    store16(dst, pack<F32>(f));
-                } else {
-                    uint32_t w[2];
+                for (int r = 0; r < 4; ++r) f[r] = o[ct][4 * g + r] * inv;
+                store16(dst, pack<F32>(f));
+            }
+        }
+    }
+}
+
+// Two transposing LDS reads as one 16-byte fragment.  ds_read_b64_tr_b16, within 16 lanes: lane j supplies the
+// address of row j/4, columns 4 (j%4) .. +3 of a 4x16 block and receives column j of its four rows.
+typedef short short4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Vec16 lds_read_tr(const char* lo, const char* hi)
+{
+    typedef __attribute__((address_space(3))) short4_t* ptr_t;
+    const uint2 x = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ptr_t)lo));
+    const uint2 y = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ptr_t)hi));
+    return Vec16{x.x, x.y, y.x, y.y};
+}
+
+// One 16-byte load per lane straight to LDS: lane l's chunk lands at dst + 16 l.  off is per lane, the rest
+// uniform.  No register receives anything, so nothing has to be kept alive while it is in flight; the caller counts
+// it (vmcnt) before the barrier that publishes the tile.  (With the compiler's builtin, every third tile waited for
+// all loads: it cannot tell three LDS buffers apart around a loop.)
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t dst)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const char* p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
+// 16-bit formats.  Bound: the matrix cores at the clock the power limit leaves them (1.65-1.8 GHz under this
+// kernel; busy 60 % of the cycles), next to as many clocks of vector work for the softmax.  What it took
+// there, on 1792 pairs of 4096 rows, bf16, d = 128 (before: 8.3-8.4 ms, busy 51 %):
+//   - Key and value tiles go from L2 straight to LDS (global_load_lds, 16 bytes per lane), with no registers in
+//     between and no LDS store instructions.  Such a load writes 64 consecutive 16-byte chunks, so rows cannot
+//     be padded; instead chunk c of row r holds the row's chunk c ^ swizzle(r), chosen by the lane's GLOBAL
+//     address, and the readers apply the same permutation.  The value tile stays row-major:
+//     ds_read_b64_tr_b16 hands a lane four consecutive keys of its channel, half of the fragment the
+//     second product wants.  8.0 ms.
+//   - Three buffers, two tiles ahead: 7.5 ms.
+//   - The loads of a tile are issued between the products of another instead of all at once: 7.1 ms.
+// Three waves per SIMD (168 registers, 48 KB of LDS per workgroup) at d = 128, four at d = 64.
+template <typename T, int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 3)))
+swa_flash16_kernel(FlashArgs a)
+{
+    constexpr int NW = 4;
+    constexpr int ROWB = D * 2;
+    constexpr int NV = ROWB / 32;       // 16-byte fragments a lane supplies for a 32-row operand
+    constexpr int CT = D / 32;          // 32-channel tiles of the output
+    constexpr int BK = 32;              // keys per tile
+    constexpr int BQ = 128;             // queries per workgroup
+    constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
+    constexpr int RPI = kWave / CPR;    // rows that one wave-wide load covers
+    constexpr int LD = BK / RPI / NW;   // such loads per wave, per tensor and tile
+    constexpr int PF = 2;               // LDS fragment reads in flight ahead of the product that uses them
+    constexpr float kSlack = 8.f;       // how far (powers of two) a tile maximum may exceed the reference maximum
+
+    __shared__ __align__(1024) char s_k0[BK * ROWB];
+    __shared__ __align__(1024) char s_k1[BK * ROWB];
+    __shared__ __align__(1024) char s_v0[BK * ROWB];
+    __shared__ __align__(1024) char s_v1[BK * ROWB];
+    __shared__ __align__(1024) char s_k2[BK * ROWB];
+    __shared__ __align__(1024) char s_v2[BK * ROWB];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31;
+    const int hb = lane >> 5;
+    // XCD-aware placement: the query blocks of one pair all read the same K and V, so they go to
+    // the same XCD, next to each other in launch order, and share the pair's rows through that
+    // XCD's L2; the XCDs work on different pairs.  Longest blocks of a pair first.
+    const int xcd = blockIdx.x % kXcds;
+    const int idx = blockIdx.x / kXcds;
+    const int64_t pair = xcd + (int64_t)kXcds * (idx / a.nqb);
+    if (pair >= a.pairs) return;
+    int s = a.cache_len[pair / a.h];
+    s = s > a.cap ? a.cap : s;
+    const int qb = a.nqb - 1 - idx % a.nqb;
+    const int q0 = qb * BQ;
+    if (q0 >= s) return;
+
+    const char* Qp = a.q + pair * (int64_t)a.cap * ROWB;
+    const char* Kp = a.k + pair * (int64_t)a.cap * ROWB;
+    const char* Vp = a.v + pair * (int64_t)a.cap * ROWB;
+    char* Op = a.out + pair * (int64_t)a.cap * ROWB;
+
+    const int t = q0 + wave * 32 + l32;          // this lane's query position
+    const int tq = t < s ? t : s - 1;            // lanes past the prompt shadow the last query
+
+    const int q_hi = (q0 + BQ < s ? q0 + BQ : s) - 1;    // last query of the workgroup
+    const int nkt = q_hi / BK + 1;                        // key tiles 0..nkt-1 cover keys 0..q_hi
+    const int w_lo = q0 + wave * 32;
+    const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
+    const int my_last = (w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
+
+    // Load x of this wave covers tile rows (wave * LD + x) * RPI + lane / CPR; the lane's chunk of the LDS
+    // row is lane % CPR.  The LDS serves 256 bytes a clock: 16 lanes of a fragment read (16 neighbouring rows
+    // of the key tile), 32 lanes of a transposing read (4 rows, 64 bytes of each).  The swizzles put what
+    // one clock serves on different banks (a row of 128 channels is as long as the banks are wide, of 64
+    // channels half as long); with only 8 rows told apart the reads measured half as fast.
+    auto swzK = [](int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); };
+    auto swzV = [](int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); };
+    uint32_t offK[LD], offV[LD];
+    auto offsets = [&](int last) {     // rows past tile row `last` re-read that one (finite values, masked later)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // computed where it is needed (twice), not kept in registers around the loop
+        const int ldr = ln / CPR, ldc = ln % CPR;
 #pragma unroll
-                    for (int r = 0; r < 2; ++r)
-                        w[r] = pack2<T>(o[ct][4 * g + 2 * r] * inv, o[ct][4 * g + 2 * r + 1] * inv);
-                    *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
-                }
+        for (int x = 0; x < LD; ++x) {
+            const int j = (wave * LD + x) * RPI + ldr;
+            const int r = j < last ? j : last;
+            offK[x] = (uint32_t)r * ROWB + (uint32_t)((ldc ^ swzK(j)) * 16);
+            offV[x] = (uint32_t)r * ROWB + (uint32_t)((ldc ^ swzV(j)) * 16);
+        }
+    };
+    // Load x = 0 .. 2 LD - 1 of the staging of tile kt (uniform base; cap <= SWA_MAX_CAP: below 8 MiB).  Before the
+    // prompt's last tile, which no full one follows, edge() aims the lanes at rows that exist.
+    auto edge = [&](int kt) {
+        if (kt * BK + BK > s) offsets(s - 1 - kt * BK);
+    };
+    auto load = [&](int x, int kt, char* dk, char* dv) {
+        const uint32_t at = (uint32_t)kt * (BK * ROWB);
+        if (x < LD) load_to_lds(Kp + at, offK[x], lds_address(dk) + (wave * LD + x) * 1024);
+        else load_to_lds(Vp + at, offV[x - LD], lds_address(dv) + (wave * LD + x - LD) * 1024);
+    };
+    auto stage = [&](int kt, char* dk, char* dv) {
+        edge(kt);
+#pragma unroll
+        for (int x = 0; x < 2 * LD; ++x) load(x, kt, dk, dv);
+    };
+    offsets(BK);
+
+    stage(0, s_k0, s_v0);
+    Vec16 qv[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) qv[v] = load16(Qp + (int64_t)tq * ROWB + v * 32 + hb * 16);
+
+    // Fragment addresses.  Key fragment v: row l32, chunk 2v + hb.  Value fragment (ct, v): keys
+    // 16v + 4hb + 0..3 and 16v + 8 + 4hb + 0..3 of channel 32 ct + l32, one transposing read each: within
+    // 16 lanes, lane j supplies the address of key j/4, channels 4 (j%4) .. +3, and receives channel j.
+    const uint32_t ka = (uint32_t)(l32 * ROWB + ((hb ^ swzK(l32)) << 4));
+    const int j16 = lane & 15;
+    const uint32_t va = (uint32_t)((4 * hb + (j16 >> 2)) * ROWB +
+                                   (((2 * ((lane >> 4) & 1) + ((j16 & 3) >> 1)) ^ swzV(j16 >> 2)) << 4) + (j16 & 1) * 8);
+
+    // The query fragments are waited for here, where the compiler sees it: it would otherwise wait for them at
+    // their first use in every round of the loop, and with them for the tiles requested since.
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+    stage(nkt > 1 ? 1 : 0, s_k1, s_v1);
+
+    float16_t o[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
+    float m = -INFINITY, l = 0.f;
+
+    auto compute = [&](int kt, const char* sk, const char* sv, int st, char* nk, char* nv) {
+        float16_t c;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] = 0.f;
+        // key fragments are read from LDS PF products ahead of their use, in this order
+        auto kfrag = [&](int v) { return load16(sk + (ka ^ (v << 5))); };
+        Vec16 kf[NV];
+#pragma unroll
+        for (int v = 0; v < PF && v < NV; ++v) kf[v] = kfrag(v);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (v + PF < NV) kf[v + PF] = kfrag(v + PF);
+            __builtin_amdgcn_sched_barrier(0);
+            c = Mfma<T>::run(kf[v], qv[v], c);   // C[key][query]
+            __builtin_amdgcn_sched_barrier(0);
+            // the loads of a later tile are issued between the products, which hide the time they wait to be
+            // accepted: the four waves' sixteen 1 KiB loads together keep the CU's 64-byte path busy for 256 clocks
+            if (v & 1) load(v >> 1, st, nk, nv);
+        }
+        // only the tiles that reach the wave's diagonal need the causal mask
+        if (kt * BK + BK - 1 > w_lo) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int key = kt * BK + 8 * (i / 4) + 4 * hb + (i % 4);
+                c[i] = (key <= tq) ? c[i] : -INFINITY;
+            }
+        }
+        float mx = c[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
+        float mx_lo, mx_hi;
+        both_halves(mx, mx_lo, mx_hi);
+        mx = fmaxf(mx_lo, mx_hi) * a.scale_log2e;     // scale > 0: max commutes
+        // tile 0 holds key 0, visible to every query, so the reference maximum is finite from
+        // the first tile on.  The reference only has to bound the exponents, not equal the true
+        // maximum (out = o / l whatever it is): it follows the tile maximum only when that
+        // exceeds it by more than kSlack powers of two, so the weights stay below 2^kSlack and
+        // the running output is rescaled a few times per query instead of at every new maximum.
+        if (__any(mx > m + kSlack)) {
+            const float m_new = (mx > m + kSlack) ? mx : m;
+            const float alpha = __builtin_amdgcn_exp2f(m - m_new);     // 0 on the first tile
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[ct][i] *= alpha;
+        }
+        float p[16];
+        float ps = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(c[i], a.scale_log2e, -m));   // 0 for masked keys
+            ps += p[i];
+        }
+        l += ps;
+        Vec16 pv[2];
+        pv[0] = pack<T>(p);
+        pv[1] = pack<T>(p + 8);
+        // value fragments likewise; product f works on channel tile f % CT with weight fragment f / CT, so that
+        // consecutive products accumulate into different tiles
+        auto vfrag = [&](int f) {
+            const int ct = f % CT, v = f / CT;
+            const char* at = sv + ((va ^ (ct << 6)) + v * 16 * ROWB);
+            return lds_read_tr(at, at + 8 * ROWB);
+        };
+        Vec16 vf[2 * CT];
+#pragma unroll
+        for (int f = 0; f < PF && f < 2 * CT; ++f) vf[f] = vfrag(f);
+#pragma unroll
+        for (int f = 0; f < 2 * CT; ++f) {
+            if (f + PF < 2 * CT) vf[f + PF] = vfrag(f + PF);
+            __builtin_amdgcn_sched_barrier(0);
+            o[f % CT] = Mfma<T>::run(vf[f], pv[f / CT], o[f % CT]);   // C[channel][query]
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // Tile kt is read while kt+1 and kt+2 are on their way (three buffers).  Loads return in order, so
+    // "all but the newest tile's" is a count.  Every read of the buffer that is about to be refilled has
+    // returned when its wave arrives at the barrier.
+    auto ready = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0070 | (2 * LD));      // vmcnt(2 LD) lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    auto tile = [&](int kt, const char* sk, const char* sv, char* nk, char* nv) {
+        const int st = kt + 2 < nkt ? kt + 2 : nkt - 1;     // past the last tile: that one again, never read
+        ready();
+        edge(st);
+        compute(kt, sk, sv, st, nk, nv);
+    };
+    int kt = 0;
+    for (; kt + 2 <= my_last; kt += 3) {
+        tile(kt, s_k0, s_v0, s_k2, s_v2);
+        tile(kt + 1, s_k1, s_v1, s_k0, s_v0);
+        tile(kt + 2, s_k2, s_v2, s_k1, s_v1);
+    }
+    if (kt <= my_last) {
+        tile(kt, s_k0, s_v0, s_k2, s_v2);
+        if (kt + 1 <= my_last) tile(kt + 1, s_k1, s_v1, s_k0, s_v0);
+    }
+    // the tiles behind this wave's last query: it still takes its part in staging them for the others
+    for (kt = my_last + 1; kt < nkt; ++kt) {
+        const int st = kt + 2 < nkt ? kt + 2 : nkt - 1;
+        const int buf = kt % 3;
+        ready();
+        edge(st);
+        stage(st, buf == 0 ? s_k2 : (buf == 1 ? s_k0 : s_k1), buf == 0 ? s_v2 : (buf == 1 ? s_v0 : s_v1));
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);                     // vmcnt(0) lgkmcnt(0): nothing stays in flight
+
+    float l_lo, l_hi;
+    both_halves(l, l_lo, l_hi);
+    l = l_lo + l_hi;
+    if (t < s) {
+        const float inv = 1.f / l;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                // channels 32 ct + 8 g + 4 hb + 0..3 of query t
+                uint32_t w[2];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) w[r] = pack2<T>(o[ct][4 * g + 2 * r] * inv, o[ct][4 * g + 2 * r + 1] * inv);
+                *reinterpret_cast<uint2*>(Op + (int64_t)t * ROWB + (32 * ct + 8 * g + 4 * hb) * 2) = make_uint2(w[0], w[1]);
             }
         }
     }
@@ -344,14 +576,14 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     if (wgs > 0x7fffffffLL) return SWA_ERR_BAD_SHAPE;
     const dim3 grid((unsigned)wgs);
     if (p.dtype == SWA_F16) {
-        if (p.d == 64) hipLaunchKernelGGL((swa_flash_prefill_kernel<F16, 64>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((swa_flash_prefill_kernel<F16, 128>), grid, dim3(256), 0, stream, a);
+        if (p.d == 64) hipLaunchKernelGGL((swa_flash16_kernel<F16, 64>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((swa_flash16_kernel<F16, 128>), grid, dim3(256), 0, stream, a);
     } else if (p.dtype == SWA_BF16) {
-        if (p.d == 64) hipLaunchKernelGGL((swa_flash_prefill_kernel<BF16, 64>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((swa_flash_prefill_kernel<BF16, 128>), grid, dim3(256), 0, stream, a);
+        if (p.d == 64) hipLaunchKernelGGL((swa_flash16_kernel<BF16, 64>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((swa_flash16_kernel<BF16, 128>), grid, dim3(256), 0, stream, a);
     } else {
-        if (p.d == 64) hipLaunchKernelGGL((swa_flash_prefill_kernel<F32, 64>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((swa_flash_prefill_kernel<F32, 128>), grid, dim3(256), 0, stream, a);
+        if (p.d == 64) hipLaunchKernelGGL(swa_flash_f32_kernel<64>, grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL(swa_flash_f32_kernel<128>, grid, dim3(256), 0, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }

@@ -1,0 +1,39 @@
+"""Prefill attention in the 16-bit formats at every number of key tiles around the rotation of its three LDS buffers,
+and at lengths around the ends of tiles and query blocks, against plain fp64 attention."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+LENS = sorted({max(1, 32 * n + e) for n in range(0, 11) for e in (-1, 0, 1)} | {255, 257, 385})
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_every_tile_count(dtype, d):
+    from paper_2403_17312_amd import binding as B
+    b, h, cap = len(LENS), 3, max(LENS) + 5
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    lens = torch.tensor(LENS, dtype=torch.int32, device="cuda")
+    beyond = torch.arange(cap, device="cuda")[None, None, :, None] >= lens[:, None, None, None]
+    for x in (q, k, v):
+        x.masked_fill_(beyond, float("nan"))          # rows past a prompt must not be used
+    out = torch.full_like(q, 7.0)
+    p = B.make_params(b, h, d, cap, 4, 8000, dtype)
+    ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    B.swa_prefill_attention(p, q, k, v, lens, out, 0, None, ws)
+    # weights are rounded once to the cache type before the second product and the output once (unit roundoff u),
+    # sums are fp32: |delta_c| <= 1.5 u (sum_j p_j |v_jc| + |out_c|) + 1e-5
+    u = 2.0 ** -11 if dtype == torch.float16 else 2.0 ** -8
+    for i, n in enumerate(LENS):
+        Q, K, V = (x[i, :, :n].double() for x in (q, k, v))
+        z = Q @ K.transpose(1, 2).contiguous() / math.sqrt(d)
+        z = z.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), -math.inf)
+        pr = torch.softmax(z, -1)
+        ref, mag = pr @ V, pr @ V.abs()
+        err = (out[i, :, :n].double() - ref).abs()
+        assert bool((err <= 1.5 * u * (mag + ref.abs()) + 1e-5).all()), f"length {n}: off by {err.max().item():.3g}"
+        assert bool((out[i, :, n:] == 7.0).all()), f"length {n}: wrote past the prompt"
