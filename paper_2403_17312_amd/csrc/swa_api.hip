@@ -265,7 +265,7 @@ int swa_prefill_scores(const swa_params* params, const void* q_tail, int32_t R, 
     if (!q_tail || !k_cache || !cache_len || !score) return SWA_ERR_NULL;
     if (R < 1 || R > SWA_MAX_PREFILL_ROWS) return SWA_ERR_BAD_SHAPE;
     if (!swa::aligned16(q_tail) || !swa::aligned16(k_cache)) return SWA_ERR_ALIGNMENT;
-    return swa::launch_prefill(*params, swa::effective_scale(params), q_tail, R, k_cache, cache_len, score, nullptr, false,
+    return swa::launch_prefill(*params, swa::effective_scale(params), q_tail, R, k_cache, cache_len, score, nullptr, false, false,
                                static_cast<hipStream_t>(stream));
 }
 
@@ -279,7 +279,7 @@ int swa_prefill_rows(const swa_params* params, const void* q_tail, int32_t R, co
     if (!q_tail || !k_cache || !cache_len || !ring) return SWA_ERR_NULL;
     if (R < 1 || R > SWA_MAX_WINDOW_ROWS) return SWA_ERR_BAD_SHAPE;
     if (!swa::aligned16(q_tail) || !swa::aligned16(k_cache)) return SWA_ERR_ALIGNMENT;
-    return swa::launch_prefill(*params, swa::effective_scale(params), q_tail, R, k_cache, cache_len, nullptr, ring, false,
+    return swa::launch_prefill(*params, swa::effective_scale(params), q_tail, R, k_cache, cache_len, nullptr, ring, false, false,
                                static_cast<hipStream_t>(stream));
 }
 
@@ -327,9 +327,12 @@ int swa_prefill_attention(const swa_params* params, const void* q, const void* k
     if (!swa::aligned16(q) || !swa::aligned16(k_cache) || !swa::aligned16(v_cache) || !swa::aligned16(out))
         return SWA_ERR_ALIGNMENT;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = swa::launch_flash_prefill(*params, swa::effective_scale(params), q, k_cache, v_cache, cache_len, out, st);
+    bool stats_written = false;
+    rc = swa::launch_flash_prefill(*params, swa::effective_scale(params), q, k_cache, v_cache, cache_len, out, R,
+                                   score, stats_written, st);
     if (rc != SWA_OK || R == 0) return rc;
-    return swa::launch_prefill(*params, swa::effective_scale(params), q, R, k_cache, cache_len, score, nullptr, true, st);
+    return swa::launch_prefill(*params, swa::effective_scale(params), q, R, k_cache, cache_len, score, nullptr, true,
+                               stats_written, st);
 }
 
 static int window_common(const swa_params* params, const void* q, const void* k_new, const void* v_new,

@@ -14,7 +14,7 @@
 // The 16 keys a lane holds are keys 8*(i/4) + 4*(l/32) + (i%4) of the tile; the value fragments are
 // read in that order, so the contraction pairs every weight with its own key.
 //
-// Two kernels: 16-bit formats (tuned), and fp32 (there for completeness).
+// Two kernels: one for the 16-bit formats, and one for short prompts and for fp32 (which is there for completeness).
 #include "swa_kernels.hpp"
 
 namespace swa {
@@ -28,9 +28,18 @@ struct FlashArgs {
     int32_t h, cap;
     int32_t pairs, nqb;    // (sequence, head) pairs and query blocks per pair in the grid
     float scale_log2e;
+    float* stat;           // [pairs, cap]: statistics of the last R rows, stat_G copies stat_cols apart, or NULL
+    int32_t R, stat_G, stat_cols;
 };
 
 constexpr int kXcds = 8;   // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
+
+// Half-precision element e (0..7) of a 16-byte vector, in the low 16 bits.
+__device__ __forceinline__ uint32_t half_of(const Vec16& v, int e)
+{
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    return (w[e >> 1] >> ((e & 1) * 16)) & 0xffffu;
+}
 
 // x of lane (l % 32) and x of lane (l % 32) + 32, in every lane: v_permlane32_swap exchanges the
 // upper half of one register with the lower half of another, so two copies of x come back as
@@ -57,16 +66,16 @@ __device__ __forceinline__ uint32_t pack2<BF16>(float f0, float f1)
     return f32x2_to_bf16x2_bits(f0, f1);
 }
 
-// fp32 (32x32x2 MFMA, four issues per 16-byte fragment): two waves per SIMD, tiles double-buffered through
-// registers (at d = 128 a single LDS buffer), the value tile transposed on its way into LDS.
-template <int D>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-swa_flash_f32_kernel(FlashArgs a)
+// Tiles staged through registers, double-buffered, the value tile transposed on its way into LDS: short prompts in
+// the 16-bit formats (three workgroups per CU, 168 registers per lane, 38 KB of LDS each), and fp32.  fp32 (32x32x2 MFMA, four issues per 16-byte fragment) is there for
+// completeness, not speed: two waves per SIMD, and at d = 128 a single LDS buffer.
+template <typename T, int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Elem<T>::kBytes == 2 ? 3 : 2)))
+swa_flash_prefill_kernel(FlashArgs a)
 {
-    typedef F32 T;
     constexpr int NT = 256;
-    constexpr int EB = 4;
-    constexpr int EPV = 4;              // elements per 16-byte fragment
+    constexpr int EB = Elem<T>::kBytes;     // 2 or 4
+    constexpr int EPV = Elem<T>::kPerVec;   // elements per 16-byte fragment: 8 or 4
     constexpr int NP = 16 / EPV;            // fragments that hold a lane's 16 weights
     constexpr int ROWB = D * EB;
     constexpr int NV = ROWB / 32;       // 16-byte vectors a lane supplies for a 32-row operand
@@ -77,9 +86,10 @@ swa_flash_f32_kernel(FlashArgs a)
     constexpr int VSTR = BK * EB + 16;  // LDS row (one channel, 32 keys) of the transposed value tile
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
     constexpr int LD = BK * CPR / NT;   // chunks per thread, per tensor and tile
+    constexpr bool kPaired = EB == 2 && LD == 2;
     constexpr float kSlack = 8.f;       // how far (powers of two) a tile maximum may exceed the reference maximum
     constexpr int PF = 3;               // LDS fragment reads in flight ahead of the product that uses them
-    constexpr int NBUF = D == 128 ? 1 : 2;   // LDS buffers (64 KB of static LDS at most)
+    constexpr int NBUF = (EB == 4 && D == 128) ? 1 : 2;   // LDS buffers (64 KB of static LDS at most)
     static_assert(LD >= 1 && BK * CPR % NT == 0, "tile must split evenly over the workgroup");
 
     __shared__ __align__(16) char s_k[NBUF][BK * KSTR];
@@ -126,7 +136,19 @@ swa_flash_f32_kernel(FlashArgs a)
     const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
     const int my_last = (w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
 
-    auto tile_key = [&](int x) { return (tid + x * NT) / CPR; };     // tile row of the thread's chunk x
+    // Which tile rows a thread stages.  With two chunks per thread (d = 128) they are an even key
+    // and its successor, which sit next to each other in a lane's key order, so their values are
+    // stored to the transposed tile as one dword; the four (even key) slots of a wave are chosen
+    // so that, with the 16 channel groups, its 64 stores hit 64 different banks.
+    auto tile_key = [&](int x) {
+        if constexpr (kPaired) {
+            const int q = tid / CPR;                 // 0..15
+            const int pr = (q & 1) + 4 * ((q >> 1) & 1) + 2 * ((q >> 2) & 1) + 8 * (q >> 3);
+            return 2 * pr + x;
+        } else {
+            return (tid + x * NT) / CPR;
+        }
+    };
     Vec16 gk[LD], gv[LD];
     auto gload = [&](int kt) {
 #pragma unroll
@@ -140,17 +162,43 @@ swa_flash_f32_kernel(FlashArgs a)
             gv[x] = load16(Vp + off);
         }
     };
+    // key j is element i16 of half-wave hbk's 16 keys: its place (in elements) in a channel's
+    // row.  16-bit: fragment v of half-wave hbk holds i16 = 8v..8v+7; fp32 fragments hold four
+    // consecutive keys, so there the natural order is already the lanes' order.
+    auto key_slot = [](int j) {
+        if constexpr (EB == 4) return j;
+        const int i16 = 4 * (j / 8) + (j % 4);
+        const int hbk = (j / 4) % 2;
+        return ((i16 / 8) * 2 + hbk) * 8 + (i16 % 8);
+    };
     auto lstore = [&](int buf) {
         const int cc = tid % CPR;
 #pragma unroll
         for (int x = 0; x < LD; ++x) store16(s_k[buf] + tile_key(x) * KSTR + cc * 16, gk[x]);
-        // fp32 fragments hold four consecutive keys: the natural order is the lanes' order
+        if constexpr (kPaired) {
+            const int posk = key_slot(tile_key(0));      // even, and key_slot(tile_key(1)) == posk + 1
+            const uint32_t w0[4] = {gv[0].x, gv[0].y, gv[0].z, gv[0].w}, w1[4] = {gv[1].x, gv[1].y, gv[1].z, gv[1].w};
 #pragma unroll
-        for (int x = 0; x < LD; ++x) {
-            const uint32_t w[4] = {gv[x].x, gv[x].y, gv[x].z, gv[x].w};
+            for (int e = 0; e < 8; ++e)      // channel e of the even key below, of its successor above: one byte permute
+                *reinterpret_cast<uint32_t*>(s_vt[buf] + vt_row(cc * 8 + e) + posk * 2) =
+                    __builtin_amdgcn_perm(w1[e >> 1], w0[e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+        } else if constexpr (EB == 2) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                *reinterpret_cast<uint32_t*>(s_vt[buf] + vt_row(cc * 4 + e) + tile_key(x) * 4) = w[e];
+            for (int x = 0; x < LD; ++x) {
+                const int posk = key_slot(tile_key(x));
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    *reinterpret_cast<uint16_t*>(s_vt[buf] + vt_row(cc * 8 + e) + posk * 2) = (uint16_t)half_of(gv[x], e);
+            }
+        } else {
+#pragma unroll
+            for (int x = 0; x < LD; ++x) {
+                const int posk = key_slot(tile_key(x));
+                const uint32_t w[4] = {gv[x].x, gv[x].y, gv[x].z, gv[x].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    *reinterpret_cast<uint32_t*>(s_vt[buf] + vt_row(cc * 4 + e) + posk * 4) = w[e];
+            }
         }
     };
 
@@ -253,6 +301,15 @@ swa_flash_f32_kernel(FlashArgs a)
     float l_lo, l_hi;
     both_halves(l, l_lo, l_hi);
     l = l_lo + l_hi;
+    // the seed's column sums need these rows' statistics: handing them over saves it one of two reads of the keys
+    const int r = t - (s - a.R);
+    if (a.stat && hb == 0 && t < s && r >= 0) {
+        float* St = a.stat + pair * (int64_t)a.cap;
+        for (int g = 0; g < a.stat_G; ++g) {
+            St[g * a.stat_cols + r] = m;
+            St[g * a.stat_cols + a.R + r] = l;
+        }
+    }
     if (t < s) {
         const float inv = 1.f / l;
 #pragma unroll
@@ -261,10 +318,18 @@ swa_flash_f32_kernel(FlashArgs a)
             for (int g = 0; g < 4; ++g) {
                 // channels 32 ct + 8 g + 4 hb + 0..3 of query t
                 char* dst = Op + (int64_t)t * ROWB + (32 * ct + 8 * g + 4 * hb) * EB;
-                float f[4];
+                if constexpr (EB == 4) {
+                    float f[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) f[r] = o[ct][4 * g + r] * inv;
-                store16(dst, pack<F32>(f));
+                    for (int r = 0; r < 4; ++r) f[r] = o[ct][4 * g + r] * inv;
+                    store16(dst, pack<F32>(f));
+                } else {
+                    uint32_t w[2];
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+                        w[r] = pack2<T>(o[ct][4 * g + 2 * r] * inv, o[ct][4 * g + 2 * r + 1] * inv);
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
+                }
             }
         }
     }
@@ -295,7 +360,7 @@ __device__ __forceinline__ uint32_t lds_address(const char* p)
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
-// 16-bit formats.  Bound: the matrix cores at the clock the power limit leaves them (1.65-1.8 GHz under this
+// 16-bit formats, prompts of more than 256 rows.  Bound: the matrix cores at the clock the power limit leaves them (1.65-1.8 GHz under this
 // kernel; busy 60 % of the cycles), next to as many clocks of vector work for the softmax.  What it took
 // there, on 1792 pairs of 4096 rows, bf16, d = 128 (before: 8.3-8.4 ms, busy 51 %):
 //   - Key and value tiles go from L2 straight to LDS (global_load_lds, 16 bytes per lane), with no registers in
@@ -540,6 +605,15 @@ swa_flash16_kernel(FlashArgs a)
     float l_lo, l_hi;
     both_halves(l, l_lo, l_hi);
     l = l_lo + l_hi;
+    // the seed's column sums need these rows' statistics: handing them over saves it one of two reads of the keys
+    const int r = t - (s - a.R);
+    if (a.stat && hb == 0 && t < s && r >= 0) {
+        float* St = a.stat + pair * (int64_t)a.cap;
+        for (int g = 0; g < a.stat_G; ++g) {
+            St[g * a.stat_cols + r] = m;
+            St[g * a.stat_cols + a.R + r] = l;
+        }
+    }
     if (t < s) {
         const float inv = 1.f / l;
 #pragma unroll
@@ -557,7 +631,8 @@ swa_flash16_kernel(FlashArgs a)
 }
 
 int launch_flash_prefill(const swa_params& p, float scale, const void* q, const void* k_cache, const void* v_cache,
-                         const int32_t* cache_len, void* out, hipStream_t stream)
+                         const int32_t* cache_len, void* out, int32_t R, float* score, bool& stats_written,
+                         hipStream_t stream)
 {
     FlashArgs a;
     a.q = static_cast<const char*>(q);
@@ -571,20 +646,28 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     const int bound = (p.len_bound > 0 && p.len_bound < p.cap) ? p.len_bound : p.cap;
     a.pairs = p.b * p.h;
     a.nqb = (bound + 127) / 128;
+    a.R = R;
+    a.stat_G = a.stat_cols = 0;
+    seed_stats_place(a.pairs, p.cap, R, a.stat_G, a.stat_cols);
+    a.stat = a.stat_G > 0 ? score : nullptr;
+    stats_written = a.stat != nullptr;
     const int64_t per_xcd = ((int64_t)a.pairs + kXcds - 1) / kXcds;
     const int64_t wgs = per_xcd * kXcds * a.nqb;
     if (wgs > 0x7fffffffLL) return SWA_ERR_BAD_SHAPE;
     const dim3 grid((unsigned)wgs);
-    if (p.dtype == SWA_F16) {
-        if (p.d == 64) hipLaunchKernelGGL((swa_flash16_kernel<F16, 64>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((swa_flash16_kernel<F16, 128>), grid, dim3(256), 0, stream, a);
-    } else if (p.dtype == SWA_BF16) {
-        if (p.d == 64) hipLaunchKernelGGL((swa_flash16_kernel<BF16, 64>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((swa_flash16_kernel<BF16, 128>), grid, dim3(256), 0, stream, a);
-    } else {
-        if (p.d == 64) hipLaunchKernelGGL(swa_flash_f32_kernel<64>, grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL(swa_flash_f32_kernel<128>, grid, dim3(256), 0, stream, a);
-    }
+    // The direct-to-LDS kernel requests two tiles past the end of every query block, which short prompts feel.  Staged
+    // through registers / direct, d = 128, 256 sequences: 40 heads x 32 rows 72 / 82 us, 32 heads x 60..250 rows 226 /
+    // 238 us, 64 x 32 x 128..512 rows 180 / 174 us (longer ones: up to 1.25 times as fast).
+    const bool direct = p.dtype != SWA_F32 && bound > 256;
+    auto go = [&](auto small, auto large) {
+        if (p.d == 64) hipLaunchKernelGGL(small, grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL(large, grid, dim3(256), 0, stream, a);
+    };
+    if (p.dtype == SWA_F32) go(swa_flash_prefill_kernel<F32, 64>, swa_flash_prefill_kernel<F32, 128>);
+    else if (p.dtype == SWA_F16 && direct) go(swa_flash16_kernel<F16, 64>, swa_flash16_kernel<F16, 128>);
+    else if (p.dtype == SWA_F16) go(swa_flash_prefill_kernel<F16, 64>, swa_flash_prefill_kernel<F16, 128>);
+    else if (direct) go(swa_flash16_kernel<BF16, 64>, swa_flash16_kernel<BF16, 128>);
+    else go(swa_flash_prefill_kernel<BF16, 64>, swa_flash_prefill_kernel<BF16, 128>);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 

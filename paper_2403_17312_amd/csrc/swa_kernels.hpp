@@ -52,7 +52,12 @@ int launch_compact(const swa_params& p, void* k_cache, void* v_cache, float* sco
                    hipStream_t stream);
 
 int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t R, const void* k_cache,
-                   const int32_t* cache_len, float* score, float* rows, bool q_in_place, hipStream_t stream);
+                   const int32_t* cache_len, float* score, float* rows, bool q_in_place, bool stats_ready,
+                   hipStream_t stream);
+
+// Row statistics of the prompt's last R rows, on their way from the attention kernel to the seed's column sums: G copies
+// inside the pair's score row, `cols` floats apart, maximum of row r at [r] and normaliser at [R + r].  G = 0: none.
+void seed_stats_place(int64_t pairs, int cap, int R, int& G, int& cols);
 
 // SWA_SPLIT_ROWS: workgroups per pair for this many pairs and this bound on the cached length
 // (1 = the one-workgroup kernel serves the call), and the launches around the selection launch
@@ -72,8 +77,10 @@ int launch_reload(const swa_params& p, const swa_host_store& st, const int32_t* 
                   int32_t max_req, void* k_cache, void* v_cache, float* score, int32_t* pos,
                   const int32_t* cache_len, int32_t* new_len, void* workspace, hipStream_t stream);
 
-// Causal attention over the whole prompt (Eq. 1-2) on MFMA: out[t] for every prompt position.
+// Causal attention over the whole prompt (Eq. 1-2) on MFMA: out[t] for every prompt position.  Where it can, it leaves
+// the statistics of the last R rows in score (seed_stats_place) and says so.
 int launch_flash_prefill(const swa_params& p, float scale, const void* q, const void* k_cache, const void* v_cache,
-                         const int32_t* cache_len, void* out, hipStream_t stream);
+                         const int32_t* cache_len, void* out, int32_t R, float* score, bool& stats_written,
+                         hipStream_t stream);
 
 }  // namespace swa

@@ -1,9 +1,11 @@
 // Prefill importance seed on MFMA: the local attention sum of Algorithm 1 line 2
 // evaluated at the end of the prompt,
 //   score[j] = sum_{r<R} softmax_causal(Q_tail K^T * scale)[r, j].
-// One workgroup (4 waves) per (sequence, head) pair.  The R x s logit tile is
-// never stored: pass 1 computes every query row's max and normaliser, pass 2
-// recomputes the logits and reduces exp(z - max_r) / sum_r over the rows.
+// One workgroup (4 waves) per (sequence, head) pair, or several, each with a slice of the keys, where there are few
+// pairs.  The R x s logit tile is never stored: pass 1 computes every query row's max and normaliser, pass 2
+// recomputes the logits and reduces exp(z - max_r) / sum_r over the rows.  After the prefill attention kernel, which
+// knows those statistics, pass 2 runs alone: one read of the keys instead of two (64 x 32 pairs of 512..2048 keys,
+// R = 32: 244 -> 163 us; 1792 pairs of 4096 keys, R = 64: 620 -> 400 us).
 //
 // MFMA operand layout used here (32x32 tiles, wave64): lane l supplies row
 // (l % 32) of its operand and the contiguous half-row (l / 32) of the head
@@ -29,7 +31,17 @@ struct PrefillArgs {
     int32_t q_in_place;   // 0: q_tail is [b,h,R,d]; 1: it is the whole prompt's [b,h,cap,d] and the
                           //    R rows are the ones at positions cache_len-R .. cache_len-1
     float scale_log2e;
+    // For the column sums the columns 0..cap are cut into G slices of `cols` (a multiple of 32), one workgroup each.
+    // A slice's first 2 R output columns (score, or row 0 of the ring) bring it the row statistics from the
+    // launch before: maximum of row r at [r], normaliser at [R + r].
+    int32_t G, cols;
+    int32_t row_tiles;    // statistics: workgroups per pair, one for every 32 query rows
 };
+
+// What one launch does.
+constexpr int kSeedWhole = 0;   // both passes, one workgroup per pair
+constexpr int kSeedStats = 1;   // row statistics of one pair, a copy for every slice
+constexpr int kSeedSums = 2;    // column sums of one slice, from the statistics of whole rows
 
 // Merge two (max, sum-of-exp2) pairs of disjoint key sets.
 __device__ __forceinline__ void merge_stats(float& M, float& L, float M2, float L2)
@@ -43,7 +55,7 @@ __device__ __forceinline__ void merge_stats(float& M, float& L, float M2, float 
 }
 
 // WR: also write the R rows themselves (the ring of the strict local attention sum).
-template <typename T, int D, int RT, bool WR>
+template <typename T, int D, int RT, bool WR, int MODE>
 __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
 {
     constexpr int NT = 256;
@@ -62,21 +74,29 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int wave = tid >> 6;
     const int l32 = lane & 31;
     const int hb = lane >> 5;
-    const int64_t pair = blockIdx.x;
+    const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : (MODE == kSeedStats ? blockIdx.x / a.row_tiles : blockIdx.x);
+    const int rt0 = MODE == kSeedStats ? blockIdx.x % a.row_tiles : 0;     // first row tile of this workgroup
+    const int g = MODE == kSeedSums ? blockIdx.x % a.G : 0;
     const int cap = a.cap;
     const int R = a.R;
     int s = a.cache_len[pair / a.h];
     s = s > cap ? cap : s;
+    // the columns this workgroup owns; it reads the key tiles among them
+    const int col0 = MODE == kSeedSums ? g * a.cols : 0;
+    const int col1 = (MODE != kSeedSums || g == a.G - 1) ? cap : col0 + a.cols;
     float* Sp = a.score ? a.score + pair * (int64_t)cap : nullptr;
     float* Rp = WR ? a.rows + pair * (int64_t)R * cap : nullptr;
 
     if (s <= 0) {
+        if (MODE == kSeedStats) return;
         if (Sp)
-            for (int j = tid; j < cap; j += NT) Sp[j] = 0.f;
+            for (int j = col0 + tid; j < col1; j += NT) Sp[j] = 0.f;
         if (Rp)
-            for (int j = tid; j < R * cap; j += NT) Rp[j] = 0.f;
+            for (int r = 0; r < R; ++r)
+                for (int j = col0 + tid; j < col1; j += NT) Rp[(int64_t)r * cap + j] = 0.f;
         return;
     }
+    float* St = MODE == kSeedWhole ? nullptr : (WR ? a.rows + pair * (int64_t)R * cap : a.score + pair * (int64_t)cap) + col0;
 
     const char* Kp = a.k_cache + pair * (int64_t)cap * ROWB;
     const int qbase = a.q_in_place ? s - R : 0;   // row index of query 0 (negative: rows before the prompt)
@@ -91,7 +111,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     Vec16 qv[RT][NV];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-        const int r = rt * 32 + l32;
+        const int r = (rt0 + rt) * 32 + l32;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int qrow = qbase + r > 0 ? qbase + r : 0;          // rows before the prompt are masked below
@@ -100,7 +120,8 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         }
     }
 
-    const int ntiles = (s + 31) / 32;
+    const int tile0 = col0 / 32;
+    const int tile1 = (s < col1 ? s : col1) > col0 ? ((s < col1 ? s : col1) + 31) / 32 : tile0;   // (col0 is a multiple of 32)
     const int t_off = s - R;   // query r sits at position t_off + r and sees keys 0..t_off+r
 
     // Unconditional tile load (rows past the end re-read the last row and are masked later), so
@@ -116,6 +137,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         for (int v = 0; v < NV; ++v) kv[v] = load16(src + v * 32);
     };
 
+    if constexpr (MODE != kSeedSums) {
     // ------------------------------ pass 1: row statistics ------------------------------
     float M[RT], L[RT];
 #pragma unroll
@@ -131,7 +153,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             for (int i = 0; i < 16; ++i) c[i] = 0.f;
 #pragma unroll
             for (int v = 0; v < NV; ++v) c = Mfma<T>::run(kv[v], qv[rt][v], c);   // C[key][query]
-            const int r = rt * 32 + l32;
+            const int r = (rt0 + rt) * 32 + l32;
             const int tmax = (r < R) ? t_off + r : -1;   // last visible key of this lane's query
             float z[16];
             float mx = -INFINITY;
@@ -151,14 +173,27 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             }
         }
     };
-    {
+    if constexpr (MODE == kSeedStats) {
+        // one workgroup has a CU to itself: three tiles per wave in flight while a fourth is reduced
+        constexpr int AHEAD = 4;
+        Vec16 kr[AHEAD][NV];
+#pragma unroll
+        for (int u = 0; u < AHEAD - 1; ++u) load_tile(tile0 + wave + u * NW, kr[u]);
+        for (int tile = tile0 + wave; tile < tile1; tile += AHEAD * NW) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                load_tile(tile + (u + AHEAD - 1) * NW, kr[(u + AHEAD - 1) % AHEAD]);
+                if (tile + u * NW < tile1) stats_tile(tile + u * NW, kr[u]);
+            }
+        }
+    } else {
         Vec16 kA[NV], kB[NV];
-        load_tile(wave, kA);
-        for (int tile = wave; tile < ntiles; tile += 2 * NW) {
+        load_tile(tile0 + wave, kA);
+        for (int tile = tile0 + wave; tile < tile1; tile += 2 * NW) {
             load_tile(tile + NW, kB);
             stats_tile(tile, kA);
             load_tile(tile + 2 * NW, kA);
-            if (tile + NW < ntiles) stats_tile(tile + NW, kB);
+            if (tile + NW < tile1) stats_tile(tile + NW, kB);
         }
     }
 #pragma unroll
@@ -176,11 +211,32 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         float Mt = s_m[0][tid], Lt = s_l[0][tid];
 #pragma unroll
         for (int v = 1; v < NW; ++v) merge_stats(Mt, Lt, s_m[v][tid], s_l[v][tid]);
+        if constexpr (MODE == kSeedStats) {
+            const int r = rt0 * 32 + tid;
+            if (r < R) {
+                for (int g2 = 0; g2 < a.G; ++g2) {
+                    St[g2 * a.cols + r] = Mt;
+                    St[g2 * a.cols + R + r] = Lt;
+                }
+            }
+        }
         const bool ok = Mt > -INFINITY && Lt > 0.f;
         s_M[tid] = ok ? Mt : 0.f;
         s_invL[tid] = ok ? 1.f / Lt : 0.f;
     }
+    if constexpr (MODE == kSeedStats) return;
     __syncthreads();
+    }
+    if constexpr (MODE == kSeedSums) {
+        if (tid < RP) {
+            const bool row = tid < R && t_off + tid >= 0;
+            const float Mt = row ? St[tid] : -INFINITY, Lt = row ? St[R + tid] : 0.f;
+            const bool ok = Mt > -INFINITY && Lt > 0.f;
+            s_M[tid] = ok ? Mt : 0.f;
+            s_invL[tid] = ok ? 1.f / Lt : 0.f;
+        }
+        __syncthreads();          // read by everyone before the slice's columns are written
+    }
 
     // ------------------------------ pass 2: column sums ---------------------------------
     auto colsum_tile = [&](int tile, const Vec16(&kv)[NV]) {
@@ -217,49 +273,94 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     {
         Vec16 kA[NV], kB[NV];
         // the keys read last by pass 1 are read first here
-        const int last = ntiles - 1 - wave;
+        const int last = tile1 - 1 - wave;
         load_tile(last, kA);
-        for (int tile = last; tile >= 0; tile -= 2 * NW) {
+        for (int tile = last; tile >= tile0; tile -= 2 * NW) {
             load_tile(tile - NW, kB);
             colsum_tile(tile, kA);
             load_tile(tile - 2 * NW, kA);
-            if (tile - NW >= 0) colsum_tile(tile - NW, kB);
+            if (tile - NW >= tile0) colsum_tile(tile - NW, kB);
         }
     }
+    const int z0 = s > col0 ? s : col0;
     if (Sp)
-        for (int j = s + tid; j < cap; j += NT) Sp[j] = 0.f;
+        for (int j = z0 + tid; j < col1; j += NT) Sp[j] = 0.f;
     if (Rp)
         for (int r = 0; r < R; ++r)
-            for (int j = s + tid; j < cap; j += NT) Rp[(int64_t)r * cap + j] = 0.f;
+            for (int j = z0 + tid; j < col1; j += NT) Rp[(int64_t)r * cap + j] = 0.f;
 }
 
-template <typename T, int D>
-static int launch_prefill_t(const PrefillArgs& a, int64_t pairs, hipStream_t stream)
+// Slices per pair for the column sums.  One workgroup per pair reads its keys twice at about 30 GB/s, and with few
+// pairs most of the chip waits for it.  The statistics of 32 rows stay with one workgroup (their sum has an order, and the
+// selection that follows can hang on its last bit), which then keeps twice as many loads in flight; the column
+// sums are independent and get one workgroup per CU in all.  32 pairs, R = 64, f16: 8192 keys 138 -> 80 us, 4096: 70 ->
+// 46, 2048: 38 -> 29, 1024: 22 -> 21; 128 pairs of 4096 keys: 76 -> 68; with 256 pairs one launch is as fast.  Every
+// slice holds the row statistics and is at least 256 keys long.
+constexpr int kSeedGrid = 256;
+static int seed_slices(int64_t pairs, int cap, int R, int& cols)
 {
-    const int rt = (a.R + 31) / 32;
-    const dim3 grid((unsigned)pairs), block(256);
-    if (a.rows) {
-        switch (rt) {
-            case 1: hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, true>), grid, block, 0, stream, a); break;
-            case 2: hipLaunchKernelGGL((swa_prefill_kernel<T, D, 2, true>), grid, block, 0, stream, a); break;
-            default: return SWA_ERR_BAD_SHAPE;
-        }
+    const int least = 2 * R > 256 ? 2 * R : 256;
+    int64_t G = (kSeedGrid + pairs - 1) / pairs;
+    if (G > cap / least) G = cap / least;
+    if (G < 1) G = 1;
+    cols = (int)((cap + G - 1) / G + 31) / 32 * 32;
+    while (G > 1 && (G - 1) * cols + 2 * R > cap) --G;         // the last slice has room for the statistics as well
+    return (int)G;
+}
+
+template <typename T, int D, int RT, bool WR>
+static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hipStream_t stream)
+{
+    const int G = seed_slices(pairs, a.cap, a.R, a.cols);
+    a.G = G;
+    const dim3 one((unsigned)pairs), all((unsigned)(pairs * G));
+    if (stats_ready) {
+        hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
+    } else if (G > 1 && a.cap >= 1024) {
+        a.row_tiles = RT;
+        hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
+        if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
+        hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
     } else {
-        switch (rt) {
-            case 1: hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, false>), grid, block, 0, stream, a); break;
-            case 2: hipLaunchKernelGGL((swa_prefill_kernel<T, D, 2, false>), grid, block, 0, stream, a); break;
-            case 3: hipLaunchKernelGGL((swa_prefill_kernel<T, D, 3, false>), grid, block, 0, stream, a); break;
-            case 4: hipLaunchKernelGGL((swa_prefill_kernel<T, D, 4, false>), grid, block, 0, stream, a); break;
-            default: return SWA_ERR_BAD_SHAPE;
-        }
+        hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedWhole>), one, dim3(256), 0, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
+template <typename T, int D>
+static int launch_prefill_t(const PrefillArgs& a, int64_t pairs, bool stats_ready, hipStream_t stream)
+{
+    const int rt = (a.R + 31) / 32;
+    if (a.rows) {
+        switch (rt) {
+            case 1: return launch_prefill_rt<T, D, 1, true>(a, pairs, stats_ready, stream);
+            case 2: return launch_prefill_rt<T, D, 2, true>(a, pairs, stats_ready, stream);
+            default: return SWA_ERR_BAD_SHAPE;
+        }
+    }
+    switch (rt) {
+        case 1: return launch_prefill_rt<T, D, 1, false>(a, pairs, stats_ready, stream);
+        case 2: return launch_prefill_rt<T, D, 2, false>(a, pairs, stats_ready, stream);
+        case 3: return launch_prefill_rt<T, D, 3, false>(a, pairs, stats_ready, stream);
+        case 4: return launch_prefill_rt<T, D, 4, false>(a, pairs, stats_ready, stream);
+        default: return SWA_ERR_BAD_SHAPE;
+    }
+}
+
+// Where swa_prefill_attention leaves the statistics of the prompt's last R rows for the sums: G copies, `cols` apart
+// (G = 0: no room for them, the seed computes its own).
+void seed_stats_place(int64_t pairs, int cap, int R, int& G, int& cols)
+{
+    cols = 0;
+    G = (R > 0 && 2 * R <= cap) ? seed_slices(pairs, cap, R, cols) : 0;
+}
+
 int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t R, const void* k_cache,
-                   const int32_t* cache_len, float* score, float* rows, bool q_in_place, hipStream_t stream)
+                   const int32_t* cache_len, float* score, float* rows, bool q_in_place, bool stats_ready,
+                   hipStream_t stream)
 {
     PrefillArgs a;
+    a.G = a.cols = a.row_tiles = 0;
     a.q_in_place = q_in_place ? 1 : 0;
     a.rows = rows;
     a.q_tail = static_cast<const char*>(q_tail);
@@ -272,11 +373,11 @@ int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t
     a.scale_log2e = scale * 1.44269504088896340736f;
     const int64_t pairs = (int64_t)p.b * p.h;
     if (p.dtype == SWA_F32) {
-        return p.d == 64 ? launch_prefill_t<F32, 64>(a, pairs, stream) : launch_prefill_t<F32, 128>(a, pairs, stream);
+        return p.d == 64 ? launch_prefill_t<F32, 64>(a, pairs, stats_ready, stream) : launch_prefill_t<F32, 128>(a, pairs, stats_ready, stream);
     } else if (p.dtype == SWA_F16) {
-        return p.d == 64 ? launch_prefill_t<F16, 64>(a, pairs, stream) : launch_prefill_t<F16, 128>(a, pairs, stream);
+        return p.d == 64 ? launch_prefill_t<F16, 64>(a, pairs, stats_ready, stream) : launch_prefill_t<F16, 128>(a, pairs, stats_ready, stream);
     } else {
-        return p.d == 64 ? launch_prefill_t<BF16, 64>(a, pairs, stream) : launch_prefill_t<BF16, 128>(a, pairs, stream);
+        return p.d == 64 ? launch_prefill_t<BF16, 64>(a, pairs, stats_ready, stream) : launch_prefill_t<BF16, 128>(a, pairs, stats_ready, stream);
     }
 }
 
