@@ -29,6 +29,20 @@ int ensure_dynamic_lds(const void* kernel, size_t bytes)
     return SWA_OK;
 }
 
+int raise_dynamic_lds(const void* kernel)
+{
+    hipFuncAttributes fa;
+    int dev = 0, lds_max = 0;
+    if (hipFuncGetAttributes(&fa, kernel) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return SWA_ERR_HIP;
+    }
+    const long long room = (long long)lds_max - (long long)fa.sharedSizeBytes;
+    if (room <= 48 * 1024) return SWA_OK;
+    return ensure_dynamic_lds(kernel, (size_t)room);
+}
+
 size_t shared_workspace_offset(const swa_params& p)
 {
     const size_t head = kWsArriveOffset + sizeof(int32_t) * (size_t)p.b;
@@ -227,7 +241,8 @@ int swa_prepare(void)
     void* ptr = nullptr;
     int rc = swa::static_scratch(&ptr);
     if (rc != SWA_OK) return rc;
-    return swa::prepare_decode();
+    rc = swa::prepare_decode();
+    return rc == SWA_OK ? swa::prepare_split() : rc;
 }
 
 int swa_check_status(const swa_params* params, void* workspace, void* stream, int32_t* status_out)

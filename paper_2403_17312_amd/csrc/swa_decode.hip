@@ -37,6 +37,7 @@
 //   * the strict local attention sum (importance = sum of a ring of the last R attention rows,
 //     whose columns follow their tokens through the compaction).
 #include "swa_kernels.hpp"
+#include "swa_select.hpp"
 
 namespace swa {
 
@@ -65,10 +66,7 @@ struct DecodeArgs {
     // sums the new importance over the heads of every sequence; phase 2 selects from that sum
     // (every head of a sequence reaches the same decision) and finishes output and compaction.
     int32_t phase;        // 0 = whole step in one launch; 1, 2 = the two halves of the head-shared
-                          // step; 3 = rows split over workgroups: the logits come from ws_z, and the
-                          // weights go to ws_p for the launches that form the output
-    const float* ws_z;    // [b,h,cap] logits of the split step
-    int32_t* ws_ok;       // [b,h]     split step: set to 1 when the pair's step has run (not skipped)
+                          // step
     float* ws_p;          // [b,h,cap] attention weights of phase 1
     float* ws_snew;       // [b,h,cap] new importance of phase 1
     float* ws_abar;       // [b,h,d]   dense attention output of phase 1
@@ -88,13 +86,6 @@ struct DecodeArgs {
 constexpr int kMaxFix = 8;           // evicted rows the subtractive schedule handles
 constexpr float kMinKeptMass = 0.05f;
 constexpr float kLog2e = 1.44269504088896340736f;
-
-// Monotone map fp32 -> uint32 (larger float <=> larger key).
-__device__ __forceinline__ uint32_t order_key(float f)
-{
-    uint32_t u = f2u(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -135,7 +126,10 @@ swa_decode_kernel(DecodeArgs a)
     // lane and keeps twice as many rows in flight in the gathered pass and in the row moves.
     constexpr bool kWide = NT >= 512;
     constexpr int UV = kWide ? 6 : 4;       // value rows in flight per group (gathered pass)
-    constexpr int SPF = 4;                  // importance values prefetched per thread
+    // Importance values (and positions) prefetched per thread.  They are live through the whole row stream; the 8-bit
+    // cache's lanes have no registers for four (with two its streaming pass does not spill: 2560 pairs of about 206 slots
+    // 35.3 -> 32.5 us a step, caches of 256..1100 slots 3-4 % faster), the others do.
+    constexpr int SPF = kQ8 ? 2 : 4;
 
     extern __shared__ __align__(16) char smem[];
     float* s_p = reinterpret_cast<float*>(smem);                       // logits -> probabilities
@@ -190,7 +184,7 @@ swa_decode_kernel(DecodeArgs a)
     // (Not for the 8-bit cache: its lanes have no registers to spare, and it measured slower.)
     constexpr bool kEarlyStage = !kQ8;
     Vec16 k0[UF], v0[UF];
-    if (kEarlyStage && a.phase != 2 && a.phase != 3) {
+    if (kEarlyStage && a.phase != 2) {
         const char* Kq = a.k_cache + pair * (int64_t)a.cap * ROWB;
         const char* Vq = a.v_cache + pair * (int64_t)a.cap * ROWB;
 #pragma unroll
@@ -269,7 +263,7 @@ swa_decode_kernel(DecodeArgs a)
         const int ncand = m - n_local;
         const int wlo = n - w_eff;                    // unordered layout: the window is pos >= wlo
         const int E = m - keep;                       // evictions of this step
-        const bool fused = (E <= kMaxFix) && (8 * E <= m) && a.phase != 3;
+        const bool fused = (E <= kMaxFix) && (8 * E <= m);
         // first stashed slot (m = nothing stashed: only the streaming schedule fills the stash)
         const int stash_lo = (fc && fused) ? (m > a.stash_rows ? m - a.stash_rows : 0) : m;
 
@@ -407,16 +401,6 @@ swa_decode_kernel(DecodeArgs a)
                 s_redA[wave] = Mg;
                 s_wS[wave] = Sg;
             }
-        } else if (a.phase == 3) {
-            // ---- rows split over workgroups: the logits were formed by the launch before ----
-            const float* Zp = a.ws_z + pair * (int64_t)cap;
-            for (int i = tid; i < m; i += NT) {
-                const float d = Zp[i];
-                s_p[i] = d;
-                Mg = fmaxf(Mg, d);
-            }
-            Mg = wave_max(Mg);
-            if (lane == 0) s_redA[wave] = Mg;
         } else {
             // ---- key-only pass -------------------------------------------------------
             if (fc) new_row_ready();
@@ -524,7 +508,7 @@ swa_decode_kernel(DecodeArgs a)
                     Sp[i] = sc;
                 }
                 if (a.phase == 1) a.ws_snew[pair * (int64_t)cap + i] = sc;
-                if (a.phase == 1 || a.phase == 3) a.ws_p[pair * (int64_t)cap + i] = p;
+                if (a.phase == 1) a.ws_p[pair * (int64_t)cap + i] = p;
                 const uint32_t key = order_key(sc);
                 s_key[i] = key;
                 if (bag ? (pold[k] < wlo) : (i < ncand)) {
@@ -549,7 +533,7 @@ swa_decode_kernel(DecodeArgs a)
                 Sp[i] = sc;
             }
             if (a.phase == 1) a.ws_snew[pair * (int64_t)cap + i] = sc;
-            if (a.phase == 1 || a.phase == 3) a.ws_p[pair * (int64_t)cap + i] = p;
+            if (a.phase == 1) a.ws_p[pair * (int64_t)cap + i] = p;
             const uint32_t key = order_key(sc);
             s_key[i] = key;
             if (bag ? (posi < wlo) : (i < ncand)) {
@@ -924,7 +908,7 @@ swa_decode_kernel(DecodeArgs a)
                 for (int k = 0; k < ec; ++k) t -= s_fix[k * D + e];
                 write_out(e, t / (1.f - pe));
             }
-        } else if (a.phase != 3) {       // (phase 3: the output is formed by the launches that follow)
+        } else {
             // gathered pass over the kept value rows: sum_kept p_i v_i / sum_kept p_i.
             // Unordered layout with many evictions (the step after a prompt): the rows that change
             // slot are moved inside this pass, so that the whole step needs one more memory round
@@ -1165,7 +1149,6 @@ swa_decode_kernel(DecodeArgs a)
             atomicOr(a.status, kStatusCapacityBit);
         } else {
             a.kept_cnt[s] = keep;
-            if (a.phase == 3) a.ws_ok[pair] = 1;
         }
         const int old = atomicAdd(&a.arrive[s], 1);
         if (old == a.h - 1) {
@@ -1234,20 +1217,7 @@ template <typename T, int D, int NT, bool RING>
 static int prepare_one()
 {
     auto kern = swa_decode_kernel<T, D, NT, RING>;
-    hipFuncAttributes fa;
-    if (hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(kern)) != hipSuccess) {
-        (void)hipGetLastError();
-        return SWA_ERR_HIP;
-    }
-    int dev = 0, lds_max = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
-        (void)hipGetLastError();
-        return SWA_ERR_HIP;
-    }
-    const long long room = (long long)lds_max - (long long)fa.sharedSizeBytes;
-    if (room <= 48 * 1024) return SWA_OK;
-    return ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (size_t)room);
+    return raise_dynamic_lds(reinterpret_cast<const void*>(kern));
 }
 
 template <typename T, int D>
@@ -1313,8 +1283,6 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     a.unordered = (a.fuse_compaction && (p.flags & SWA_UNORDERED)) ? 1 : 0;
     const bool shared = a.unordered && (p.flags & SWA_HEAD_SHARED);
     a.phase = 0;
-    a.ws_z = nullptr;
-    a.ws_ok = nullptr;
     a.ws_p = a.ws_snew = a.ws_abar = a.ws_tot = nullptr;
     if (shared) {
         char* base = static_cast<char*>(workspace) + shared_workspace_offset(p);
@@ -1347,28 +1315,11 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
                          : launch_decode_t<BF16, 128>(args, pairs, lds_bytes, nt, stream);
     };
     if (p.flags & SWA_SPLIT_ROWS) {
-        // rows of a pair over G workgroups: logits, then selection (this kernel, phase 3), then the output
+        // rows of a pair over G workgroups
         const int G = split_factor(pairs, bound);
-        if (G > 1) {
-            char* base = static_cast<char*>(workspace) + shared_workspace_offset(p);
-            const size_t slab = (size_t)p.b * p.h * p.cap * sizeof(float);
-            float* ws_z = reinterpret_cast<float*>(base);
-            float* ws_pp = reinterpret_cast<float*>(base + slab);
-            float* ws_part = reinterpret_cast<float*>(base + 2 * slab);
-            int32_t* ws_ok = reinterpret_cast<int32_t*>(base + 2 * slab +
-                                                        (size_t)pairs * kMaxSplit * (p.d + 1) * sizeof(float));
-            int rc = launch_split(p, scale, 1, G, q, k_new, v_new, k_cache, v_cache, cache_len, kept_idx, kept_cnt,
-                                  ws_z, ws_pp, ws_part, ws_ok, out, stream);
-            if (rc != SWA_OK) return rc;
-            a.phase = 3;
-            a.ws_z = ws_z;
-            a.ws_p = ws_pp;
-            a.ws_ok = ws_ok;
-            rc = launch(a);
-            if (rc != SWA_OK) return rc;
-            return launch_split(p, scale, 2, G, q, k_new, v_new, k_cache, v_cache, cache_len, kept_idx, kept_cnt,
-                                ws_z, ws_pp, ws_part, ws_ok, out, stream);
-        }
+        if (G > 1)
+            return launch_split(p, scale, G, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len, seq_len, kept_idx,
+                                kept_cnt, out, probs_dbg, workspace, stream);
     }
     if (!shared) return launch(a);
     a.phase = 1;

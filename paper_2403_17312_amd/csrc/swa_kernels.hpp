@@ -14,6 +14,9 @@ namespace swa {
 // the library keeps besides the address of the static scratch array.
 int ensure_dynamic_lds(const void* kernel, size_t bytes);
 
+// Raises that limit to what the current device allows next to the kernel's static LDS.
+int raise_dynamic_lds(const void* kernel);
+
 // Raises that limit for every instantiation of the decode kernel on the current device.
 int prepare_decode();
 
@@ -60,14 +63,13 @@ int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t
 void seed_stats_place(int64_t pairs, int cap, int R, int& G, int& cols);
 
 // SWA_SPLIT_ROWS: workgroups per pair for this many pairs and this bound on the cached length
-// (1 = the one-workgroup kernel serves the call), and the launches around the selection launch
-// (which = 1: logits of every cached key to ws_z; which = 2: output from ws_p and the kept list).
+// (1 = the one-workgroup kernel serves the call), the launches of the step, and their LDS limits.
 constexpr int kMaxSplit = 16;
 int split_factor(int64_t pairs, int len_bound);
-int launch_split(const swa_params& p, float scale, int which, int G, const void* q, const void* k_new,
-                 const void* v_new, const void* k_cache, const void* v_cache, const int32_t* cache_len,
-                 const int32_t* kept_idx, const int32_t* kept_cnt, float* ws_z, float* ws_p, float* ws_part,
-                 int32_t* ws_ok, void* out, hipStream_t stream);
+int launch_split(const swa_params& p, float scale, int G, const void* q, const void* k_new, const void* v_new, void* k_cache,
+                 void* v_cache, float* score, int32_t* pos, int32_t* cache_len, const int32_t* seq_len, int32_t* kept_idx,
+                 int32_t* kept_cnt, void* out, float* probs_dbg, void* workspace, hipStream_t stream);
+int prepare_split();
 
 // Token-level offload tier (Section V-A, Algorithm 2): evicted rows to the host store, requested rows back.
 int launch_offload(const swa_params& p, const void* k_cache, const void* v_cache, const float* score,

@@ -1,0 +1,49 @@
+"""The split-rows step's own selection launch: kept sets and importance against the one-workgroup kernel bit for bit,
+with many equal keys, budgets at the edges, lengths around the threads' runs, and both forms of the output pass."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d,cap", [(torch.float16, 128, 2200), (torch.float32, 64, 4099), (torch.bfloat16, 64, 16384),
+                                         (torch.float32, 128, 9000)])
+@pytest.mark.parametrize("w,sparsity", [(0, 9999), (7, 0), (64, 5000), (-1, 8000), (3000, 9000)])
+@pytest.mark.parametrize("scores", ["spread", "ties"])
+def test_selection_matches_the_one_workgroup_kernel(dtype, d, cap, w, sparsity, scores):
+    from paper_2403_17312_amd import binding as B
+    lens = [0, 1, 1023, 1024, 2047, cap - 2, cap - 1, cap]            # the last one is full: skipped and reported
+    b, h = len(lens), 3
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, V = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    old = torch.rand((b, h, cap), generator=g, device="cuda")
+    if scores == "ties":
+        old = torch.floor(old * 3)
+        q.zero_()                                                      # equal weights: importance ties everywhere
+    got = []
+    for flags in (0, B.SWA_SPLIT_ROWS):
+        p = B.make_params(b, h, d, cap, w, sparsity, dtype, flags=flags)
+        st = B.DecodeState(p, debug_probs=True)
+        st.K.copy_(K)
+        st.V.copy_(V)
+        st.score.copy_(old)
+        st.cache_len.copy_(torch.tensor(lens, dtype=torch.int32))
+        st.seq_len.copy_(torch.tensor([n + 1 for n in lens], dtype=torch.int32))
+        st.decode_step(q, kn, vn)
+        assert st.check_status() == B.SWA_ERR_CAPACITY
+        got.append(st)
+    one, two = got
+    assert one.cache_len.tolist() == two.cache_len.tolist() and one.kept_cnt.tolist() == two.kept_cnt.tolist()
+    u = {torch.float32: 2.0 ** -20, torch.float16: 2.0 ** -10, torch.bfloat16: 2.0 ** -7}[dtype]
+    for i, n in enumerate(lens[:-1]):
+        k = one.kept_cnt[i].item()
+        assert torch.equal(one.score[i, :, :n + 1], two.score[i, :, :n + 1]), n
+        assert torch.equal(one.probs[i], two.probs[i]), n
+        assert torch.equal(one.kept_idx[i, :, :k], two.kept_idx[i, :, :k]), n
+        for a in ("K", "V", "pos"):
+            assert torch.equal(getattr(one, a)[i, :, :n + 1], getattr(two, a)[i, :, :n + 1]), (n, a)
+        # the same fp32 terms added in another order, rounded once to the output type
+        x, y = one.out[i].double(), two.out[i].double()
+        assert bool(((x - y).abs() <= u * (y.abs() + 1.0)).all()), n
+    assert torch.equal(one.out[-1], two.out[-1]) and torch.equal(two.score[-1], old[-1])
