@@ -130,13 +130,14 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_contiguous():
         raise ValueError("tensors handed to the SWA library must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()          # every pointer argument is declared c_void_p: ctypes converts the integer
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        # the current stream's handle without a Stream object around it (0.3 instead of 1.5 us of every call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(rc: int, what: str) -> None:
