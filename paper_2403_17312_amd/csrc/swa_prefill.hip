@@ -5,7 +5,8 @@
 // pairs.  The R x s logit tile is never stored: pass 1 computes every query row's max and normaliser, pass 2
 // recomputes the logits and reduces exp(z - max_r) / sum_r over the rows.  After the prefill attention kernel, which
 // knows those statistics, pass 2 runs alone: one read of the keys instead of two (64 x 32 pairs of 512..2048 keys,
-// R = 32: 244 -> 163 us; 1792 pairs of 4096 keys, R = 64: 620 -> 400 us).
+// R = 32: 244 -> 163 us; 1792 pairs of 4096 keys, R = 64: 620 -> about 400 us, by the
+// difference of whole calls).
 //
 // MFMA operand layout used here (32x32 tiles, wave64): lane l supplies row
 // (l % 32) of its operand and the contiguous half-row (l / 32) of the head

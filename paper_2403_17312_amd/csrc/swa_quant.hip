@@ -36,7 +36,7 @@ __device__ __forceinline__ float divide_by(float x, float lam, float inv)
 // 64 channels in registers between the two passes (64 of a thread's registers; 64 channels are one 128-byte line of
 // every row, and halving the rows' width lets two workgroups of 1024 rows share a CU, so that one loads while the other
 // stores); rows beyond those are read again.
-// 2560 pairs x 1024 rows x 128 channels, K and V: 0.68 -> 0.45 ms (two reads of the cache and a division
+// 2560 pairs x 1024 rows x 128 channels, K and V: 0.68 -> 0.45 ms by the difference of whole passes (two reads of the cache and a division
 // per element before).
 template <int D, int NT>
 __global__ void __launch_bounds__(NT) swa_quantize_kernel(QuantArgs a)

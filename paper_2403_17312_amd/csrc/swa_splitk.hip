@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(NT) swa_split_logits_kernel(SplitArgs a)
 // importance is requested at once, keys stay in registers between the phases, and 1024 threads share the work.
 // Weights are bit-identical to the one-workgroup kernel's: its 512 threads' sums are added up in its order.
 // 32 pairs x 8192 rows, f16, d = 128: 33 us with the one-workgroup kernel in this place, plus 14 us for the two launches
-// that formed the output; now 25 us with the output (whole step 63 -> 46 us).
+// that formed the output; now about 31 us with the output (whole step 62 -> 47 us).
 template <typename T, int D>
 __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs a)
 {
