@@ -359,7 +359,9 @@ int swa_decode_step_window_q8(const swa_params *params, const void *q, const voi
  * position t < cache_len[s]:
  *   out[t] = sum_{j<=t} softmax_{j<=t}(q[t] . K[j] * scale) V[j], rounded once to dtype;
  * if R > 0, score gets the column sums of the last R rows of that attention-weight matrix
- * (queries q[cache_len-R .. cache_len-1]), exactly as swa_prefill_scores would with those rows.
+ * (queries q[cache_len-R .. cache_len-1]): the sum that swa_prefill_scores forms with those rows, equal to
+ * it up to fp32 rounding and not bit for bit (the rows' maxima and normalisers may come from the attention kernel,
+ * which adds them in another order).  len_bound must hold here: statistics of rows beyond it are never formed.
  * Runs on MFMA (flash-style: the s x s weight matrix is never stored).
  *   q, out [b,h,cap,d] dtype (rows >= cache_len are neither read nor written);
  *   k_cache, v_cache (in); cache_len [b] (in); 0 <= R <= SWA_MAX_PREFILL_ROWS;

@@ -34,6 +34,10 @@ struct FlashArgs {
 
 constexpr int kXcds = 8;   // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
 
+// Where the reference maximum of a row's running sum starts.  Finite, so that keys whose logit is -inf weigh nothing
+// (exp2(-inf - reference) = 0) also when they come before the row's first finite logit.
+constexpr float kNoReference = -3.0e38f;
+
 // Half-precision element e (0..7) of a 16-byte vector, in the low 16 bits.
 __device__ __forceinline__ uint32_t half_of(const Vec16& v, int e)
 {
@@ -207,7 +211,7 @@ swa_flash_prefill_kernel(FlashArgs a)
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
-    float m = -INFINITY, l = 0.f;
+    float m = kNoReference, l = 0.f;
 
     gload(0);
     lstore(0);
@@ -250,11 +254,10 @@ swa_flash_prefill_kernel(FlashArgs a)
             float mx_lo, mx_hi;
             both_halves(mx, mx_lo, mx_hi);
             mx = fmaxf(mx_lo, mx_hi) * a.scale_log2e;     // scale > 0: max commutes
-            // tile 0 holds key 0, visible to every query, so the reference maximum is finite from
-            // the first tile on.  The reference only has to bound the exponents, not equal the true
-            // maximum (out = o / l whatever it is): it follows the tile maximum only when that
-            // exceeds it by more than kSlack powers of two, so the weights stay below 2^kSlack and
-            // the running output is rescaled a few times per query instead of at every new maximum.
+            // The reference only has to bound the exponents, not equal the true maximum (out = o / l
+            // whatever it is): it follows the tile maximum only when that exceeds it by more than kSlack
+            // powers of two, so the weights stay below 2^kSlack and the running output is rescaled
+            // a few times per query instead of at every new maximum.
             const float m_new = (mx > m + kSlack) ? mx : m;
             const float alpha = __builtin_amdgcn_exp2f(m - m_new);     // 0 on the first tile, else mostly 1
             float p[16];
@@ -487,7 +490,7 @@ swa_flash16_kernel(FlashArgs a)
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
-    float m = -INFINITY, l = 0.f;
+    float m = kNoReference, l = 0.f;
 
     auto compute = [&](int kt, const char* sk, const char* sv, int st, char* nk, char* nv) {
         float16_t c;
@@ -522,11 +525,10 @@ swa_flash16_kernel(FlashArgs a)
         float mx_lo, mx_hi;
         both_halves(mx, mx_lo, mx_hi);
         mx = fmaxf(mx_lo, mx_hi) * a.scale_log2e;     // scale > 0: max commutes
-        // tile 0 holds key 0, visible to every query, so the reference maximum is finite from
-        // the first tile on.  The reference only has to bound the exponents, not equal the true
-        // maximum (out = o / l whatever it is): it follows the tile maximum only when that
-        // exceeds it by more than kSlack powers of two, so the weights stay below 2^kSlack and
-        // the running output is rescaled a few times per query instead of at every new maximum.
+        // The reference only has to bound the exponents, not equal the true maximum (out = o / l
+        // whatever it is): it follows the tile maximum only when that exceeds it by more than kSlack
+        // powers of two, so the weights stay below 2^kSlack and the running output is rescaled
+        // a few times per query instead of at every new maximum.
         if (__any(mx > m + kSlack)) {
             const float m_new = (mx > m + kSlack) ? mx : m;
             const float alpha = __builtin_amdgcn_exp2f(m - m_new);     // 0 on the first tile

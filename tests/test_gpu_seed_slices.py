@@ -53,3 +53,36 @@ def test_slices(dtype, d, cap, R):
             torch.testing.assert_close(got[i].double(), want.sum(1), rtol=1e-5, atol=1e-12)
         if rows is not None:
             torch.testing.assert_close(rows[i].double(), want, rtol=1e-5, atol=1e-12)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("cap", [200, 330])                # the attention kernel for short prompts, the one for longer ones
+def test_leading_keys_without_weight(dtype, cap):
+    """Keys whose logits are -inf before a row's first finite logit weigh nothing: in the statistics that the attention
+    kernel hands over as in the seed on its own, and in the attention output."""
+    from paper_2403_17312_amd import binding as B
+    b, h, d, R, dead = 2, 3, 64, 16, 40
+    lens = [cap - 1, 70]
+    g = torch.Generator(device="cuda").manual_seed(23)
+    k, v, q = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    k[:, :, :dead, 5] = -math.inf
+    q[..., 5] = q[..., 5].abs() + 0.5
+    tail = torch.stack([q[i, :, n - R:n] for i, n in enumerate(lens)]).contiguous()
+    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    p = B.make_params(b, h, d, cap, 4, 8000, dtype)
+    ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    alone, after = (torch.full((b, h, cap), float("nan"), device="cuda") for _ in range(2))
+    out = torch.zeros_like(q)
+    B.swa_prefill_scores(p, tail, R, k, cl, alone, ws)
+    B.swa_prefill_attention(p, q, k, v, cl, out, R, after, ws)
+    # weights and output rounded once each (unit roundoff u), fp32 sums
+    u = {torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8, torch.float32: 2.0 ** -20}[dtype]
+    for i, n in enumerate(lens):
+        want = torch.zeros((h, cap), device="cuda", dtype=torch.float64)
+        want[:, :n] = reference(tail[i], k[i], n, R, d).sum(1)
+        for got in (alone, after):
+            torch.testing.assert_close(got[i].double(), want, rtol=1e-5, atol=1e-12)
+        w = reference(q[i, :, :n], k[i], n, n, d)[:, dead:]
+        ref, mag = w @ v[i, :, :n].double(), w @ v[i, :, :n].double().abs()
+        err = (out[i, :, dead:n].double() - ref).abs()
+        assert bool((err <= 1.5 * u * (mag + ref.abs()) + 1e-5).all()), f"length {n}: off by {err.max().item():.3g}"
