@@ -1,0 +1,18 @@
+"""What the compiler cannot check in the kernel sources."""
+import glob
+import os
+import re
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_inline_assembly_names_the_special_registers_it_writes():
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2403_17312_amd", "csrc", "*.h*"))):
+        text = re.sub(r"//[^\n]*", "", open(path).read())
+        for asm in re.findall(r"\basm\s+volatile\s*\((.*?)\);", text, flags=re.S):
+            code, _, operands = asm.partition(":")
+            for reg in re.findall(r"\b(?:s_mov_b32|s_add_u32)\s+(m0)\b", code):
+                seen += 1
+                assert f'"{reg}"' in operands.rpartition(":")[2], f"{os.path.basename(path)}: {reg} is written and not named"
+    assert seen
