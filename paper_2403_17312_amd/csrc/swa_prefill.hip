@@ -32,10 +32,13 @@ struct PrefillArgs {
     int32_t q_in_place;   // 0: q_tail is [b,h,R,d]; 1: it is the whole prompt's [b,h,cap,d] and the
                           //    R rows are the ones at positions cache_len-R .. cache_len-1
     float scale_log2e;
-    // For the column sums the columns 0..cap are cut into G slices of `cols` (a multiple of 32), one workgroup each.
+    // For the column sums the columns are cut into G slices of `cols` (a multiple of 32; the last one ends at cap), one
+    // workgroup each.
     // A slice's first 2 R output columns (score, or row 0 of the ring) bring it the row statistics from the
     // launch before: maximum of row r at [r], normaliser at [R + r].
     int32_t G, cols;
+    int32_t bound;        // on the lengths: where the slices are laid (host side)
+    bool stated;          // the bound is the caller's, not the capacity (host side)
     int32_t row_tiles;    // statistics: workgroups per pair, one for every 32 query rows
 };
 
@@ -294,30 +297,46 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
 // Slices per pair for the column sums.  One workgroup per pair reads its keys twice at about 30 GB/s, and with few
 // pairs most of the chip waits for it.  The statistics of 32 rows stay with one workgroup (their sum has an order, and the
 // selection that follows can hang on its last bit), which then keeps twice as many loads in flight; the column
-// sums are independent and get one workgroup per CU in all.  32 pairs, R = 64, f16: 8192 keys 138 -> 80 us, 4096: 70 ->
-// 46, 2048: 38 -> 29, 1024: 22 -> 21; 128 pairs of 4096 keys: 76 -> 68; with 256 pairs one launch is as fast.  Every
-// slice holds the row statistics and is at least 256 keys long.
+// sums are independent and get one workgroup per CU in all, over the columns up to the bound on the lengths (the last
+// slice has the rest).  Every slice holds the row statistics and is at least 256 keys long.
 constexpr int kSeedGrid = 256;
-static int seed_slices(int64_t pairs, int cap, int R, int& cols)
+static int seed_slices(int64_t pairs, int bound, int R, int& cols)
 {
     const int least = 2 * R > 256 ? 2 * R : 256;
     int64_t G = (kSeedGrid + pairs - 1) / pairs;
-    if (G > cap / least) G = cap / least;
+    if (G > bound / least) G = bound / least;
     if (G < 1) G = 1;
-    cols = (int)((cap + G - 1) / G + 31) / 32 * 32;
-    while (G > 1 && (G - 1) * cols + 2 * R > cap) --G;         // the last slice has room for the statistics as well
+    cols = (int)((bound + G - 1) / G + 31) / 32 * 32;
+    while (G > 1 && (G - 1) * cols + 2 * R > bound) --G;         // the last slice has room for the statistics as well
     return (int)G;
+}
+
+// Statistics and sliced sums in a launch each, or everything in one launch?  The statistics read the keys once per 32 rows, with
+// one workgroup per 32 rows of a pair: two launches pay while those workgroups find a CU of their own and the keys
+// are long enough for the second launch.  One / two launches in us, f16, d = 128, R = 64 (R = 16 and 128, the ring's
+// rows, d = 64 and fp32 draw the line in the same places):
+//    32 pairs   1024 keys 22 / 19, 2048 38 / 28, 4096 70 / 45, 8192 137 / 79
+//    64 pairs   1024 keys 22 / 21, 2048 39 / 31, 8192 140 / 89
+//   128 pairs   1024 keys 23 / 24, 2048 40 / 38, 4096 74 / 67, 8192 143 / 125
+//   160 pairs   1024 keys 24 / 37, 4096 75 / 108, 8192 150 / 207
+// With 65 to 128 pairs only under a stated bound: without one the slices are laid over the whole capacity, and prompts that fill
+// a quarter of it lose more (128 pairs x 4096 keys in 16384 slots 77 / 87) than full ones gain.  Up to 64 pairs
+// the gain is worth the risk: short prompts under a long bound lose 2 to 5 us (32 pairs x 32 keys 7 / 10).
+bool seed_in_two(int64_t pairs, int bound, bool stated, int R)
+{
+    if (pairs <= 64) return bound >= 1024;
+    return stated && pairs <= 128 && pairs * ((R + 31) / 32) <= 256 && bound >= 4096;
 }
 
 template <typename T, int D, int RT, bool WR>
 static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hipStream_t stream)
 {
-    const int G = seed_slices(pairs, a.cap, a.R, a.cols);
+    const int G = seed_slices(pairs, a.bound, a.R, a.cols);
     a.G = G;
     const dim3 one((unsigned)pairs), all((unsigned)(pairs * G));
     if (stats_ready) {
         hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
-    } else if (G > 1 && a.cap >= 1024) {
+    } else if (G > 1 && seed_in_two(pairs, a.bound, a.stated, a.R)) {
         a.row_tiles = RT;
         hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
         if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
@@ -350,10 +369,10 @@ static int launch_prefill_t(const PrefillArgs& a, int64_t pairs, bool stats_read
 
 // Where swa_prefill_attention leaves the statistics of the prompt's last R rows for the sums: G copies, `cols` apart
 // (G = 0: no room for them, the seed computes its own).
-void seed_stats_place(int64_t pairs, int cap, int R, int& G, int& cols)
+void seed_stats_place(int64_t pairs, int bound, int R, int& G, int& cols)
 {
     cols = 0;
-    G = (R > 0 && 2 * R <= cap) ? seed_slices(pairs, cap, R, cols) : 0;
+    G = (R > 0 && 2 * R <= bound) ? seed_slices(pairs, bound, R, cols) : 0;
 }
 
 int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t R, const void* k_cache,
@@ -370,6 +389,8 @@ int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t
     a.score = score;
     a.h = p.h;
     a.cap = p.cap;
+    a.stated = p.len_bound > 0;
+    a.bound = (p.len_bound > 0 && p.len_bound < p.cap) ? p.len_bound : p.cap;
     a.R = R;
     a.scale_log2e = scale * 1.44269504088896340736f;
     const int64_t pairs = (int64_t)p.b * p.h;

@@ -86,3 +86,41 @@ def test_leading_keys_without_weight(dtype, cap):
         ref, mag = w @ v[i, :, :n].double(), w @ v[i, :, :n].double().abs()
         err = (out[i, :, dead:n].double() - ref).abs()
         assert bool((err <= 1.5 * u * (mag + ref.abs()) + 1e-5).all()), f"length {n}: off by {err.max().item():.3g}"
+
+
+@pytest.mark.parametrize("dtype,d,R", [(torch.float16, 128, 64), (torch.bfloat16, 64, 100), (torch.float32, 64, 16)])
+@pytest.mark.parametrize("bound", [130, 900, 1030, 2050])
+def test_bound_below_the_capacity(dtype, d, R, bound):
+    """A stated bound on the lengths places the slices; the columns behind it are cleared all the same."""
+    from paper_2403_17312_amd import binding as B
+    cap = 2600
+    lens = [0, 1, R, bound // 2, bound - 33, bound - 2, bound - 1]
+    b, h = len(lens), 2
+    g = torch.Generator(device="cuda").manual_seed(17)
+    q, k, v = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    tail = torch.randn((b, h, R, d), generator=g, device="cuda").to(dtype)
+    for i, n in enumerate(lens):
+        for x in (q, k, v):
+            x[i, :, n:] = float("nan")
+        r = min(R, n)
+        if n:
+            tail[i, :, R - r:] = q[i, :, n - r:n]
+    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    p = B.make_params(b, h, d, cap, 4, 8000, dtype, len_bound=bound)
+    ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    alone, after = (torch.full((b, h, cap), float("nan"), device="cuda") for _ in range(2))
+    B.swa_prefill_scores(p, tail, R, k, cl, alone, ws)
+    B.swa_prefill_attention(p, q, k, v, cl, torch.zeros_like(q), R, after, ws)
+    rows = None
+    if R <= B.SWA_MAX_WINDOW_ROWS:
+        rows = torch.full((b, h, R, cap), float("nan"), device="cuda")
+        B.swa_prefill_rows(p, tail, R, k, cl, rows, ws)
+    for i, n in enumerate(lens):
+        want = torch.zeros((h, R, cap), device="cuda", dtype=torch.float64)
+        if n:
+            want[:, :, :n] = reference(tail[i], k[i], n, R, d)
+        # as in test_slices
+        for got in (alone, after):
+            torch.testing.assert_close(got[i].double(), want.sum(1), rtol=1e-5, atol=1e-12)
+        if rows is not None:
+            torch.testing.assert_close(rows[i].double(), want, rtol=1e-5, atol=1e-12)
