@@ -15,6 +15,8 @@
 // read in that order, so the contraction pairs every weight with its own key.
 //
 // Two kernels: one for the 16-bit formats, and one for short prompts and for fp32 (which is there for completeness).
+#include <type_traits>
+
 #include "swa_kernels.hpp"
 
 namespace swa {
@@ -71,8 +73,9 @@ __device__ __forceinline__ uint32_t pack2<BF16>(float f0, float f1)
 }
 
 // Tiles staged through registers, double-buffered, the value tile transposed on its way into LDS: short prompts in
-// the 16-bit formats (three workgroups per CU, 168 registers per lane, 38 KB of LDS each), and fp32.  fp32 (32x32x2 MFMA, four issues per 16-byte fragment) is there for
-// completeness, not speed: two waves per SIMD, and at d = 128 a single LDS buffer.
+// the 16-bit formats (three workgroups per CU, 168 registers per lane, 38 KB of LDS each), and fp32.  fp32 (32x32x2
+// MFMA, four issues per 16-byte fragment) is there for completeness, not speed: two waves per SIMD, and at d = 128 a
+// single LDS buffer.
 template <typename T, int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Elem<T>::kBytes == 2 ? 3 : 2)))
 swa_flash_prefill_kernel(FlashArgs a)
@@ -367,9 +370,9 @@ __device__ __forceinline__ uint32_t lds_address(const char* p)
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
-// 16-bit formats, prompts of more than 256 rows.  Bound: the matrix cores at the clock the power limit leaves them (1.65-1.8 GHz under this
-// kernel; busy 60 % of the cycles), next to as many clocks of vector work for the softmax.  What it took
-// there, on 1792 pairs of 4096 rows, bf16, d = 128 (before: 8.3-8.4 ms, busy 51 %):
+// 16-bit formats, prompts of more than 256 rows.  Bound: the matrix cores at the clock the power limit leaves them
+// (1.65-1.8 GHz under this kernel; busy 60 % of the cycles), next to as many clocks of vector work for the
+// softmax.  What it took there, on 1792 pairs of 4096 rows, bf16, d = 128 (before: 8.3-8.4 ms, busy 51 %):
 //   - Key and value tiles go from L2 straight to LDS (global_load_lds, 16 bytes per lane), with no registers in
 //     between and no LDS store instructions.  Such a load writes 64 consecutive 16-byte chunks, so rows cannot
 //     be padded; instead chunk c of row r holds the row's chunk c ^ swizzle(r), chosen by the lane's GLOBAL
@@ -487,7 +490,7 @@ swa_flash16_kernel(FlashArgs a)
     // The query fragments are waited for here, where the compiler sees it: it would otherwise wait for them at
     // their first use in every round of the loop, and with them for the tiles requested since.
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
-    stage(nkt > 1 ? 1 : 0, s_k1, s_v1);
+    if (nkt > 1) stage(1, s_k1, s_v1);
 
     float16_t o[CT];
 #pragma unroll
@@ -496,7 +499,11 @@ swa_flash16_kernel(FlashArgs a)
         for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
     float m = kNoReference, l = 0.f;
 
-    auto compute = [&](int kt, const char* sk, const char* sv, int st, char* nk, char* nv) {
+    // all: two more tiles are to come for certain
+    auto compute = [&](auto all, int kt, const char* sk, const char* sv, char* nk, char* nv) __attribute__((always_inline)) {
+        const int st = kt + 2;
+        const bool more = all.value || st < nkt;
+        if (more) edge(st);
         float16_t c;
 #pragma unroll
         for (int i = 0; i < 16; ++i) c[i] = 0.f;
@@ -513,7 +520,7 @@ swa_flash16_kernel(FlashArgs a)
             __builtin_amdgcn_sched_barrier(0);
             // the loads of a later tile are issued between the products, which hide the time they wait to be
             // accepted: the four waves' sixteen 1 KiB loads together keep the CU's 64-byte path busy for 256 clocks
-            if (v & 1) load(v >> 1, st, nk, nv);
+            if ((v & 1) && more) load(v >> 1, st, nk, nv);
         }
         // only the tiles that reach the wave's diagonal need the causal mask
         if (kt * BK + BK - 1 > w_lo) {
@@ -573,40 +580,43 @@ swa_flash16_kernel(FlashArgs a)
         }
     };
 
-    // Tile kt is read while kt+1 and kt+2 are on their way (three buffers).  Loads return in order, so
-    // "all but the newest tile's" is a count.  Every read of the buffer that is about to be refilled has
-    // returned when its wave arrives at the barrier.
-    auto ready = [&]() {
-        __builtin_amdgcn_s_waitcnt(0x0070 | (2 * LD));      // vmcnt(2 LD) lgkmcnt(0)
+    // Tile kt is read while kt+1 and kt+2 are on their way (three buffers).  Loads return in order, so "all but
+    // the newest tile's" is a count; behind the last tile nothing is requested, and the count is zero.  Every read of
+    // the buffer that is about to be refilled has returned when its wave arrives at the barrier.
+    auto ready = [&](bool newer) {
+        if (newer) __builtin_amdgcn_s_waitcnt(0x0070 | (2 * LD));      // vmcnt(2 LD) lgkmcnt(0)
+        else __builtin_amdgcn_s_waitcnt(0x0070);                       // vmcnt(0) lgkmcnt(0)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    auto tile = [&](int kt, const char* sk, const char* sv, char* nk, char* nv) {
-        const int st = kt + 2 < nkt ? kt + 2 : nkt - 1;     // past the last tile: that one again, never read
-        ready();
-        edge(st);
-        compute(kt, sk, sv, st, nk, nv);
+    auto tile = [&](auto all, int kt, const char* sk, const char* sv, char* nk, char* nv) __attribute__((always_inline)) {
+        ready(all.value || kt + 1 < nkt);
+        compute(all, kt, sk, sv, nk, nv);
     };
+    // The last tiles of a query block ask whether there is one more to request (asking in every round cost 2 to 9 % on
+    // prompts of 1000 and more rows).
     int kt = 0;
-    for (; kt + 2 <= my_last; kt += 3) {
-        tile(kt, s_k0, s_v0, s_k2, s_v2);
-        tile(kt + 1, s_k1, s_v1, s_k0, s_v0);
-        tile(kt + 2, s_k2, s_v2, s_k1, s_v1);
+    for (; kt + 2 <= my_last && kt + 4 < nkt; kt += 3) {
+        tile(std::true_type(), kt, s_k0, s_v0, s_k2, s_v2);
+        tile(std::true_type(), kt + 1, s_k1, s_v1, s_k0, s_v0);
+        tile(std::true_type(), kt + 2, s_k2, s_v2, s_k1, s_v1);
     }
-    if (kt <= my_last) {
-        tile(kt, s_k0, s_v0, s_k2, s_v2);
-        if (kt + 1 <= my_last) tile(kt + 1, s_k1, s_v1, s_k0, s_v0);
-    }
+    // at most four are left: kt + 4 >= nkt, or kt + 2 > my_last
+    if (kt <= my_last) tile(std::false_type(), kt, s_k0, s_v0, s_k2, s_v2);
+    if (kt + 1 <= my_last) tile(std::false_type(), kt + 1, s_k1, s_v1, s_k0, s_v0);
+    if (kt + 2 <= my_last) tile(std::false_type(), kt + 2, s_k2, s_v2, s_k1, s_v1);
+    if (kt + 3 <= my_last) tile(std::false_type(), kt + 3, s_k0, s_v0, s_k2, s_v2);
     // the tiles behind this wave's last query: it still takes its part in staging them for the others
     for (kt = my_last + 1; kt < nkt; ++kt) {
-        const int st = kt + 2 < nkt ? kt + 2 : nkt - 1;
+        const int st = kt + 2;
         const int buf = kt % 3;
-        ready();
-        edge(st);
-        stage(st, buf == 0 ? s_k2 : (buf == 1 ? s_k0 : s_k1), buf == 0 ? s_v2 : (buf == 1 ? s_v0 : s_v1));
+        ready(kt + 1 < nkt);
+        if (st < nkt) {
+            edge(st);
+            stage(st, buf == 0 ? s_k2 : (buf == 1 ? s_k0 : s_k1), buf == 0 ? s_v2 : (buf == 1 ? s_v0 : s_v1));
+        }
     }
-    __builtin_amdgcn_s_waitcnt(0x0070);                     // vmcnt(0) lgkmcnt(0): nothing stays in flight
 
     float l_lo, l_hi;
     both_halves(l, l_lo, l_hi);
@@ -661,9 +671,10 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     const int64_t wgs = per_xcd * kXcds * a.nqb;
     if (wgs > 0x7fffffffLL) return SWA_ERR_BAD_SHAPE;
     const dim3 grid((unsigned)wgs);
-    // The direct-to-LDS kernel requests two tiles past the end of every query block, which short prompts feel.  Staged
-    // through registers / direct, d = 128, 256 sequences: 40 heads x 32 rows 72 / 82 us, 32 heads x 60..250 rows 226 /
-    // 238 us, 64 x 32 x 128..512 rows 180 / 174 us (longer ones: up to 1.25 times as fast).
+    // The direct-to-LDS kernel has a longer start and end, which short prompts feel.  Staged through registers / direct in
+    // us, f16 at d = 128, bf16 at d = 128, f16 at d = 64: 256 x 40 pairs of 32 rows 250 / 255, 232 / 242, 114 / 117; 256 x 32 of
+    // 60..250 rows 523 / 535, 511 / 527, 281 / 286; 64 x 32 of 128..512 rows 167 / 160, 161 / 156, 95 / 87 (longer
+    // ones: up to 1.25 times as fast).
     const bool direct = p.dtype != SWA_F32 && bound > 256;
     auto go = [&](auto small, auto large) {
         if (p.d == 64) hipLaunchKernelGGL(small, grid, dim3(256), 0, stream, a);

@@ -37,3 +37,41 @@ def test_every_tile_count(dtype, d):
         err = (out[i, :, :n].double() - ref).abs()
         assert bool((err <= 1.5 * u * (mag + ref.abs()) + 1e-5).all()), f"length {n}: off by {err.max().item():.3g}"
         assert bool((out[i, :, n:] == 7.0).all()), f"length {n}: wrote past the prompt"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("cap,bound,R", [(256, 0, 0), (256, 0, 64), (256, 0, 128), (255, 0, 128), (250, 0, 1), (390, 256, 100),
+                                         (390, 256, 128), (390, 257, 128), (390, 255, 128), (64, 0, 33), (64, 0, 32)])
+def test_either_side_of_the_short_prompt_line(dtype, d, cap, bound, R):
+    """The kernel for short prompts (bound of at most 256 rows) and the other one just above: outputs, and the importance seed
+    from statistics that the attention kernel hands over (2 R up to the bound) or that the seed forms itself."""
+    from paper_2403_17312_amd import binding as B
+    top = min(cap, bound - 1) if bound else cap
+    lens = sorted({n for n in (0, 1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 160, 254, 255, 256, top - 1, top) if n <= top})
+    b, h = len(lens), 3
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    beyond = torch.arange(cap, device="cuda")[None, None, :, None] >= cl[:, None, None, None]
+    for x in (q, k, v):
+        x.masked_fill_(beyond, float("nan"))          # rows past a prompt must not be used
+    out = torch.full_like(q, 7.0)
+    score = torch.full((b, h, cap), float("nan"), device="cuda") if R else None
+    p = B.make_params(b, h, d, cap, 4, 8000, dtype, len_bound=bound)
+    ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    B.swa_prefill_attention(p, q, k, v, cl, out, R, score, ws)
+    u = 2.0 ** -11 if dtype == torch.float16 else 2.0 ** -8          # as in test_every_tile_count
+    for i, n in enumerate(lens):
+        Q, K, V = (x[i, :, :n].double() for x in (q, k, v))
+        z = Q @ K.transpose(1, 2).contiguous() / math.sqrt(d)
+        z = z.masked_fill(torch.ones(n, n, device="cuda", dtype=torch.bool).triu(1), -math.inf)
+        pr = torch.softmax(z, -1)
+        ref, mag = pr @ V, pr @ V.abs()
+        err = (out[i, :, :n].double() - ref).abs()
+        assert bool((err <= 1.5 * u * (mag + ref.abs()) + 1e-5).all()), f"length {n}: off by {err.max().item():.3g}"
+        assert bool((out[i, :, n:] == 7.0).all()), f"length {n}: wrote past the prompt"
+        if R:
+            # fp32 logits, exponentials and sums over at most 256 keys and 128 rows, exponents up to about 10
+            torch.testing.assert_close(score[i, :, :n].double(), pr[:, max(0, n - R):].sum(1), rtol=1e-5, atol=1e-12)
+            assert bool((score[i, :, n:] == 0.0).all()), f"length {n}: score beyond the prompt"
