@@ -151,9 +151,9 @@ int swa_prepare(void);
  * swa_params.flags bit, on its own (the two-call form: swa_decode_step, then swa_compact_kv whenever
  * the caller wants): the rows of one (sequence, head) pair are split over several workgroups.  For
  * few pairs with long caches - small batches, long contexts, caches that are compacted rarely or
- * never - one workgroup per pair leaves most of the GPU idle.  The call then enqueues two kernels (logits
- * of a slice of the keys per workgroup; softmax, importance, selection and output per pair), or four where many rows are
- * kept (partial outputs over slices of the kept list; their sum), and needs the larger workspace that
+ * never - one workgroup per pair leaves most of the GPU idle.  The call then enqueues three kernels (logits
+ * of a slice of the keys per workgroup; softmax, importance and selection per pair; output of a part
+ * of the channels per workgroup) and needs the larger workspace that
  * swa_workspace_bytes reports for this flag.  Attention weights, importance and the kept set are
  * bit-identical to the one-workgroup form; the output's partial sums are added in another order.
  * With many pairs or short caches (more than 128 pairs, or a length bound below 2048 rows: there the

@@ -51,9 +51,10 @@ size_t shared_workspace_offset(const swa_params& p)
 
 int split_factor(int64_t pairs, int len_bound)
 {
-    // Four launches instead of one pay only when one workgroup per pair leaves most CUs idle for long:
-    // measured break-even near 128 pairs of 4096 rows; below 2048 rows the extra launches cost more
-    // than the slices gain.
+    // Three launches instead of one pay only when one workgroup per pair leaves most CUs idle for long.  The line
+    // was drawn with an earlier form of four launches; with three (f16, d = 128, one workgroup / split in us, a fifth or all of
+    // the rows kept): 96 pairs x 2048 rows 37 / 30, 29 / 30; 128 pairs x 2048 39 / 33, 30 / 35; x 4096 64 / 48, 54 / 57;
+    // x 8192 115 / 76, 103 / 102.
     if (pairs > 128 || len_bound < 2048) return 1;
     // enough workgroups to put about four on every CU, every slice at least 128 rows long
     int64_t g = (1024 + pairs - 1) / pairs;
@@ -210,6 +211,7 @@ size_t swa_workspace_bytes(const swa_params* params)
     if (params->flags & SWA_HEAD_SHARED)
         bytes += sizeof(float) * ((size_t)params->b * params->h * params->cap * 2 + (size_t)params->b * params->h * params->d +
                                   (size_t)params->b * params->cap);
+    // (logits, weights, flags; the middle term held partial outputs in an earlier form, and the size that callers were told stays)
     if (params->flags & SWA_SPLIT_ROWS)
         bytes += sizeof(float) * ((size_t)params->b * params->h * params->cap * 2 +
                                   (size_t)params->b * params->h * swa::kMaxSplit * (params->d + 1) +

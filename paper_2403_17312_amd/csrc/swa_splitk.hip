@@ -1,16 +1,14 @@
 // Decode step with one pair's rows split over several workgroups (SWA_SPLIT_ROWS): for few
 // (sequence, head) pairs with long caches - small batches, long contexts, caches that are compacted
 // rarely or never - one workgroup per pair cannot keep the memory system busy.  The step then runs
-// as two or four launches:
+// as three launches:
 //   1. swa_split_logits_kernel   G workgroups per pair: logits q . k_i * scale of a slice of the
 //                                cached keys (Eq. 1 numerator), written to the workspace;
 //   2. swa_split_select_kernel   one workgroup per pair: append, softmax over the stored logits,
-//                                importance accumulation, budget and selection (Alg. 1 lines 1-5), kept list;
-//                                with few kept rows also the output (Alg. 1 lines 6-8), and the step ends here;
-//   3. swa_split_gather_kernel   G workgroups per pair: partial sums  sum p_i v_i  and  sum p_i
-//                                over a slice of the kept list;
-//   4. swa_split_merge_kernel    one workgroup per pair: partials added in slice order, divided,
-//                                rounded once to the output type.
+//                                importance accumulation, budget and selection (Alg. 1 lines 1-5),
+//                                kept list and the kept tokens' weights to memory;
+//   3. swa_split_gather_kernel   one workgroup per pair and 64 bytes of a row: out = sum p_i v_i / sum p_i
+//                                over the kept list (Alg. 1 lines 6-8), rounded once to the output type.
 // The logits are formed exactly as the one-workgroup kernel forms them (same products, same
 // reduction order), so weights, importance and the kept set are bit-identical to that form; only
 // the order in which the output's partial sums are added differs.
@@ -35,17 +33,19 @@ struct SplitArgs {
     int32_t* status;
     int32_t* arrive;
     float* ws_z;        // [pairs, cap] logits
-    float* ws_p;        // [pairs, cap] attention weights of launch 2
-    float* ws_part;     // [pairs, G, D + 1] partial outputs and their weight sums
+    float* ws_p;        // [pairs, cap] weights of the kept tokens, in the order of the kept list
     int32_t* ws_ok;     // [pairs] 1 once launch 2 has finished the pair's step (0: skipped, cache full)
     char* out;
+    int64_t pairs;
     int32_t h, cap, G;
     int32_t w, sparsity_bp, lds_slots;
-    int32_t gather_here;   // launch 2 forms the output itself
     float scale;
 };
 
 constexpr int kSelThreads = 1024;    // launch 2: a whole CU's worth of one pair
+constexpr int kGatherThreads = 1024;
+constexpr int kPieceBytes = 128;     // of a value row, per workgroup of launch 3
+constexpr int kXcds = 8;             // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
 constexpr int kSelPer = SWA_MAX_CAP / kSelThreads;   // slots per thread at most
 
 // Launch 1.  cache_len is the length BEFORE the step's append; slot `len` is the new token, whose
@@ -97,8 +97,7 @@ __global__ void __launch_bounds__(NT) swa_split_logits_kernel(SplitArgs a)
 // Bound: the dependent chain of one workgroup (a few pairs on 256 CUs), so every load of the pair's logits and
 // importance is requested at once, keys stay in registers between the phases, and 1024 threads share the work.
 // Weights are bit-identical to the one-workgroup kernel's: its 512 threads' sums are added up in its order.
-// 32 pairs x 8192 rows, f16, d = 128: 33 us with the one-workgroup kernel in this place, plus 14 us for the two launches
-// that formed the output; now about 31 us with the output (whole step 62 -> 47 us).
+// 32 pairs x 8192 rows, f16, d = 128: 17 us (33 with the one-workgroup kernel in this place).
 template <typename T, int D>
 __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs a)
 {
@@ -107,7 +106,6 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     constexpr int SUMT = 512;               // threads of the one-workgroup kernel on such caches
     constexpr int EPV = Elem<T>::kPerVec;
     constexpr int LPR = D / EPV;
-    constexpr int NG = NT / LPR;
     constexpr int ROWB = D * Elem<T>::kBytes;
     extern __shared__ __align__(16) char smem[];
     float* s_p = reinterpret_cast<float*>(smem);                       // exponentials, then weights
@@ -116,8 +114,6 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     __shared__ SelectScratch<NT> s_sel;
     __shared__ float s_red[NW];
     __shared__ float s_sum[SUMT / kWave];
-    __shared__ float s_acc[NW * D];
-    __shared__ float s_ps[NW];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -143,8 +139,11 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
             sc[k] = i < len ? Sp[i] : 0.f;
         }
         // append: the new row's key, value and position
-        if (tid < LPR) store16(a.k_cache + (pair * (int64_t)cap + len) * ROWB + tid * 16, load16(a.k_new + pair * ROWB + tid * 16));
-        else if (tid < 2 * LPR) store16(a.v_cache + (pair * (int64_t)cap + len) * ROWB + (tid - LPR) * 16, load16(a.v_new + pair * ROWB + (tid - LPR) * 16));
+        if (tid < 2 * LPR) {
+            const int at = (tid % LPR) * 16;
+            const char* row = tid < LPR ? a.k_new : a.v_new;
+            store16((tid < LPR ? a.k_cache : a.v_cache) + (pair * (int64_t)cap + len) * ROWB + at, load16(row + pair * ROWB + at));
+        }
         if (tid == 0) a.pos[pair * (int64_t)cap + len] = n - 1;
 
         float mx = -INFINITY;
@@ -188,7 +187,6 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
                 const float v = sc[k] + p;
                 Sp[i] = v;
                 s_p[i] = p;
-                if (!a.gather_here) Wp[i] = p;
                 key[k] = order_key(v);
                 s_key[i] = key[k];
             }
@@ -200,96 +198,50 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
         }
 
         int32_t* kout = a.kept_idx + pair * (int64_t)cap;
-        uint32_t thr = 0u;
-        int rem = 0, n_eq = 0;
-        if (n_global > 0 && keep < m) {
-            auto each = [&](auto f) {
-#pragma unroll
-                for (int k = 0; k < kSelPer; ++k)
-                    if (tid + k * NT < ncand) f(key[k]);
-            };
-            select_threshold<NT>(s_sel, n_global, each, thr, rem, n_eq);
+        if (keep == m) {                                    // everything stays
+            __syncthreads();
+            for (int i = tid; i < m; i += NT) {
+                kout[i] = i;
+                Wp[i] = s_p[i];
+            }
         } else {
+            uint32_t thr = 0u;
+            int rem = 0, n_eq = 0;
+            if (n_global > 0) {
+                auto each = [&](auto f) {
+#pragma unroll
+                    for (int k = 0; k < kSelPer; ++k)
+                        if (tid + k * NT < ncand) f(key[k]);
+                };
+                select_threshold<NT>(s_sel, n_global, each, thr, rem, n_eq);
+            } else {
+                __syncthreads();
+            }
+            // every thread owns a run of slots; ties go to the lowest slots
+            const int per = (m + NT - 1) / NT;
+            const int lo = tid * per;
+            const int hi = lo + per < m ? lo + per : m;
+            uint64_t surem = 0ull, eqm = 0ull;
+            for (int k = 0; lo + k < hi; ++k) {
+                const int i = lo + k;
+                if (i >= ncand) {
+                    surem |= 1ull << k;
+                } else if (n_global > 0) {
+                    const uint32_t q = s_key[i];
+                    if (q > thr) surem |= 1ull << k;
+                    else if (q == thr) eqm |= 1ull << k;
+                }
+            }
+            const uint64_t kept = keep_mask<NT>(s_sel.cnt, surem, eqm, rem);
+            int at = 0, total = 0;
+            block_scan<NT>(s_sel.cnt, (int)__popcll(kept), at, total);
+            for (int k = 0; lo + k < hi; ++k)
+                if ((kept >> k) & 1ull) s_kept[at++] = (uint16_t)(lo + k);
             __syncthreads();
-        }
-        // every thread owns a run of slots; ties go to the lowest slots
-        const int per = (m + NT - 1) / NT;
-        const int lo = tid * per;
-        const int hi = lo + per < m ? lo + per : m;
-        uint64_t surem = 0ull, eqm = 0ull;
-        for (int k = 0; lo + k < hi; ++k) {
-            const int i = lo + k;
-            if (i >= ncand || keep == m) {
-                surem |= 1ull << k;
-            } else if (n_global > 0) {
-                const uint32_t q = s_key[i];
-                if (q > thr) surem |= 1ull << k;
-                else if (q == thr) eqm |= 1ull << k;
-            }
-        }
-        const uint64_t kept = keep_mask<NT>(s_sel.cnt, surem, eqm, rem);
-        int at = 0, total = 0;
-        block_scan<NT>(s_sel.cnt, (int)__popcll(kept), at, total);
-        for (int k = 0; lo + k < hi; ++k)
-            if ((kept >> k) & 1ull) s_kept[at++] = (uint16_t)(lo + k);
-        __syncthreads();
-        for (int j = tid; j < keep; j += NT) kout[j] = s_kept[j];
-
-        if (a.gather_here) {
-            // out = sum_kept p_i v_i / sum_kept p_i (Alg. 1 lines 6-8), eight value rows per group in flight
-            constexpr int UV = 8;
-            const int sub = tid % LPR;
-            const int grp = tid / LPR;
-            const char* Vp = a.v_cache + pair * (int64_t)cap * ROWB;
-            const Vec16 nv = load16(a.v_new + pair * ROWB + sub * 16);
-            float acc[EPV];
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
-            float ps = 0.f;
-            for (int j0 = 0; j0 < keep; j0 += NG * UV) {
-                Vec16 vv[UV];
-                float pw[UV];
-#pragma unroll
-                for (int u = 0; u < UV; ++u) {
-                    const int j = j0 + u * NG + grp;
-                    pw[u] = 0.f;
-                    vv[u] = Vec16{0u, 0u, 0u, 0u};
-                    if (j < keep) {
-                        int i = s_kept[j];
-                        i = i > len ? len : i;
-                        pw[u] = s_p[i];
-                        vv[u] = i == len ? nv : load16_stream(Vp + (int64_t)i * ROWB + sub * 16);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < UV; ++u) {
-                    float f[EPV];
-                    unpack<T>(vv[u], f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) acc[e] = __builtin_fmaf(pw[u], f[e], acc[e]);
-                    ps += pw[u];
-                }
-            }
-#pragma unroll
-            for (int o = LPR; o < kWave; o <<= 1) {
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
-                ps += __shfl_xor(ps, o, kWave);
-            }
-            if (lane < LPR) {
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) s_acc[wave * D + sub * EPV + e] = acc[e];
-                if (lane == 0) s_ps[wave] = ps;
-            }
-            __syncthreads();
-            if (tid < D) {
-                float t = 0.f, pst = 0.f;
-#pragma unroll
-                for (int v = 0; v < NW; ++v) {
-                    t += s_acc[v * D + tid];
-                    pst += s_ps[v];
-                }
-                store_elem<T>(a.out + pair * ROWB, tid, keep > 0 ? t / pst : 0.f);   // an empty budget: an empty sum
+            for (int j = tid; j < keep; j += NT) {
+                const int i = s_kept[j];
+                kout[j] = i;
+                Wp[j] = s_p[i];
             }
         }
     }
@@ -310,53 +262,64 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     }
 }
 
-// Launch 3.  Slice g of the kept list of the pair: weighted value rows and their weights.
-template <typename T, int D, int NT>
-__global__ void __launch_bounds__(NT) swa_split_gather_kernel(SplitArgs a)
+// Launch 3.  Output of one pair from its kept list, 128 bytes of the row per workgroup.
+//
+// Bound: what a CU can load (about 100 GB/s with random rows) and the launch's own latency.  Whole rows in slices of the list, or inside
+// launch 2, would need either a fourth launch that adds the slices up or a choice by the number of kept rows, which
+// the host does not know: a compacted cache or a wide window keeps many times the share that the sparsity
+// names.  Channels need no sum across workgroups, whatever is kept.  64-byte pieces are 1 to 5 us faster with few pairs and much
+// kept, but slower from about 96 pairs on (128 pairs x 8192 kept rows, whole step 118 against 102 us).
+// Whole step, f16, d = 128, this form / partial sums and a fourth launch / output in launch 2, in us: 32 pairs, 20 of 2048 rows
+// kept 20.6 / 26.3 / 19.4; 410 of 2048 23.2 / 28.8 / 23.1; all of 2048 21.4 / 28.2 / 33.3; 1638 of 8192 40.1 / 45.3 / 46.5; all
+// of 8192 52.8 / 59.2 / 98; 128 pairs, all of 8192 102 / 130 / 136.
+template <typename T, int D>
+__global__ void __launch_bounds__(kGatherThreads) swa_split_gather_kernel(SplitArgs a)
 {
-    constexpr int EPV = Elem<T>::kPerVec;
-    constexpr int LPR = D / EPV;
-    constexpr int NG = NT / LPR;
+    constexpr int NT = kGatherThreads;
     constexpr int NW = NT / kWave;
+    constexpr int EPV = Elem<T>::kPerVec;
     constexpr int ROWB = D * Elem<T>::kBytes;
+    constexpr int LPR = kPieceBytes / 16;         // lanes per piece of a row
+    constexpr int PIECES = ROWB / kPieceBytes;
+    constexpr int CH = LPR * EPV;                 // channels of a piece
+    constexpr int NG = NT / LPR;
     constexpr int UV = 8;
-    __shared__ float s_acc[NW * D];
+    __shared__ float s_acc[NW * CH];
     __shared__ float s_ps[NW];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int sub = tid % LPR;
     const int grp = tid / LPR;
-    const int64_t pair = blockIdx.x / a.G;
-    const int g = blockIdx.x % a.G;
-    const int s = (int)(pair / a.h);
-    if (a.ws_ok[pair] == 0) return;                    // a skipped pair: nothing is written for it
-    int keep = a.kept_cnt[s];
+    // the pieces of a pair go to the XCD that ran its selection, next to each other: they share lines, list and weights
+    const int64_t b = blockIdx.x / kXcds;
+    const int piece = (int)(b % PIECES);
+    const int64_t pair = b / PIECES * kXcds + blockIdx.x % kXcds;
+    if (pair >= a.pairs || a.ws_ok[pair] == 0) return;          // (a skipped pair: nothing is written for it)
+    int keep = a.kept_cnt[(int)(pair / a.h)];
     keep = keep < 0 ? 0 : (keep > a.cap ? a.cap : keep);
-    const int per = (keep + a.G - 1) / a.G;
-    const int lo = g * per;
-    const int hi = lo + per < keep ? lo + per : keep;
-    const char* Vp = a.v_cache + pair * (int64_t)a.cap * ROWB;
-    const float* Pp = a.ws_p + pair * (int64_t)a.cap;
+    const char* Vp = a.v_cache + pair * (int64_t)a.cap * ROWB + piece * kPieceBytes + sub * 16;
+    const float* Wp = a.ws_p + pair * (int64_t)a.cap;
     const int32_t* idx = a.kept_idx + pair * (int64_t)a.cap;
     float acc[EPV];
 #pragma unroll
     for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
     float ps = 0.f;
-    for (int j0 = lo; j0 < hi; j0 += NG * UV) {
-        Vec16 vv[UV];
+    for (int j0 = 0; j0 < keep; j0 += NG * UV) {
+        int i[UV];
         float pw[UV];
+        Vec16 vv[UV];
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
             const int j = j0 + u * NG + grp;
-            pw[u] = 0.f;
+            i[u] = j < keep ? idx[j] : 0;
+            pw[u] = j < keep ? Wp[j] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < UV; ++u) {
+            i[u] = i[u] < 0 ? 0 : (i[u] >= a.cap ? a.cap - 1 : i[u]);
             vv[u] = Vec16{0u, 0u, 0u, 0u};
-            if (j < hi) {
-                int i = idx[j];
-                i = i < 0 ? 0 : (i >= a.cap ? a.cap - 1 : i);
-                pw[u] = Pp[i];
-                vv[u] = load16_stream(Vp + (int64_t)i * ROWB + sub * 16);
-            }
+            if (j0 + u * NG + grp < keep) vv[u] = load16_stream(Vp + (int64_t)i[u] * ROWB);
         }
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
@@ -375,46 +338,19 @@ __global__ void __launch_bounds__(NT) swa_split_gather_kernel(SplitArgs a)
     }
     if (lane < LPR) {
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) s_acc[wave * D + sub * EPV + e] = acc[e];
+        for (int e = 0; e < EPV; ++e) s_acc[wave * CH + sub * EPV + e] = acc[e];
         if (lane == 0) s_ps[wave] = ps;
     }
     __syncthreads();
-    float* part = a.ws_part + (pair * a.G + g) * (int64_t)(D + 1);
-    for (int e = tid; e < D; e += NT) {
-        float t = 0.f;
+    if (tid < CH) {
+        float t = 0.f, pst = 0.f;
 #pragma unroll
-        for (int v = 0; v < NW; ++v) t += s_acc[v * D + e];
-        part[e] = t;
+        for (int v = 0; v < NW; ++v) {
+            t += s_acc[v * CH + tid];
+            pst += s_ps[v];
+        }
+        store_elem<T>(a.out + pair * ROWB, piece * CH + tid, keep > 0 ? t / pst : 0.f);   // an empty budget: an empty sum
     }
-    if (tid == 0) {
-        float t = 0.f;
-#pragma unroll
-        for (int v = 0; v < NW; ++v) t += s_ps[v];
-        part[D] = t;
-    }
-}
-
-// Launch 4.  out = (sum over the slices of the partial sums) / (sum of their weights), slice 0 first.
-template <typename T, int D>
-__global__ void __launch_bounds__(D) swa_split_merge_kernel(SplitArgs a)
-{
-    constexpr int ROWB = D * Elem<T>::kBytes;
-    const int e = threadIdx.x;
-    const int64_t pair = blockIdx.x;
-    const int s = (int)(pair / a.h);
-    const int keep = a.kept_cnt[s];
-    if (a.ws_ok[pair] == 0) return;                    // a skipped (full) sequence: nothing is written
-    if (keep <= 0) {                                   // a budget that keeps no token: an empty sum
-        store_elem<T>(a.out + pair * ROWB, e, 0.f);
-        return;
-    }
-    const float* part = a.ws_part + pair * a.G * (int64_t)(D + 1);
-    float t = 0.f, ps = 0.f;
-    for (int g = 0; g < a.G; ++g) {
-        t += part[g * (D + 1) + e];
-        ps += part[g * (D + 1) + D];
-    }
-    store_elem<T>(a.out + pair * ROWB, e, t / ps);
 }
 
 template <typename T, int D>
@@ -430,10 +366,8 @@ static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
     if (rc != SWA_OK) return rc;
     hipLaunchKernelGGL(sel, dim3((unsigned)pairs), dim3(kSelThreads), lds, stream, a);
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
-    if (a.gather_here) return SWA_OK;
-    hipLaunchKernelGGL((swa_split_gather_kernel<T, D, NT>), grid, dim3(NT), 0, stream, a);
-    if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
-    hipLaunchKernelGGL((swa_split_merge_kernel<T, D>), dim3((unsigned)pairs), dim3(D), 0, stream, a);
+    const int64_t pieces = (pairs + kXcds - 1) / kXcds * kXcds * (D * Elem<T>::kBytes / kPieceBytes);
+    hipLaunchKernelGGL((swa_split_gather_kernel<T, D>), dim3((unsigned)pieces), dim3(kGatherThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
@@ -464,8 +398,8 @@ int launch_split(const swa_params& p, float scale, int G, const void* q, const v
     a.arrive = reinterpret_cast<int32_t*>(ws + kWsArriveOffset);
     a.ws_z = reinterpret_cast<float*>(base);
     a.ws_p = reinterpret_cast<float*>(base + slab);
-    a.ws_part = reinterpret_cast<float*>(base + 2 * slab);
-    a.ws_ok = reinterpret_cast<int32_t*>(base + 2 * slab + (size_t)pairs * kMaxSplit * (p.d + 1) * sizeof(float));
+    a.ws_ok = reinterpret_cast<int32_t*>(base + 2 * slab);
+    a.pairs = pairs;
     a.h = p.h;
     a.cap = p.cap;
     a.G = G;
@@ -473,9 +407,6 @@ int launch_split(const swa_params& p, float scale, int G, const void* q, const v
     a.sparsity_bp = p.sparsity_bp;
     a.lds_slots = (bound + 63) & ~63;
     a.scale = scale;
-    // One workgroup gathers about 100 GB/s; two launches more cost about 14 us and gather 16 times as wide.  The caller's
-    // bound on the length stands in for the number of kept rows, which the device knows.
-    a.gather_here = (int64_t)bound * (10000 - p.sparsity_bp) / 10000 * cache_row_bytes(p) <= (1 << 20);
     if (p.dtype == SWA_F32) {
         return p.d == 64 ? launch_split_t<F32, 64>(a, pairs, stream) : launch_split_t<F32, 128>(a, pairs, stream);
     } else if (p.dtype == SWA_F16) {

@@ -47,3 +47,39 @@ def test_selection_matches_the_one_workgroup_kernel(dtype, d, cap, w, sparsity, 
         x, y = one.out[i].double(), two.out[i].double()
         assert bool(((x - y).abs() <= u * (y.abs() + 1.0)).all()), n
     assert torch.equal(one.out[-1], two.out[-1]) and torch.equal(two.score[-1], old[-1])
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("w,sparsity,ahead", [(64, 8000, 1), (64, 8000, 5), (1500, 9500, 1), (0, 9999, 1), (0, 9000, 3)])
+def test_output_whatever_is_kept(dtype, d, w, sparsity, ahead):
+    """A cache of a much longer sequence (nearly everything is kept), a wide window, and budgets of a few rows: the launch
+    that forms the output, with a number of pairs that is no multiple of the XCDs."""
+    from paper_2403_17312_amd import binding as B
+    b, h, cap = 2, 5, 2500
+    lens = [2499, 2049]
+    g = torch.Generator(device="cuda").manual_seed(13)
+    K, V = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    old = torch.rand((b, h, cap), generator=g, device="cuda")
+    p = B.make_params(b, h, d, cap, w, sparsity, dtype, flags=B.SWA_SPLIT_ROWS)
+    st = B.DecodeState(p, debug_probs=True)
+    st.K.copy_(K)
+    st.V.copy_(V)
+    st.score.copy_(old)
+    st.cache_len.copy_(torch.tensor(lens, dtype=torch.int32))
+    st.seq_len.copy_(torch.tensor([ahead * (n + 1) for n in lens], dtype=torch.int32))
+    st.decode_step(q, kn, vn)
+    assert st.check_status() == B.SWA_OK
+    u = {torch.float32: 2.0 ** -20, torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}[dtype]
+    for i, n in enumerate(lens):
+        k = B.swa_budget(ahead * (n + 1), n + 1, w, sparsity)[0]
+        assert st.kept_cnt[i].item() == k
+        at = st.kept_idx[i, :, :k].long()
+        rows = torch.cat([V[i, :, :n], vn[i][:, None]], 1).double()
+        pk = torch.gather(st.probs[i].double(), 1, at)
+        vk = torch.gather(rows, 1, at[..., None].expand(-1, -1, d))
+        want, mag = ((pk[:, None] @ x)[:, 0] / pk.sum(1, keepdim=True) if k else torch.zeros((h, d), device="cuda", dtype=torch.float64)
+                     for x in (vk, vk.abs()))
+        # fp32 sums of at most 2500 terms (2^-20 of their magnitude), one rounding to the output type
+        assert bool(((st.out[i].double() - want).abs() <= u * want.abs() + 2.0 ** -20 * mag).all()), (n, k)
