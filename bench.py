@@ -741,7 +741,7 @@ def main():
                    "step": STEP_TEXT[args.step_mode]
                            + ("; 8-bit compressed cache (swa_quantize_kv once, then swa_decode_step_q8)"
                               if args.kv_int8 else "")
-                           + ("; SWA_SPLIT_ROWS (a pair's rows over several workgroups, four launches)"
+                           + ("; SWA_SPLIT_ROWS (a pair's rows over several workgroups, three launches)"
                               if args.split_rows else "")},
         "roofline": roof,
         "whole_step_alg_gbs": res["alg_gbs_whole_step"],

@@ -136,6 +136,7 @@ def _ptr(t: Optional[torch.Tensor]):
 def _stream(stream) -> int:
     if stream is None:
         # the current stream's handle without a Stream object around it (0.3 instead of 1.5 us of every call)
+        # (private functions of torch, for want of public ones; the public way is torch.cuda.current_stream().cuda_stream)
         return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

@@ -398,7 +398,7 @@ def test_strict_window_on_the_compressed_cache_and_with_the_head_reduced_set(env
 
 
 def test_rows_split_over_workgroups_matches_the_oracle_and_the_one_workgroup_form(env):
-    # SWA_SPLIT_ROWS: few pairs with long caches; the step runs as four launches
+    # SWA_SPLIT_ROWS: few pairs with long caches; the step runs as three launches
     O, B, W, LS = env
     for dtype, d, b, h, hi, ce in [("f16", 128, 1, 4, 2500, 0), ("bf16", 128, 2, 2, 2300, 3), ("f32", 64, 1, 3, 2100, 1),
                                    ("f16", 64, 2, 3, 900, 0), ("bf16", 64, 1, 1, 5000, 2)]:   # 900: the one-workgroup fall-back
@@ -437,7 +437,7 @@ def test_rows_split_over_workgroups_matches_the_oracle_and_the_one_workgroup_for
         if t % 2 == 1:
             for st in states:
                 st.compact()
-    # a full cache: the sequence is skipped by all four launches and reported
+    # a full cache: the sequence is skipped by all three launches and reported
     b, h, d, cap = 2, 2, 128, 512
     params = B.make_params(b, h, d, cap, 4, 5000, torch.float16, flags=B.SWA_SPLIT_ROWS)
     st = B.DecodeState(params)
