@@ -664,7 +664,7 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     a.nqb = (bound + 127) / 128;
     a.R = R;
     a.stat_G = a.stat_cols = 0;
-    seed_stats_place(a.pairs, bound, R, a.stat_G, a.stat_cols);
+    seed_stats_place(a.pairs, bound, p.cap, R, a.stat_G, a.stat_cols);
     a.stat = a.stat_G > 0 ? score : nullptr;
     stats_written = a.stat != nullptr;
     const int64_t per_xcd = ((int64_t)a.pairs + kXcds - 1) / kXcds;

@@ -60,7 +60,7 @@ int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t
 
 // Row statistics of the prompt's last R rows, on their way from the attention kernel to the seed's column sums: G copies
 // inside the pair's score row, `cols` floats apart, maximum of row r at [r] and normaliser at [R + r].  G = 0: none.
-void seed_stats_place(int64_t pairs, int bound, int R, int& G, int& cols);
+void seed_stats_place(int64_t pairs, int bound, int cap, int R, int& G, int& cols);
 
 // Whether the seed on its own runs as two launches (bound on the lengths: stated by the caller, or the capacity).
 bool seed_in_two(int64_t pairs, int bound, bool stated, int R);

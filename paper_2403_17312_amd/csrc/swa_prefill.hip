@@ -298,16 +298,16 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
 // pairs most of the chip waits for it.  The statistics of 32 rows stay with one workgroup (their sum has an order, and the
 // selection that follows can hang on its last bit), which then keeps twice as many loads in flight; the column
 // sums are independent and get one workgroup per CU in all, over the columns up to the bound on the lengths (the last
-// slice has the rest).  Every slice holds the row statistics and is at least 256 keys long.
+// slice has the rest).  Every slice holds the row statistics and is about 256 keys long at least.
 constexpr int kSeedGrid = 256;
-static int seed_slices(int64_t pairs, int bound, int R, int& cols)
+static int seed_slices(int64_t pairs, int bound, int cap, int R, int& cols)
 {
     const int least = 2 * R > 256 ? 2 * R : 256;
     int64_t G = (kSeedGrid + pairs - 1) / pairs;
-    if (G > bound / least) G = bound / least;
-    if (G < 1) G = 1;
+    if (G > (bound + least - 1) / least) G = (bound + least - 1) / least;
     cols = (int)((bound + G - 1) / G + 31) / 32 * 32;
-    while (G > 1 && (G - 1) * cols + 2 * R > bound) --G;         // the last slice has room for the statistics as well
+    if (cols < 2 * R) cols = (2 * R + 31) / 32 * 32;
+    while (G > 1 && (G - 1) * cols + 2 * R > cap) --G;         // the last slice has room for the statistics as well
     return (int)G;
 }
 
@@ -331,7 +331,7 @@ bool seed_in_two(int64_t pairs, int bound, bool stated, int R)
 template <typename T, int D, int RT, bool WR>
 static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hipStream_t stream)
 {
-    const int G = seed_slices(pairs, a.bound, a.R, a.cols);
+    const int G = seed_slices(pairs, a.bound, a.cap, a.R, a.cols);
     a.G = G;
     const dim3 one((unsigned)pairs), all((unsigned)(pairs * G));
     if (stats_ready) {
@@ -369,10 +369,10 @@ static int launch_prefill_t(const PrefillArgs& a, int64_t pairs, bool stats_read
 
 // Where swa_prefill_attention leaves the statistics of the prompt's last R rows for the sums: G copies, `cols` apart
 // (G = 0: no room for them, the seed computes its own).
-void seed_stats_place(int64_t pairs, int bound, int R, int& G, int& cols)
+void seed_stats_place(int64_t pairs, int bound, int cap, int R, int& G, int& cols)
 {
     cols = 0;
-    G = (R > 0 && 2 * R <= bound) ? seed_slices(pairs, bound, R, cols) : 0;
+    G = (R > 0 && 2 * R <= cap) ? seed_slices(pairs, bound, cap, R, cols) : 0;
 }
 
 int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t R, const void* k_cache,

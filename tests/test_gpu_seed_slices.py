@@ -89,7 +89,7 @@ def test_leading_keys_without_weight(dtype, cap):
 
 
 @pytest.mark.parametrize("dtype,d,R", [(torch.float16, 128, 64), (torch.bfloat16, 64, 100), (torch.float32, 64, 16)])
-@pytest.mark.parametrize("bound", [130, 900, 1030, 2050])
+@pytest.mark.parametrize("bound", [130, 257, 900, 1030, 2050])
 def test_bound_below_the_capacity(dtype, d, R, bound):
     """A stated bound on the lengths places the slices; the columns behind it are cleared all the same."""
     from paper_2403_17312_amd import binding as B

@@ -23,3 +23,24 @@ def test_seed_takes_two_launches_only_where_they_pay(L, pairs, bound, R, two):
     rule.restype = ctypes.c_bool
     assert rule(ctypes.c_int64(pairs), bound, ctypes.c_bool(True), R) is two
     assert rule(ctypes.c_int64(pairs), bound, ctypes.c_bool(False), R) is (two and pairs <= 64)
+
+
+def test_every_slice_of_the_seed_holds_its_statistics(L):
+    """2 R floats at the start of every slice of the columns, inside the slice and inside the row."""
+    import random
+    place = getattr(L, "_ZN3swa16seed_stats_placeEliiiRiS0_")
+    place.restype = None
+    rng = random.Random(7)
+    for _ in range(20000):
+        cap = rng.choice((rng.randrange(1, 600), rng.randrange(1, 16385)))
+        bound, R = rng.randrange(1, cap + 1), rng.randrange(0, 129)
+        pairs = rng.choice((1, 3, 8, 22, 32, 64, 100, 128, 255, 256, 4000))
+        G, cols = ctypes.c_int(-1), ctypes.c_int(-1)
+        place(ctypes.c_int64(pairs), bound, cap, R, ctypes.byref(G), ctypes.byref(cols))
+        if R == 0 or 2 * R > cap:
+            assert G.value == 0
+            continue
+        assert G.value >= 1 and cols.value % 32 == 0
+        for g in range(G.value):
+            end = cap if g == G.value - 1 else (g + 1) * cols.value
+            assert g * cols.value + 2 * R <= end, (pairs, bound, cap, R, G.value, cols.value)
