@@ -77,7 +77,9 @@ typedef struct {
     int32_t len_bound;   /* 0, or an upper bound on cache_len[s] + 1 over all sequences for this
                             call: lets swa_decode_step size its LDS to the live cache instead of
                             cap.  A sequence that exceeds it is skipped and reported exactly like
-                            a full cache (capacity status bit). */
+                            a full cache (capacity status bit).  swa_prefill_scores, swa_prefill_rows
+                            and swa_quantize_kv take it as a hint on the prompts' lengths: it chooses
+                            between forms with the same results. */
     int32_t flags;       /* 0 or a combination of the SWA_* flag bits below */
 } swa_params;
 

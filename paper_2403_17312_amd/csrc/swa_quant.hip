@@ -306,7 +306,7 @@ static void launch_longer(const QuantArgs& a, bool stated, hipStream_t stream)
 // Where the chip holds all pieces at once (few pairs) latency decides and the longer prompts' kernel serves all lengths
 // (64 pairs: 16 rows 3.7 / 4.7, 64 rows 4.7 / 5.0, 128 rows 6.2 / 5.4, 256 rows 9.3 / 6.5).
 // A stated bound says that some prompt is about that long, so the longer prompts' kernel gets one workgroup per
-// piece, and the other is left out up to four rounds of the chip (2 us of 90 at 512 pairs x 1024 rows).  Without one the
+// piece, and the other is left out up to eight rounds of the chip (2 us of 90 at 512 pairs x 1024 rows).  Without one the
 // longer prompts' kernel may find nothing to do (every prompt short, in a large cache) and comes with a narrow grid,
 // 4 rounds of the chip at NT = 512 and 1 at 1024 (in us, 2560 pairs: 16 rows in caches of 1088 17, of 2112 16, with one
 // workgroup per piece 22 and 33, without this launch 13; 1024 rows in 1088 516, with one workgroup per piece 463).
@@ -316,7 +316,7 @@ static void launch_quantize_d(QuantArgs a, int stated, hipStream_t stream)
     const int nt = (a.cap <= 576 || (stated && stated <= 385)) ? 256 : ((a.cap <= 1280 || (stated && stated <= 1025)) ? 512 : 1024);
     const int line = nt == 256 ? 112 : (nt == 512 ? 256 : 448);
     const int bound = stated && stated < a.cap ? stated : a.cap;
-    if (a.items * nt <= (stated ? 4 : 1) * 256 * 1024 && bound > 64) a.short_rows = -1;
+    if (a.items * nt <= (stated ? 8 : 1) * 256 * 1024 && bound > 64) a.short_rows = -1;
     else if (bound <= 64 || (stated && bound <= line)) a.short_rows = a.cap;
     else a.short_rows = line;
     if (a.short_rows >= 0) {

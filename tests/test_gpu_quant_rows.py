@@ -40,7 +40,7 @@ def test_rows(d, cap, lens):
 
 @pytest.mark.parametrize("stated", [False, True])
 @pytest.mark.parametrize("d,h,cap,lens", [(64, 62, 64, [0, 1, 63, 64, 17]), (64, 62, 576, [0, 3, 111, 112, 113, 575, 576, 200, 40]),
-                                          (128, 150, 1280, [1280, 0, 255, 256, 257, 1024]), (128, 150, 1280, [200, 31, 256]), (64, 400, 1280, [300, 1024, 16, 384]),
+                                          (128, 150, 1280, [1280, 0, 255, 256, 257, 1024]), (128, 150, 1280, [200, 31, 256]), (64, 400, 1280, [300, 1024, 16, 384]), (64, 700, 1280, [300, 1024, 16, 256]),
                                           (64, 130, 2200, [16, 2200, 447, 448, 449, 1500]), (64, 130, 2200, [448, 0])])
 def test_short_and_longer_prompts_side_by_side(d, h, cap, lens, stated):
     """More pieces than the chip holds at once: the kernel for short prompts and the one for longer ones divide the pairs
