@@ -58,6 +58,7 @@ struct DecodeArgs {
     int32_t* status;
     int32_t* arrive;
     int32_t h, cap, lds_slots, w, sparsity_bp;
+    int32_t key_slots;    // selection keys in LDS: lds_slots, or 0 where they are formed from the new importance instead
     float scale;
     int32_t fuse_compaction;
     int32_t unordered;    // fused compaction fills holes instead of shifting rows (order by pos only)
@@ -140,13 +141,23 @@ swa_decode_kernel(DecodeArgs a)
     uint16_t* s_kept = reinterpret_cast<uint16_t*>(s_key);
     // Fused compaction only: the new importance values and the old positions wait in LDS
     // until the selection is known, then go straight to their compacted slots.
-    float* s_sc = reinterpret_cast<float*>(s_key + a.lds_slots);
+    float* s_sc = reinterpret_cast<float*>(s_key + a.key_slots);
     int32_t* s_pos = reinterpret_cast<int32_t*>(s_sc + a.lds_slots);
     // ... and the newest stash_rows key/value rows are parked in LDS while they stream by: the
     // token evicted in the steady state sits just behind the window, so the rows that have to
     // move down (and the evicted row itself) are then served from LDS instead of being re-read.
     const bool fc = a.fuse_compaction != 0;
     const bool bag = a.unordered != 0;
+    // Unordered compaction of long caches with a selection of the pair's own: the keys are a function of the new importance,
+    // which waits in LDS anyway, so they get no array (16 instead of 20 bytes a slot: a 4096-token prompt's workgroups
+    // fit a CU twice, and the step after it streams keys in one while the other selects; 1792 pairs, bf16: 600 -> 545 us).
+    // The instantiations that serve short caches only always have the array (without it the strict window lost 1 %).
+    constexpr bool kMayDropKeys = !RING && NT >= (kQ8 ? 256 : 512);
+    const bool own_keys = !kMayDropKeys || a.key_slots != 0;
+    auto key_of = [&](int i) {
+        const uint32_t u = own_keys ? s_key[i] : f2u(s_sc[i]);
+        return own_keys ? u : order_key(u2f(u));
+    };
     // Unordered compaction only: source slot of every final slot, the holes below `keep` and the
     // kept rows above it that fill them (at most half of the slots each).
     uint16_t* s_src = reinterpret_cast<uint16_t*>(s_pos + a.lds_slots);
@@ -510,7 +521,7 @@ swa_decode_kernel(DecodeArgs a)
                 if (a.phase == 1) a.ws_snew[pair * (int64_t)cap + i] = sc;
                 if (a.phase == 1) a.ws_p[pair * (int64_t)cap + i] = p;
                 const uint32_t key = order_key(sc);
-                s_key[i] = key;
+                if (own_keys) s_key[i] = key;
                 if (bag ? (pold[k] < wlo) : (i < ncand)) {
                     const uint32_t t = bag ? (uint32_t)pold[k] : (uint32_t)i;
                     const unsigned long long c = ((unsigned long long)key << 32) | (uint32_t)(~t);
@@ -535,7 +546,7 @@ swa_decode_kernel(DecodeArgs a)
             if (a.phase == 1) a.ws_snew[pair * (int64_t)cap + i] = sc;
             if (a.phase == 1) a.ws_p[pair * (int64_t)cap + i] = p;
             const uint32_t key = order_key(sc);
-            s_key[i] = key;
+            if (own_keys) s_key[i] = key;
             if (bag ? (posi < wlo) : (i < ncand)) {
                 const uint32_t t = bag ? (uint32_t)posi : (uint32_t)i;
                 const unsigned long long c = ((unsigned long long)key << 32) | (uint32_t)(~t);
@@ -665,7 +676,7 @@ swa_decode_kernel(DecodeArgs a)
                     for (int i = tid; i < 256; i += NT) s_hist[i] = 0;
                     __syncthreads();
                     for (int i = tid; i < m; i += NT) {
-                        const uint32_t key = s_key[i];
+                        const uint32_t key = key_of(i);
                         const bool c_i = bag ? (s_pos[i] < wlo) : (i < ncand);
                         if (c_i && (key & mask) == prefix) atomicAdd(&s_hist[(key >> shift) & 255u], 1);
                     }
@@ -741,7 +752,7 @@ swa_decode_kernel(DecodeArgs a)
                     if (posi >= wlo) {
                         kept = true;
                     } else if (n_global > 0) {
-                        const uint32_t key = s_key[i];
+                        const uint32_t key = key_of(i);
                         if (key > prefix) {
                             kept = true;
                         } else if (key == prefix) {
@@ -750,7 +761,7 @@ swa_decode_kernel(DecodeArgs a)
                             } else {
                                 int rank = 0;
                                 for (int j = 0; j < m; ++j)
-                                    rank += (s_key[j] == prefix && s_pos[j] < posi) ? 1 : 0;
+                                    rank += (key_of(j) == prefix && s_pos[j] < posi) ? 1 : 0;
                                 kept = rank < rem;
                             }
                         }
@@ -1296,9 +1307,10 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
 
     const int64_t pairs = (int64_t)p.b * p.h;
     const int rowb = cache_row_bytes(p);
-    const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 20 : 16) : 8) +
-                             (size_t)a.stash_rows * rowb * 2;
     const int nt = decode_block_threads(pairs, bound, (p.flags & SWA_KV_INT8) != 0);
+    a.key_slots = (a.unordered && !shared && !ring && nt >= ((p.flags & SWA_KV_INT8) ? 256 : 512)) ? 0 : a.lds_slots;
+    const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 16 : 12) : 4) +
+                             (size_t)a.key_slots * 4 + (size_t)a.stash_rows * rowb * 2;
 
     auto launch = [&](const DecodeArgs& args) -> int {
         if (p.flags & SWA_KV_INT8) {
