@@ -36,53 +36,10 @@
 //     multiplied in registers, scale and zero point are folded into the query and the output);
 //   * the strict local attention sum (importance = sum of a ring of the last R attention rows,
 //     whose columns follow their tokens through the compaction).
-#include "swa_kernels.hpp"
+#include "swa_decode.hpp"
 #include "swa_select.hpp"
 
 namespace swa {
-
-struct DecodeArgs {
-    const char* q;
-    const char* k_new;
-    const char* v_new;
-    char* k_cache;
-    char* v_cache;
-    float* score;
-    int32_t* pos;
-    int32_t* cache_len;
-    const int32_t* seq_len;
-    int32_t* kept_idx;
-    int32_t* kept_cnt;
-    char* out;
-    float* probs_dbg;
-    int32_t* status;
-    int32_t* arrive;
-    int32_t h, cap, lds_slots, w, sparsity_bp;
-    int32_t key_slots;    // selection keys in LDS: lds_slots, or 0 where they are formed from the new importance instead
-    float scale;
-    int32_t fuse_compaction;
-    int32_t unordered;    // fused compaction fills holes instead of shifting rows (order by pos only)
-    // Head-shared selection runs as three launches: phase 1 streams the cache and publishes the
-    // new importance, the attention weights and the dense output of every pair; a small kernel
-    // sums the new importance over the heads of every sequence; phase 2 selects from that sum
-    // (every head of a sequence reaches the same decision) and finishes output and compaction.
-    int32_t phase;        // 0 = whole step in one launch; 1, 2 = the two halves of the head-shared
-                          // step
-    float* ws_p;          // [b,h,cap] attention weights of phase 1
-    float* ws_snew;       // [b,h,cap] new importance of phase 1
-    float* ws_abar;       // [b,h,d]   dense attention output of phase 1
-    float* ws_tot;        // [b,cap]   new importance summed over the heads
-    int32_t stash_rows;   // fused compaction: newest rows kept in LDS during the streaming pass
-    // Compressed cache (Section V-B): per (pair, channel) scale and zero point of keys and values,
-    // four fp32 arrays of qstride = b*h*d values each (lambda_K, z_K, lambda_V, z_V).
-    const float* qparams;
-    int64_t qstride;
-    // Strict local attention sum (Algorithm 1 line 2): the last ring_rows attention rows per pair,
-    // [b,h,ring_rows,cap]; this step overwrites row ring_row and the importance is the sum of
-    // the rows.  NULL: running sum in `score`.
-    float* ring;
-    int32_t ring_rows, ring_row;
-};
 
 constexpr int kMaxFix = 8;           // evicted rows the subtractive schedule handles
 constexpr float kMinKeptMass = 0.05f;
@@ -151,8 +108,8 @@ swa_decode_kernel(DecodeArgs a)
     // Unordered compaction of long caches with a selection of the pair's own: the keys are a function of the new importance,
     // which waits in LDS anyway, so they get no array (16 instead of 20 bytes a slot: a 4096-token prompt's workgroups
     // fit a CU twice, and the step after it streams keys in one while the other selects; 1792 pairs, bf16: 600 -> 545 us).
-    // The instantiations that serve short caches only always have the array (without it the strict window lost 1 %).
-    constexpr bool kMayDropKeys = !RING && NT >= (kQ8 ? 256 : 512);
+    // The other instantiations always have the array (without it the strict window and the 8-bit cache lost 1 %).
+    constexpr bool kMayDropKeys = !RING && !kQ8 && NT >= 512;
     const bool own_keys = !kMayDropKeys || a.key_slots != 0;
     auto key_of = [&](int i) {
         const uint32_t u = own_keys ? s_key[i] : f2u(s_sc[i]);
@@ -1308,7 +1265,14 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     const int64_t pairs = (int64_t)p.b * p.h;
     const int rowb = cache_row_bytes(p);
     const int nt = decode_block_threads(pairs, bound, (p.flags & SWA_KV_INT8) != 0);
-    a.key_slots = (a.unordered && !shared && !ring && nt >= ((p.flags & SWA_KV_INT8) ? 256 : 512)) ? 0 : a.lds_slots;
+    // Without the keys' array only where one more workgroup fits a CU for it (its LDS, next to at most 10 KiB of the kernel's
+    // own; 16 waves by registers): forming the keys again for every digit of the selection is not free.
+    auto per_cu = [&](int slot_bytes) {
+        const int by_lds = 160 * 1024 / (a.lds_slots * slot_bytes + 10 * 1024), by_waves = 16 * kWave / nt;
+        return by_lds < by_waves ? by_lds : by_waves;
+    };
+    const bool may_drop = a.unordered && !shared && !ring && nt >= 512;          // (the 8-bit cache has at most 256 threads)
+    a.key_slots = (may_drop && per_cu(16) > per_cu(20)) ? 0 : a.lds_slots;
     const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 16 : 12) : 4) +
                              (size_t)a.key_slots * 4 + (size_t)a.stash_rows * rowb * 2;
 
@@ -1333,6 +1297,8 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
             return launch_split(p, scale, G, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len, seq_len, kept_idx,
                                 kept_cnt, out, probs_dbg, workspace, stream);
     }
+    const ShortForm form = short_form(p, pairs, bound);
+    if (form.nt) return launch_short(a, p, pairs, form, stream);
     if (!shared) return launch(a);
     a.phase = 1;
     int rc = launch(a);
