@@ -128,7 +128,7 @@ typedef struct {
  * the globally dynamic tokens of sequence s are the top-k of sum_hd score[s, hd, i], and all heads
  * of the sequence keep the same token set.  score stays per head (each head accumulates its own
  * attention weights); the sum over the heads is taken in fp32, head 0 first.  The call enqueues
- * three kernels (stream and publish; sum over the heads; select and finish) and needs the larger
+ * two or three kernels (stream and publish; sum over the heads; select and finish) and needs the larger
  * workspace that swa_workspace_bytes reports for these flags.
  */
 #define SWA_HEAD_SHARED 4

@@ -42,7 +42,6 @@
 namespace swa {
 
 constexpr int kMaxFix = 8;           // evicted rows the subtractive schedule handles
-constexpr float kMinKeptMass = 0.05f;
 constexpr float kLog2e = 1.44269504088896340736f;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -1297,18 +1296,27 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
             return launch_split(p, scale, G, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len, seq_len, kept_idx,
                                 kept_cnt, out, probs_dbg, workspace, stream);
     }
-    const ShortForm form = short_form(p, pairs, bound);
-    if (form.nt) return launch_short(a, p, pairs, form, stream);
+    const ShortForm form = short_form(p, pairs, bound, ring != nullptr);
+    if (form.nt && !shared) return launch_short(a, p, pairs, form, stream);
     if (!shared) return launch(a);
     a.phase = 1;
-    int rc = launch(a);
+    int rc = form.nt ? launch_short_shared(a, p, pairs, form, stream) : launch(a);
     if (rc != SWA_OK) return rc;
+    // The second launch sums over the heads itself while that is less than a launch of its own: every pair's workgroup reads the
+    // importance of all heads.  Three launches of the streaming kernel / two and the sum between them / two, us a step: 84 pairs of
+    // 12 heads x 234 slots, bf16, d = 64 13.0 / 11.7 / 9.5; f16, d = 128: 32 of 32 x 106 12.4 / 10.4 / 8.4; 896 of 56 x
+    // 106 19.7 / 17.4 / 15.7; 1024 of 32 x 180 25.0 / 23.7 / 22.7; 2560 of 40 x 106 38.5 / 35.3 / 36.1, x 180 55.0 / 53.7 / 56.1.
+    if (form.nt && pairs * p.h * bound <= (8 << 20)) {
+        a.ws_tot = nullptr;
+        a.phase = 2;
+        return launch_short_shared(a, p, pairs, form, stream);
+    }
     hipLaunchKernelGGL(swa_headsum_kernel, dim3((unsigned)((bound + kHeadSumThreads - 1) / kHeadSumThreads), (unsigned)p.b),
                        dim3(kHeadSumThreads), 0, stream,
                        a.ws_snew, a.cache_len, a.ws_tot, (int)p.h, (int)p.cap);
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     a.phase = 2;
-    return launch(a);
+    return form.nt ? launch_short_shared(a, p, pairs, form, stream) : launch(a);
 }
 
 }  // namespace swa

@@ -5,6 +5,8 @@
 
 namespace swa {
 
+constexpr float kMinKeptMass = 0.05f;      // below it the evicted rows are not subtracted: too little would be left
+
 struct DecodeArgs {
     const char* q;
     const char* k_new;
@@ -52,7 +54,8 @@ struct DecodeArgs {
 struct ShortForm {
     int nt, u;      // threads per workgroup, rows per lane
 };
-ShortForm short_form(const swa_params& p, int64_t pairs, int len_bound);
+ShortForm short_form(const swa_params& p, int64_t pairs, int len_bound, bool ring);
 int launch_short(const DecodeArgs& a, const swa_params& p, int64_t pairs, ShortForm f, hipStream_t stream);
+int launch_short_shared(const DecodeArgs& a, const swa_params& p, int64_t pairs, ShortForm f, hipStream_t stream);   // a.phase
 
 }  // namespace swa

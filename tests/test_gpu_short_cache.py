@@ -10,7 +10,7 @@ W, SPARSITY = 4, 8000                       # nint(n / 5) tokens are kept
 
 def _state(B, form, dtype, d, lens, cap, ties, R, g):
     """Inputs of one step: every length with nothing, one token, a few and half of the tokens to evict."""
-    h = 3
+    h = 19 if form == "shared" else 3
     b = len(lens) * 4
     cl = [n for n in lens for _ in range(4)]
     seq = []
@@ -27,8 +27,9 @@ def _state(B, form, dtype, d, lens, cap, ties, R, g):
         x["q"].zero_()
     x["pos"] = torch.full((b, h, cap), -1, dtype=torch.int32, device="cuda")
     for i, n in enumerate(cl):              # distinct earlier positions; in any order where the form allows it
+        same = torch.randperm(max(seq[i] - 1, n), generator=g, device="cuda")[:n].to(torch.int32)
         for j in range(h):
-            at = torch.randperm(max(seq[i] - 1, n), generator=g, device="cuda")[:n].to(torch.int32)
+            at = same if form.startswith("shared") else torch.randperm(max(seq[i] - 1, n), generator=g, device="cuda")[:n].to(torch.int32)
             x["pos"][i, j, :n] = at if form != "two_call" else at.sort().values
         x["K"][i, :, n:] = float("nan")     # behind the cache: never used
         x["V"][i, :, n:] = float("nan")
@@ -36,7 +37,7 @@ def _state(B, form, dtype, d, lens, cap, ties, R, g):
         x["ring"] = torch.rand((b, h, R, cap), generator=g, device="cuda")
         if ties:
             x["ring"] = torch.floor(x["ring"] * 2)
-    if form == "int8":
+    if form.endswith("8"):
         x["K"], x["V"] = (torch.randint(0, 256, (b, h, cap, d), generator=g, device="cuda", dtype=torch.uint8) for _ in range(2))
         x["qp"] = torch.rand((4, b, h, d), generator=g, device="cuda") * 0.02 + 0.005
         x["qp"][1::2] = torch.randint(100, 156, (2, b, h, d), generator=g, device="cuda").float()
@@ -45,7 +46,8 @@ def _state(B, form, dtype, d, lens, cap, ties, R, g):
 
 def _step(B, form, dtype, d, cap, b, h, x, bound, R):
     x = {k: v.clone() for k, v in x.items()}
-    flags = {"unordered": 3, "window": 3, "int8": 3 | B.SWA_KV_INT8, "two_call": 0}[form]
+    flags = {"unordered": 3, "window": 3, "int8": 3 | B.SWA_KV_INT8, "two_call": 0, "shared": 7,
+             "shared8": 7 | B.SWA_KV_INT8}[form]
     p = B.make_params(b, h, d, cap, W, SPARSITY, dtype, len_bound=bound, flags=flags)
     ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
     x["kc"] = torch.zeros_like(x["cl"])
@@ -53,7 +55,7 @@ def _step(B, form, dtype, d, cap, b, h, x, bound, R):
     x["out"] = torch.zeros((b, h, d), dtype=dtype, device="cuda")
     x["probs"] = torch.full((b, h, cap), 9.0, device="cuda")
     tail = (x["score"], x["pos"], x["cl"], x["sl"], x["ki"], x["kc"], x["out"], x["probs"], ws)
-    if form == "int8":
+    if form.endswith("8"):
         B.swa_decode_step_q8(p, x["q"], x["kn"], x["vn"], x["K"], x["V"], x["qp"], *tail)
     elif form == "window":
         B.swa_decode_step_window(p, x["q"], x["kn"], x["vn"], x["K"], x["V"], x["ring"], R, R // 2, *tail)
@@ -68,6 +70,8 @@ def _step(B, form, dtype, d, cap, b, h, x, bound, R):
     ("unordered", torch.float16, 64, 0), ("unordered", torch.bfloat16, 64, 0), ("unordered", torch.float32, 64, 0),
     ("two_call", torch.float16, 128, 0), ("two_call", torch.float32, 64, 0), ("two_call", torch.bfloat16, 64, 0),
     ("int8", torch.float16, 128, 0), ("int8", torch.float16, 64, 0),
+    ("shared", torch.float16, 128, 0), ("shared", torch.bfloat16, 64, 0), ("shared", torch.float32, 64, 0),
+    ("shared", torch.float32, 128, 0), ("shared8", torch.float16, 128, 0), ("shared8", torch.float16, 64, 0),
     ("window", torch.float16, 128, 1), ("window", torch.float16, 128, 33), ("window", torch.bfloat16, 64, 64),
     ("window", torch.float32, 64, 16), ("window", torch.float32, 128, 40)])
 @pytest.mark.parametrize("bound", [33, 64, 128, 192, 256])
@@ -77,7 +81,7 @@ def test_step_matches_the_streaming_kernel(form, dtype, d, R, bound, ties):
     cap = 611
     lens = sorted({0, 1, 5, 31, 32, bound // 2, bound - 33 if bound > 40 else 7, bound - 2, bound - 1})
     g = torch.Generator(device="cuda").manual_seed(bound * 7 + d)
-    b, h, x = _state(B, form, dtype, d, lens, cap, ties, R, g)
+    b, h, x = _state(B, form, dtype, d, lens, cap, ties, R, g)          # (19 heads: more than one round of loads of their sum)
     one, two = (_step(B, form, dtype, d, cap, b, h, x, n, R) for n in (0, bound))
     assert torch.equal(one["kc"], two["kc"]) and torch.equal(one["cl"], two["cl"]) and torch.equal(one["probs"], two["probs"])
     for i in range(b):
