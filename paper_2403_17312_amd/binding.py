@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libswa_hip.so (the C ABI declared in include/swa.h).
+"""Thin binding of libswa_hip.so (the C ABI declared in include/swa.h): ctypes, and a native half for the calls of a step.
 
 Argument marshalling only: every step of the decode path runs in the HIP kernels
 behind the C entry points.  PyTorch supplies device memory (tensors) and the
@@ -60,11 +60,17 @@ class SwaError(RuntimeError):
 
 
 _lib = None
+_native = None      # the native half (csrc/swa_native.cpp), bound to the entry points of _lib
+
+# Entry points whose arguments the native half converts: fn(params, arguments..., stream) -> status, or None where an argument is
+# not a plain tensor, an integer or None; the call then takes the general path below, with its errors.
+NATIVE = ("swa_decode_step", "swa_decode_step_q8", "swa_decode_step_window", "swa_decode_step_window_q8", "swa_decode_step_static",
+          "swa_compact_kv", "swa_prefill_scores", "swa_prefill_rows", "swa_prefill_attention", "swa_quantize_kv")
 
 
 def lib():
-    """Loads libswa_hip.so; raises if it has not been built."""
-    global _lib
+    """Loads libswa_hip.so and the binding's native half; raises if they have not been built."""
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -111,8 +117,20 @@ def lib():
         L.swa_prefill_attention.argtypes = [pp, vp, vp, vp, i32p, vp, ctypes.c_int32, vp, vp, vp]
         L.swa_probe_stream_read.restype = ctypes.c_int
         L.swa_probe_stream_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
-        _lib = L
+        try:
+            from . import _swa_native as N
+        except ImportError as e:
+            raise RuntimeError("_swa_native.so is missing or was built for another torch: build it with "
+                               "`python -m paper_2403_17312_amd.build` (there is no fallback path)") from e
+        N.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE}, SwaParams)
+        _lib, _native = L, N
     return _lib
+
+
+def _fast():
+    if _native is None or _lib is None:
+        lib()
+    return _native
 
 
 def strerror(code: int) -> str:
@@ -168,11 +186,14 @@ def swa_prepare() -> None:
 
 def swa_decode_step_static(params: SwaParams, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len,
                            seq_len, kept_idx, kept_cnt, out, probs_dbg, stream=None) -> None:
-    _check(lib().swa_decode_step_static(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                        _ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(pos),
-                                        _ptr(cache_len), _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt),
-                                        _ptr(out), _ptr(probs_dbg), _stream(stream)),
-           "swa_decode_step_static")
+    rc = _fast().swa_decode_step_static(params, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len, seq_len, kept_idx,
+        kept_cnt, out, probs_dbg, stream)
+    if rc is None:
+        rc = lib().swa_decode_step_static(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
+            _ptr(v_cache), _ptr(score), _ptr(pos), _ptr(cache_len), _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt), _ptr(out),
+            _ptr(probs_dbg), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_decode_step_static")
 
 
 def swa_check_status(params: SwaParams, workspace: Optional[torch.Tensor], stream=None) -> int:
@@ -184,71 +205,93 @@ def swa_check_status(params: SwaParams, workspace: Optional[torch.Tensor], strea
 
 def swa_prefill_scores(params: SwaParams, q_tail, R: int, k_cache, cache_len, score, workspace,
                        stream=None) -> None:
-    _check(lib().swa_prefill_scores(ctypes.byref(params), _ptr(q_tail), int(R), _ptr(k_cache),
-                                    _ptr(cache_len), _ptr(score), _ptr(workspace),
-                                    _stream(stream)), "swa_prefill_scores")
+    rc = _fast().swa_prefill_scores(params, q_tail, R, k_cache, cache_len, score, workspace, stream)
+    if rc is None:
+        rc = lib().swa_prefill_scores(ctypes.byref(params), _ptr(q_tail), int(R), _ptr(k_cache), _ptr(cache_len), _ptr(score),
+            _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_prefill_scores")
 
 
 def swa_decode_step(params: SwaParams, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len,
                     seq_len, kept_idx, kept_cnt, out, probs_dbg, workspace, stream=None) -> None:
-    _check(lib().swa_decode_step(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                 _ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(pos),
-                                 _ptr(cache_len), _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt),
-                                 _ptr(out), _ptr(probs_dbg), _ptr(workspace), _stream(stream)),
-           "swa_decode_step")
+    rc = _fast().swa_decode_step(params, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len, seq_len, kept_idx,
+        kept_cnt, out, probs_dbg, workspace, stream)
+    if rc is None:
+        rc = lib().swa_decode_step(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
+            _ptr(score), _ptr(pos), _ptr(cache_len), _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt), _ptr(out), _ptr(probs_dbg),
+            _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_decode_step")
 
 
 def swa_quantize_kv(params: SwaParams, k_cache, v_cache, cache_len, k_codes, v_codes, qparams,
                     stream=None) -> None:
-    _check(lib().swa_quantize_kv(ctypes.byref(params), _ptr(k_cache), _ptr(v_cache), _ptr(cache_len),
-                                 _ptr(k_codes), _ptr(v_codes), _ptr(qparams), _stream(stream)),
-           "swa_quantize_kv")
+    rc = _fast().swa_quantize_kv(params, k_cache, v_cache, cache_len, k_codes, v_codes, qparams, stream)
+    if rc is None:
+        rc = lib().swa_quantize_kv(ctypes.byref(params), _ptr(k_cache), _ptr(v_cache), _ptr(cache_len), _ptr(k_codes),
+            _ptr(v_codes), _ptr(qparams), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_quantize_kv")
 
 
 def swa_decode_step_q8(params: SwaParams, q, k_new, v_new, k_codes, v_codes, qparams, score, pos,
                        cache_len, seq_len, kept_idx, kept_cnt, out, probs_dbg, workspace,
                        stream=None) -> None:
-    _check(lib().swa_decode_step_q8(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                    _ptr(k_codes), _ptr(v_codes), _ptr(qparams), _ptr(score),
-                                    _ptr(pos), _ptr(cache_len), _ptr(seq_len), _ptr(kept_idx),
-                                    _ptr(kept_cnt), _ptr(out), _ptr(probs_dbg), _ptr(workspace),
-                                    _stream(stream)), "swa_decode_step_q8")
+    rc = _fast().swa_decode_step_q8(params, q, k_new, v_new, k_codes, v_codes, qparams, score, pos, cache_len, seq_len,
+        kept_idx, kept_cnt, out, probs_dbg, workspace, stream)
+    if rc is None:
+        rc = lib().swa_decode_step_q8(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_codes), _ptr(v_codes),
+            _ptr(qparams), _ptr(score), _ptr(pos), _ptr(cache_len), _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt), _ptr(out),
+            _ptr(probs_dbg), _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_decode_step_q8")
 
 
 def swa_prefill_rows(params: SwaParams, q_tail, R: int, k_cache, cache_len, ring, workspace,
                      stream=None) -> None:
-    _check(lib().swa_prefill_rows(ctypes.byref(params), _ptr(q_tail), int(R), _ptr(k_cache),
-                                  _ptr(cache_len), _ptr(ring), _ptr(workspace), _stream(stream)),
-           "swa_prefill_rows")
+    rc = _fast().swa_prefill_rows(params, q_tail, R, k_cache, cache_len, ring, workspace, stream)
+    if rc is None:
+        rc = lib().swa_prefill_rows(ctypes.byref(params), _ptr(q_tail), int(R), _ptr(k_cache), _ptr(cache_len), _ptr(ring),
+            _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_prefill_rows")
 
 
 def swa_decode_step_window(params: SwaParams, q, k_new, v_new, k_cache, v_cache, ring, R: int,
                            ring_row: int, score, pos, cache_len, seq_len, kept_idx, kept_cnt, out,
                            probs_dbg, workspace, stream=None) -> None:
-    _check(lib().swa_decode_step_window(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                        _ptr(k_cache), _ptr(v_cache), _ptr(ring), int(R),
-                                        int(ring_row), _ptr(score), _ptr(pos), _ptr(cache_len),
-                                        _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt), _ptr(out),
-                                        _ptr(probs_dbg), _ptr(workspace), _stream(stream)),
-           "swa_decode_step_window")
+    rc = _fast().swa_decode_step_window(params, q, k_new, v_new, k_cache, v_cache, ring, R, ring_row, score, pos, cache_len,
+        seq_len, kept_idx, kept_cnt, out, probs_dbg, workspace, stream)
+    if rc is None:
+        rc = lib().swa_decode_step_window(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
+            _ptr(v_cache), _ptr(ring), int(R), int(ring_row), _ptr(score), _ptr(pos), _ptr(cache_len), _ptr(seq_len),
+            _ptr(kept_idx), _ptr(kept_cnt), _ptr(out), _ptr(probs_dbg), _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_decode_step_window")
 
 
 def swa_decode_step_window_q8(params: SwaParams, q, k_new, v_new, k_codes, v_codes, qparams, ring, R: int,
                               ring_row: int, score, pos, cache_len, seq_len, kept_idx, kept_cnt, out,
                               probs_dbg, workspace, stream=None) -> None:
-    _check(lib().swa_decode_step_window_q8(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                           _ptr(k_codes), _ptr(v_codes), _ptr(qparams), _ptr(ring), int(R),
-                                           int(ring_row), _ptr(score), _ptr(pos), _ptr(cache_len),
-                                           _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt), _ptr(out),
-                                           _ptr(probs_dbg), _ptr(workspace), _stream(stream)),
-           "swa_decode_step_window_q8")
+    rc = _fast().swa_decode_step_window_q8(params, q, k_new, v_new, k_codes, v_codes, qparams, ring, R, ring_row, score, pos,
+        cache_len, seq_len, kept_idx, kept_cnt, out, probs_dbg, workspace, stream)
+    if rc is None:
+        rc = lib().swa_decode_step_window_q8(ctypes.byref(params), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_codes),
+            _ptr(v_codes), _ptr(qparams), _ptr(ring), int(R), int(ring_row), _ptr(score), _ptr(pos), _ptr(cache_len),
+            _ptr(seq_len), _ptr(kept_idx), _ptr(kept_cnt), _ptr(out), _ptr(probs_dbg), _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_decode_step_window_q8")
 
 
 def swa_prefill_attention(params: SwaParams, q, k_cache, v_cache, cache_len, out, R: int, score,
                           workspace, stream=None) -> None:
-    _check(lib().swa_prefill_attention(ctypes.byref(params), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                       _ptr(cache_len), _ptr(out), int(R), _ptr(score),
-                                       _ptr(workspace), _stream(stream)), "swa_prefill_attention")
+    rc = _fast().swa_prefill_attention(params, q, k_cache, v_cache, cache_len, out, R, score, workspace, stream)
+    if rc is None:
+        rc = lib().swa_prefill_attention(ctypes.byref(params), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(cache_len),
+            _ptr(out), int(R), _ptr(score), _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_prefill_attention")
 
 
 class HostStore:
@@ -290,9 +333,12 @@ def swa_probe_stream_read(src, nbytes: int, sink, stream=None) -> None:
 
 def swa_compact_kv(params: SwaParams, k_cache, v_cache, score, pos, kept_idx, kept_cnt, cache_len,
                    workspace, stream=None) -> None:
-    _check(lib().swa_compact_kv(ctypes.byref(params), _ptr(k_cache), _ptr(v_cache), _ptr(score),
-                                _ptr(pos), _ptr(kept_idx), _ptr(kept_cnt), _ptr(cache_len),
-                                _ptr(workspace), _stream(stream)), "swa_compact_kv")
+    rc = _fast().swa_compact_kv(params, k_cache, v_cache, score, pos, kept_idx, kept_cnt, cache_len, workspace, stream)
+    if rc is None:
+        rc = lib().swa_compact_kv(ctypes.byref(params), _ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(pos), _ptr(kept_idx),
+            _ptr(kept_cnt), _ptr(cache_len), _ptr(workspace), _stream(stream))
+    if rc != SWA_OK:
+        raise SwaError(rc, "swa_compact_kv")
 
 
 class DecodeState:

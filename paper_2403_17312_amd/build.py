@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libswa_hip.so")
+NATIVE_PATH = os.path.join(HERE, "_swa_native.so")
 SOURCES = ["swa_api.hip", "swa_decode.hip", "swa_short.hip", "swa_short_shared.hip", "swa_compact.hip", "swa_prefill.hip", "swa_quant.hip", "swa_flash.hip", "swa_offload.hip", "swa_splitk.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -37,10 +38,30 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_native() -> str:
+    """Compile the binding's native half (an extension module that reads torch tensors; host code only)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "swa_native.cpp"), "-o", NATIVE_PATH,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on swa_native.cpp:\n{r.stderr}")
+    return NATIVE_PATH
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every HIP source and link libswa_hip.so.  Always recompiles."""
+    """Compile every HIP source, link libswa_hip.so, and compile the binding's native half.  Always recompiles."""
     with ThreadPoolExecutor(max_workers=4) as ex:
+        native = ex.submit(build_native)
         objs = list(ex.map(_compile, SOURCES))
+        native.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
