@@ -1160,21 +1160,20 @@ static int launch_decode_nt(const DecodeArgs& a, int64_t pairs, size_t lds_bytes
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
+// Threads per workgroup that decode_block_threads() gives for a cache format: 128 or 256 on the 8-bit cache, else 256 or 512.
+template <typename T>
+constexpr int narrow_threads() { return Elem<T>::kBytes == 1 ? 128 : 256; }
+
 template <typename T, int D>
 static int launch_decode_t(const DecodeArgs& a, int64_t pairs, size_t lds_bytes, int nt, hipStream_t stream)
 {
+    constexpr int N = narrow_threads<T>();
     if (a.ring) {
-        switch (nt) {
-            case 128: return launch_decode_nt<T, D, 128, true>(a, pairs, lds_bytes, stream);
-            case 256: return launch_decode_nt<T, D, 256, true>(a, pairs, lds_bytes, stream);
-            default: return launch_decode_nt<T, D, 512, true>(a, pairs, lds_bytes, stream);
-        }
+        return nt == N ? launch_decode_nt<T, D, N, true>(a, pairs, lds_bytes, stream)
+                       : launch_decode_nt<T, D, 2 * N, true>(a, pairs, lds_bytes, stream);
     }
-    switch (nt) {
-        case 128: return launch_decode_nt<T, D, 128, false>(a, pairs, lds_bytes, stream);
-        case 256: return launch_decode_nt<T, D, 256, false>(a, pairs, lds_bytes, stream);
-        default: return launch_decode_nt<T, D, 512, false>(a, pairs, lds_bytes, stream);
-    }
+    return nt == N ? launch_decode_nt<T, D, N, false>(a, pairs, lds_bytes, stream)
+                   : launch_decode_nt<T, D, 2 * N, false>(a, pairs, lds_bytes, stream);
 }
 
 // Raise the dynamic-LDS limit of every instantiation to what the device allows next to the
@@ -1190,12 +1189,11 @@ static int prepare_one()
 template <typename T, int D>
 static int prepare_t()
 {
-    int rc = prepare_one<T, D, 128, false>();
-    if (rc == SWA_OK) rc = prepare_one<T, D, 256, false>();
-    if (rc == SWA_OK) rc = prepare_one<T, D, 512, false>();
-    if (rc == SWA_OK) rc = prepare_one<T, D, 128, true>();
-    if (rc == SWA_OK) rc = prepare_one<T, D, 256, true>();
-    if (rc == SWA_OK) rc = prepare_one<T, D, 512, true>();
+    constexpr int N = narrow_threads<T>();
+    int rc = prepare_one<T, D, N, false>();
+    if (rc == SWA_OK) rc = prepare_one<T, D, 2 * N, false>();
+    if (rc == SWA_OK) rc = prepare_one<T, D, N, true>();
+    if (rc == SWA_OK) rc = prepare_one<T, D, 2 * N, true>();
     return rc;
 }
 
