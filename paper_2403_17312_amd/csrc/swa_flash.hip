@@ -29,6 +29,7 @@ struct FlashArgs {
     const int32_t* cache_len;
     int32_t h, cap;
     int32_t pairs, nqb;    // (sequence, head) pairs and query blocks per pair in the grid
+    int32_t per_xcd, tail; // pairs per XCD, and how many of them (the last ones) are dealt out block by block
     float scale_log2e;
     float* stat;           // [pairs, cap]: statistics of the last R rows, stat_G copies stat_cols apart, or NULL
     int32_t R, stat_G, stat_cols;
@@ -39,6 +40,39 @@ constexpr int kXcds = 8;   // workgroups are dealt round-robin to the 8 XCDs, ea
 // Where the reference maximum of a row's running sum starts.  Finite, so that keys whose logit is -inf weigh nothing
 // (exp2(-inf - reference) = 0) also when they come before the row's first finite logit.
 constexpr float kNoReference = -3.0e38f;
+
+// Which queries a workgroup serves: `bq` of them from q0 on, of a prompt of s rows.  False: none.
+//
+// XCD-aware placement: the query blocks of one pair all read the same K and V, so they go to the same XCD, next to each other
+// in launch order, and share the pair's rows through that XCD's L2; the XCDs work on different pairs.  Longest blocks of
+// a pair first.  The last pairs of an XCD (a.tail of them, about 128 blocks, a little more than run at once) are dealt out
+// block by block instead: their longest blocks start together and the short ones fill in behind, where pair by
+// pair the last pair's longest block would run on alone.  32 pairs x 4096 rows, f16, d = 128: 177 -> 153 us; 128 of 300..1200
+// 48 -> 42; dealt out like that as a whole, large batches lose what the L2 gave them (2048 of 512..2048: 1253 -> 1919).
+// The blocks are laid from the prompt's end (to a multiple of 32, so that a wave's queries meet one diagonal tile): what is
+// left over is the first block, which has the fewest keys, and its idle waves cost least.  2048 pairs of 512..2048 rows 1253 -> 1196 us.
+__device__ __forceinline__ bool query_block(const FlashArgs& a, int bq, int64_t& pair, int& s, int& q0)
+{
+    const int idx = blockIdx.x / kXcds;
+    const int head = a.per_xcd - a.tail;
+    int at, qb;
+    if (idx < head * a.nqb) {
+        at = idx / a.nqb;
+        qb = a.nqb - 1 - (idx - at * a.nqb);
+    } else {
+        const int r = idx - head * a.nqb;
+        qb = a.nqb - 1 - r / a.tail;
+        at = head + r % a.tail;
+    }
+    pair = blockIdx.x % kXcds + (int64_t)kXcds * at;
+    if (pair >= a.pairs) return false;
+    s = a.cache_len[(uint32_t)pair / (uint32_t)a.h];
+    s = s > a.cap ? a.cap : s;
+    const int q_end = (s + 31) & ~31;
+    const int blocks = (q_end + bq - 1) / bq;
+    q0 = q_end - (blocks - qb) * bq;                     // (negative in a first block that is not full)
+    return qb < blocks;
+}
 
 // Half-precision element e (0..7) of a 16-byte vector, in the low 16 bits.
 __device__ __forceinline__ uint32_t half_of(const Vec16& v, int e)
@@ -113,18 +147,9 @@ swa_flash_prefill_kernel(FlashArgs a)
     const int wave = tid >> 6;
     const int l32 = lane & 31;
     const int hb = lane >> 5;
-    // XCD-aware placement: the query blocks of one pair all read the same K and V, so they go to
-    // the same XCD, next to each other in launch order, and share the pair's rows through that
-    // XCD's L2; the XCDs work on different pairs.  Longest blocks of a pair first.
-    const int xcd = blockIdx.x % kXcds;
-    const int idx = blockIdx.x / kXcds;
-    const int64_t pair = xcd + (int64_t)kXcds * (idx / a.nqb);
-    if (pair >= a.pairs) return;
-    int s = a.cache_len[pair / a.h];
-    s = s > a.cap ? a.cap : s;
-    const int qb = a.nqb - 1 - idx % a.nqb;
-    const int q0 = qb * BQ;
-    if (q0 >= s) return;
+    int64_t pair;
+    int s, q0;
+    if (!query_block(a, BQ, pair, s, q0)) return;
 
     const char* Qp = a.q + pair * (int64_t)a.cap * ROWB;
     const char* Kp = a.k + pair * (int64_t)a.cap * ROWB;
@@ -132,7 +157,7 @@ swa_flash_prefill_kernel(FlashArgs a)
     char* Op = a.out + pair * (int64_t)a.cap * ROWB;
 
     const int t = q0 + wave * 32 + l32;          // this lane's query position
-    const int tq = t < s ? t : s - 1;            // lanes past the prompt shadow the last query
+    const int tq = t < 0 ? 0 : (t < s ? t : s - 1);      // lanes outside the prompt shadow a query of it
     Vec16 qv[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) qv[v] = load16(Qp + (int64_t)tq * ROWB + v * 32 + hb * 16);
@@ -141,7 +166,7 @@ swa_flash_prefill_kernel(FlashArgs a)
     const int nkt = q_hi / BK + 1;                        // key tiles 0..nkt-1 cover keys 0..q_hi
     const int w_lo = q0 + wave * 32;
     const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
-    const int my_last = (w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
+    const int my_last = (w_lo >= 0 && w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
 
     // Which tile rows a thread stages.  With two chunks per thread (d = 128) they are an even key
     // and its successor, which sit next to each other in a lane's key order, so their values are
@@ -309,14 +334,14 @@ swa_flash_prefill_kernel(FlashArgs a)
     l = l_lo + l_hi;
     // the seed's column sums need these rows' statistics: handing them over saves it one of two reads of the keys
     const int r = t - (s - a.R);
-    if (a.stat && hb == 0 && t < s && r >= 0) {
+    if (a.stat && hb == 0 && t >= 0 && t < s && r >= 0) {
         float* St = a.stat + pair * (int64_t)a.cap;
         for (int g = 0; g < a.stat_G; ++g) {
             St[g * a.stat_cols + r] = m;
             St[g * a.stat_cols + a.R + r] = l;
         }
     }
-    if (t < s) {
+    if (t >= 0 && t < s) {
         const float inv = 1.f / l;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
@@ -410,18 +435,9 @@ swa_flash16_kernel(FlashArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31;
     const int hb = lane >> 5;
-    // XCD-aware placement: the query blocks of one pair all read the same K and V, so they go to
-    // the same XCD, next to each other in launch order, and share the pair's rows through that
-    // XCD's L2; the XCDs work on different pairs.  Longest blocks of a pair first.
-    const int xcd = blockIdx.x % kXcds;
-    const int idx = blockIdx.x / kXcds;
-    const int64_t pair = xcd + (int64_t)kXcds * (idx / a.nqb);
-    if (pair >= a.pairs) return;
-    int s = a.cache_len[pair / a.h];
-    s = s > a.cap ? a.cap : s;
-    const int qb = a.nqb - 1 - idx % a.nqb;
-    const int q0 = qb * BQ;
-    if (q0 >= s) return;
+    int64_t pair;
+    int s, q0;
+    if (!query_block(a, BQ, pair, s, q0)) return;
 
     const char* Qp = a.q + pair * (int64_t)a.cap * ROWB;
     const char* Kp = a.k + pair * (int64_t)a.cap * ROWB;
@@ -429,13 +445,13 @@ swa_flash16_kernel(FlashArgs a)
     char* Op = a.out + pair * (int64_t)a.cap * ROWB;
 
     const int t = q0 + wave * 32 + l32;          // this lane's query position
-    const int tq = t < s ? t : s - 1;            // lanes past the prompt shadow the last query
+    const int tq = t < 0 ? 0 : (t < s ? t : s - 1);      // lanes outside the prompt shadow a query of it
 
     const int q_hi = (q0 + BQ < s ? q0 + BQ : s) - 1;    // last query of the workgroup
     const int nkt = q_hi / BK + 1;                        // key tiles 0..nkt-1 cover keys 0..q_hi
     const int w_lo = q0 + wave * 32;
     const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
-    const int my_last = (w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
+    const int my_last = (w_lo >= 0 && w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
 
     // Load x of this wave covers tile rows (wave * LD + x) * RPI + lane / CPR; the lane's chunk of the LDS
     // row is lane % CPR.  The LDS serves 256 bytes a clock: 16 lanes of a fragment read (16 neighbouring rows
@@ -623,14 +639,14 @@ swa_flash16_kernel(FlashArgs a)
     l = l_lo + l_hi;
     // the seed's column sums need these rows' statistics: handing them over saves it one of two reads of the keys
     const int r = t - (s - a.R);
-    if (a.stat && hb == 0 && t < s && r >= 0) {
+    if (a.stat && hb == 0 && t >= 0 && t < s && r >= 0) {
         float* St = a.stat + pair * (int64_t)a.cap;
         for (int g = 0; g < a.stat_G; ++g) {
             St[g * a.stat_cols + r] = m;
             St[g * a.stat_cols + a.R + r] = l;
         }
     }
-    if (t < s) {
+    if (t >= 0 && t < s) {
         const float inv = 1.f / l;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
@@ -662,13 +678,15 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     const int bound = (p.len_bound > 0 && p.len_bound < p.cap) ? p.len_bound : p.cap;
     a.pairs = p.b * p.h;
     a.nqb = (bound + 127) / 128;
+    a.per_xcd = (a.pairs + kXcds - 1) / kXcds;
+    a.tail = (128 + a.nqb - 1) / a.nqb;
+    if (a.tail > a.per_xcd) a.tail = a.per_xcd;
     a.R = R;
     a.stat_G = a.stat_cols = 0;
     seed_stats_place(a.pairs, bound, p.cap, R, a.stat_G, a.stat_cols);
     a.stat = a.stat_G > 0 ? score : nullptr;
     stats_written = a.stat != nullptr;
-    const int64_t per_xcd = ((int64_t)a.pairs + kXcds - 1) / kXcds;
-    const int64_t wgs = per_xcd * kXcds * a.nqb;
+    const int64_t wgs = (int64_t)a.per_xcd * kXcds * a.nqb;
     if (wgs > 0x7fffffffLL) return SWA_ERR_BAD_SHAPE;
     const dim3 grid((unsigned)wgs);
     // The direct-to-LDS kernel has a longer start and end, which short prompts feel.  Staged through registers / direct in

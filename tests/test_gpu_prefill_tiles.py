@@ -75,3 +75,21 @@ def test_either_side_of_the_short_prompt_line(dtype, d, cap, bound, R):
             # fp32 logits, exponentials and sums over at most 256 keys and 128 rows, exponents up to about 10
             torch.testing.assert_close(score[i, :, :n].double(), pr[:, max(0, n - R):].sum(1), rtol=1e-5, atol=1e-12)
             assert bool((score[i, :, n:] == 0.0).all()), f"length {n}: score beyond the prompt"
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float16, 128), (torch.bfloat16, 64), (torch.float32, 64)])
+@pytest.mark.parametrize("b,h,bound", [(61, 7, 400), (1, 5, 700), (9, 1, 1100), (131, 8, 129)])
+def test_every_query_block_is_dealt_out_once(dtype, d, b, h, bound):
+    """Pairs dealt out one after the other, block by block, and both in one launch, against launches of one sequence each."""
+    from paper_2403_17312_amd import binding as B
+    g = torch.Generator(device="cuda").manual_seed(8)
+    lens = [(i * 37) % (bound + 1) for i in range(b - 1)] + [bound]
+    q, k, v = (torch.randn((b, h, bound, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(1024, dtype=torch.uint8, device="cuda")
+    got, one = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+    B.swa_prefill_attention(B.make_params(b, h, d, bound, 4, 8000, dtype), q, k, v, cl, got, 0, None, ws)
+    p = B.make_params(1, h, d, bound, 4, 8000, dtype)
+    for i in range(b):
+        B.swa_prefill_attention(p, q[i:i + 1], k[i:i + 1], v[i:i + 1], cl[i:i + 1], one[i:i + 1], 0, None, ws)
+    assert torch.equal(got, one)
