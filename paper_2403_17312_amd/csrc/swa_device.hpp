@@ -91,6 +91,13 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
     return f32x2_to_bf16x2_bits(f, 0.f) & 0xffffu;
 }
 
+// Two fp32 values rounded to fp16 (nearest even) in one dword: v_cvt_pk_f16_f32 on gfx950.
+__device__ __forceinline__ uint32_t f32x2_to_f16x2_bits(float lo, float hi)
+{
+    const float2_t f = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, half2_t));
+}
+
 __device__ __forceinline__ uint32_t f32_to_f16_bits(float f)
 {
     _Float16 h = (_Float16)f;
@@ -269,10 +276,10 @@ template <>
 __device__ __forceinline__ Vec16 pack<F16>(const float* f)
 {
     Vec16 v;
-    v.x = f32_to_f16_bits(f[0]) | (f32_to_f16_bits(f[1]) << 16);
-    v.y = f32_to_f16_bits(f[2]) | (f32_to_f16_bits(f[3]) << 16);
-    v.z = f32_to_f16_bits(f[4]) | (f32_to_f16_bits(f[5]) << 16);
-    v.w = f32_to_f16_bits(f[6]) | (f32_to_f16_bits(f[7]) << 16);
+    v.x = f32x2_to_f16x2_bits(f[0], f[1]);
+    v.y = f32x2_to_f16x2_bits(f[2], f[3]);
+    v.z = f32x2_to_f16x2_bits(f[4], f[5]);
+    v.w = f32x2_to_f16x2_bits(f[6], f[7]);
     return v;
 }
 template <>

@@ -98,12 +98,54 @@ __device__ __forceinline__ uint32_t pack2(float f0, float f1);
 template <>
 __device__ __forceinline__ uint32_t pack2<F16>(float f0, float f1)
 {
-    return f32_to_f16_bits(f0) | (f32_to_f16_bits(f1) << 16);
+    return f32x2_to_f16x2_bits(f0, f1);
 }
 template <>
 __device__ __forceinline__ uint32_t pack2<BF16>(float f0, float f1)
 {
     return f32x2_to_bf16x2_bits(f0, f1);
+}
+
+// The 16 weights of one lane's query and key tile, exp2(c scale - m), their sum, and the rescaling that goes with them.
+//
+// The reference m only has to bound the exponents, not equal the maximum (out = o / l whatever it is).  So the weights are
+// formed with the reference as it is, and only where a lane's sum shows that it is too low (some weight above
+// 2^8, or not finite, as on the first tile) is the tile's maximum looked for, the running output o and sum l rescaled
+// and the weights formed again: a few times per query.  With the maximum looked for on every tile, and fp16 weights rounded one
+// by one: 1792 pairs x 4096, bf16 6.96 -> 6.82 ms; 2048 of 512..2048, f16 1179 -> 1139 us, d = 64 695 -> 628.
+constexpr float kSlack = 8.f;           // how far (powers of two) a logit may exceed the reference
+constexpr float kTooMuch = 4096.f;      // sum of a lane's 16 weights beyond which one of them must exceed 2^kSlack
+template <int CT>
+__device__ __forceinline__ float tile_weights(const float16_t& c, float scale_log2e, float& m, float& l, float16_t (&o)[CT], float (&p)[16])
+{
+    float ps;
+    auto weights = [&]() __attribute__((always_inline)) {
+        ps = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(c[i], scale_log2e, -m));   // 0 for masked keys
+            ps += p[i];
+        }
+    };
+    weights();
+    if (__any(ps > kTooMuch)) {
+        float mx = c[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
+        float mx_lo, mx_hi;
+        both_halves(mx, mx_lo, mx_hi);
+        mx = fmaxf(mx_lo, mx_hi) * scale_log2e;       // scale > 0: max commutes
+        const float m_new = (mx > m + kSlack) ? mx : m;
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);     // 0 on the first tile
+        m = m_new;
+        l *= alpha;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[ct][i] *= alpha;
+        weights();
+    }
+    return ps;
 }
 
 // Tiles staged through registers, double-buffered, the value tile transposed on its way into LDS: short prompts in
@@ -128,7 +170,6 @@ swa_flash_prefill_kernel(FlashArgs a)
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
     constexpr int LD = BK * CPR / NT;   // chunks per thread, per tensor and tile
     constexpr bool kPaired = EB == 2 && LD == 2;
-    constexpr float kSlack = 8.f;       // how far (powers of two) a tile maximum may exceed the reference maximum
     constexpr int PF = 3;               // LDS fragment reads in flight ahead of the product that uses them
     constexpr int NBUF = (EB == 4 && D == 128) ? 1 : 2;   // LDS buffers (64 KB of static LDS at most)
     static_assert(LD >= 1 && BK * CPR % NT == 0, "tile must split evenly over the workgroup");
@@ -276,34 +317,9 @@ swa_flash_prefill_kernel(FlashArgs a)
                     c[i] = (key <= tq) ? c[i] : -INFINITY;
                 }
             }
-            float mx = c[0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
-            float mx_lo, mx_hi;
-            both_halves(mx, mx_lo, mx_hi);
-            mx = fmaxf(mx_lo, mx_hi) * a.scale_log2e;     // scale > 0: max commutes
-            // The reference only has to bound the exponents, not equal the true maximum (out = o / l
-            // whatever it is): it follows the tile maximum only when that exceeds it by more than kSlack
-            // powers of two, so the weights stay below 2^kSlack and the running output is rescaled
-            // a few times per query instead of at every new maximum.
-            const float m_new = (mx > m + kSlack) ? mx : m;
-            const float alpha = __builtin_amdgcn_exp2f(m - m_new);     // 0 on the first tile, else mostly 1
             float p[16];
-            float ps = 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(c[i], a.scale_log2e, -m_new));   // 0 for masked keys
-                ps += p[i];
-            }
-            l = l * alpha + ps;
-            m = m_new;
-            // the running maximum settles after a few tiles: rescale only when some query's moved
-            if (__any(alpha != 1.f)) {
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[ct][i] *= alpha;
-            }
+            const float ps = tile_weights(c, a.scale_log2e, m, l, o, p);
+            l += ps;
             Vec16 pv[NP];
 #pragma unroll
             for (int v = 0; v < NP; ++v) pv[v] = pack<T>(p + v * EPV);
@@ -407,32 +423,41 @@ __device__ __forceinline__ uint32_t lds_address(const char* p)
 //   - Three buffers, two tiles ahead: 7.5 ms.
 //   - The loads of a tile are issued between the products of another instead of all at once: 7.1 ms.
 // Three waves per SIMD (168 registers, 48 KB of LDS per workgroup) at d = 128, four at d = 64.
-template <typename T, int D>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 3)))
+//
+// QW waves of 32 queries each, times KS groups of them that share the keys: group g takes the tiles g, g + KS, ... with LDS
+// buffers of its own, and the groups' sums are merged at the end.  KS > 1 is for grids that leave the chip idle (flash_form).
+template <typename T, int D, int QW, int KS>
+__global__ void __launch_bounds__(64 * QW * KS) __attribute__((amdgpu_waves_per_eu(KS > 1 ? 2 : (D == 64 ? 4 : 3))))
 swa_flash16_kernel(FlashArgs a)
 {
-    constexpr int NW = 4;
     constexpr int ROWB = D * 2;
     constexpr int NV = ROWB / 32;       // 16-byte fragments a lane supplies for a 32-row operand
     constexpr int CT = D / 32;          // 32-channel tiles of the output
     constexpr int BK = 32;              // keys per tile
-    constexpr int BQ = 128;             // queries per workgroup
+    constexpr int BQ = 32 * QW;         // queries per workgroup
+    constexpr int TILE = BK * ROWB;
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
     constexpr int RPI = kWave / CPR;    // rows that one wave-wide load covers
-    constexpr int LD = BK / RPI / NW;   // such loads per wave, per tensor and tile
+    constexpr int LD = BK / RPI / QW;   // such loads per wave, per tensor and tile
+    constexpr int LPS = 4 * LD / NV;    // of them behind every second product of the first contraction
     constexpr int PF = 2;               // LDS fragment reads in flight ahead of the product that uses them
-    constexpr float kSlack = 8.f;       // how far (powers of two) a tile maximum may exceed the reference maximum
 
-    __shared__ __align__(1024) char s_k0[BK * ROWB];
-    __shared__ __align__(1024) char s_k1[BK * ROWB];
-    __shared__ __align__(1024) char s_v0[BK * ROWB];
-    __shared__ __align__(1024) char s_v1[BK * ROWB];
-    __shared__ __align__(1024) char s_k2[BK * ROWB];
-    __shared__ __align__(1024) char s_v2[BK * ROWB];
+    // three buffers for a key and a value tile: of the workgroup, or (dynamic) of every group
+    constexpr int OWN = KS == 1 ? TILE : 16;
+    __shared__ __align__(1024) char o_k0[OWN], o_k1[OWN], o_v0[OWN], o_v1[OWN], o_k2[OWN], o_v2[OWN];
+    extern __shared__ __align__(1024) char smem[];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % QW;      // within its group
+    const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / QW;
+    char* const mine = KS == 1 ? nullptr : smem + kg * 6 * TILE;
+    char* const s_k0 = KS == 1 ? o_k0 : mine;
+    char* const s_v0 = KS == 1 ? o_v0 : mine + TILE;
+    char* const s_k1 = KS == 1 ? o_k1 : mine + 2 * TILE;
+    char* const s_v1 = KS == 1 ? o_v1 : mine + 3 * TILE;
+    char* const s_k2 = KS == 1 ? o_k2 : mine + 4 * TILE;
+    char* const s_v2 = KS == 1 ? o_v2 : mine + 5 * TILE;
     const int l32 = lane & 31;
     const int hb = lane >> 5;
     int64_t pair;
@@ -448,10 +473,15 @@ swa_flash16_kernel(FlashArgs a)
     const int tq = t < 0 ? 0 : (t < s ? t : s - 1);      // lanes outside the prompt shadow a query of it
 
     const int q_hi = (q0 + BQ < s ? q0 + BQ : s) - 1;    // last query of the workgroup
-    const int nkt = q_hi / BK + 1;                        // key tiles 0..nkt-1 cover keys 0..q_hi
+    const int all_tiles = q_hi / BK + 1;                  // key tiles 0..all_tiles-1 cover keys 0..q_hi
+    // This group's tiles, counted 0..nkt-1; tile kt is tile kg + KS kt of the prompt.  Every wave passes `rounds` barriers.
+    const int rounds = (all_tiles + KS - 1) / KS;
+    const int nkt = KS == 1 ? all_tiles : (all_tiles - kg + KS - 1) / KS;
+    auto key0 = [&](int kt) { return (kg + KS * kt) * BK; };
     const int w_lo = q0 + wave * 32;
     const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
-    const int my_last = (w_lo >= 0 && w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
+    const int last_tile = (w_lo >= 0 && w_lo < s) ? w_hi / BK : -1;
+    const int my_last = KS == 1 ? last_tile : (last_tile >= kg ? (last_tile - kg) / KS : -1);   // last one with a visible key for this wave
 
     // Load x of this wave covers tile rows (wave * LD + x) * RPI + lane / CPR; the lane's chunk of the LDS
     // row is lane % CPR.  The LDS serves 256 bytes a clock: 16 lanes of a fragment read (16 neighbouring rows
@@ -476,10 +506,10 @@ swa_flash16_kernel(FlashArgs a)
     // Load x = 0 .. 2 LD - 1 of the staging of tile kt (uniform base; cap <= SWA_MAX_CAP: below 8 MiB).  Before the
     // prompt's last tile, which no full one follows, edge() aims the lanes at rows that exist.
     auto edge = [&](int kt) {
-        if (kt * BK + BK > s) offsets(s - 1 - kt * BK);
+        if (key0(kt) + BK > s) offsets(s - 1 - key0(kt));
     };
     auto load = [&](int x, int kt, char* dk, char* dv) {
-        const uint32_t at = (uint32_t)kt * (BK * ROWB);
+        const uint32_t at = (uint32_t)key0(kt) * ROWB;
         if (x < LD) load_to_lds(Kp + at, offK[x], lds_address(dk) + (wave * LD + x) * 1024);
         else load_to_lds(Vp + at, offV[x - LD], lds_address(dv) + (wave * LD + x - LD) * 1024);
     };
@@ -490,7 +520,7 @@ swa_flash16_kernel(FlashArgs a)
     };
     offsets(BK);
 
-    stage(0, s_k0, s_v0);
+    if (KS == 1 || nkt > 0) stage(0, s_k0, s_v0);
     Vec16 qv[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) qv[v] = load16(Qp + (int64_t)tq * ROWB + v * 32 + hb * 16);
@@ -536,43 +566,20 @@ swa_flash16_kernel(FlashArgs a)
             __builtin_amdgcn_sched_barrier(0);
             // the loads of a later tile are issued between the products, which hide the time they wait to be
             // accepted: the four waves' sixteen 1 KiB loads together keep the CU's 64-byte path busy for 256 clocks
-            if ((v & 1) && more) load(v >> 1, st, nk, nv);
+            if ((v & 1) && more)
+#pragma unroll
+                for (int x = 0; x < LPS; ++x) load((v >> 1) * LPS + x, st, nk, nv);
         }
         // only the tiles that reach the wave's diagonal need the causal mask
-        if (kt * BK + BK - 1 > w_lo) {
+        if (key0(kt) + BK - 1 > w_lo) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int key = kt * BK + 8 * (i / 4) + 4 * hb + (i % 4);
+                const int key = key0(kt) + 8 * (i / 4) + 4 * hb + (i % 4);
                 c[i] = (key <= tq) ? c[i] : -INFINITY;
             }
         }
-        float mx = c[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, c[i]);
-        float mx_lo, mx_hi;
-        both_halves(mx, mx_lo, mx_hi);
-        mx = fmaxf(mx_lo, mx_hi) * a.scale_log2e;     // scale > 0: max commutes
-        // The reference only has to bound the exponents, not equal the true maximum (out = o / l
-        // whatever it is): it follows the tile maximum only when that exceeds it by more than kSlack
-        // powers of two, so the weights stay below 2^kSlack and the running output is rescaled
-        // a few times per query instead of at every new maximum.
-        if (__any(mx > m + kSlack)) {
-            const float m_new = (mx > m + kSlack) ? mx : m;
-            const float alpha = __builtin_amdgcn_exp2f(m - m_new);     // 0 on the first tile
-            m = m_new;
-            l *= alpha;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[ct][i] *= alpha;
-        }
         float p[16];
-        float ps = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(c[i], a.scale_log2e, -m));   // 0 for masked keys
-            ps += p[i];
-        }
+        const float ps = tile_weights(c, a.scale_log2e, m, l, o, p);
         l += ps;
         Vec16 pv[2];
         pv[0] = pack<T>(p);
@@ -633,6 +640,38 @@ swa_flash16_kernel(FlashArgs a)
             stage(st, buf == 0 ? s_k2 : (buf == 1 ? s_k0 : s_k1), buf == 0 ? s_v2 : (buf == 1 ? s_v0 : s_v1));
         }
     }
+    if constexpr (KS > 1) {
+        for (int r = nkt; r < rounds; ++r) ready(false);
+        // The groups' sums over their keys, to the first group's waves.  No load is on its way any more; the buffers are free
+        // once every wave has arrived.
+        constexpr int PER = CT * 16 + 2;
+        float* part = reinterpret_cast<float*>(smem) + lane;
+        __syncthreads();
+        if (kg > 0) {
+            float* p = part + ((kg - 1) * QW + wave) * PER * kWave;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) p[(ct * 16 + i) * kWave] = o[ct][i];
+            p[(PER - 2) * kWave] = m;
+            p[(PER - 1) * kWave] = l;
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int g = 1; g < KS; ++g) {
+            const float* p = part + ((g - 1) * QW + wave) * PER * kWave;
+            const float m2 = p[(PER - 2) * kWave], l2 = p[(PER - 1) * kWave];
+            const float top = fmaxf(m, m2);
+            const float f1 = __builtin_amdgcn_exp2f(m - top), f2 = __builtin_amdgcn_exp2f(m2 - top);
+            m = top;
+            l = l * f1 + l2 * f2;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[ct][i] = o[ct][i] * f1 + p[(ct * 16 + i) * kWave] * f2;
+        }
+    }
 
     float l_lo, l_hi;
     both_halves(l, l_lo, l_hi);
@@ -662,6 +701,37 @@ swa_flash16_kernel(FlashArgs a)
     }
 }
 
+// The grid for blocks of bq queries and prompts of at most `bound` rows (false: more workgroups than a launch can have).
+static bool flash_grid(FlashArgs& a, int bound, int bq, int64_t& wgs)
+{
+    a.nqb = (bound + bq - 1) / bq;
+    a.per_xcd = (a.pairs + kXcds - 1) / kXcds;
+    a.tail = (128 + a.nqb - 1) / a.nqb;
+    if (a.tail > a.per_xcd) a.tail = a.per_xcd;
+    wgs = (int64_t)a.per_xcd * kXcds * a.nqb;
+    return wgs <= 0x7fffffffLL;
+}
+
+template <typename T, int D, int QW, int KS>
+static int launch_flash16_form(FlashArgs a, int bound, hipStream_t stream)
+{
+    int64_t wgs = 0;
+    if (!flash_grid(a, bound, 32 * QW, wgs)) return SWA_ERR_BAD_SHAPE;
+    constexpr size_t lds = KS == 1 ? 0 : (size_t)KS * 6 * 32 * D * 2;
+    static_assert(KS == 1 || lds >= (size_t)(KS - 1) * QW * (D / 2 + 2) * 256, "the groups' sums fit where the tiles were");
+    auto kern = swa_flash16_kernel<T, D, QW, KS>;
+    const int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (rc != SWA_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * QW * KS), lds, stream, a);
+    return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
+}
+
+template <typename T, int D>
+static int launch_flash16(const FlashArgs& a, int bound, hipStream_t stream)
+{
+    return launch_flash16_form<T, D, 4, 1>(a, bound, stream);
+}
+
 int launch_flash_prefill(const swa_params& p, float scale, const void* q, const void* k_cache, const void* v_cache,
                          const int32_t* cache_len, void* out, int32_t R, float* score, bool& stats_written,
                          hipStream_t stream)
@@ -677,31 +747,27 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     a.scale_log2e = scale * 1.44269504088896340736f;
     const int bound = (p.len_bound > 0 && p.len_bound < p.cap) ? p.len_bound : p.cap;
     a.pairs = p.b * p.h;
-    a.nqb = (bound + 127) / 128;
-    a.per_xcd = (a.pairs + kXcds - 1) / kXcds;
-    a.tail = (128 + a.nqb - 1) / a.nqb;
-    if (a.tail > a.per_xcd) a.tail = a.per_xcd;
     a.R = R;
     a.stat_G = a.stat_cols = 0;
     seed_stats_place(a.pairs, bound, p.cap, R, a.stat_G, a.stat_cols);
     a.stat = a.stat_G > 0 ? score : nullptr;
     stats_written = a.stat != nullptr;
-    const int64_t wgs = (int64_t)a.per_xcd * kXcds * a.nqb;
-    if (wgs > 0x7fffffffLL) return SWA_ERR_BAD_SHAPE;
-    const dim3 grid((unsigned)wgs);
     // The direct-to-LDS kernel has a longer start and end, which short prompts feel.  Staged through registers / direct in
     // us, f16 at d = 128, bf16 at d = 128, f16 at d = 64: 256 x 40 pairs of 32 rows 250 / 255, 232 / 242, 114 / 117; 256 x 32 of
     // 60..250 rows 523 / 535, 511 / 527, 281 / 286; 64 x 32 of 128..512 rows 167 / 160, 161 / 156, 95 / 87 (longer
     // ones: up to 1.25 times as fast).
     const bool direct = p.dtype != SWA_F32 && bound > 256;
+    if (direct) {
+        if (p.dtype == SWA_F16) return p.d == 64 ? launch_flash16<F16, 64>(a, bound, stream) : launch_flash16<F16, 128>(a, bound, stream);
+        return p.d == 64 ? launch_flash16<BF16, 64>(a, bound, stream) : launch_flash16<BF16, 128>(a, bound, stream);
+    }
+    int64_t wgs = 0;
+    if (!flash_grid(a, bound, 128, wgs)) return SWA_ERR_BAD_SHAPE;
     auto go = [&](auto small, auto large) {
-        if (p.d == 64) hipLaunchKernelGGL(small, grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL(large, grid, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(p.d == 64 ? small : large, dim3((unsigned)wgs), dim3(256), 0, stream, a);
     };
     if (p.dtype == SWA_F32) go(swa_flash_prefill_kernel<F32, 64>, swa_flash_prefill_kernel<F32, 128>);
-    else if (p.dtype == SWA_F16 && direct) go(swa_flash16_kernel<F16, 64>, swa_flash16_kernel<F16, 128>);
     else if (p.dtype == SWA_F16) go(swa_flash_prefill_kernel<F16, 64>, swa_flash_prefill_kernel<F16, 128>);
-    else if (direct) go(swa_flash16_kernel<BF16, 64>, swa_flash16_kernel<BF16, 128>);
     else go(swa_flash_prefill_kernel<BF16, 64>, swa_flash_prefill_kernel<BF16, 128>);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
