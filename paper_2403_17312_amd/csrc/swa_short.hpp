@@ -231,7 +231,8 @@ swa_short_kernel(DecodeArgs a)
 #pragma unroll
             for (int u = C; u < U; ++u) z[u] = 0.f;
         };
-        float p[SL], sc[SL];
+        // the output is formed with the exponentials themselves, one rounding less than with the weights p
+        float p[SL], ex[SL], sc[SL];
         if constexpr (PHASE != 2) {
         const int stages = (m + NG * UE - 1) / (NG * UE);
         if (stages <= 1) rows(std::integral_constant<int, UE>());
@@ -269,6 +270,7 @@ swa_short_kernel(DecodeArgs a)
         }
 #pragma unroll
         for (int k = 0; k < SL; ++k) {
+            ex[k] = p[k];
             p[k] = p[k] / sum;
             const int i = lane + k * kWave;
             if (i >= len) {
@@ -333,7 +335,7 @@ swa_short_kernel(DecodeArgs a)
 #pragma unroll
             for (int k = 0; k < SL; ++k) {
                 const int i = lane + k * kWave;
-                p[k] = i < m ? pw[k] : 0.f;
+                ex[k] = p[k] = i < m ? pw[k] : 0.f;
                 sc[k] = sold[k];
                 if (i >= len) pold[k] = n - 1;
             }
@@ -428,12 +430,13 @@ swa_short_kernel(DecodeArgs a)
         }
 
         // ---- output: sum over the kept rows, in registers -------------------------------------
-        float pk[SL];
+        float pk[SL];                                    // (negative: not kept)
         float ps = 0.f;
 #pragma unroll
         for (int k = 0; k < SL; ++k) {
-            pk[k] = ((kept[k] >> lane) & 1ull) ? p[k] : 0.f;
-            ps += pk[k];
+            const bool in = (kept[k] >> lane) & 1ull;
+            pk[k] = in ? ex[k] : -1.f;
+            ps += in ? ex[k] : 0.f;
         }
         ps = wave_sum(ps);
         // the new token's share, in one group of rows
@@ -446,7 +449,7 @@ swa_short_kernel(DecodeArgs a)
             float f[EPV];
             unpack<T>(nv, f);
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) acc[e] = (grp == 0 && wn != 0.f) ? wn * f[e] : 0.f;
+            for (int e = 0; e < EPV; ++e) acc[e] = (grp == 0 && !(wn < 0.f)) ? wn * f[e] : 0.f;
         }
         bool subtract = false;
         if constexpr (PHASE == 2) {
@@ -489,7 +492,7 @@ swa_short_kernel(DecodeArgs a)
             const int row = u * NG + grp;
             float wr = w[u];
             Vec16 x = vv[u];
-            if (row >= len || wr == 0.f) {                 // evicted, new or past the end: whatever the slot holds
+            if (row >= len || wr < 0.f) {                  // evicted, new or past the end: whatever the slot holds
                 wr = 0.f;
                 x = Vec16{0u, 0u, 0u, 0u};
             }

@@ -116,3 +116,29 @@ def test_a_cache_beyond_the_stated_bound_is_skipped_and_reported():
     st.decode_compact_step(q, q, q)
     assert st.check_status() == B.SWA_ERR_CAPACITY and st.cache_len.tolist()[1:] == [64, 299]
     assert bool((st.out[1:] == 7.0).all()) and not bool((st.out[0] == 7.0).any()) and torch.equal(st.score[1:], before[1:])
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("evict", [0, 1, 3])
+def test_a_kept_row_counts_although_its_weight_underflows(dtype, evict):
+    """0 x inf of a kept value row is NaN as in the sum over the kept rows; what an evicted row holds does not matter."""
+    from paper_2403_17312_amd import binding as B
+    b, h, d, cap, n = 2, 3, 128, 300, 60
+    x = {"cl": torch.tensor([n, n], dtype=torch.int32, device="cuda"),
+         "sl": torch.tensor([5 * (n + 1 - evict)] * 2, dtype=torch.int32, device="cuda")}
+    g = torch.Generator(device="cuda").manual_seed(evict)
+    x["K"], x["V"] = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    x["kn"], x["vn"] = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    x["q"] = torch.ones((b, h, d), dtype=dtype, device="cuda")
+    x["score"] = torch.ones((b, h, cap), device="cuda")
+    x["score"][..., :evict] = 0.0                                   # these go
+    x["pos"] = torch.arange(cap, dtype=torch.int32, device="cuda").repeat(b, h, 1).contiguous()
+    x["K"][:, :, [0, 20]] = -30.0                                   # logits 340 below the others: weight 0
+    x["V"][0, :, 0, 5] = float("inf")                               # (evicted, if anything is)
+    x["V"][1, :, 20, 7] = float("inf")                              # kept
+    out = _step(B, "unordered", dtype, d, cap, b, h, x, 64, 0)["out"].float()
+    want = torch.zeros((b, h, d), dtype=torch.bool, device="cuda")
+    want[1, :, 7] = True
+    if evict == 0:
+        want[0, :, 5] = True
+    assert torch.equal(out.isnan(), want)
