@@ -23,7 +23,7 @@ FLAGS = [
 
 # MFMA kernels: keep the accumulators in ordinary vector registers (no copies in and out of the
 # accumulation file around every softmax step).
-EXTRA = {"swa_flash.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("swa_flash.hip", "swa_prefill.hip")}
 
 
 def _compile(src: str) -> str:

@@ -18,6 +18,8 @@
 //           (row statistics reduce inside the lane);
 //   pass 2: A = query tile, B = key tile   -> lane owns ONE key, 16 queries
 //           (column sums reduce inside the lane).
+#include <type_traits>
+
 #include "swa_kernels.hpp"
 
 namespace swa {
@@ -34,18 +36,18 @@ struct PrefillArgs {
     float scale_log2e;
     // For the column sums the columns are cut into G slices of `cols` (a multiple of 32; the last one ends at cap), one
     // workgroup each.
-    // A slice's first 2 R output columns (score, or row 0 of the ring) bring it the row statistics from the
-    // launch before: maximum of row r at [r], normaliser at [R + r].
+    // A slice's first 2 R `chains` output columns (score, or row 0 of the ring) bring it the row statistics from the
+    // launch before: for every chain maximum of row r at [r], normaliser at [R + r], the next chain's 2 R columns further on.
     int32_t G, cols;
     int32_t bound;        // on the lengths: where the slices are laid (host side)
     bool stated;          // the bound is the caller's, not the capacity (host side)
-    int32_t row_tiles;    // statistics: workgroups per pair, one for every 32 query rows
+    int32_t chains;       // statistics: parts of the keys whose sums are still to be merged, kChains or 1
 };
 
 // What one launch does.
 constexpr int kSeedWhole = 0;   // both passes, one workgroup per pair
-constexpr int kSeedStats = 1;   // row statistics of one pair, a copy for every slice
-constexpr int kSeedSums = 2;    // column sums of one slice, from the statistics of whole rows
+constexpr int kSeedSums = 1;    // column sums of one slice, from the row statistics of another launch
+constexpr int kChains = 4;      // row statistics: key tile t belongs to chain t % 4, whose sums are merged in ascending order
 
 // Merge two (max, sum-of-exp2) pairs of disjoint key sets.
 __device__ __forceinline__ void merge_stats(float& M, float& L, float M2, float L2)
@@ -56,6 +58,191 @@ __device__ __forceinline__ void merge_stats(float& M, float& L, float M2, float 
     const float b = (M2 == -INFINITY) ? 0.f : L2 * exp2f(M2 - Mn);
     M = Mn;
     L = a + b;
+}
+
+// Row statistics of this lane's query after one more key tile: C[key][query] of the tile, its keys up to tmax (the
+// last one that the query sees).
+__device__ __forceinline__ void add_tile_stats(const float16_t& c, int tile, int hb, int tmax, float scale_log2e, float& M, float& L)
+{
+    float z[16];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int key = tile * 32 + 8 * (i / 4) + 4 * hb + (i % 4);
+        z[i] = (key <= tmax) ? c[i] * scale_log2e : -INFINITY;
+        mx = fmaxf(mx, z[i]);
+    }
+    if (mx > -INFINITY) {
+        const float Mn = fmaxf(M, mx);
+        float acc = L * __builtin_amdgcn_exp2f(M - Mn);   // 0 while M is -inf
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc += __builtin_amdgcn_exp2f(z[i] - Mn);
+        M = Mn;
+        L = acc;
+    }
+}
+
+// The same without branches, for tiles that every row sees to their end (SEEN) or any.
+template <bool SEEN>
+__device__ __forceinline__ void add_tile_stats_flat(const float16_t& c, int tile, int hb, int tmax, float scale_log2e, float& M,
+                                                    float& L)
+{
+#pragma clang fp contract(off)
+    float z[16];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int key = tile * 32 + 8 * (i / 4) + 4 * hb + (i % 4);
+        z[i] = c[i] * scale_log2e;
+        if (!SEEN) z[i] = (key <= tmax) ? z[i] : -INFINITY;
+        mx = fmaxf(mx, z[i]);
+    }
+    const float Mn = fmaxf(M, mx);
+    float acc = __builtin_fmaf(L, __builtin_amdgcn_exp2f(M - Mn), __builtin_amdgcn_exp2f(z[0] - Mn));   // (0 + .. while M is -inf)
+#pragma unroll
+    for (int i = 1; i < 16; ++i) acc += __builtin_amdgcn_exp2f(z[i] - Mn);
+    asm volatile("" : "+v"(acc));                         // (formed in any case: a branch here would end the overlap)
+    L = mx > -INFINITY ? acc : L;
+    M = mx > -INFINITY ? Mn : M;
+}
+
+// Row statistics of 32 query rows over one chain of key tiles (NW = 1) or over all four, merged (NW = 4): the same sums in the
+// same order as in the kernel below, whose pass 1 this is where a pair's keys are long and pairs few.
+//
+// Bound: the chain of a tile's steps in the one wave that owns it, 0.6 us a tile (32 pairs x 8192 keys, f16, d = 128, R =
+// 64: 38 us; 60 with the operands' own layout and 64 workgroups).  A tile's rows are loaded as they lie, whole lines by one
+// instruction (an operand's own layout takes 32 bytes of a line at a time, and lines were lost between their
+// uses), and reach that layout by way of LDS, in which a row's 16-byte chunks are permuted by the row
+// so that the lanes of a read spread over the banks.  A chain cannot be cut (its sum has an order), so its one wave
+// overlaps what a tile needs: loads, LDS, products and exponentials of different tiles.
+template <typename T, int D, bool WR, int NW>
+__global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(1, 1)))
+swa_seed_stats_kernel(PrefillArgs a)
+{
+    constexpr int ROWB = D * Elem<T>::kBytes;
+    constexpr int NV = (ROWB / 2) / 16;
+    constexpr int CPR = ROWB / 16;                   // chunks of a row
+    constexpr int RPI = kWave / CPR;                 // rows per load instruction
+    constexpr int NL = 32 / RPI;                     // loads per lane and tile
+    constexpr int AHEAD = ROWB >= 512 ? 2 : 4;      // tiles requested ahead, 32 KiB of them (even: fragments alternate)
+    constexpr int NF = ROWB >= 512 ? 1 : 2;         // tiles of fragments (rows of 512 bytes leave no registers for a second)
+    __shared__ __align__(16) char s_tile[NW][32 * ROWB];
+    __shared__ float s_m[NW][32], s_l[NW][32];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int l32 = lane & 31;
+    const int hb = lane >> 5;
+    // the row tiles of a pair read the same keys: their workgroups are a multiple of the number of XCDs apart
+    // where the pairs are, and share an L2
+    const uint32_t per = (uint32_t)(kChains / NW), all = gridDim.x / (uint32_t)((a.R + 31) / 32);
+    const int rt0 = (int)(blockIdx.x / all);
+    const int64_t pair = (blockIdx.x % all) / per;
+    const int chain = NW == 1 ? (int)(blockIdx.x % per) : wave;
+    const int cap = a.cap;
+    const int R = a.R;
+    int s = a.cache_len[pair / a.h];
+    s = s > cap ? cap : s;
+    if (s <= 0) return;
+    const char* Kp = a.k_cache + pair * (int64_t)cap * ROWB;
+    const int qbase = a.q_in_place ? s - R : 0;
+    const char* Qp = a.q_tail + pair * (int64_t)(a.q_in_place ? cap : R) * ROWB;
+    const int r = rt0 * 32 + l32;
+    const int qrow = qbase + r > 0 ? qbase + r : 0;
+    Vec16 qv[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        qv[v] = (r < R) ? load16(Qp + (int64_t)qrow * ROWB + v * 32 + hb * 16) : Vec16{0u, 0u, 0u, 0u};
+    const int tmax = (r < R) ? s - R + r : -1;
+    const int tiles = (s + 31) / 32;
+
+    const int lrow = lane / CPR, lchunk = lane % CPR;
+    const uint32_t lane_at = (uint32_t)lrow * ROWB + (uint32_t)lchunk * 16, last_at = (uint32_t)(s - 1) * ROWB + (uint32_t)lchunk * 16;
+    // tile t of the chain (unconditional: rows past the end re-read the last one and are masked)
+    auto request = [&](int t, Vec16(&kr)[NL]) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const uint32_t at = lane_at + (uint32_t)((chain + t * kChains) * 32 + j * RPI) * ROWB;
+            kr[j] = load16(Kp + (at < last_at ? at : last_at));
+        }
+    };
+    char* buf = s_tile[wave];
+    auto stage = [&](const Vec16(&kr)[NL], Vec16(&f)[NV]) {
+        __builtin_amdgcn_wave_barrier();             // (a wave's LDS accesses are carried out in order)
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int row = j * RPI + lrow;
+            *reinterpret_cast<Vec16*>(buf + row * ROWB + ((lchunk ^ (row & (CPR - 1))) * 16)) = kr[j];
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            f[v] = *reinterpret_cast<const Vec16*>(buf + l32 * ROWB + (((2 * v + hb) ^ (l32 & (CPR - 1))) * 16));
+    };
+    auto products = [&](const Vec16(&f)[NV]) -> float16_t {
+        float16_t c;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) c = Mfma<T>::run(f[v], qv[v], c);      // C[key][query]
+        return c;
+    };
+    // While a tile's weights are summed, the next one's products run and the rows of the one behind it go through LDS.
+    float M = -INFINITY, L = 0.f;
+    const int nt = (tiles - chain + kChains - 1) / kChains;      // (0 or less: nothing to do)
+    const int seen = (s - R + rt0 * 32 + 1) / 32;                // tiles below it: every row sees all keys
+    Vec16 kr[AHEAD][NL], f[NF][NV];
+    float16_t c;
+    if (nt > 0) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) request(u, kr[u]);
+        stage(kr[0], f[0]);
+        c = products(f[0]);
+        stage(kr[1], f[1 % NF]);
+        request(AHEAD, kr[0]);
+        request(AHEAD + 1, kr[1]);
+    }
+    for (int t = 0; t < nt; t += AHEAD) {
+        auto some = [&](auto all_seen) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                if (NF > 1) stage(kr[(u + 2) % AHEAD], f[u % NF]);          // tile t + u + 2
+                const float16_t next = products(f[(u + 1) % NF]);
+                if (NF == 1) stage(kr[(u + 2) % AHEAD], f[0]);
+                add_tile_stats_flat<all_seen.value>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 64 / NV + 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x400, 16 / NV, 0);
+                }
+                c = next;
+                request(t + u + AHEAD + 2, kr[(u + 2) % AHEAD]);
+            }
+        };
+        if (chain + (t + AHEAD - 1) * kChains < seen) some(std::true_type());
+        else some(std::false_type());
+    }
+    const float M2 = __shfl_xor(M, 32, kWave);
+    const float L2 = __shfl_xor(L, 32, kWave);
+    merge_stats(M, L, M2, L2);
+    if constexpr (NW > 1) {
+        if (hb == 0) {
+            s_m[wave][l32] = M;
+            s_l[wave][l32] = L;
+        }
+        __syncthreads();
+        if (wave != 0 || hb != 0) return;
+#pragma unroll
+        for (int v = 1; v < NW; ++v) merge_stats(M, L, s_m[v][l32], s_l[v][l32]);
+    }
+    if (hb == 0 && r < R) {
+        float* St = (WR ? a.rows + pair * (int64_t)R * cap : a.score + pair * (int64_t)cap) + (NW == 1 ? chain * 2 * R : 0);
+        for (int g = 0; g < a.G; ++g) {
+            St[(int64_t)g * a.cols + r] = M;
+            St[(int64_t)g * a.cols + R + r] = L;
+        }
+    }
 }
 
 // WR: also write the R rows themselves (the ring of the strict local attention sum).
@@ -78,8 +265,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int wave = tid >> 6;
     const int l32 = lane & 31;
     const int hb = lane >> 5;
-    const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : (MODE == kSeedStats ? blockIdx.x / a.row_tiles : blockIdx.x);
-    const int rt0 = MODE == kSeedStats ? blockIdx.x % a.row_tiles : 0;     // first row tile of this workgroup
+    const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : blockIdx.x;
     const int g = MODE == kSeedSums ? blockIdx.x % a.G : 0;
     const int cap = a.cap;
     const int R = a.R;
@@ -92,7 +278,6 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     float* Rp = WR ? a.rows + pair * (int64_t)R * cap : nullptr;
 
     if (s <= 0) {
-        if (MODE == kSeedStats) return;
         if (Sp)
             for (int j = col0 + tid; j < col1; j += NT) Sp[j] = 0.f;
         if (Rp)
@@ -115,7 +300,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     Vec16 qv[RT][NV];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-        const int r = (rt0 + rt) * 32 + l32;
+        const int r = rt * 32 + l32;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int qrow = qbase + r > 0 ? qbase + r : 0;          // rows before the prompt are masked below
@@ -157,40 +342,12 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             for (int i = 0; i < 16; ++i) c[i] = 0.f;
 #pragma unroll
             for (int v = 0; v < NV; ++v) c = Mfma<T>::run(kv[v], qv[rt][v], c);   // C[key][query]
-            const int r = (rt0 + rt) * 32 + l32;
+            const int r = rt * 32 + l32;
             const int tmax = (r < R) ? t_off + r : -1;   // last visible key of this lane's query
-            float z[16];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int key = tile * 32 + 8 * (i / 4) + 4 * hb + (i % 4);
-                z[i] = (key <= tmax) ? c[i] * a.scale_log2e : -INFINITY;
-                mx = fmaxf(mx, z[i]);
-            }
-            if (mx > -INFINITY) {
-                const float Mn = fmaxf(M[rt], mx);
-                float acc = L[rt] * __builtin_amdgcn_exp2f(M[rt] - Mn);   // 0 while M is -inf
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc += __builtin_amdgcn_exp2f(z[i] - Mn);
-                M[rt] = Mn;
-                L[rt] = acc;
-            }
+            add_tile_stats(c, tile, hb, tmax, a.scale_log2e, M[rt], L[rt]);
         }
     };
-    if constexpr (MODE == kSeedStats) {
-        // one workgroup has a CU to itself: three tiles per wave in flight while a fourth is reduced
-        constexpr int AHEAD = 4;
-        Vec16 kr[AHEAD][NV];
-#pragma unroll
-        for (int u = 0; u < AHEAD - 1; ++u) load_tile(tile0 + wave + u * NW, kr[u]);
-        for (int tile = tile0 + wave; tile < tile1; tile += AHEAD * NW) {
-#pragma unroll
-            for (int u = 0; u < AHEAD; ++u) {
-                load_tile(tile + (u + AHEAD - 1) * NW, kr[(u + AHEAD - 1) % AHEAD]);
-                if (tile + u * NW < tile1) stats_tile(tile + u * NW, kr[u]);
-            }
-        }
-    } else {
+    {
         Vec16 kA[NV], kB[NV];
         load_tile(tile0 + wave, kA);
         for (int tile = tile0 + wave; tile < tile1; tile += 2 * NW) {
@@ -215,26 +372,26 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         float Mt = s_m[0][tid], Lt = s_l[0][tid];
 #pragma unroll
         for (int v = 1; v < NW; ++v) merge_stats(Mt, Lt, s_m[v][tid], s_l[v][tid]);
-        if constexpr (MODE == kSeedStats) {
-            const int r = rt0 * 32 + tid;
-            if (r < R) {
-                for (int g2 = 0; g2 < a.G; ++g2) {
-                    St[g2 * a.cols + r] = Mt;
-                    St[g2 * a.cols + R + r] = Lt;
-                }
-            }
-        }
         const bool ok = Mt > -INFINITY && Lt > 0.f;
         s_M[tid] = ok ? Mt : 0.f;
         s_invL[tid] = ok ? 1.f / Lt : 0.f;
     }
-    if constexpr (MODE == kSeedStats) return;
     __syncthreads();
     }
     if constexpr (MODE == kSeedSums) {
         if (tid < RP) {
             const bool row = tid < R && t_off + tid >= 0;
-            const float Mt = row ? St[tid] : -INFINITY, Lt = row ? St[R + tid] : 0.f;
+            float Mt = row ? St[tid] : -INFINITY, Lt = row ? St[R + tid] : 0.f;
+            if (a.chains > 1) {
+                float M2[kChains], L2[kChains];
+#pragma unroll
+                for (int v = 1; v < kChains; ++v) {
+                    M2[v] = row ? St[v * 2 * R + tid] : -INFINITY;
+                    L2[v] = row ? St[v * 2 * R + R + tid] : 0.f;
+                }
+#pragma unroll
+                for (int v = 1; v < kChains; ++v) merge_stats(Mt, Lt, M2[v], L2[v]);
+            }
             const bool ok = Mt > -INFINITY && Lt > 0.f;
             s_M[tid] = ok ? Mt : 0.f;
             s_invL[tid] = ok ? 1.f / Lt : 0.f;
@@ -312,20 +469,32 @@ static int seed_slices(int64_t pairs, int bound, int cap, int R, int& cols)
 }
 
 // Statistics and sliced sums in a launch each, or everything in one launch?  The statistics read the keys once per 32 rows, with
-// one workgroup per 32 rows of a pair: two launches pay while those workgroups find a CU of their own and the keys
-// are long enough for the second launch.  One / two launches in us, f16, d = 128, R = 64 (R = 16 and 128, the ring's
-// rows, d = 64 and fp32 draw the line in the same places):
-//    32 pairs   1024 keys 22 / 19, 2048 38 / 28, 4096 70 / 45, 8192 137 / 79
-//    64 pairs   1024 keys 22 / 21, 2048 39 / 31, 8192 140 / 89
-//   128 pairs   1024 keys 23 / 24, 2048 40 / 38, 4096 74 / 67, 8192 143 / 125
-//   160 pairs   1024 keys 24 / 37, 4096 75 / 108, 8192 150 / 207
+// one workgroup per 32 rows of a pair or four: two launches pay while those find a CU of their own and the keys
+// are long enough for the second launch.  One / two launches in us, f16, d = 128, R = 64 (the ring's rows, d = 64
+// and fp32 draw the line in the same places; in parentheses two launches with the statistics in the operands' own layout,
+// one workgroup per 32 rows):
+//     8 pairs   1024 keys 21 / 16, 2048 36 / 20, 4096 65 / 27, 8192 124 / 43
+//    32 pairs    512 keys 14 / 14, 1024 21 / 16 (19), 2048 36 / 21 (28), 4096 66 / 29 (45), 8192 128 / 47 (79)
+//    64 pairs    512 keys 14 / 14, 1024 21 / 17 (21), 2048 36 / 22 (31), 4096 67 / 34, 8192 129 / 58 (89)
+//   128 pairs   1024 keys 22 / 22 (24), 2048 37 / 31 (38), 4096 68 / 49 (67), 8192 135 / 86 (125)
+//   160 pairs   1024 keys 22 / 33, 4096 69 / 81, 8192 141 / 153
+// R = 128, 64 pairs x 1024 keys 36 / 22; R = 16, fp32, d = 128, 12 pairs x 1024 keys 43 / 36.
 // With 65 to 128 pairs only under a stated bound: without one the slices are laid over the whole capacity, and prompts that fill
-// a quarter of it lose more (128 pairs x 4096 keys in 16384 slots 77 / 87) than full ones gain.  Up to 64 pairs
-// the gain is worth the risk: short prompts under a long bound lose 2 to 5 us (32 pairs x 32 keys 7 / 10).
+// a quarter of it gain little (128 pairs x 4096 keys in 16384 slots 71 / 67); and from 4096 keys on, where the gain is
+// more than a few microseconds.  Up to 64 pairs short prompts under a long bound lose 2 to 5 us (32 pairs x 32 keys 7 / 11).
 bool seed_in_two(int64_t pairs, int bound, bool stated, int R)
 {
     if (pairs <= 64) return bound >= 1024;
     return stated && pairs <= 128 && pairs * ((R + 31) / 32) <= 256 && bound >= 4096;
+}
+
+// Does every chain of the statistics get a workgroup of its own?  Where a slice has the room to bring all of them along.  (Not
+// with rows of 512 bytes: fp32 products bound that kernel wherever its waves sit, and one wave alone
+// runs out of registers.)
+static bool seed_chains_apart(int G, int cols, int cap, int R)
+{
+    const int room = 2 * kChains * R;
+    return cols >= room && (int64_t)(G - 1) * cols + room <= cap;
 }
 
 template <typename T, int D, int RT, bool WR>
@@ -337,8 +506,14 @@ static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hip
     if (stats_ready) {
         hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
     } else if (G > 1 && seed_in_two(pairs, a.bound, a.stated, a.R)) {
-        a.row_tiles = RT;
-        hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
+        constexpr bool kMayPart = D * Elem<T>::kBytes < 512;
+        if (kMayPart && seed_chains_apart(G, a.cols, a.cap, a.R)) {
+            a.chains = kChains;
+            if constexpr (kMayPart)
+                hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, 1>), dim3((unsigned)(pairs * RT * kChains)), dim3(kWave), 0, stream, a);
+        } else {
+            hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, kChains>), dim3((unsigned)(pairs * RT)), dim3(kChains * kWave), 0, stream, a);
+        }
         if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
         hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
     } else {
@@ -380,7 +555,8 @@ int launch_prefill(const swa_params& p, float scale, const void* q_tail, int32_t
                    hipStream_t stream)
 {
     PrefillArgs a;
-    a.G = a.cols = a.row_tiles = 0;
+    a.G = a.cols = 0;
+    a.chains = 1;
     a.q_in_place = q_in_place ? 1 : 0;
     a.rows = rows;
     a.q_tail = static_cast<const char*>(q_tail);

@@ -124,3 +124,30 @@ def test_bound_below_the_capacity(dtype, d, R, bound):
             torch.testing.assert_close(got[i].double(), want.sum(1), rtol=1e-5, atol=1e-12)
         if rows is not None:
             torch.testing.assert_close(rows[i].double(), want, rtol=1e-5, atol=1e-12)
+
+
+@pytest.mark.parametrize("dtype,d,cap,R", [(torch.float16, 128, 4200, 64), (torch.bfloat16, 64, 4200, 33),
+                                           (torch.float16, 64, 2200, 32), (torch.float32, 64, 4200, 64), (torch.float32, 128, 2200, 7)])
+def test_statistics_in_four_chains(dtype, d, cap, R):
+    """Few pairs, slices wide enough for the statistics of every chain: prompts that end around a round of the chains' tiles."""
+    from paper_2403_17312_amd import binding as B
+    lens = [R - 1, 33, 127, 128, 129, 1023, 1025, 2047, 2049, cap]
+    b, h = len(lens), 1
+    g = torch.Generator(device="cuda").manual_seed(29)
+    k = torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype)
+    tail = torch.randn((b, h, R, d), generator=g, device="cuda").to(dtype)
+    for i, n in enumerate(lens):
+        k[i, :, n:] = float("nan")
+    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    p = B.make_params(b, h, d, cap, 4, 8000, dtype)
+    ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    score = torch.full((b, h, cap), float("nan"), device="cuda")
+    B.swa_prefill_scores(p, tail, R, k, cl, score, ws)
+    rows = torch.full((b, h, R, cap), float("nan"), device="cuda")
+    B.swa_prefill_rows(p, tail, R, k, cl, rows, ws)
+    for i, n in enumerate(lens):
+        want = torch.zeros((h, R, cap), device="cuda", dtype=torch.float64)
+        want[:, :, :n] = reference(tail[i], k[i], n, R, d)
+        # fp32 logits, exponentials and sums over at most 4200 keys and 64 rows, exponents up to about 10
+        torch.testing.assert_close(score[i].double(), want.sum(1), rtol=1e-5, atol=1e-12)
+        torch.testing.assert_close(rows[i].double(), want, rtol=1e-5, atol=1e-12)
