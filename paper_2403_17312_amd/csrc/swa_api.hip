@@ -244,7 +244,7 @@ int swa_prepare(void)
     int rc = swa::static_scratch(&ptr);
     if (rc != SWA_OK) return rc;
     rc = swa::prepare_decode();
-    return rc == SWA_OK ? swa::prepare_split() : rc;
+    return rc;
 }
 
 int swa_check_status(const swa_params* params, void* workspace, void* stream, int32_t* status_out)

@@ -66,13 +66,12 @@ void seed_stats_place(int64_t pairs, int bound, int cap, int R, int& G, int& col
 bool seed_in_two(int64_t pairs, int bound, bool stated, int R);
 
 // SWA_SPLIT_ROWS: workgroups per pair for this many pairs and this bound on the cached length
-// (1 = the one-workgroup kernel serves the call), the launches of the step, and their LDS limits.
+// (1 = the one-workgroup kernel serves the call), and the launches of the step.
 constexpr int kMaxSplit = 16;
 int split_factor(int64_t pairs, int len_bound);
 int launch_split(const swa_params& p, float scale, int G, const void* q, const void* k_new, const void* v_new, void* k_cache,
                  void* v_cache, float* score, int32_t* pos, int32_t* cache_len, const int32_t* seq_len, int32_t* kept_idx,
                  int32_t* kept_cnt, void* out, float* probs_dbg, void* workspace, hipStream_t stream);
-int prepare_split();
 
 // Token-level offload tier (Section V-A, Algorithm 2): evicted rows to the host store, requested rows back.
 int launch_offload(const swa_params& p, const void* k_cache, const void* v_cache, const float* score,

@@ -1,5 +1,4 @@
-// Workgroup-level pieces of the selection (Algorithm 1 lines 3-5): the threshold of a top-k over 32-bit keys, and the
-// prefix sum that places what was kept.
+// Workgroup-level piece of the selection (Algorithm 1 lines 3-5): the threshold of a top-k over 32-bit keys.
 #pragma once
 
 #include "swa_device.hpp"
@@ -13,13 +12,36 @@ __device__ __forceinline__ uint32_t order_key(float f)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Sum over the lanes up to and including this one.
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);      // row_shr 1, 2, 4, 8 within 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // lane 15 of a row into the next, odd rows
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // lane 31 into the upper half
+    return v;
+}
+
+template <int CTRL>
+__device__ __forceinline__ void min_max_dpp(uint32_t& lo, uint32_t& hi)
+{
+    const uint32_t a = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, CTRL, 0xf, 0xf, true);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, 0xf, 0xf, true);
+    lo = a < lo ? a : lo;
+    hi = b > hi ? b : hi;
+}
+
 // LDS of one workgroup's selection.
 template <int NT>
 struct SelectScratch {
-    int32_t hist[2 * NT];          // two bins per thread
+    int32_t hist[2 * NT];          // two bins per thread, zero before and after a selection
     uint32_t lo[NT / kWave], hi[NT / kWave];
     int32_t cnt[NT / kWave];
     int32_t sel[3];
+    int32_t listed;                // keys of the bin that holds the threshold, once they are few
+    uint32_t list[kWave];
 };
 
 // The `want`-th largest (want >= 1, at most the number of candidates) of the candidate keys, as a
@@ -28,8 +50,9 @@ struct SelectScratch {
 //
 // Histogram select with 2 NT bins over the range the keys really span (a radix select from the top of the word has its
 // first digit, sign and exponent, shared by nearly all keys, and its counters serialise), refined inside the
-// bin that holds the threshold until all of that bin is kept or its keys are equal.  Importance values of
-// a cache are spread enough that this takes two rounds as a rule, and never more than four.
+// bin that holds the threshold until all of that bin is kept, its keys are equal or there are so few that
+// they can be listed and ranked.  Importance values of a cache are spread enough that this takes one round and
+// the list as a rule, and never more than four rounds.
 template <int NT, typename Each>
 __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want, Each each, uint32_t& thr, int& rem, int& n_eq)
 {
@@ -45,8 +68,12 @@ __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want,
         kmin = key < kmin ? key : kmin;
         kmax = key > kmax ? key : kmax;
     });
+    min_max_dpp<0xB1>(kmin, kmax);
+    min_max_dpp<0x4E>(kmin, kmax);
+    min_max_dpp<0x141>(kmin, kmax);
+    min_max_dpp<0x140>(kmin, kmax);
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
+    for (int o = 16; o < kWave; o <<= 1) {
         const uint32_t a = (uint32_t)__shfl_xor((int)kmin, o, kWave), b = (uint32_t)__shfl_xor((int)kmax, o, kWave);
         kmin = a < kmin ? a : kmin;
         kmax = b > kmax ? b : kmax;
@@ -58,6 +85,7 @@ __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want,
     if (tid == 0) {
         s.sel[0] = 0;
         s.sel[1] = s.sel[2] = want;
+        s.listed = 0;
     }
     __syncthreads();
 #pragma unroll
@@ -71,24 +99,19 @@ __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want,
     for (;;) {
         const int bits = top ? 32 - __builtin_clz(top) : 0;
         const int shift = bits > LB ? bits - LB : 0;
-        s.hist[2 * tid] = 0;
-        s.hist[2 * tid + 1] = 0;
-        __syncthreads();
         each([&](uint32_t key) {
             const uint32_t off = key - lo;
             if (key >= lo && off <= top) atomicAdd(&s.hist[off >> shift], 1);
         });
         __syncthreads();
         const int c0 = s.hist[2 * tid], c1 = s.hist[2 * tid + 1];
-        int suf = c0 + c1;                                // inclusive suffix sum over the wave's lanes
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int t = __shfl_down(suf, o, kWave);
-            if (lane + o < kWave) suf += t;
-        }
-        if (lane == 0) s.cnt[wave] = suf;
+        s.hist[2 * tid] = 0;
+        s.hist[2 * tid + 1] = 0;
+        const int upto = wave_scan(c0 + c1);
+        const int total = __builtin_amdgcn_readlane(upto, kWave - 1);
+        if (lane == 0) s.cnt[wave] = total;
         __syncthreads();
-        int above = suf - c0 - c1;                        // keys in higher bins
+        int above = total - upto;                         // keys in higher bins
 #pragma unroll
         for (int v = 0; v < NW; ++v)
             if (v > wave) above += s.cnt[v];
@@ -105,55 +128,31 @@ __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want,
         lo += (uint32_t)s.sel[0] << shift;
         top = (1u << shift) - 1u;
         left = s.sel[1];
-        if (shift == 0 || left == s.sel[2]) break;        // equal keys, or the whole bin is kept
+        n_eq = s.sel[2];
+        if (shift == 0 || left == n_eq) break;            // equal keys, or the whole bin is kept
+        if (n_eq <= kWave) {
+            // a bin of few keys: listed, and every wave ranks them for itself
+            each([&](uint32_t key) {
+                if (key >= lo && key - lo <= top) s.list[atomicAdd(&s.listed, 1)] = key;
+            });
+            __syncthreads();
+            const uint32_t mine = lane < n_eq ? s.list[lane] : 0u;
+            int larger = 0, equal = 0;
+            for (int j = 0; j < n_eq; ++j) {
+                const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
+                larger += o > mine ? 1 : 0;
+                equal += o == mine ? 1 : 0;
+            }
+            const uint64_t at = __ballot(lane < n_eq && larger < left && left <= larger + equal);
+            const int l = __builtin_ctzll(at);
+            lo = (uint32_t)__builtin_amdgcn_readlane((int)mine, l);
+            left -= __builtin_amdgcn_readlane(larger, l);
+            n_eq = __builtin_amdgcn_readlane(equal, l);
+            break;
+        }
     }
     thr = lo;
     rem = left;
-    n_eq = s.sel[2];
-}
-
-// Exclusive prefix sum of v over the threads of the workgroup, and the total.  s_cnt: NT / 64 words of LDS.
-template <int NT>
-__device__ __forceinline__ void block_scan(int32_t* s_cnt, int v, int& before, int& total)
-{
-    constexpr int NW = NT / kWave;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int t = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += t;
-    }
-    if (lane == kWave - 1) s_cnt[wave] = inc;
-    __syncthreads();
-    int wb = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const int c = s_cnt[w];
-        if (w < wave) wb += c;
-        tot += c;
-    }
-    before = wb + inc - v;
-    total = tot;
-    __syncthreads();
-}
-
-// Ordered compaction of one thread's contiguous run of at most 64 slots: the slots to keep as a mask.  surem: kept for
-// sure; eqm: equal to the threshold, of which the workgroup keeps the first rem.
-template <int NT>
-__device__ __forceinline__ uint64_t keep_mask(int32_t* s_cnt, uint64_t surem, uint64_t eqm, int rem)
-{
-    int eq_before = 0, eq_total = 0;
-    block_scan<NT>(s_cnt, (int)__popcll(eqm), eq_before, eq_total);
-    int take = rem - eq_before;
-    while (take > 0 && eqm != 0ull) {
-        const uint64_t low = eqm & (~eqm + 1ull);
-        surem |= low;
-        eqm ^= low;
-        --take;
-    }
-    return surem;
 }
 
 }  // namespace swa

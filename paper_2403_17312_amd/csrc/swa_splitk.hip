@@ -7,7 +7,7 @@
 //   2. swa_split_select_kernel   one workgroup per pair: append, softmax over the stored logits,
 //                                importance accumulation, budget and selection (Alg. 1 lines 1-5),
 //                                kept list and the kept tokens' weights to memory;
-//   3. swa_split_gather_kernel   one workgroup per pair and 64 bytes of a row: out = sum p_i v_i / sum p_i
+//   3. swa_split_gather_kernel   one workgroup per pair and 128 bytes of a row: out = sum p_i v_i / sum p_i
 //                                over the kept list (Alg. 1 lines 6-8), rounded once to the output type.
 // The logits are formed exactly as the one-workgroup kernel forms them (same products, same
 // reduction order), so weights, importance and the kept set are bit-identical to that form; only
@@ -38,7 +38,7 @@ struct SplitArgs {
     char* out;
     int64_t pairs;
     int32_t h, cap, G;
-    int32_t w, sparsity_bp, lds_slots;
+    int32_t w, sparsity_bp, lds_slots, row_bytes;
     float scale;
 };
 
@@ -46,10 +46,13 @@ constexpr int kSelThreads = 1024;    // launch 2: a whole CU's worth of one pair
 constexpr int kGatherThreads = 1024;
 constexpr int kPieceBytes = 128;     // of a value row, per workgroup of launch 3
 constexpr int kXcds = 8;             // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
-constexpr int kSelPer = SWA_MAX_CAP / kSelThreads;   // slots per thread at most
+constexpr int kSelPer = SWA_MAX_CAP / kSelThreads;   // slots per thread of launch 2 at most
 
 // Launch 1.  cache_len is the length BEFORE the step's append; slot `len` is the new token, whose
 // key comes from k_new (launch 2 writes it to the cache).
+//
+// Bound: HBM, and the time until the first rows arrive.  A stage's rows are reduced while the next one's travel, and the new token
+// does not lengthen a slice (32 pairs x 8192 rows, f16, d = 128: 15.8 -> 13.5 us, 5.0 TB/s).
 template <typename T, int D, int NT>
 __global__ void __launch_bounds__(NT) swa_split_logits_kernel(SplitArgs a)
 {
@@ -57,7 +60,7 @@ __global__ void __launch_bounds__(NT) swa_split_logits_kernel(SplitArgs a)
     constexpr int LPR = D / EPV;
     constexpr int NG = NT / LPR;
     constexpr int ROWB = D * Elem<T>::kBytes;
-    constexpr int UK = 8;
+    constexpr int UK = 8;                              // rows per lane and stage; two stages are in flight
     const int tid = threadIdx.x;
     const int sub = tid % LPR;
     const int grp = tid / LPR;
@@ -65,62 +68,89 @@ __global__ void __launch_bounds__(NT) swa_split_logits_kernel(SplitArgs a)
     const int g = blockIdx.x % a.G;
     const int s = (int)(pair / a.h);
     const int len = a.cache_len[s];
-    const int m = len + 1;
     if (g == 0 && tid == 0) a.ws_ok[pair] = 0;         // launch 2 sets it when it completes the pair
-    if (len < 0 || m > a.cap) return;                  // launch 2 reports the full cache
-    const int per = (m + a.G - 1) / a.G;
+    if (len < 0 || len >= a.cap) return;                 // launch 2 reports the full cache
+    const int per = (len + a.G - 1) / a.G;
     const int lo = g * per;
-    const int hi = lo + per < m ? lo + per : m;
+    const int hi = lo + per < len ? lo + per : len;
     const char* Kp = a.k_cache + pair * (int64_t)a.cap * ROWB;
     float* Zp = a.ws_z + pair * (int64_t)a.cap;
     QFrag<T> qf;
     qf.load(load16(a.q + pair * ROWB + sub * 16));
-    const Vec16 nk = load16(a.k_new + pair * ROWB + sub * 16);
-    for (int base = lo; base < hi; base += NG * UK) {
-        Vec16 kv[UK];
+    // (rows past the end re-read the slice's last one)
+    auto request = [&](int base, Vec16(&kv)[UK]) {
 #pragma unroll
         for (int u = 0; u < UK; ++u) {
             const int row = base + u * NG + grp;
-            kv[u] = (row < len && row < hi) ? load16_stream(Kp + (int64_t)row * ROWB + sub * 16) : nk;
+            kv[u] = load16_stream(Kp + (uint32_t)(row < hi ? row : hi - 1) * ROWB + sub * 16);
         }
+    };
+    auto reduce = [&](int base, const Vec16(&kv)[UK]) {
 #pragma unroll
         for (int u = 0; u < UK; ++u) {
             const int row = base + u * NG + grp;
             const float d = group_sum<LPR>(qf.dot(kv[u], 0.f)) * a.scale;
             if (sub == 0 && row < hi) Zp[row] = d;
         }
+    };
+    constexpr int STEP = NG * UK;
+    Vec16 kA[UK], kB[UK];
+    if (lo < hi) request(lo, kA);
+    for (int base = lo; base < hi; base += 2 * STEP) {
+        if (base + STEP < hi) request(base + STEP, kB);
+        reduce(base, kA);
+        if (base + STEP >= hi) break;
+        if (base + 2 * STEP < hi) request(base + 2 * STEP, kA);
+        reduce(base + STEP, kB);
+    }
+    if (g == a.G - 1 && tid < kWave) {                 // the new token
+        const float d = group_sum<LPR>(qf.dot(load16(a.k_new + pair * ROWB + sub * 16), 0.f)) * a.scale;
+        if (tid == 0) Zp[len] = d;
     }
 }
 
 // Launch 2.  Softmax over the stored logits, importance, budget and selection of one pair; append of the new token.
 //
 // Bound: the dependent chain of one workgroup (a few pairs on 256 CUs), so every load of the pair's logits and
-// importance is requested at once, keys stay in registers between the phases, and 1024 threads share the work.
-// Weights are bit-identical to the one-workgroup kernel's: its 512 threads' sums are added up in its order.
-// 32 pairs x 8192 rows, f16, d = 128: 17 us (33 with the one-workgroup kernel in this place).
-template <typename T, int D>
+// importance is requested at once, before the length is known, weights and keys stay in registers between the phases, and 1024
+// threads share the work.  PER: slots per thread.  Weights are bit-identical to the one-workgroup kernel's: its 512 threads'
+// sums are added up in its order.
+// 32 pairs x 8192 rows, f16, d = 128: 14.6 us (17 with weights and keys in LDS, two rounds of histograms and runs of
+// slots per thread, 33 with the one-workgroup kernel in this place).
+template <int PER>
 __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs a)
 {
     constexpr int NT = kSelThreads;
     constexpr int NW = NT / kWave;
     constexpr int SUMT = 512;               // threads of the one-workgroup kernel on such caches
-    constexpr int EPV = Elem<T>::kPerVec;
-    constexpr int LPR = D / EPV;
-    constexpr int ROWB = D * Elem<T>::kBytes;
-    extern __shared__ __align__(16) char smem[];
-    float* s_p = reinterpret_cast<float*>(smem);                       // exponentials, then weights
-    uint32_t* s_key = reinterpret_cast<uint32_t*>(s_p + a.lds_slots);
-    uint16_t* s_kept = reinterpret_cast<uint16_t*>(s_key);             // over the keys, once all of them are read
+    constexpr int CHUNKS = kSelPer * NW;    // runs of 64 slots: chunk k NW + w is wave w's register k
+    static_assert(NT == 2 * SUMT && CHUNKS == 4 * kWave, "how the sum is shared out and the chunks are scanned");
+    __shared__ float s_x[PER][SUMT];                               // exponentials of the upper half of the threads
     __shared__ SelectScratch<NT> s_sel;
     __shared__ float s_red[NW];
     __shared__ float s_sum[SUMT / kWave];
+    __shared__ __align__(16) uint32_t s_chunk[CHUNKS];                 // kept for sure | equal to the threshold << 16
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t pair = blockIdx.x;
     const int s = (int)(pair / a.h);
     const int cap = a.cap;
+    const float* Zp = a.ws_z + pair * (int64_t)cap;
+    float* Sp = a.score + pair * (int64_t)cap;
+    float* Wp = a.ws_p + pair * (int64_t)cap;
+    // requested before the length is known: what lies at or beyond it is not used
+    float z[PER], sc[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (k * NT >= a.lds_slots) continue;
+        const int i = tid + k * NT < cap ? tid + k * NT : cap - 1;
+        z[k] = Zp[i];
+        sc[k] = Sp[i];
+    }
+    s_sel.hist[2 * tid] = 0;
+    s_sel.hist[2 * tid + 1] = 0;
     const int len = a.cache_len[s];
     const int n = a.seq_len[s];
     const int m = len + 1;
@@ -128,27 +158,25 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     int keep = 0, n_local = 0, n_global = 0, w_eff = 0;
 
     if (!overflow) {
-        const float* Zp = a.ws_z + pair * (int64_t)cap;
-        float* Sp = a.score + pair * (int64_t)cap;
-        float* Wp = a.ws_p + pair * (int64_t)cap;
-        float z[kSelPer], sc[kSelPer];
 #pragma unroll
-        for (int k = 0; k < kSelPer; ++k) {
+        for (int k = 0; k < PER; ++k) {
             const int i = tid + k * NT;
-            z[k] = i < m ? Zp[i] : -INFINITY;
-            sc[k] = i < len ? Sp[i] : 0.f;
+            z[k] = i < m ? z[k] : -INFINITY;
+            sc[k] = i < len ? sc[k] : 0.f;
         }
         // append: the new row's key, value and position
-        if (tid < 2 * LPR) {
-            const int at = (tid % LPR) * 16;
-            const char* row = tid < LPR ? a.k_new : a.v_new;
-            store16((tid < LPR ? a.k_cache : a.v_cache) + (pair * (int64_t)cap + len) * ROWB + at, load16(row + pair * ROWB + at));
+        const int lpr = a.row_bytes / 16;
+        if (tid < 2 * lpr) {
+            const int at = (tid < lpr ? tid : tid - lpr) * 16;
+            const char* row = tid < lpr ? a.k_new : a.v_new;
+            store16((tid < lpr ? a.k_cache : a.v_cache) + (pair * (int64_t)cap + len) * a.row_bytes + at,
+                    load16(row + pair * a.row_bytes + at));
         }
         if (tid == 0) a.pos[pair * (int64_t)cap + len] = n - 1;
 
         float mx = -INFINITY;
 #pragma unroll
-        for (int k = 0; k < kSelPer; ++k) mx = fmaxf(mx, z[k]);
+        for (int k = 0; k < PER; ++k) mx = fmaxf(mx, z[k]);
         mx = wave_max(mx);
         if (lane == 0) s_red[wave] = mx;
         __syncthreads();
@@ -156,17 +184,21 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
 #pragma unroll
         for (int v = 1; v < NW; ++v) mx = fmaxf(mx, s_red[v]);
 #pragma unroll
-        for (int k = 0; k < kSelPer; ++k) {
-            const int i = tid + k * NT;
-            if (i < m) {
-                z[k] = expf(z[k] - mx);
-                s_p[i] = z[k];
-            }
+        for (int k = 0; k < PER; ++k) {
+            if (k * NT >= m) continue;
+            z[k] = tid + k * NT < m ? expf(z[k] - mx) : 0.f;
+            if (tid >= SUMT) s_x[k][tid - SUMT] = z[k];
         }
         __syncthreads();
         if (tid < SUMT) {
+            // thread t of the one-workgroup kernel adds up slots t, t + 512, t + 1024, ...  (a zero past the end changes nothing)
             float sum = 0.f;
-            for (int i = tid; i < m; i += SUMT) sum += s_p[i];
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                if (k * NT >= m) continue;
+                sum += z[k];
+                sum += s_x[k][tid];
+            }
             sum = wave_sum(sum);
             if (lane == 0) s_sum[wave] = sum;
         }
@@ -177,71 +209,89 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
 
         budget(n, m, a.w, a.sparsity_bp, keep, n_local, n_global, w_eff);
         const int ncand = m - n_local;
-        uint32_t key[kSelPer];
+        uint32_t key[PER];
 #pragma unroll
-        for (int k = 0; k < kSelPer; ++k) {
+        for (int k = 0; k < PER; ++k) {
+            if (k * NT >= m) continue;
             const int i = tid + k * NT;
-            key[k] = 0u;
             if (i < m) {
-                const float p = z[k] / sum;
-                const float v = sc[k] + p;
+                z[k] = z[k] / sum;                          // the weight
+                const float v = sc[k] + z[k];
                 Sp[i] = v;
-                s_p[i] = p;
                 key[k] = order_key(v);
-                s_key[i] = key[k];
             }
         }
         if (a.probs_dbg) {
-            __syncthreads();
             float* dbg = a.probs_dbg + pair * (int64_t)cap;
-            for (int i = tid; i < cap; i += NT) dbg[i] = (i < m) ? s_p[i] : 0.f;
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (tid + k * NT < m) dbg[tid + k * NT] = z[k];
+            for (int i = m + tid; i < cap; i += NT) dbg[i] = 0.f;
         }
 
         int32_t* kout = a.kept_idx + pair * (int64_t)cap;
         if (keep == m) {                                    // everything stays
-            __syncthreads();
-            for (int i = tid; i < m; i += NT) {
-                kout[i] = i;
-                Wp[i] = s_p[i];
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                const int i = tid + k * NT;
+                if (i < m) {
+                    kout[i] = i;
+                    Wp[i] = z[k];
+                }
             }
         } else {
-            uint32_t thr = 0u;
+            // Kept: slots from ncand on, the candidates before it with keys above thr, and of those equal to it the `rem` lowest slots.
+            uint32_t thr = 0xffffffffu;
             int rem = 0, n_eq = 0;
             if (n_global > 0) {
                 auto each = [&](auto f) {
 #pragma unroll
-                    for (int k = 0; k < kSelPer; ++k)
+                    for (int k = 0; k < PER; ++k) {
+                        if (k * NT >= ncand) continue;
                         if (tid + k * NT < ncand) f(key[k]);
+                    }
                 };
                 select_threshold<NT>(s_sel, n_global, each, thr, rem, n_eq);
-            } else {
-                __syncthreads();
             }
-            // every thread owns a run of slots; ties go to the lowest slots
-            const int per = (m + NT - 1) / NT;
-            const int lo = tid * per;
-            const int hi = lo + per < m ? lo + per : m;
-            uint64_t surem = 0ull, eqm = 0ull;
-            for (int k = 0; lo + k < hi; ++k) {
-                const int i = lo + k;
-                if (i >= ncand) {
-                    surem |= 1ull << k;
-                } else if (n_global > 0) {
-                    const uint32_t q = s_key[i];
-                    if (q > thr) surem |= 1ull << k;
-                    else if (q == thr) eqm |= 1ull << k;
+            // The kept list: a wave's 64 slots of a register are one run, so ballots place them within it and a scan of the runs' counts
+            // (every wave for itself) places the runs.
+            const uint64_t lower = (1ull << lane) - 1ull;
+            uint32_t sure = 0u, tied = 0u;                      // bit k: slot tid + k NT
+            for (int k = PER; k < kSelPer; ++k)
+                if (lane == 0) s_chunk[k * NW + wave] = 0u;
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                uint32_t c = 0u;
+                if (k * NT < m) {
+                    const int i = tid + k * NT;
+                    const bool cand = i < ncand;
+                    const bool in = i < m && (!cand || key[k] > thr), eq = cand && key[k] == thr;
+                    sure |= in ? 1u << k : 0u;
+                    tied |= eq ? 1u << k : 0u;
+                    c = (uint32_t)__popcll(__ballot(in)) | ((uint32_t)__popcll(__ballot(eq)) << 16);
                 }
+                if (lane == 0) s_chunk[k * NW + wave] = c;
             }
-            const uint64_t kept = keep_mask<NT>(s_sel.cnt, surem, eqm, rem);
-            int at = 0, total = 0;
-            block_scan<NT>(s_sel.cnt, (int)__popcll(kept), at, total);
-            for (int k = 0; lo + k < hi; ++k)
-                if ((kept >> k) & 1ull) s_kept[at++] = (uint16_t)(lo + k);
             __syncthreads();
-            for (int j = tid; j < keep; j += NT) {
-                const int i = s_kept[j];
-                kout[j] = i;
-                Wp[j] = s_p[i];
+            const uint4 c4 = *reinterpret_cast<const uint4*>(&s_chunk[4 * lane]);
+            const uint32_t own = c4.x + c4.y + c4.z + c4.w;
+            const uint32_t inc = (uint32_t)wave_scan((int)own);
+            const int part = wave & 3;                          // chunk k NW + wave: lane (k NW + wave) / 4, its entry `part`
+            const uint32_t first = inc - own + (part > 0 ? c4.x : 0u) + (part > 1 ? c4.y : 0u) + (part > 2 ? c4.z : 0u);
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                if (k * NT >= m) continue;
+                const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)first, k * (NW / 4) + wave / 4);
+                const int eq = (int)(before >> 16);
+                const bool t = (tied >> k) & 1u;
+                const uint64_t tm = __ballot(t);
+                const bool in = ((sure >> k) & 1u) || (t && eq + (int)__popcll(tm & lower) < rem);
+                const uint64_t mask = __ballot(in);
+                if (in) {
+                    const int at = (int)(before & 0xffffu) + (eq < rem ? eq : rem) + (int)__popcll(mask & lower);
+                    kout[at] = tid + k * NT;
+                    Wp[at] = z[k];
+                }
             }
         }
     }
@@ -269,9 +319,10 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
 // the host does not know: a compacted cache or a wide window keeps many times the share that the sparsity
 // names.  Channels need no sum across workgroups, whatever is kept.  64-byte pieces are 1 to 5 us faster with few pairs and much
 // kept, but slower from about 96 pairs on (128 pairs x 8192 kept rows, whole step 118 against 102 us).
-// Whole step, f16, d = 128, this form / partial sums and a fourth launch / output in launch 2, in us: 32 pairs, 20 of 2048 rows
-// kept 20.6 / 26.3 / 19.4; 410 of 2048 23.2 / 28.8 / 23.1; all of 2048 21.4 / 28.2 / 33.3; 1638 of 8192 40.1 / 45.3 / 46.5; all
-// of 8192 52.8 / 59.2 / 98; 128 pairs, all of 8192 102 / 130 / 136.
+// Whole step, f16, d = 128, this form / partial sums and a fourth launch / output in launch 2, in us (launches 1 and 2 have become 3
+// to 6 us faster since, in all three): 32 pairs, 20 of 2048 rows kept 20.6 / 26.3 / 19.4; 410 of 2048 23.2 / 28.8 / 23.1; all of
+// 2048 21.4 / 28.2 / 33.3; 1638 of 8192 40.1 / 45.3 / 46.5; all of 8192 52.8 / 59.2 / 98; 128 pairs, all of 8192 102 / 130 / 136.
+// This form now: 14.7, 14.9, 17.3, 35.1, 49.5 and 97.  Reading the list a round ahead changed nothing, or cost 2 %.
 template <typename T, int D>
 __global__ void __launch_bounds__(kGatherThreads) swa_split_gather_kernel(SplitArgs a)
 {
@@ -353,6 +404,19 @@ __global__ void __launch_bounds__(kGatherThreads) swa_split_gather_kernel(SplitA
     }
 }
 
+// Slots per thread: as many as the bound on the lengths asks for (the loops over them are unrolled, and code that no slot needs is
+// still fetched), a little more than the powers of two for the answer behind a prompt.
+static int launch_select(const SplitArgs& a, int64_t pairs, hipStream_t stream)
+{
+    const dim3 grid((unsigned)pairs), block(kSelThreads);
+    const int per = (a.lds_slots + kSelThreads - 1) / kSelThreads;
+    if (per <= 3) hipLaunchKernelGGL((swa_split_select_kernel<3>), grid, block, 0, stream, a);
+    else if (per <= 5) hipLaunchKernelGGL((swa_split_select_kernel<5>), grid, block, 0, stream, a);
+    else if (per <= 9) hipLaunchKernelGGL((swa_split_select_kernel<9>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((swa_split_select_kernel<kSelPer>), grid, block, 0, stream, a);
+    return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
+}
+
 template <typename T, int D>
 static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
 {
@@ -360,12 +424,7 @@ static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
     const dim3 grid((unsigned)(pairs * a.G));
     hipLaunchKernelGGL((swa_split_logits_kernel<T, D, NT>), grid, dim3(NT), 0, stream, a);
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
-    auto sel = swa_split_select_kernel<T, D>;
-    const size_t lds = (size_t)a.lds_slots * 8;
-    const int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(sel), lds);
-    if (rc != SWA_OK) return rc;
-    hipLaunchKernelGGL(sel, dim3((unsigned)pairs), dim3(kSelThreads), lds, stream, a);
-    if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
+    if (launch_select(a, pairs, stream) != SWA_OK) return SWA_ERR_HIP;
     const int64_t pieces = (pairs + kXcds - 1) / kXcds * kXcds * (D * Elem<T>::kBytes / kPieceBytes);
     hipLaunchKernelGGL((swa_split_gather_kernel<T, D>), dim3((unsigned)pieces), dim3(kGatherThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
@@ -406,6 +465,7 @@ int launch_split(const swa_params& p, float scale, int G, const void* q, const v
     a.w = p.w;
     a.sparsity_bp = p.sparsity_bp;
     a.lds_slots = (bound + 63) & ~63;
+    a.row_bytes = cache_row_bytes(p);
     a.scale = scale;
     if (p.dtype == SWA_F32) {
         return p.d == 64 ? launch_split_t<F32, 64>(a, pairs, stream) : launch_split_t<F32, 128>(a, pairs, stream);
@@ -413,22 +473,6 @@ int launch_split(const swa_params& p, float scale, int G, const void* q, const v
         return p.d == 64 ? launch_split_t<F16, 64>(a, pairs, stream) : launch_split_t<F16, 128>(a, pairs, stream);
     }
     return p.d == 64 ? launch_split_t<BF16, 64>(a, pairs, stream) : launch_split_t<BF16, 128>(a, pairs, stream);
-}
-
-template <typename T>
-static int prepare_split_t()
-{
-    int rc = raise_dynamic_lds(reinterpret_cast<const void*>(swa_split_select_kernel<T, 64>));
-    if (rc == SWA_OK) rc = raise_dynamic_lds(reinterpret_cast<const void*>(swa_split_select_kernel<T, 128>));
-    return rc;
-}
-
-int prepare_split()
-{
-    int rc = prepare_split_t<F32>();
-    if (rc == SWA_OK) rc = prepare_split_t<F16>();
-    if (rc == SWA_OK) rc = prepare_split_t<BF16>();
-    return rc;
 }
 
 }  // namespace swa
