@@ -423,41 +423,29 @@ __device__ __forceinline__ uint32_t lds_address(const char* p)
 //   - Three buffers, two tiles ahead: 7.5 ms.
 //   - The loads of a tile are issued between the products of another instead of all at once: 7.1 ms.
 // Three waves per SIMD (168 registers, 48 KB of LDS per workgroup) at d = 128, four at d = 64.
-//
-// QW waves of 32 queries each, times KS groups of them that share the keys: group g takes the tiles g, g + KS, ... with LDS
-// buffers of its own, and the groups' sums are merged at the end.  KS > 1 is for grids that leave the chip idle (flash_form).
-template <typename T, int D, int QW, int KS>
-__global__ void __launch_bounds__(64 * QW * KS) __attribute__((amdgpu_waves_per_eu(KS > 1 ? 2 : (D == 64 ? 4 : 3))))
+template <typename T, int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 3)))
 swa_flash16_kernel(FlashArgs a)
 {
+    constexpr int NW = 4;
     constexpr int ROWB = D * 2;
     constexpr int NV = ROWB / 32;       // 16-byte fragments a lane supplies for a 32-row operand
     constexpr int CT = D / 32;          // 32-channel tiles of the output
     constexpr int BK = 32;              // keys per tile
-    constexpr int BQ = 32 * QW;         // queries per workgroup
+    constexpr int BQ = 128;             // queries per workgroup
     constexpr int TILE = BK * ROWB;
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
     constexpr int RPI = kWave / CPR;    // rows that one wave-wide load covers
-    constexpr int LD = BK / RPI / QW;   // such loads per wave, per tensor and tile
+    constexpr int LD = BK / RPI / NW;   // such loads per wave, per tensor and tile
     constexpr int LPS = 4 * LD / NV;    // of them behind every second product of the first contraction
     constexpr int PF = 2;               // LDS fragment reads in flight ahead of the product that uses them
 
-    // three buffers for a key and a value tile: of the workgroup, or (dynamic) of every group
-    constexpr int OWN = KS == 1 ? TILE : 16;
-    __shared__ __align__(1024) char o_k0[OWN], o_k1[OWN], o_v0[OWN], o_v1[OWN], o_k2[OWN], o_v2[OWN];
-    extern __shared__ __align__(1024) char smem[];
+    // three buffers for a key and a value tile
+    __shared__ __align__(1024) char s_k0[TILE], s_k1[TILE], s_v0[TILE], s_v1[TILE], s_k2[TILE], s_v2[TILE];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % QW;      // within its group
-    const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / QW;
-    char* const mine = KS == 1 ? nullptr : smem + kg * 6 * TILE;
-    char* const s_k0 = KS == 1 ? o_k0 : mine;
-    char* const s_v0 = KS == 1 ? o_v0 : mine + TILE;
-    char* const s_k1 = KS == 1 ? o_k1 : mine + 2 * TILE;
-    char* const s_v1 = KS == 1 ? o_v1 : mine + 3 * TILE;
-    char* const s_k2 = KS == 1 ? o_k2 : mine + 4 * TILE;
-    char* const s_v2 = KS == 1 ? o_v2 : mine + 5 * TILE;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31;
     const int hb = lane >> 5;
     int64_t pair;
@@ -473,15 +461,10 @@ swa_flash16_kernel(FlashArgs a)
     const int tq = t < 0 ? 0 : (t < s ? t : s - 1);      // lanes outside the prompt shadow a query of it
 
     const int q_hi = (q0 + BQ < s ? q0 + BQ : s) - 1;    // last query of the workgroup
-    const int all_tiles = q_hi / BK + 1;                  // key tiles 0..all_tiles-1 cover keys 0..q_hi
-    // This group's tiles, counted 0..nkt-1; tile kt is tile kg + KS kt of the prompt.  Every wave passes `rounds` barriers.
-    const int rounds = (all_tiles + KS - 1) / KS;
-    const int nkt = KS == 1 ? all_tiles : (all_tiles - kg + KS - 1) / KS;
-    auto key0 = [&](int kt) { return (kg + KS * kt) * BK; };
+    const int nkt = q_hi / BK + 1;                        // key tiles 0..nkt-1 cover keys 0..q_hi
     const int w_lo = q0 + wave * 32;
     const int w_hi = (w_lo + 31 < s - 1) ? w_lo + 31 : s - 1;
-    const int last_tile = (w_lo >= 0 && w_lo < s) ? w_hi / BK : -1;
-    const int my_last = KS == 1 ? last_tile : (last_tile >= kg ? (last_tile - kg) / KS : -1);   // last one with a visible key for this wave
+    const int my_last = (w_lo >= 0 && w_lo < s) ? w_hi / BK : -1;      // last tile with a visible key for this wave
 
     // Load x of this wave covers tile rows (wave * LD + x) * RPI + lane / CPR; the lane's chunk of the LDS
     // row is lane % CPR.  The LDS serves 256 bytes a clock: 16 lanes of a fragment read (16 neighbouring rows
@@ -506,10 +489,10 @@ swa_flash16_kernel(FlashArgs a)
     // Load x = 0 .. 2 LD - 1 of the staging of tile kt (uniform base; cap <= SWA_MAX_CAP: below 8 MiB).  Before the
     // prompt's last tile, which no full one follows, edge() aims the lanes at rows that exist.
     auto edge = [&](int kt) {
-        if (key0(kt) + BK > s) offsets(s - 1 - key0(kt));
+        if (kt * BK + BK > s) offsets(s - 1 - kt * BK);
     };
     auto load = [&](int x, int kt, char* dk, char* dv) {
-        const uint32_t at = (uint32_t)key0(kt) * ROWB;
+        const uint32_t at = (uint32_t)kt * (BK * ROWB);
         if (x < LD) load_to_lds(Kp + at, offK[x], lds_address(dk) + (wave * LD + x) * 1024);
         else load_to_lds(Vp + at, offV[x - LD], lds_address(dv) + (wave * LD + x - LD) * 1024);
     };
@@ -520,7 +503,7 @@ swa_flash16_kernel(FlashArgs a)
     };
     offsets(BK);
 
-    if (KS == 1 || nkt > 0) stage(0, s_k0, s_v0);
+    stage(0, s_k0, s_v0);
     Vec16 qv[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) qv[v] = load16(Qp + (int64_t)tq * ROWB + v * 32 + hb * 16);
@@ -571,10 +554,10 @@ swa_flash16_kernel(FlashArgs a)
                 for (int x = 0; x < LPS; ++x) load((v >> 1) * LPS + x, st, nk, nv);
         }
         // only the tiles that reach the wave's diagonal need the causal mask
-        if (key0(kt) + BK - 1 > w_lo) {
+        if (kt * BK + BK - 1 > w_lo) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int key = key0(kt) + 8 * (i / 4) + 4 * hb + (i % 4);
+                const int key = kt * BK + 8 * (i / 4) + 4 * hb + (i % 4);
                 c[i] = (key <= tq) ? c[i] : -INFINITY;
             }
         }
@@ -640,39 +623,6 @@ swa_flash16_kernel(FlashArgs a)
             stage(st, buf == 0 ? s_k2 : (buf == 1 ? s_k0 : s_k1), buf == 0 ? s_v2 : (buf == 1 ? s_v0 : s_v1));
         }
     }
-    if constexpr (KS > 1) {
-        for (int r = nkt; r < rounds; ++r) ready(false);
-        // The groups' sums over their keys, to the first group's waves.  No load is on its way any more; the buffers are free
-        // once every wave has arrived.
-        constexpr int PER = CT * 16 + 2;
-        float* part = reinterpret_cast<float*>(smem) + lane;
-        __syncthreads();
-        if (kg > 0) {
-            float* p = part + ((kg - 1) * QW + wave) * PER * kWave;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) p[(ct * 16 + i) * kWave] = o[ct][i];
-            p[(PER - 2) * kWave] = m;
-            p[(PER - 1) * kWave] = l;
-        }
-        __syncthreads();
-        if (kg > 0) return;
-#pragma unroll
-        for (int g = 1; g < KS; ++g) {
-            const float* p = part + ((g - 1) * QW + wave) * PER * kWave;
-            const float m2 = p[(PER - 2) * kWave], l2 = p[(PER - 1) * kWave];
-            const float top = fmaxf(m, m2);
-            const float f1 = __builtin_amdgcn_exp2f(m - top), f2 = __builtin_amdgcn_exp2f(m2 - top);
-            m = top;
-            l = l * f1 + l2 * f2;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[ct][i] = o[ct][i] * f1 + p[(ct * 16 + i) * kWave] * f2;
-        }
-    }
-
     float l_lo, l_hi;
     both_halves(l, l_lo, l_hi);
     l = l_lo + l_hi;
@@ -712,24 +662,13 @@ static bool flash_grid(FlashArgs& a, int bound, int bq, int64_t& wgs)
     return wgs <= 0x7fffffffLL;
 }
 
-template <typename T, int D, int QW, int KS>
-static int launch_flash16_form(FlashArgs a, int bound, hipStream_t stream)
+template <typename T, int D>
+static int launch_flash16(FlashArgs a, int bound, hipStream_t stream)
 {
     int64_t wgs = 0;
-    if (!flash_grid(a, bound, 32 * QW, wgs)) return SWA_ERR_BAD_SHAPE;
-    constexpr size_t lds = KS == 1 ? 0 : (size_t)KS * 6 * 32 * D * 2;
-    static_assert(KS == 1 || lds >= (size_t)(KS - 1) * QW * (D / 2 + 2) * 256, "the groups' sums fit where the tiles were");
-    auto kern = swa_flash16_kernel<T, D, QW, KS>;
-    const int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-    if (rc != SWA_OK) return rc;
-    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(64 * QW * KS), lds, stream, a);
+    if (!flash_grid(a, bound, 128, wgs)) return SWA_ERR_BAD_SHAPE;
+    hipLaunchKernelGGL((swa_flash16_kernel<T, D>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
-}
-
-template <typename T, int D>
-static int launch_flash16(const FlashArgs& a, int bound, hipStream_t stream)
-{
-    return launch_flash16_form<T, D, 4, 1>(a, bound, stream);
 }
 
 int launch_flash_prefill(const swa_params& p, float scale, const void* q, const void* k_cache, const void* v_cache,
