@@ -68,7 +68,8 @@ __device__ __forceinline__ bool query_block(const FlashArgs& a, int bq, int64_t&
     if (pair >= a.pairs) return false;
     s = a.cache_len[(uint32_t)pair / (uint32_t)a.h];
     s = s > a.cap ? a.cap : s;
-    const int q_end = (s + 31) & ~31;
+    int q_end = (s + 31) & ~31;
+    q_end = q_end < a.nqb * bq ? q_end : a.nqb * bq;     // (a prompt beyond the stated bound: its rows up to the bound)
     const int blocks = (q_end + bq - 1) / bq;
     q0 = q_end - (blocks - qb) * bq;                     // (negative in a first block that is not full)
     return qb < blocks;

@@ -93,3 +93,26 @@ def test_every_query_block_is_dealt_out_once(dtype, d, b, h, bound):
     for i in range(b):
         B.swa_prefill_attention(p, q[i:i + 1], k[i:i + 1], v[i:i + 1], cl[i:i + 1], one[i:i + 1], 0, None, ws)
     assert torch.equal(got, one)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float16, 128), (torch.bfloat16, 64), (torch.float32, 64)])
+@pytest.mark.parametrize("bound", [100, 128, 300])
+def test_rows_below_a_bound_that_a_prompt_exceeds(dtype, d, bound):
+    """A prompt longer than the stated bound: the rows below the bound are those of the same call without one."""
+    from paper_2403_17312_amd import binding as B
+    b, h, cap = 4, 3, 700
+    g = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    lens = [bound - 1, bound, bound + 61, cap]
+    cl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(1024, dtype=torch.uint8, device="cuda")
+    got, want = torch.full_like(q, 7.0), torch.full_like(q, 7.0)
+    B.swa_prefill_attention(B.make_params(b, h, d, cap, 4, 8000, dtype, len_bound=bound), q, k, v, cl, got, 0, None, ws)
+    B.swa_prefill_attention(B.make_params(b, h, d, cap, 4, 8000, dtype), q, k, v, cl, want, 0, None, ws)
+    # two kernels where one side is served by the one for short prompts: each within 1.5 u (sum_j p_j |v_jc| + |out_c|) + 1e-5 of the
+    # exact result (test_every_tile_count), and both terms are at most max |v| < 7
+    u = {torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8, torch.float32: 2.0 ** -20}[dtype]
+    for i, n in enumerate(lens):
+        top = min(n, bound)
+        err = (got[i, :, :top].float() - want[i, :, :top].float()).abs().max().item()
+        assert err <= 2 * (1.5 * u * 2 * 7 + 1e-5), (n, err)
