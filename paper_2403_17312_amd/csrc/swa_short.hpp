@@ -3,9 +3,14 @@
 // What bounds the step there is latency, not bytes: 512 pairs of 106 rows are 28 MB, 4 us of reading, and the streaming
 // kernel (swa_decode.hip) takes 6.8 us a workgroup, 4.0 for rows that arrive in four stages and 2.7 for the phases
 // behind them (softmax, selection, the evicted row's second read, output, importance), with a barrier between each two.  Here
-//   - every key and value row of the pair is requested at once, the first half before the length is known;
+//   - every key and value row of the pair is requested at once, the first quarter before the length is known;
 //   - the value rows stay in registers until the selection is known, so the output is the sum over the kept rows
 //     alone and nothing is read twice;
+//   - where most rows go (the step after a short prompt) the values wait for the selection instead and only kept rows' are read,
+//     candidates are ranked by 32-bit counts that all waves share, and rows and ring columns that change slot are moved many at
+//     a time.  Streaming kernel / this one with all values read, 64-bit counts and moves one by one / as it is, us a step with four
+//     fifths of the rows evicted: 512 pairs x 206, f16, d = 128 20.5 / 23.8 / 18.7; 4096 x 256, f16, d = 64 66.8 / 78.8 / 58.2, strict
+//     window of 16 rows 86 / 126 / 74, head-shared 90 / 119 / 73;
 //   - every wave holds all logits, importance values and positions (one to four slots per lane) and forms softmax,
 //     importance and selection for itself: one barrier behind the logits, one before the output.
 // Weights, importance and kept set are bit-identical to the streaming kernel's (same products, same order of additions).
@@ -51,15 +56,17 @@ swa_short_kernel(DecodeArgs a)
     typedef typename Act<T>::type AT;
     constexpr int XROWB = D * Elem<AT>::kBytes;
     constexpr bool kQ8 = Elem<T>::kBytes == 1;
-    constexpr int PARTS = NW / SL;                       // strict window: waves that share the rows of a chunk's ring
+    constexpr int PARTS = NW / SL;                       // waves that share what a chunk has to do
     constexpr int kRingAhead = PARTS > 1 ? 16 : 32;      // ring entries per lane requested ahead
     static_assert(ROWS % kWave == 0 && kWave % NG == 0 && SL <= NW, "every wave has a chunk of 64 slots at most");
 
     __shared__ float s_z[ROWS];                          // logits
     __shared__ float s_sc[RING ? ROWS : 1];              // new importance
-    __shared__ unsigned long long s_cand[ROWS];          // several evictions: (key, ~token) of the candidates
-    __shared__ uint64_t s_mask[SL];                      // several evictions: kept slots
-    __shared__ uint16_t s_hole[ROWS], s_dst[ROWS];       // several evictions, unordered: holes, and every slot's final slot
+    __shared__ __align__(16) uint32_t s_key[ROWS];       // several evictions: what the candidates are ranked by
+    __shared__ uint16_t s_above[PARTS > 1 ? PARTS * ROWS : 1];         // ... their ranks, by parts of the keys
+    __shared__ uint64_t s_mask[SL];                      // ... and which slots are kept
+    __shared__ int32_t s_in[SL], s_top;
+    __shared__ uint16_t s_hole[ROWS], s_mov[ROWS];       // several evictions, unordered: holes, and the slots that fill them
     __shared__ float s_acc[NW * D];
     __shared__ __align__(16) unsigned char s_newc[kQ8 ? 2 * D : 16];   // codes of the new K and V rows
     __shared__ __align__(16) float s_qs[kQ8 ? D : 4];
@@ -209,22 +216,28 @@ swa_short_kernel(DecodeArgs a)
         const int wlo = n - w_eff;                       // unordered layout: the window is pos >= wlo
         const int E = m - keep;
 
+        const bool listed = E > 1 || (E == 1 && n_global <= 0);
+        // Where most rows go (the step after a prompt), the values wait until the selection is known, and only those of kept rows are
+        // read; the first launch of the head-shared step has no use for them then.
+        const bool late = PHASE == 1 ? listed : 2 * E > m;
+
         // ---- the other rows, logits -------------------------------------------------------------
         // As many rows per lane as the length needs, in steps of UE (the counts are written out so that the compiler knows
         // what is in flight when a key row is used).  Lanes past the end read slot `len`; what they find has no weight.
         float z[U];
-        auto rows = [&](auto count) __attribute__((always_inline)) {
+        auto rows = [&](auto count, auto values) __attribute__((always_inline)) {
             constexpr int C = count.value;
+            constexpr int CV = values.value ? C : UE;
 #pragma unroll
             for (int u = UE; u < C; ++u) {
                 kv[u] = load16_stream(Kp + at(u, len));
             }
 #pragma unroll
-            for (int u = UE; u < C; ++u) {
+            for (int u = UE; u < CV; ++u) {
                 vv[u] = load16_stream(Vp + at(u, len));
             }
 #pragma unroll
-            for (int u = C; u < U; ++u) vv[u] = Vec16{0u, 0u, 0u, 0u};
+            for (int u = CV; u < U; ++u) vv[u] = Vec16{0u, 0u, 0u, 0u};
             new_rows();
 #pragma unroll
             for (int u = 0; u < C; ++u) z[u] = group_sum<LPR>(qf.dot(kv[u], 0.f)) * a.scale;
@@ -235,10 +248,11 @@ swa_short_kernel(DecodeArgs a)
         float p[SL], ex[SL], sc[SL];
         if constexpr (PHASE != 2) {
         const int stages = (m + NG * UE - 1) / (NG * UE);
-        if (stages <= 1) rows(std::integral_constant<int, UE>());
-        else if (stages == 2) rows(std::integral_constant<int, 2 * UE>());
-        else if (stages == 3) rows(std::integral_constant<int, 3 * UE>());
-        else rows(std::integral_constant<int, U>());
+        if (late) rows(std::integral_constant<int, U>(), std::false_type());
+        else if (stages <= 1) rows(std::integral_constant<int, UE>(), std::true_type());
+        else if (stages == 2) rows(std::integral_constant<int, 2 * UE>(), std::true_type());
+        else if (stages == 3) rows(std::integral_constant<int, 3 * UE>(), std::true_type());
+        else rows(std::integral_constant<int, U>(), std::true_type());
         // every lane of a group has the group's logits: lane u of it stores row u's
         {
             float zs = z[0];
@@ -355,7 +369,7 @@ swa_short_kernel(DecodeArgs a)
         };
         uint64_t kept[SL];                               // kept slots, the same in every lane
         int jstar = m;                                   // one eviction: the evicted slot (m = none)
-        const bool listed = E > 1 || (E == 1 && n_global <= 0);
+        int moves = 0, final_slot = kNowhere;            // listed, unordered: rows that change slot; where this lane's slot goes
         if (!listed || PHASE == 1) {
             if (E == 1 && PHASE != 1) {
                 unsigned long long best = ~0ull;
@@ -378,31 +392,73 @@ swa_short_kernel(DecodeArgs a)
                 kept[k] = __ballot(i < m && i != jstar);
             }
         } else {
-            // A candidate is kept if fewer than n_global candidates go before it: larger importance, or the same and an
-            // earlier token.  Rare (the step after a short prompt, a budget that was cut), so it is simply counted.
+            // Kept: what is no candidate, and of the candidates the n_global that come first, by larger importance, then by earlier
+            // token.  A candidate's rank is counted, over the keys first and, where equal ones lie across the line, over their
+            // tokens; the waves of a chunk share the count.  (Looking for the last kept key bit by bit in registers took twice as long.)
             if (bag) {
                 int present = 0;
 #pragma unroll
                 for (int k = 0; k < SL; ++k) present += (int)__popcll(__ballot(lane + k * kWave < m && pold[k] >= wlo));
                 n_global = keep - present;
             }
-#pragma unroll
-            for (int k = 0; k < SL; ++k)
-                if (k == wave) s_cand[mine] = candidate(k) ? rank_key(k) : 0ull;
-            __syncthreads();
+            bool open = false, stays = false;            // this lane's slot of the chunk
+            uint32_t key = 0u, token = 0u;
 #pragma unroll
             for (int k = 0; k < SL; ++k) {
-                if (k != wave) continue;
-                const bool cand = candidate(k);
-                const unsigned long long c = rank_key(k);
-                int before = 0;
-                for (int j = 0; j < m; ++j) before += s_cand[j] > c ? 1 : 0;
-                const uint64_t b = __ballot(mine < m && (!cand || before < n_global));
-                if (lane == 0) s_mask[k] = b;
+                const bool c = candidate(k);
+                const unsigned long long r = rank_key(k);
+                open = k == chunk ? c : open;
+                key = k == chunk ? (uint32_t)(r >> 32) : key;
+                token = k == chunk ? (uint32_t)r : token;
+                kept[k] = __ballot(lane + k * kWave < m && !c);
             }
-            __syncthreads();
+            stays = mine < m && !open;
+            int left = n_global;                         // how many of the open ones stay
+            for (int round = 0; round < 2 && left > 0; ++round) {
+                const uint32_t own = open ? (round ? token : key) : 0u;
+                if (owner) s_key[mine] = own;
+                if (tid == 0) s_top = 0;
+                __syncthreads();
+                const int part = wave / SL;
+                const int hi = (part + 1) * (ROWS / PARTS) < m ? (part + 1) * (ROWS / PARTS) : m;
+                int above = 0;
+                for (int j = part * (ROWS / PARTS); j < hi; j += 16) {
 #pragma unroll
-            for (int k = 0; k < SL; ++k) kept[k] = s_mask[k];
+                    for (int u = 0; u < 16; u += 4) {
+                        const uint4 v = *reinterpret_cast<const uint4*>(&s_key[j + u]);
+                        above += (v.x > own ? 1 : 0) + (v.y > own ? 1 : 0) + (v.z > own ? 1 : 0) + (v.w > own ? 1 : 0);
+                    }
+                }
+                if constexpr (PARTS > 1) {
+                    if (part < PARTS) s_above[part * ROWS + mine] = (uint16_t)above;
+                    __syncthreads();
+                    above = 0;
+#pragma unroll
+                    for (int q = 0; q < PARTS; ++q) above += s_above[q * ROWS + mine];
+                }
+                const bool in = open && above < left;
+                const uint64_t b = __ballot(in || stays), c = __ballot(in);
+                if (owner && lane == 0) {
+                    s_mask[wave] = b;
+                    s_in[wave] = (int)__popcll(c);
+                }
+                __syncthreads();
+                int got = 0;
+#pragma unroll
+                for (int k = 0; k < SL; ++k) {
+                    kept[k] = s_mask[k];
+                    got += s_in[k];
+                }
+                if (__builtin_amdgcn_readfirstlane(got) <= left) break;
+                // equal keys across the line: those with the most keys above them
+                if (owner && in) atomicMax(&s_top, above);
+                __syncthreads();
+                const int top = __builtin_amdgcn_readfirstlane(s_top);
+                stays = stays || (in && above < top);
+                open = in && above == top;
+                left -= top;
+                __syncthreads();
+            }
             if (bag) {
                 // holes below `keep` are filled by kept rows above it, in ascending order both
                 auto below = [&](int limit, int k) -> uint64_t {           // slots of chunk k below limit
@@ -418,14 +474,15 @@ swa_short_kernel(DecodeArgs a)
                     if (k == wave) {
                         if ((hm >> lane) & 1ull) s_hole[holes + (int)__popcll(hm & lower)] = (uint16_t)mine;
                         mr = movers + (int)__popcll(mm & lower);
+                        if ((mm >> lane) & 1ull) s_mov[mr] = (uint16_t)mine;
                         is_kept = (kept[k] >> lane) & 1ull;
                     }
                     holes += (int)__popcll(hm);
                     movers += (int)__popcll(mm);
                 }
                 __syncthreads();
-                if (owner) s_dst[mine] = !is_kept ? kNowhere : (mine < keep ? mine : (mr < holes ? s_hole[mr] : kNowhere));
-                __syncthreads();
+                if (is_kept) final_slot = mine < keep ? mine : (mr < holes ? (int)s_hole[mr] : kNowhere);
+                moves = holes < movers ? holes : movers;
             }
         }
 
@@ -451,7 +508,7 @@ swa_short_kernel(DecodeArgs a)
 #pragma unroll
             for (int e = 0; e < EPV; ++e) acc[e] = (grp == 0 && !(wn < 0.f)) ? wn * f[e] : 0.f;
         }
-        bool subtract = false;
+        bool subtract = PHASE == 1 && late;              // (then the second launch sums the kept rows up)
         if constexpr (PHASE == 2) {
             // one row or none leaves the dense output; where little weight would be left the kept rows are added up instead
             float pj = p[0];
@@ -478,15 +535,16 @@ swa_short_kernel(DecodeArgs a)
                     store16(a.out + pair * XROWB + sub * 16, pack<T>(f));
                 }
             }
-            if (!subtract) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) vv[u] = load16(Vp + at(u, len));
-            }
         }
         if (!subtract) {
         float w[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) w[u] = __shfl(pk[u * NG / kWave], u * NG % kWave + grp, kWave);
+        if (PHASE == 2 || late) {
+#pragma unroll
+            for (int u = PHASE == 2 ? 0 : UE; u < U; ++u)
+                if (u * NG + grp < len && !(w[u] < 0.f)) vv[u] = load16(Vp + at(u, len));
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int row = u * NG + grp;
@@ -527,18 +585,12 @@ swa_short_kernel(DecodeArgs a)
                     if (in) kout[first + (int)__popcll(kept[k] & ((1ull << lane) - 1ull))] = mine;
                 } else {
                     int dst = kNowhere;
-                    if (in) dst = listed ? (int)s_dst[mine] : (mine == len && hole < m ? hole : mine);
+                    if (in) dst = listed ? final_slot : (mine == len && hole < m ? hole : mine);
                     if (dst < keep) {
                         Sp[dst] = sc[k];
                         if (dst != mine || mine == len) Pp[dst] = pold[k];
                         if (kout) kout[dst] = mine;
-                        if constexpr (RING) {
-                            Rg[(int64_t)a.ring_row * cap + dst] = p[k];
-                            // the other rows of the ring follow a token that moved; the new token has none
-                            if (listed && (dst != mine || mine == len))
-                                for (int j = 0; j < a.ring_rows; ++j)
-                                    if (j != a.ring_row) Rg[(int64_t)j * cap + dst] = mine == len ? 0.f : Rg[(int64_t)j * cap + mine];
-                        }
+                        if constexpr (RING) Rg[(int64_t)a.ring_row * cap + dst] = p[k];
                     }
                 }
             }
@@ -557,18 +609,45 @@ swa_short_kernel(DecodeArgs a)
                 }
             }
         } else {
+            // The rows that change slot, the new token's among them; nobody reads what lies in their final slots.
+            for (int r0 = grp; r0 < moves; r0 += 2 * NG) {
+                Vec16 x[2], y[2];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int row = u * NG + grp;
-                const int dst = row < m ? (int)s_dst[row] : kNowhere;
-                if (dst < keep && (dst != row || row == len)) {
-                    Vec16 x = nk, y = nv;
-                    if (row < len) {
-                        x = load16(Kp + row * ROWB + sub * 16);
-                        y = load16(Vp + row * ROWB + sub * 16);
+                for (int u = 0; u < 2; ++u) {
+                    x[u] = nk;
+                    y[u] = nv;
+                    const int src = r0 + u * NG < moves ? (int)s_mov[r0 + u * NG] : len;
+                    if (src != len) {
+                        x[u] = load16(Kp + src * ROWB + sub * 16);
+                        y[u] = load16(Vp + src * ROWB + sub * 16);
                     }
-                    store16(Kp + dst * ROWB + sub * 16, x);
-                    store16(Vp + dst * ROWB + sub * 16, y);
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (r0 + u * NG < moves) {
+                        const int dst = s_hole[r0 + u * NG];
+                        store16(Kp + dst * ROWB + sub * 16, x[u]);
+                        store16(Vp + dst * ROWB + sub * 16, y[u]);
+                    }
+                }
+            }
+            if constexpr (RING) {
+                // the other rows of the ring follow them; the new token has none there
+                for (int j0 = wave; j0 < a.ring_rows; j0 += 4 * NW) {
+                    for (int r = lane; r < moves; r += kWave) {
+                        const int src = s_mov[r], dst = s_hole[r];
+                        float v[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int j = j0 + u * NW;
+                            v[u] = (src != len && j < a.ring_rows) ? Rg[(int64_t)j * cap + src] : 0.f;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int j = j0 + u * NW;
+                            if (j < a.ring_rows && j != a.ring_row) Rg[(int64_t)j * cap + dst] = v[u];
+                        }
+                    }
                 }
             }
         }
