@@ -65,6 +65,9 @@ void seed_stats_place(int64_t pairs, int bound, int cap, int R, int& G, int& col
 // Whether the seed on its own runs as two launches (bound on the lengths: stated by the caller, or the capacity).
 bool seed_in_two(int64_t pairs, int bound, bool stated, int R);
 
+// Whether its row statistics then come from four workgroups per 32 rows, whose sums the column sums merge, or from one.
+bool seed_chains_apart(int G, int cols, int cap, int R);
+
 // SWA_SPLIT_ROWS: workgroups per pair for this many pairs and this bound on the cached length
 // (1 = the one-workgroup kernel serves the call), and the launches of the step.
 constexpr int kMaxSplit = 16;

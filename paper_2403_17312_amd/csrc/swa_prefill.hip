@@ -46,7 +46,8 @@ struct PrefillArgs {
 
 // What one launch does.
 constexpr int kSeedWhole = 0;   // both passes, one workgroup per pair
-constexpr int kSeedSums = 1;    // column sums of one slice, from the row statistics of another launch
+constexpr int kSeedStats = 1;   // row statistics of 32 rows of one pair, a copy for every slice
+constexpr int kSeedSums = 2;    // column sums of one slice, from the row statistics of another launch
 constexpr int kChains = 4;      // row statistics: key tile t belongs to chain t % 4, whose sums are merged in ascending order
 
 // Merge two (max, sum-of-exp2) pairs of disjoint key sets.
@@ -110,11 +111,13 @@ __device__ __forceinline__ void add_tile_stats_flat(const float16_t& c, int tile
 // same order as in the kernel below, whose pass 1 this is where a pair's keys are long and pairs few.
 //
 // Bound: the chain of a tile's steps in the one wave that owns it, 0.6 us a tile (32 pairs x 8192 keys, f16, d = 128, R =
-// 64: 38 us; 60 with the operands' own layout and 64 workgroups).  A tile's rows are loaded as they lie, whole lines by one
+// 64: 37 us; 60 with the operands' own layout and 64 workgroups).  A tile's rows are loaded as they lie, whole lines by one
 // instruction (an operand's own layout takes 32 bytes of a line at a time, and lines were lost between their
 // uses), and reach that layout by way of LDS, in which a row's 16-byte chunks are permuted by the row
 // so that the lanes of a read spread over the banks.  A chain cannot be cut (its sum has an order), so its one wave
-// overlaps what a tile needs: loads, LDS, products and exponentials of different tiles.
+// overlaps what a tile needs: loads, LDS, products and exponentials of different tiles.  Rows of 512 bytes (fp32, d = 128) leave no
+// registers for that and are bound by their products; they keep the operands' own layout (kSeedStats below; whole seed, 32
+// pairs x 4096 keys, R = 64: 111 us, 118 by way of LDS; 32 keys 17.6 / 21.9).
 template <typename T, int D, bool WR, int NW>
 __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(1, 1)))
 swa_seed_stats_kernel(PrefillArgs a)
@@ -124,8 +127,8 @@ swa_seed_stats_kernel(PrefillArgs a)
     constexpr int CPR = ROWB / 16;                   // chunks of a row
     constexpr int RPI = kWave / CPR;                 // rows per load instruction
     constexpr int NL = 32 / RPI;                     // loads per lane and tile
-    constexpr int AHEAD = ROWB >= 512 ? 2 : 4;      // tiles requested ahead, 32 KiB of them (even: fragments alternate)
-    constexpr int NF = ROWB >= 512 ? 1 : 2;         // tiles of fragments (rows of 512 bytes leave no registers for a second)
+    constexpr int AHEAD = 4;                         // tiles requested ahead (even: the two tiles of fragments alternate)
+    static_assert(ROWB < 512, "no registers for wider rows");
     __shared__ __align__(16) char s_tile[NW][32 * ROWB];
     __shared__ float s_m[NW][32], s_l[NW][32];
 
@@ -191,14 +194,14 @@ swa_seed_stats_kernel(PrefillArgs a)
     float M = -INFINITY, L = 0.f;
     const int nt = (tiles - chain + kChains - 1) / kChains;      // (0 or less: nothing to do)
     const int seen = (s - R + rt0 * 32 + 1) / 32;                // tiles below it: every row sees all keys
-    Vec16 kr[AHEAD][NL], f[NF][NV];
+    Vec16 kr[AHEAD][NL], f[2][NV];
     float16_t c;
     if (nt > 0) {
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) request(u, kr[u]);
         stage(kr[0], f[0]);
         c = products(f[0]);
-        stage(kr[1], f[1 % NF]);
+        stage(kr[1], f[1]);
         request(AHEAD, kr[0]);
         request(AHEAD + 1, kr[1]);
     }
@@ -206,9 +209,8 @@ swa_seed_stats_kernel(PrefillArgs a)
         auto some = [&](auto all_seen) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
-                if (NF > 1) stage(kr[(u + 2) % AHEAD], f[u % NF]);          // tile t + u + 2
-                const float16_t next = products(f[(u + 1) % NF]);
-                if (NF == 1) stage(kr[(u + 2) % AHEAD], f[0]);
+                stage(kr[(u + 2) % AHEAD], f[u % 2]);                       // tile t + u + 2
+                const float16_t next = products(f[(u + 1) % 2]);
                 add_tile_stats_flat<all_seen.value>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
@@ -265,7 +267,10 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int wave = tid >> 6;
     const int l32 = lane & 31;
     const int hb = lane >> 5;
-    const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : blockIdx.x;
+    constexpr bool kStats = MODE == kSeedStats;
+    const int row_tiles = kStats ? (a.R + 31) / 32 : 1;
+    const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : blockIdx.x / row_tiles;
+    const int rt0 = kStats ? blockIdx.x % row_tiles : 0;        // first row tile of this workgroup
     const int g = MODE == kSeedSums ? blockIdx.x % a.G : 0;
     const int cap = a.cap;
     const int R = a.R;
@@ -278,6 +283,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     float* Rp = WR ? a.rows + pair * (int64_t)R * cap : nullptr;
 
     if (s <= 0) {
+        if (kStats) return;
         if (Sp)
             for (int j = col0 + tid; j < col1; j += NT) Sp[j] = 0.f;
         if (Rp)
@@ -300,7 +306,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     Vec16 qv[RT][NV];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-        const int r = rt * 32 + l32;
+        const int r = (rt0 + rt) * 32 + l32;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int qrow = qbase + r > 0 ? qbase + r : 0;          // rows before the prompt are masked below
@@ -342,12 +348,25 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             for (int i = 0; i < 16; ++i) c[i] = 0.f;
 #pragma unroll
             for (int v = 0; v < NV; ++v) c = Mfma<T>::run(kv[v], qv[rt][v], c);   // C[key][query]
-            const int r = rt * 32 + l32;
+            const int r = (rt0 + rt) * 32 + l32;
             const int tmax = (r < R) ? t_off + r : -1;   // last visible key of this lane's query
             add_tile_stats(c, tile, hb, tmax, a.scale_log2e, M[rt], L[rt]);
         }
     };
-    {
+    if constexpr (kStats) {
+        // one workgroup has a CU to itself: three tiles per wave in flight while a fourth is reduced
+        constexpr int AHEAD = 4;
+        Vec16 kr[AHEAD][NV];
+#pragma unroll
+        for (int u = 0; u < AHEAD - 1; ++u) load_tile(tile0 + wave + u * NW, kr[u]);
+        for (int tile = tile0 + wave; tile < tile1; tile += AHEAD * NW) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                load_tile(tile + (u + AHEAD - 1) * NW, kr[(u + AHEAD - 1) % AHEAD]);
+                if (tile + u * NW < tile1) stats_tile(tile + u * NW, kr[u]);
+            }
+        }
+    } else {
         Vec16 kA[NV], kB[NV];
         load_tile(tile0 + wave, kA);
         for (int tile = tile0 + wave; tile < tile1; tile += 2 * NW) {
@@ -372,10 +391,21 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         float Mt = s_m[0][tid], Lt = s_l[0][tid];
 #pragma unroll
         for (int v = 1; v < NW; ++v) merge_stats(Mt, Lt, s_m[v][tid], s_l[v][tid]);
+        if constexpr (kStats) {
+            const int r = rt0 * 32 + tid;
+            if (r < R) {
+                for (int g2 = 0; g2 < a.G; ++g2) {
+                    St[(int64_t)g2 * a.cols + r] = Mt;
+                    St[(int64_t)g2 * a.cols + R + r] = Lt;
+                }
+            }
+            return;
+        }
         const bool ok = Mt > -INFINITY && Lt > 0.f;
         s_M[tid] = ok ? Mt : 0.f;
         s_invL[tid] = ok ? 1.f / Lt : 0.f;
     }
+    if constexpr (kStats) return;
     __syncthreads();
     }
     if constexpr (MODE == kSeedSums) {
@@ -452,10 +482,10 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
 }
 
 // Slices per pair for the column sums.  One workgroup per pair reads its keys twice at about 30 GB/s, and with few
-// pairs most of the chip waits for it.  The statistics of 32 rows stay with one workgroup (their sum has an order, and the
-// selection that follows can hang on its last bit), which then keeps twice as many loads in flight; the column
-// sums are independent and get one workgroup per CU in all, over the columns up to the bound on the lengths (the last
-// slice has the rest).  Every slice holds the row statistics and is about 256 keys long at least.
+// pairs most of the chip waits for it.  The statistics of 32 rows are four chains of key tiles, one wave each, merged in a fixed
+// order (the selection that follows can hang on the sum's last bit): in one workgroup, or in four whose sums
+// the column sums' launch merges.  The column sums are independent and get one workgroup per CU in all, over the columns up to the
+// bound on the lengths (the last slice has the rest).  Every slice holds the row statistics and is about 256 keys long at least.
 constexpr int kSeedGrid = 256;
 static int seed_slices(int64_t pairs, int bound, int cap, int R, int& cols)
 {
@@ -488,10 +518,8 @@ bool seed_in_two(int64_t pairs, int bound, bool stated, int R)
     return stated && pairs <= 128 && pairs * ((R + 31) / 32) <= 256 && bound >= 4096;
 }
 
-// Does every chain of the statistics get a workgroup of its own?  Where a slice has the room to bring all of them along.  (Not
-// with rows of 512 bytes: fp32 products bound that kernel wherever its waves sit, and one wave alone
-// runs out of registers.)
-static bool seed_chains_apart(int G, int cols, int cap, int R)
+// Does every chain of the statistics get a workgroup of its own?  Where a slice has the room to bring all of them along.
+bool seed_chains_apart(int G, int cols, int cap, int R)
 {
     const int room = 2 * kChains * R;
     return cols >= room && (int64_t)(G - 1) * cols + room <= cap;
@@ -506,11 +534,11 @@ static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hip
     if (stats_ready) {
         hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
     } else if (G > 1 && seed_in_two(pairs, a.bound, a.stated, a.R)) {
-        constexpr bool kMayPart = D * Elem<T>::kBytes < 512;
-        if (kMayPart && seed_chains_apart(G, a.cols, a.cap, a.R)) {
+        if constexpr (D * Elem<T>::kBytes >= 512) {
+            hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
+        } else if (seed_chains_apart(G, a.cols, a.cap, a.R)) {
             a.chains = kChains;
-            if constexpr (kMayPart)
-                hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, 1>), dim3((unsigned)(pairs * RT * kChains)), dim3(kWave), 0, stream, a);
+            hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, 1>), dim3((unsigned)(pairs * RT * kChains)), dim3(kWave), 0, stream, a);
         } else {
             hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, kChains>), dim3((unsigned)(pairs * RT)), dim3(kChains * kWave), 0, stream, a);
         }
