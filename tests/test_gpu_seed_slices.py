@@ -1,5 +1,6 @@
 """The importance seed where its keys are cut into slices (few pairs, long caches), and where the attention kernel hands
 over the row statistics: every prompt length around the slices' ends, against plain fp64 attention weights."""
+import ctypes
 import math
 
 import pytest
@@ -128,11 +129,19 @@ def test_bound_below_the_capacity(dtype, d, R, bound):
 
 @pytest.mark.parametrize("dtype,d,cap,R", [(torch.float16, 128, 4200, 64), (torch.bfloat16, 64, 4200, 33),
                                            (torch.float16, 64, 2200, 32), (torch.float32, 64, 4200, 64), (torch.float32, 128, 2200, 7)])
-def test_statistics_in_four_chains(dtype, d, cap, R):
-    """Few pairs, slices wide enough for the statistics of every chain: prompts that end around a round of the chains' tiles."""
+@pytest.mark.parametrize("h", [1, 4])
+def test_statistics_in_four_chains(dtype, d, cap, R, h):
+    """Few pairs, the statistics' four chains in one workgroup (slices of 256 columns) and in one each (slices that can bring all
+    four along): prompts that end around a round of the chains' tiles."""
     from paper_2403_17312_amd import binding as B
     lens = [R - 1, 33, 127, 128, 129, 1023, 1025, 2047, 2049, cap]
-    b, h = len(lens), 1
+    b = len(lens)
+    if dtype != torch.float32 or d == 64:                  # (rows of 512 bytes have a form of their own)
+        place, apart = (getattr(B.lib(), n) for n in ("_ZN3swa16seed_stats_placeEliiiRiS0_", "_ZN3swa17seed_chains_apartEiiii"))
+        place.restype, apart.restype = None, ctypes.c_bool
+        G, cols = ctypes.c_int(), ctypes.c_int()
+        place(ctypes.c_int64(b * h), cap, cap, R, ctypes.byref(G), ctypes.byref(cols))
+        assert apart(G, cols, cap, R) is (h == 4)
     g = torch.Generator(device="cuda").manual_seed(29)
     k = torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype)
     tail = torch.randn((b, h, R, d), generator=g, device="cuda").to(dtype)

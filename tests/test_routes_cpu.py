@@ -44,3 +44,17 @@ def test_every_slice_of_the_seed_holds_its_statistics(L):
         for g in range(G.value):
             end = cap if g == G.value - 1 else (g + 1) * cols.value
             assert g * cols.value + 2 * R <= end, (pairs, bound, cap, R, G.value, cols.value)
+
+
+@pytest.mark.parametrize("pairs,bound,cap,R,apart", [
+    (32, 8192, 8256, 64, True), (32, 8192, 8192, 64, True), (40, 4200, 4200, 64, True), (40, 4200, 4200, 33, True),
+    (128, 4096, 4096, 64, True), (10, 4200, 4200, 64, False), (10, 2200, 2200, 32, False), (64, 1024, 1024, 64, False),
+    (64, 1024, 1024, 16, True)])
+def test_chains_of_the_statistics_get_workgroups_where_a_slice_can_bring_them_along(L, pairs, bound, cap, R, apart):
+    place, rule = L._ZN3swa16seed_stats_placeEliiiRiS0_, L._ZN3swa17seed_chains_apartEiiii
+    place.restype, rule.restype = None, ctypes.c_bool
+    G, cols = ctypes.c_int(), ctypes.c_int()
+    place(ctypes.c_int64(pairs), bound, cap, R, ctypes.byref(G), ctypes.byref(cols))
+    assert rule(G, cols, cap, R) is apart
+    for g in range(G.value if apart else 0):          # 8 R floats at the start of every slice, inside it and inside the row
+        assert g * cols.value + 8 * R <= (cap if g == G.value - 1 else (g + 1) * cols.value)
