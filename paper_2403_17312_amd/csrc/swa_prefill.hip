@@ -201,11 +201,14 @@ swa_seed_stats_kernel(PrefillArgs a)
         for (int u = 0; u < AHEAD; ++u) request(u, kr[u]);
         stage(kr[0], f[0]);
         c = products(f[0]);
-        stage(kr[1], f[1]);
+        if (nt > 1) stage(kr[1], f[1]);
+    }
+    if (nt > AHEAD) {
         request(AHEAD, kr[0]);
         request(AHEAD + 1, kr[1]);
     }
-    for (int t = 0; t < nt; t += AHEAD) {
+    int t = 0;
+    for (; t + AHEAD < nt; t += AHEAD) {
         auto some = [&](auto all_seen) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) {
@@ -224,6 +227,18 @@ swa_seed_stats_kernel(PrefillArgs a)
         };
         if (chain + (t + AHEAD - 1) * kChains < seen) some(std::true_type());
         else some(std::false_type());
+    }
+    // The chain's last tiles, one to four of them: nothing is formed or waited for behind its end.  (With the loop above for them as
+    // well a prompt of 32 keys pays for eight tiles: whole seed, 32 pairs in 4096 slots, R = 64, fp32, d = 64 16.0 / 10.9 us, f16, d = 128
+    // 10.5 / 8.6.)
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+        if (t + u >= nt) break;
+        float16_t next = c;
+        if (t + u + 2 < nt) stage(kr[(u + 2) % AHEAD], f[u % 2]);
+        if (t + u + 1 < nt) next = products(f[(u + 1) % 2]);
+        add_tile_stats_flat<false>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
+        c = next;
     }
     const float M2 = __shfl_xor(M, 32, kWave);
     const float L2 = __shfl_xor(L, 32, kWave);
@@ -508,10 +523,10 @@ static int seed_slices(int64_t pairs, int bound, int cap, int R, int& cols)
 //    64 pairs    512 keys 14 / 14, 1024 21 / 17 (21), 2048 36 / 22 (31), 4096 67 / 34, 8192 129 / 58 (89)
 //   128 pairs   1024 keys 22 / 22 (24), 2048 37 / 31 (38), 4096 68 / 49 (67), 8192 135 / 86 (125)
 //   160 pairs   1024 keys 22 / 33, 4096 69 / 81, 8192 141 / 153
-// R = 128, 64 pairs x 1024 keys 36 / 22; R = 16, fp32, d = 128, 12 pairs x 1024 keys 43 / 36.
+// R = 128, 64 pairs x 1024 keys 36 / 21; R = 16, fp32, d = 128, 12 pairs x 1024 keys 43 / 36.
 // With 65 to 128 pairs only under a stated bound: without one the slices are laid over the whole capacity, and prompts that fill
 // a quarter of it gain little (128 pairs x 4096 keys in 16384 slots 71 / 67); and from 4096 keys on, where the gain is
-// more than a few microseconds.  Up to 64 pairs short prompts under a long bound lose 2 to 5 us (32 pairs x 32 keys 7 / 11).
+// more than a few microseconds.  Up to 64 pairs short prompts under a long bound lose 1 to 4 us (32 pairs x 32 keys 7 / 9).
 bool seed_in_two(int64_t pairs, int bound, bool stated, int R)
 {
     if (pairs <= 64) return bound >= 1024;
