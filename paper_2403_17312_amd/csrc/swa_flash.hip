@@ -29,6 +29,7 @@ struct FlashArgs {
     const int32_t* cache_len;
     int32_t h, cap;
     int32_t pairs, nqb;    // (sequence, head) pairs and query blocks per pair in the grid
+    int32_t front;         // query blocks are laid from the prompt's start (else from its end)
     int32_t per_xcd, tail; // pairs per XCD, and how many of them (the last ones) are dealt out block by block
     float scale_log2e;
     float* stat;           // [pairs, cap]: statistics of the last R rows, stat_G copies stat_cols apart, or NULL
@@ -51,6 +52,10 @@ constexpr float kNoReference = -3.0e38f;
 // 48 -> 42; dealt out like that as a whole, large batches lose what the L2 gave them (2048 of 512..2048: 1253 -> 1919).
 // The blocks are laid from the prompt's end (to a multiple of 32, so that a wave's queries meet one diagonal tile): what is
 // left over is the first block, which has the fewest keys, and its idle waves cost least.  2048 pairs of 512..2048 rows 1253 -> 1196 us.
+// While every block has a CU of its own (a.front) the longest one decides, and what is left over is better there, as its last block,
+// whose few waves run alone: from the end / from the start, us, 32 pairs x 161 rows, f16, d = 128 9.2 / 8.2, bf16, d = 64 7.0 / 6.2, fp32, d
+// = 64 17.8 / 16.7; 32 x 700 18.0 / 17.0, 13.6 / 12.4, 54.3 / 52.5; one block more than CUs and it is the other way round (64 x 513, f16,
+// d = 128 15.8 / 18.9).
 __device__ __forceinline__ bool query_block(const FlashArgs& a, int bq, int64_t& pair, int& s, int& q0)
 {
     const int idx = blockIdx.x / kXcds;
@@ -68,6 +73,10 @@ __device__ __forceinline__ bool query_block(const FlashArgs& a, int bq, int64_t&
     if (pair >= a.pairs) return false;
     s = a.cache_len[(uint32_t)pair / (uint32_t)a.h];
     s = s > a.cap ? a.cap : s;
+    if (a.front) {
+        q0 = qb * bq;
+        return q0 < s;
+    }
     int q_end = (s + 31) & ~31;
     q_end = q_end < a.nqb * bq ? q_end : a.nqb * bq;     // (a prompt beyond the stated bound: its rows up to the bound)
     const int blocks = (q_end + bq - 1) / bq;
@@ -659,6 +668,7 @@ static bool flash_grid(FlashArgs& a, int bound, int bq, int64_t& wgs)
     a.per_xcd = (a.pairs + kXcds - 1) / kXcds;
     a.tail = (128 + a.nqb - 1) / a.nqb;
     if (a.tail > a.per_xcd) a.tail = a.per_xcd;
+    a.front = (int64_t)a.pairs * a.nqb <= 256;
     wgs = (int64_t)a.per_xcd * kXcds * a.nqb;
     return wgs <= 0x7fffffffLL;
 }
