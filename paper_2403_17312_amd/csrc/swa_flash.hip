@@ -46,10 +46,12 @@ constexpr float kNoReference = -3.0e38f;
 //
 // XCD-aware placement: the query blocks of one pair all read the same K and V, so they go to the same XCD, next to each other
 // in launch order, and share the pair's rows through that XCD's L2; the XCDs work on different pairs.  Longest blocks of
-// a pair first.  The last pairs of an XCD (a.tail of them, about 128 blocks, a little more than run at once) are dealt out
-// block by block instead: their longest blocks start together and the short ones fill in behind, where pair by
+// a pair first.  The last pairs of an XCD (a.tail of them, about 128 blocks, a little more than run at once, in the 16-bit formats) are
+// dealt out block by block instead: their longest blocks start together and the short ones fill in behind, where pair by
 // pair the last pair's longest block would run on alone.  32 pairs x 4096 rows, f16, d = 128: 177 -> 153 us; 128 of 300..1200
 // 48 -> 42; dealt out like that as a whole, large batches lose what the L2 gave them (2048 of 512..2048: 1253 -> 1919).
+// fp32 is bound by its products and gains from more of it: 512 blocks.  Pair by pair from the start / 128 / 512, us, d = 64: 2048
+// pairs x 129 134 / 144 / 99, x 161 164 / 177 / 131, x 420 755 / 816 / 685, 256 x 2048 1421 / 1267 / 1178.
 // The blocks are laid from the prompt's end (to a multiple of 32, so that a wave's queries meet one diagonal tile): what is
 // left over is the first block, which has the fewest keys, and its idle waves cost least.  2048 pairs of 512..2048 rows 1253 -> 1196 us.
 // While every block has a CU of its own (a.front) the longest one decides, and what is left over is better there, as its last block,
@@ -662,11 +664,11 @@ swa_flash16_kernel(FlashArgs a)
 }
 
 // The grid for blocks of bq queries and prompts of at most `bound` rows (false: more workgroups than a launch can have).
-static bool flash_grid(FlashArgs& a, int bound, int bq, int64_t& wgs)
+static bool flash_grid(FlashArgs& a, int bound, int bq, bool f32, int64_t& wgs)
 {
     a.nqb = (bound + bq - 1) / bq;
     a.per_xcd = (a.pairs + kXcds - 1) / kXcds;
-    a.tail = (128 + a.nqb - 1) / a.nqb;
+    a.tail = ((f32 ? 512 : 128) + a.nqb - 1) / a.nqb;
     if (a.tail > a.per_xcd) a.tail = a.per_xcd;
     a.front = (int64_t)a.pairs * a.nqb <= 256;
     wgs = (int64_t)a.per_xcd * kXcds * a.nqb;
@@ -677,7 +679,7 @@ template <typename T, int D>
 static int launch_flash16(FlashArgs a, int bound, hipStream_t stream)
 {
     int64_t wgs = 0;
-    if (!flash_grid(a, bound, 128, wgs)) return SWA_ERR_BAD_SHAPE;
+    if (!flash_grid(a, bound, 128, false, wgs)) return SWA_ERR_BAD_SHAPE;
     hipLaunchKernelGGL((swa_flash16_kernel<T, D>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
@@ -712,7 +714,7 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
         return p.d == 64 ? launch_flash16<BF16, 64>(a, bound, stream) : launch_flash16<BF16, 128>(a, bound, stream);
     }
     int64_t wgs = 0;
-    if (!flash_grid(a, bound, 128, wgs)) return SWA_ERR_BAD_SHAPE;
+    if (!flash_grid(a, bound, 128, p.dtype == SWA_F32, wgs)) return SWA_ERR_BAD_SHAPE;
     auto go = [&](auto small, auto large) {
         hipLaunchKernelGGL(p.d == 64 ? small : large, dim3((unsigned)wgs), dim3(256), 0, stream, a);
     };
