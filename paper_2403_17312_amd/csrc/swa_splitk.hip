@@ -156,6 +156,13 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     const int m = len + 1;
     const bool overflow = (m > cap) || (m > a.lds_slots) || (len < 0);
     int keep = 0, n_local = 0, n_global = 0, w_eff = 0;
+    // A length to compare slots with, anew in every phase: PER lane masks carried from phase to phase take more scalar registers than
+    // there are (43 and 120 of them spilled at 9 and 16 slots a thread; four fifths evicted, f16, d = 128, whole step, 32 pairs x 8192
+    // 35.3 -> 34.4 us, x 12000 50.1 -> 47.7; 4 pairs x 12000, bf16, d = 64 32.3 -> 30.2).
+    auto anew = [](int v) {
+        asm volatile("" : "+s"(v));
+        return v;
+    };
 
     if (!overflow) {
 #pragma unroll
@@ -183,19 +190,21 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
         mx = s_red[0];
 #pragma unroll
         for (int v = 1; v < NW; ++v) mx = fmaxf(mx, s_red[v]);
+        const int m1 = anew(m);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            if (k * NT >= m) continue;
-            z[k] = tid + k * NT < m ? expf(z[k] - mx) : 0.f;
+            if (k * NT >= m1) continue;
+            z[k] = tid + k * NT < m1 ? expf(z[k] - mx) : 0.f;
             if (tid >= SUMT) s_x[k][tid - SUMT] = z[k];
         }
         __syncthreads();
         if (tid < SUMT) {
             // thread t of the one-workgroup kernel adds up slots t, t + 512, t + 1024, ...  (a zero past the end changes nothing)
             float sum = 0.f;
+            const int m2 = anew(m);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                if (k * NT >= m) continue;
+                if (k * NT >= m2) continue;
                 sum += z[k];
                 sum += s_x[k][tid];
             }
@@ -210,11 +219,12 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
         budget(n, m, a.w, a.sparsity_bp, keep, n_local, n_global, w_eff);
         const int ncand = m - n_local;
         uint32_t key[PER];
+        const int m3 = anew(m);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            if (k * NT >= m) continue;
+            if (k * NT >= m3) continue;
             const int i = tid + k * NT;
-            if (i < m) {
+            if (i < m3) {
                 z[k] = z[k] / sum;                          // the weight
                 const float v = sc[k] + z[k];
                 Sp[i] = v;
@@ -245,10 +255,11 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
             int rem = 0, n_eq = 0;
             if (n_global > 0) {
                 auto each = [&](auto f) {
+                    const int n = anew(ncand);
 #pragma unroll
                     for (int k = 0; k < PER; ++k) {
-                        if (k * NT >= ncand) continue;
-                        if (tid + k * NT < ncand) f(key[k]);
+                        if (k * NT >= n) continue;
+                        if (tid + k * NT < n) f(key[k]);
                     }
                 };
                 select_threshold<NT>(s_sel, n_global, each, thr, rem, n_eq);
@@ -259,13 +270,14 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
             uint32_t sure = 0u, tied = 0u;                      // bit k: slot tid + k NT
             for (int k = PER; k < kSelPer; ++k)
                 if (lane == 0) s_chunk[k * NW + wave] = 0u;
+            const int m4 = anew(m), n4 = anew(ncand);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 uint32_t c = 0u;
-                if (k * NT < m) {
+                if (k * NT < m4) {
                     const int i = tid + k * NT;
-                    const bool cand = i < ncand;
-                    const bool in = i < m && (!cand || key[k] > thr), eq = cand && key[k] == thr;
+                    const bool cand = i < n4;
+                    const bool in = i < m4 && (!cand || key[k] > thr), eq = cand && key[k] == thr;
                     sure |= in ? 1u << k : 0u;
                     tied |= eq ? 1u << k : 0u;
                     c = (uint32_t)__popcll(__ballot(in)) | ((uint32_t)__popcll(__ballot(eq)) << 16);
@@ -278,9 +290,10 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
             const uint32_t inc = (uint32_t)wave_scan((int)own);
             const int part = wave & 3;                          // chunk k NW + wave: lane (k NW + wave) / 4, its entry `part`
             const uint32_t first = inc - own + (part > 0 ? c4.x : 0u) + (part > 1 ? c4.y : 0u) + (part > 2 ? c4.z : 0u);
+            const int m5 = anew(m);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                if (k * NT >= m) continue;
+                if (k * NT >= m5) continue;
                 const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)first, k * (NW / 4) + wave / 4);
                 const int eq = (int)(before >> 16);
                 const bool t = (tied >> k) & 1u;
