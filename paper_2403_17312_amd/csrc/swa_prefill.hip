@@ -170,14 +170,20 @@ swa_seed_stats_kernel(PrefillArgs a)
         }
     };
     char* buf = s_tile[wave];
+    // Rows pass between the lanes of one wave: its LDS accesses are carried out in order, the fences keep the compiler from changing it.
+    auto wave_order = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    };
     auto stage = [&](const Vec16(&kr)[NL], Vec16(&f)[NV]) {
-        __builtin_amdgcn_wave_barrier();             // (a wave's LDS accesses are carried out in order)
+        wave_order();
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
             const int row = j * RPI + lrow;
             *reinterpret_cast<Vec16*>(buf + row * ROWB + ((lchunk ^ (row & (CPR - 1))) * 16)) = kr[j];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_order();
 #pragma unroll
         for (int v = 0; v < NV; ++v)
             f[v] = *reinterpret_cast<const Vec16*>(buf + l32 * ROWB + (((2 * v + hb) ^ (l32 & (CPR - 1))) * 16));

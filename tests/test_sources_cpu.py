@@ -16,3 +16,15 @@ def test_inline_assembly_names_the_special_registers_it_writes():
                 seen += 1
                 assert f'"{reg}"' in operands.rpartition(":")[2], f"{os.path.basename(path)}: {reg} is written and not named"
     assert seen
+
+
+def test_a_wave_barrier_stands_between_fences():
+    """The barrier of one wave orders no memory accesses for the compiler: where lanes exchange through LDS, fences have to."""
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2403_17312_amd", "csrc", "*.h*"))):
+        text = re.sub(r"//[^\n]*", "", open(path).read())
+        for m in re.finditer(r"__builtin_amdgcn_wave_barrier\(\);", text):
+            seen += 1
+            assert re.search(r'__builtin_amdgcn_fence\(__ATOMIC_RELEASE, "wavefront"[^;]*;\s*$', text[:m.start()]), os.path.basename(path)
+            assert re.match(r'\s*__builtin_amdgcn_fence\(__ATOMIC_ACQUIRE, "wavefront"', text[m.end():]), os.path.basename(path)
+    assert seen
