@@ -2,13 +2,15 @@
 
 Argument marshalling only: every step of the decode path runs in the HIP kernels
 behind the C entry points.  PyTorch supplies device memory (tensors) and the
-stream.  There is no fallback: if the library has not been built, or a call
-fails, an exception is raised.
+stream.  There is no fallback for the library: if it has not been built, or a call
+fails, an exception is raised.  The native half only saves host time; without it ctypes
+converts the arguments of every call.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -60,7 +62,7 @@ class SwaError(RuntimeError):
 
 
 _lib = None
-_native = None      # the native half (csrc/swa_native.cpp), bound to the entry points of _lib
+_native = None      # the native half (csrc/swa_native.cpp), bound to the entry points of _lib, or _General
 
 # Entry points whose arguments the native half converts: fn(params, arguments..., stream) -> status, or None where an argument is
 # not a plain tensor, an integer or None; the call then takes the general path below, with its errors.
@@ -68,8 +70,28 @@ NATIVE = ("swa_decode_step", "swa_decode_step_q8", "swa_decode_step_window", "sw
           "swa_compact_kv", "swa_prefill_scores", "swa_prefill_rows", "swa_prefill_attention", "swa_quantize_kv")
 
 
+class _General:
+    """Stands for the native half where there is none: every call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_half(L):
+    try:
+        from . import _swa_native as N
+        if N.torch_version != torch.__version__:
+            raise ImportError(f"_swa_native.so was built for torch {N.torch_version}, this is {torch.__version__}")
+    except (ImportError, AttributeError) as e:
+        warnings.warn(f"calls convert their arguments in Python, a few microseconds each: {e} "
+                      "(`python -m paper_2403_17312_amd.build` builds the native half)")
+        return _General()
+    N.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE}, SwaParams)
+    return N
+
+
 def lib():
-    """Loads libswa_hip.so and the binding's native half; raises if they have not been built."""
+    """Loads libswa_hip.so, which must have been built, and the binding's native half, if that has been."""
     global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
@@ -117,13 +139,7 @@ def lib():
         L.swa_prefill_attention.argtypes = [pp, vp, vp, vp, i32p, vp, ctypes.c_int32, vp, vp, vp]
         L.swa_probe_stream_read.restype = ctypes.c_int
         L.swa_probe_stream_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
-        try:
-            from . import _swa_native as N
-        except ImportError as e:
-            raise RuntimeError("_swa_native.so is missing or was built for another torch: build it with "
-                               "`python -m paper_2403_17312_amd.build` (there is no fallback path)") from e
-        N.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE}, SwaParams)
-        _lib, _native = L, N
+        _lib, _native = L, _native_half(L)
     return _lib
 
 

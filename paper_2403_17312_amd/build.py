@@ -2,9 +2,12 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
+from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -38,14 +41,23 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build_native() -> str:
-    """Compile the binding's native half (an extension module that reads torch tensors; host code only)."""
+def build_native() -> Optional[str]:
+    """Compile the binding's native half (an extension module that reads torch tensors; host code only).  Without a host compiler or
+    the headers of torch and Python there is none, and the binding does without."""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
+    needs = [os.path.join(root, "include", "torch", "csrc", "autograd", "python_variable.h"),
+             os.path.join(sysconfig.get_paths()["include"], "Python.h")]
+    missing = [f for f in needs if not os.path.exists(f)] + ([] if shutil.which("g++") else ["g++"])
+    if missing:
+        if os.path.exists(NATIVE_PATH):
+            os.remove(NATIVE_PATH)                       # (of another build: its calls may not be this library's)
+        warnings.warn(f"the binding's native half is not built, for want of {', '.join(missing)}: calls convert their arguments in Python")
+        return None
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DSWA_TORCH_VERSION="{torch.__version__}"',
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "swa_native.cpp"), "-o", NATIVE_PATH,

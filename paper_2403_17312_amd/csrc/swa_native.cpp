@@ -165,4 +165,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_swa_native", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__swa_native() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__swa_native()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", SWA_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -1,6 +1,8 @@
 """The binding's native half against its general path in Python: the same answers and errors, without a GPU (every call here is
 refused before the device is touched, or never made)."""
 import os
+import sys
+import types
 
 import pytest
 import torch
@@ -82,3 +84,34 @@ def test_a_stream_object_and_a_parameter_are_taken(B, path):
         for call in _calls(B, p, t, Stream()):
             with pytest.raises(B.SwaError):
                 call()
+
+
+@pytest.mark.parametrize("module", [None, types.SimpleNamespace(torch_version="1.0"), types.SimpleNamespace()])
+def test_without_a_native_half_of_this_torch_the_general_path_serves(B, monkeypatch, module):
+    """No native half, or one that was built for another torch."""
+    name = "paper_2403_17312_amd._swa_native"
+    monkeypatch.setitem(sys.modules, name, module)
+    if module is None:
+        monkeypatch.delattr(sys.modules["paper_2403_17312_amd"], "_swa_native", raising=False)
+    else:
+        monkeypatch.setattr(sys.modules["paper_2403_17312_amd"], "_swa_native", module, raising=False)
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_native", None)
+    with pytest.warns(UserWarning, match="in Python"):
+        B.lib()
+    bad = B.make_params(1, 1, 65, 8, 1, 5000, torch.float16)
+    for call in _calls(B, bad, torch.zeros(64)):
+        with pytest.raises(B.SwaError) as e:
+            call()
+        assert e.value.code == B.SWA_ERR_UNSUPPORTED_D
+
+
+def test_a_build_without_a_host_compiler_leaves_no_native_half(tmp_path, monkeypatch):
+    from paper_2403_17312_amd import build
+    stale = tmp_path / "_swa_native.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "NATIVE_PATH", str(stale))
+    monkeypatch.setenv("PATH", str(tmp_path))
+    with pytest.warns(UserWarning, match="not built, for want of g"):
+        assert build.build_native() is None
+    assert not stale.exists()
