@@ -72,51 +72,54 @@ template <typename... A>
 struct Entry<int (*)(const swa_params*, A...)> {
     static constexpr size_t N = sizeof...(A);            // the stream is the last one
 
+    // The arguments, or false where the general path has to look at them.
     template <size_t... I>
-    static PyObject* call(void* fn, PyObject* const* args, std::index_sequence<I...>)
+    static bool convert_all(PyObject* const* args, swa_params& p, std::tuple<A...>& a, std::index_sequence<I...>)
     {
-        std::tuple<A...> a;
         Arg r = Arg::ok;
         ((I + 1 < N && r == Arg::ok ? (void)(r = convert(args[1 + I], std::get<I>(a))) : (void)0), ...);
-        if (r != Arg::ok) Py_RETURN_NONE;
+        if (r != Arg::ok) return false;
         if (args[N] == Py_None) {
             std::get<N - 1>(a) = reinterpret_cast<void*>(c10::hip::getCurrentHIPStream().stream());
         } else {
-            if (!PyLong_CheckExact(args[N])) Py_RETURN_NONE;
+            if (!PyLong_CheckExact(args[N])) return false;
             std::get<N - 1>(a) = PyLong_AsVoidPtr(args[N]);
-            if (PyErr_Occurred()) {
-                PyErr_Clear();
-                Py_RETURN_NONE;
-            }
+            if (PyErr_Occurred()) return false;
         }
-        if (reinterpret_cast<PyObject*>(Py_TYPE(args[0])) != params_type) Py_RETURN_NONE;
+        if (reinterpret_cast<PyObject*>(Py_TYPE(args[0])) != params_type) return false;
         Py_buffer params;
-        if (PyObject_GetBuffer(args[0], &params, PyBUF_SIMPLE) != 0) {
-            PyErr_Clear();
-            Py_RETURN_NONE;
-        }
-        if (params.len != (Py_ssize_t)sizeof(swa_params)) {
-            PyBuffer_Release(&params);
-            Py_RETURN_NONE;
-        }
-        const swa_params p = *static_cast<const swa_params*>(params.buf);
+        if (PyObject_GetBuffer(args[0], &params, PyBUF_SIMPLE) != 0) return false;
+        const bool fits = params.len == (Py_ssize_t)sizeof(swa_params);
+        if (fits) p = *static_cast<const swa_params*>(params.buf);
         PyBuffer_Release(&params);
-        int rc = 0;
-        Py_BEGIN_ALLOW_THREADS
-        rc = reinterpret_cast<int (*)(const swa_params*, A...)>(fn)(&p, std::get<I>(a)...);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(rc);
+        return fits;
+    }
+
+    // Without the interpreter's lock.  An exception that leaves the library ends the process here, as it does by way of ctypes: caught
+    // further out it would find the lock released and the call made a second time.
+    static int make(void* fn, const swa_params& p, const std::tuple<A...>& a) noexcept
+    {
+        PyThreadState* const held = PyEval_SaveThread();
+        const int rc = std::apply([&](A... v) { return reinterpret_cast<int (*)(const swa_params*, A...)>(fn)(&p, v...); }, a);
+        PyEval_RestoreThread(held);
+        return rc;
     }
 
     static PyObject* run(void* fn, PyObject* const* args, Py_ssize_t n)
     {
         if (!fn || n != (Py_ssize_t)N + 1) Py_RETURN_NONE;
+        std::tuple<A...> a;
+        swa_params p;
+        bool ready = false;
         try {
-            return call(fn, args, std::make_index_sequence<N>());
+            ready = convert_all(args, p, a, std::make_index_sequence<N>());
         } catch (...) {                                  // a tensor without storage, no device: the general path reports it
+        }
+        if (!ready) {
             PyErr_Clear();
             Py_RETURN_NONE;
         }
+        return PyLong_FromLong(make(fn, p, a));
     }
 };
 

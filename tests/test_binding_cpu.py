@@ -1,7 +1,11 @@
 """The binding's native half against its general path in Python: the same answers and errors, without a GPU (every call here is
 refused before the device is touched, or never made)."""
 import os
+import shutil
+import signal
+import subprocess
 import sys
+import textwrap
 import types
 
 import pytest
@@ -115,3 +119,25 @@ def test_a_build_without_a_host_compiler_leaves_no_native_half(tmp_path, monkeyp
     with pytest.warns(UserWarning, match="not built, for want of g"):
         assert build.build_native() is None
     assert not stale.exists()
+
+
+@pytest.mark.skipif(not shutil.which("g++"), reason="builds a library that throws")
+def test_an_exception_out_of_the_library_ends_the_process(B, tmp_path):
+    """As by way of ctypes: it is not taken for an argument that the general path has to look at, with the interpreter's lock released
+    and the call made again."""
+    if isinstance(B._native, B._General):
+        pytest.skip("no native half here")
+    (tmp_path / "throws.cpp").write_text('extern "C" int swa_compact_kv(...) { throw 1; }\n')
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(tmp_path / "throws.so"), str(tmp_path / "throws.cpp")], check=True)
+    code = textwrap.dedent(f"""
+        import ctypes, torch
+        from paper_2403_17312_amd import binding as B
+        B.lib()
+        fn = ctypes.CDLL({str(tmp_path / "throws.so")!r}).swa_compact_kv
+        B._native.bind({{"swa_compact_kv": ctypes.cast(fn, ctypes.c_void_p).value}}, B.SwaParams)
+        t = torch.zeros(64)
+        print("came back", B._native.swa_compact_kv(B.make_params(1, 1, 64, 8, 1, 5000, torch.float16), t, t, t, t, t, t, t, t, 0))
+    """)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == -signal.SIGABRT and "terminate called" in r.stderr and "came back" not in r.stdout, r
