@@ -697,8 +697,11 @@ swa_decode_kernel(DecodeArgs a)
                 // ---- unordered layout: holes below `keep` are filled by kept rows above it ----
                 // A candidate is kept if its key exceeds the threshold, or equals it and is one of
                 // the `rem` earliest tokens among the equals (rank by position, found by a scan
-                // of the candidates only when some equal key has to lose).
+                // of the candidates only when some equal key has to lose: one word a slot to compare, the key or the
+                // importance that has it).
                 const int n_eq = (n_global > 0) ? s_sel[2] : 0;
+                const uint32_t* s_word = own_keys ? s_key : reinterpret_cast<const uint32_t*>(s_sc);
+                const uint32_t equal = own_keys ? prefix : ((prefix & 0x80000000u) ? prefix ^ 0x80000000u : ~prefix);
                 uint64_t keptm = 0ull;
                 for (int k = 0; k < per; ++k) {
                     const int i = lo + k;
@@ -717,7 +720,7 @@ swa_decode_kernel(DecodeArgs a)
                             } else {
                                 int rank = 0;
                                 for (int j = 0; j < m; ++j)
-                                    rank += (key_of(j) == prefix && s_pos[j] < posi) ? 1 : 0;
+                                    rank += (s_word[j] == equal && s_pos[j] < posi) ? 1 : 0;
                                 kept = rank < rem;
                             }
                         }
