@@ -1271,7 +1271,12 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
         const int by_lds = 160 * 1024 / (a.lds_slots * slot_bytes + 10 * 1024), by_waves = 16 * kWave / nt;
         return by_lds < by_waves ? by_lds : by_waves;
     };
-    const bool may_drop = a.unordered && !shared && !ring && nt >= 512;          // (the 8-bit cache has at most 256 threads)
+    // And only from three rounds of the chip on, with rows below 512 bytes: two workgroups on a CU stream a cache that loses nothing or
+    // one token 10 % slower than one after the other while the pairs are few, and 2 % where they are many.  With / without the array,
+    // us, 4400 slots, none, a twentieth and four fifths evicted: 512 pairs, f16, d = 128 214, 351, 263 / 230, 280, 222; 1024 398, 681,
+    // 495 / 408, 542, 433; 1024, bf16, d = 64 219, 342, 278 / 213, 283, 239; 1024, fp32, d = 64 401, 561, 460 / 409, 503, 420, d = 128
+    // 785, 1022, 842 / 793, 968, 783 (384 pairs 305, 445, 367 / 342, 379, 334).
+    const bool may_drop = a.unordered && !shared && !ring && nt >= 512 && pairs >= 768 && rowb < 512;      // (not the 8-bit cache: nt <= 256)
     a.key_slots = (may_drop && per_cu(16) > per_cu(20)) ? 0 : a.lds_slots;
     const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 16 : 12) : 4) +
                              (size_t)a.key_slots * 4 + (size_t)a.stash_rows * rowb * 2;
