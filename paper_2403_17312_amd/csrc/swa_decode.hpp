@@ -28,16 +28,17 @@ struct DecodeArgs {
     float scale;
     int32_t fuse_compaction;
     int32_t unordered;    // fused compaction fills holes instead of shifting rows (order by pos only)
-    // Head-shared selection runs as three launches: phase 1 streams the cache and publishes the
+    // Head-shared selection runs as two or three launches: phase 1 streams the cache and publishes the
     // new importance, the attention weights and the dense output of every pair; a small kernel
-    // sums the new importance over the heads of every sequence; phase 2 selects from that sum
-    // (every head of a sequence reaches the same decision) and finishes output and compaction.
+    // sums the new importance over the heads of every sequence, where phase 2 does not do that itself (short caches,
+    // ws_tot = NULL); phase 2 selects from that sum (every head of a sequence reaches the same decision) and finishes
+    // output and compaction.
     int32_t phase;        // 0 = whole step in one launch; 1, 2 = the two halves of the head-shared
                           // step
     float* ws_p;          // [b,h,cap] attention weights of phase 1
     float* ws_snew;       // [b,h,cap] new importance of phase 1
     float* ws_abar;       // [b,h,d]   dense attention output of phase 1
-    float* ws_tot;        // [b,cap]   new importance summed over the heads
+    float* ws_tot;        // [b,cap]   new importance summed over the heads (NULL: phase 2 sums)
     int32_t stash_rows;   // fused compaction: newest rows kept in LDS during the streaming pass
     // Compressed cache (Section V-B): per (pair, channel) scale and zero point of keys and values,
     // four fp32 arrays of qstride = b*h*d values each (lambda_K, z_K, lambda_V, z_V).

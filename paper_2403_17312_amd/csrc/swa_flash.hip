@@ -42,7 +42,9 @@ constexpr int kXcds = 8;   // workgroups are dealt round-robin to the 8 XCDs, ea
 // (exp2(-inf - reference) = 0) also when they come before the row's first finite logit.
 constexpr float kNoReference = -3.0e38f;
 
-// Which queries a workgroup serves: `bq` of them from q0 on, of a prompt of s rows.  False: none.
+constexpr int BQ = 128;             // queries per workgroup
+
+// Which queries a workgroup serves: BQ of them from q0 on, of a prompt of s rows.  False: none.
 //
 // XCD-aware placement: the query blocks of one pair all read the same K and V, so they go to the same XCD, next to each other
 // in launch order, and share the pair's rows through that XCD's L2; the XCDs work on different pairs.  Longest blocks of
@@ -58,7 +60,7 @@ constexpr float kNoReference = -3.0e38f;
 // whose few waves run alone: from the end / from the start, us, 32 pairs x 161 rows, f16, d = 128 9.2 / 8.2, bf16, d = 64 7.0 / 6.2, fp32, d
 // = 64 17.8 / 16.7; 32 x 700 18.0 / 17.0, 13.6 / 12.4, 54.3 / 52.5; one block more than CUs and it is the other way round (64 x 513, f16,
 // d = 128 15.8 / 18.9).
-__device__ __forceinline__ bool query_block(const FlashArgs& a, int bq, int64_t& pair, int& s, int& q0)
+__device__ __forceinline__ bool query_block(const FlashArgs& a, int64_t& pair, int& s, int& q0)
 {
     const int idx = blockIdx.x / kXcds;
     const int head = a.per_xcd - a.tail;
@@ -76,13 +78,13 @@ __device__ __forceinline__ bool query_block(const FlashArgs& a, int bq, int64_t&
     s = a.cache_len[(uint32_t)pair / (uint32_t)a.h];
     s = s > a.cap ? a.cap : s;
     if (a.front) {
-        q0 = qb * bq;
+        q0 = qb * BQ;
         return q0 < s;
     }
     int q_end = (s + 31) & ~31;
-    q_end = q_end < a.nqb * bq ? q_end : a.nqb * bq;     // (a prompt beyond the stated bound: its rows up to the bound)
-    const int blocks = (q_end + bq - 1) / bq;
-    q0 = q_end - (blocks - qb) * bq;                     // (negative in a first block that is not full)
+    q_end = q_end < a.nqb * BQ ? q_end : a.nqb * BQ;     // (a prompt beyond the stated bound: its rows up to the bound)
+    const int blocks = (q_end + BQ - 1) / BQ;
+    q0 = q_end - (blocks - qb) * BQ;                     // (negative in a first block that is not full)
     return qb < blocks;
 }
 
@@ -121,11 +123,12 @@ __device__ __forceinline__ uint32_t pack2<BF16>(float f0, float f1)
 // The 16 weights of one lane's query and key tile, exp2(c scale - m), their sum, and the rescaling that goes with them.
 //
 // The reference m only has to bound the exponents, not equal the maximum (out = o / l whatever it is).  So the weights are
-// formed with the reference as it is, and only where a lane's sum shows that it is too low (some weight above
-// 2^8, or not finite, as on the first tile) is the tile's maximum looked for, the running output o and sum l rescaled
+// formed with the reference as it is, and only where a lane's sum shows that it is too low (a sum above 2^12, so some weight
+// above 2^8, or not finite, as on the first tile) is the tile's maximum looked for, the running output o and sum l rescaled
 // and the weights formed again: a few times per query.  With the maximum looked for on every tile, and fp16 weights rounded one
 // by one: 1792 pairs x 4096, bf16 6.96 -> 6.82 ms; 2048 of 512..2048, f16 1179 -> 1139 us, d = 64 695 -> 628.
-constexpr float kSlack = 8.f;           // how far (powers of two) a logit may exceed the reference
+// A single weight may reach 2^12 that way, which fp16 holds and fp32 sums.
+constexpr float kSlack = 8.f;           // how far (powers of two) all 16 logits may exceed the reference
 constexpr float kTooMuch = 4096.f;      // sum of a lane's 16 weights beyond which one of them must exceed 2^kSlack
 template <int CT>
 __device__ __forceinline__ float tile_weights(const float16_t& c, float scale_log2e, float& m, float& l, float16_t (&o)[CT], float (&p)[16])
@@ -176,7 +179,6 @@ swa_flash_prefill_kernel(FlashArgs a)
     constexpr int NV = ROWB / 32;       // 16-byte vectors a lane supplies for a 32-row operand
     constexpr int CT = D / 32;          // 32-channel tiles of the output
     constexpr int BK = 32;              // keys per tile
-    constexpr int BQ = 128;             // queries per workgroup
     constexpr int KSTR = ROWB + 16;     // LDS row of the key tile, padded against bank conflicts
     constexpr int VSTR = BK * EB + 16;  // LDS row (one channel, 32 keys) of the transposed value tile
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
@@ -202,7 +204,7 @@ swa_flash_prefill_kernel(FlashArgs a)
     const int hb = lane >> 5;
     int64_t pair;
     int s, q0;
-    if (!query_block(a, BQ, pair, s, q0)) return;
+    if (!query_block(a, pair, s, q0)) return;
 
     const char* Qp = a.q + pair * (int64_t)a.cap * ROWB;
     const char* Kp = a.k + pair * (int64_t)a.cap * ROWB;
@@ -444,12 +446,11 @@ swa_flash16_kernel(FlashArgs a)
     constexpr int NV = ROWB / 32;       // 16-byte fragments a lane supplies for a 32-row operand
     constexpr int CT = D / 32;          // 32-channel tiles of the output
     constexpr int BK = 32;              // keys per tile
-    constexpr int BQ = 128;             // queries per workgroup
     constexpr int TILE = BK * ROWB;
     constexpr int CPR = ROWB / 16;      // 16-byte chunks per cache row
     constexpr int RPI = kWave / CPR;    // rows that one wave-wide load covers
     constexpr int LD = BK / RPI / NW;   // such loads per wave, per tensor and tile
-    constexpr int LPS = 4 * LD / NV;    // of them behind every second product of the first contraction
+    static_assert(2 * LD == NV / 2, "one of them behind every second product of the first contraction");
     constexpr int PF = 2;               // LDS fragment reads in flight ahead of the product that uses them
 
     // three buffers for a key and a value tile
@@ -462,7 +463,7 @@ swa_flash16_kernel(FlashArgs a)
     const int hb = lane >> 5;
     int64_t pair;
     int s, q0;
-    if (!query_block(a, BQ, pair, s, q0)) return;
+    if (!query_block(a, pair, s, q0)) return;
 
     const char* Qp = a.q + pair * (int64_t)a.cap * ROWB;
     const char* Kp = a.k + pair * (int64_t)a.cap * ROWB;
@@ -561,9 +562,7 @@ swa_flash16_kernel(FlashArgs a)
             __builtin_amdgcn_sched_barrier(0);
             // the loads of a later tile are issued between the products, which hide the time they wait to be
             // accepted: the four waves' sixteen 1 KiB loads together keep the CU's 64-byte path busy for 256 clocks
-            if ((v & 1) && more)
-#pragma unroll
-                for (int x = 0; x < LPS; ++x) load((v >> 1) * LPS + x, st, nk, nv);
+            if ((v & 1) && more) load(v >> 1, st, nk, nv);
         }
         // only the tiles that reach the wave's diagonal need the causal mask
         if (kt * BK + BK - 1 > w_lo) {
@@ -663,25 +662,16 @@ swa_flash16_kernel(FlashArgs a)
     }
 }
 
-// The grid for blocks of bq queries and prompts of at most `bound` rows (false: more workgroups than a launch can have).
-static bool flash_grid(FlashArgs& a, int bound, int bq, bool f32, int64_t& wgs)
+// The grid for prompts of at most `bound` rows (false: more workgroups than a launch can have).
+static bool flash_grid(FlashArgs& a, int bound, bool f32, int64_t& wgs)
 {
-    a.nqb = (bound + bq - 1) / bq;
+    a.nqb = (bound + BQ - 1) / BQ;
     a.per_xcd = (a.pairs + kXcds - 1) / kXcds;
     a.tail = ((f32 ? 512 : 128) + a.nqb - 1) / a.nqb;
     if (a.tail > a.per_xcd) a.tail = a.per_xcd;
     a.front = (int64_t)a.pairs * a.nqb <= 256;
     wgs = (int64_t)a.per_xcd * kXcds * a.nqb;
     return wgs <= 0x7fffffffLL;
-}
-
-template <typename T, int D>
-static int launch_flash16(FlashArgs a, int bound, hipStream_t stream)
-{
-    int64_t wgs = 0;
-    if (!flash_grid(a, bound, 128, false, wgs)) return SWA_ERR_BAD_SHAPE;
-    hipLaunchKernelGGL((swa_flash16_kernel<T, D>), dim3((unsigned)wgs), dim3(256), 0, stream, a);
-    return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
 int launch_flash_prefill(const swa_params& p, float scale, const void* q, const void* k_cache, const void* v_cache,
@@ -709,17 +699,15 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     // 60..250 rows 523 / 535, 511 / 527, 281 / 286; 64 x 32 of 128..512 rows 167 / 160, 161 / 156, 95 / 87 (longer
     // ones: up to 1.25 times as fast).
     const bool direct = p.dtype != SWA_F32 && bound > 256;
-    if (direct) {
-        if (p.dtype == SWA_F16) return p.d == 64 ? launch_flash16<F16, 64>(a, bound, stream) : launch_flash16<F16, 128>(a, bound, stream);
-        return p.d == 64 ? launch_flash16<BF16, 64>(a, bound, stream) : launch_flash16<BF16, 128>(a, bound, stream);
-    }
     int64_t wgs = 0;
-    if (!flash_grid(a, bound, 128, p.dtype == SWA_F32, wgs)) return SWA_ERR_BAD_SHAPE;
+    if (!flash_grid(a, bound, p.dtype == SWA_F32, wgs)) return SWA_ERR_BAD_SHAPE;
     auto go = [&](auto small, auto large) {
         hipLaunchKernelGGL(p.d == 64 ? small : large, dim3((unsigned)wgs), dim3(256), 0, stream, a);
     };
     if (p.dtype == SWA_F32) go(swa_flash_prefill_kernel<F32, 64>, swa_flash_prefill_kernel<F32, 128>);
+    else if (p.dtype == SWA_F16 && direct) go(swa_flash16_kernel<F16, 64>, swa_flash16_kernel<F16, 128>);
     else if (p.dtype == SWA_F16) go(swa_flash_prefill_kernel<F16, 64>, swa_flash_prefill_kernel<F16, 128>);
+    else if (direct) go(swa_flash16_kernel<BF16, 64>, swa_flash16_kernel<BF16, 128>);
     else go(swa_flash_prefill_kernel<BF16, 64>, swa_flash_prefill_kernel<BF16, 128>);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
