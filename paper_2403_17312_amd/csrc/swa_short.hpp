@@ -699,4 +699,23 @@ constexpr int short_rows()
 template <typename T, int D>
 constexpr int short_unroll(int u) { return Elem<T>::kBytes == 1 && D == 64 ? u / 2 : u; }
 
+// go<T, D, NT, U>() for the form and the formats of a call.
+template <typename T, int D, typename G>
+int with_form(ShortForm f, const G& g)
+{
+    if (f.nt == 128) return g.template go<T, D, 128, short_unroll<T, D>(8)>();
+    if (f.nt == 512) return g.template go<T, D, 512, short_unroll<T, D>(8)>();
+    if (f.u == 12) return g.template go<T, D, 256, short_unroll<T, D>(12)>();
+    return g.template go<T, D, 256, short_unroll<T, D>(8)>();
+}
+
+template <typename G>
+int with_form(const swa_params& p, ShortForm f, const G& g)
+{
+    if (p.flags & SWA_KV_INT8) return p.d == 64 ? with_form<Q8, 64>(f, g) : with_form<Q8, 128>(f, g);
+    if (p.dtype == SWA_F32) return p.d == 64 ? with_form<F32, 64>(f, g) : with_form<F32, 128>(f, g);
+    if (p.dtype == SWA_F16) return p.d == 64 ? with_form<F16, 64>(f, g) : with_form<F16, 128>(f, g);
+    return p.d == 64 ? with_form<BF16, 64>(f, g) : with_form<BF16, 128>(f, g);
+}
+
 }  // namespace swa
