@@ -348,9 +348,9 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         int krow = tile * 32 + l32;
         krow = krow < s ? krow : s - 1;
         krow = krow < 0 ? 0 : krow;
-        const char* src = Kp + (int64_t)krow * ROWB + lane_off;
+        const uint32_t at = (uint32_t)krow * ROWB + (uint32_t)lane_off;      // (cap <= SWA_MAX_CAP: below 8 MiB)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) kv[v] = load16(src + v * 32);
+        for (int v = 0; v < NV; ++v) kv[v] = load16(Kp + at + v * 32);
     };
 
     if constexpr (MODE != kSeedSums) {
@@ -433,7 +433,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         if (tid < RP) {
             const bool row = tid < R && t_off + tid >= 0;
             float Mt = row ? St[tid] : -INFINITY, Lt = row ? St[R + tid] : 0.f;
-            if (a.chains > 1) {
+            if (ROWB < 512 && a.chains > 1) {          // (rows of 512 bytes come merged; their kernels have no register to spare)
                 float M2[kChains], L2[kChains];
 #pragma unroll
                 for (int v = 1; v < kChains; ++v) {
