@@ -207,44 +207,52 @@ swa_seed_stats_kernel(PrefillArgs a)
         for (int u = 0; u < AHEAD; ++u) request(u, kr[u]);
         stage(kr[0], f[0]);
         c = products(f[0]);
-        if (nt > 1) stage(kr[1], f[1]);
     }
+    // A chain's last tiles from t on, fewer than a round or as many: nothing is formed or waited for behind its end.  (In the loop below a
+    // prompt of 32 keys pays for eight tiles: whole seed, 32 pairs in 4096 slots, R = 64, fp32, d = 64 16.4 / 11.5 us, f16, d = 128 11.0 /
+    // 9.5.)  In 16 bits for chains of no more than a round alone: behind the loop it cost 0.5 us from 1024 keys on, and 700 keys are
+    // fast as they are (kernel before this one / now 20.7 / 18.3 us).  fp32 gains more than that: 700 keys 31.0 / 27.6.
+    constexpr bool kRest = Elem<T>::kBytes == 4;
+    auto rest = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (t + u >= nt) break;
+            float16_t next = c;
+            if (t + u + 2 < nt) stage(kr[(u + 2) % AHEAD], f[u % 2]);
+            if (t + u + 1 < nt) next = products(f[(u + 1) % 2]);
+            add_tile_stats_flat<false>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
+            c = next;
+        }
+    };
     if (nt > AHEAD) {
+        stage(kr[1], f[1]);
         request(AHEAD, kr[0]);
         request(AHEAD + 1, kr[1]);
-    }
-    int t = 0;
-    for (; t + AHEAD < nt; t += AHEAD) {
-        auto some = [&](auto all_seen) __attribute__((always_inline)) {
+        int t = 0;
+        for (; kRest ? t + AHEAD <= nt : t < nt; t += AHEAD) {
+            auto some = [&](auto all_seen) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < AHEAD; ++u) {
-                stage(kr[(u + 2) % AHEAD], f[u % 2]);                       // tile t + u + 2
-                const float16_t next = products(f[(u + 1) % 2]);
-                add_tile_stats_flat<all_seen.value>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
+                for (int u = 0; u < AHEAD; ++u) {
+                    stage(kr[(u + 2) % AHEAD], f[u % 2]);                       // tile t + u + 2
+                    const float16_t next = products(f[(u + 1) % 2]);
+                    add_tile_stats_flat<all_seen.value>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 64 / NV + 2, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x400, 16 / NV, 0);
+                    for (int v = 0; v < NV; ++v) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 64 / NV + 2, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x400, 16 / NV, 0);
+                    }
+                    c = next;
+                    request(t + u + AHEAD + 2, kr[(u + 2) % AHEAD]);
                 }
-                c = next;
-                request(t + u + AHEAD + 2, kr[(u + 2) % AHEAD]);
-            }
-        };
-        if (chain + (t + AHEAD - 1) * kChains < seen) some(std::true_type());
-        else some(std::false_type());
-    }
-    // The chain's last tiles, one to four of them: nothing is formed or waited for behind its end.  (With the loop above for them as
-    // well a prompt of 32 keys pays for eight tiles: whole seed, 32 pairs in 4096 slots, R = 64, fp32, d = 64 16.0 / 10.9 us, f16, d = 128
-    // 10.5 / 8.6.)
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) {
-        if (t + u >= nt) break;
-        float16_t next = c;
-        if (t + u + 2 < nt) stage(kr[(u + 2) % AHEAD], f[u % 2]);
-        if (t + u + 1 < nt) next = products(f[(u + 1) % 2]);
-        add_tile_stats_flat<false>(c, chain + (t + u) * kChains, hb, tmax, a.scale_log2e, M, L);
-        c = next;
+            };
+            if (chain + (t + AHEAD - 1) * kChains < seen) some(std::true_type());
+            else some(std::false_type());
+        }
+        if constexpr (kRest) rest(t);
+    } else {
+        if (nt > 1) stage(kr[1], f[1]);
+        rest(0);
     }
     const float M2 = __shfl_xor(M, 32, kWave);
     const float L2 = __shfl_xor(L, 32, kWave);
