@@ -30,6 +30,8 @@ Prints ONE JSON line.
 from __future__ import annotations
 
 import argparse
+import collections
+import ctypes
 import json
 import math
 import os
@@ -172,6 +174,20 @@ def replicas_for(step_bytes):
     return max(2, math.ceil(SWEEP_MIN_BYTES / max(1, min(step_bytes))))
 
 
+def decode_kernel_of(B, params, ring, rule=[]):
+    """Name of the kernel that streams the cache in a decode call with these params: the library's own choice, which it makes from
+    the sizes and the stated bound (short_form, split_factor)."""
+    if not rule:
+        L = B.lib()
+        rule += [getattr(L, "_ZN3swa10short_formERK10swa_paramslib"), getattr(L, "_ZN3swa12split_factorEli")]
+        rule[0].restype = ctypes.c_uint64            # {int threads, rows per lane}; no threads: not served
+    pairs, bound = params.b * params.h, min(params.len_bound or params.cap, params.cap)
+    if params.flags & B.SWA_SPLIT_ROWS and rule[1](ctypes.c_int64(pairs), bound) > 1:
+        return "swa_split_logits_kernel"
+    form = rule[0](ctypes.byref(params), ctypes.c_int64(pairs), bound, ctypes.c_bool(ring))
+    return "swa_short_kernel" if form & 0xffffffff else "swa_decode_kernel"
+
+
 def bench_workload(wl, steps, warmup, mode, torch, B, W, fused=True, want_kernel_times=True, kv_int8=False,
                    compact_every=1, split_rows=False):
     """Times `steps` decode steps (None = whole trajectories on every replica) after `warmup` untimed ones."""
@@ -252,6 +268,7 @@ def bench_workload(wl, steps, warmup, mode, torch, B, W, fused=True, want_kernel
     # -------- timed region: exactly `steps` steps; an event between the steps right after a prompt (the first
     # R of the schedule) and the steady ones splits the time without bracketing single launches
     reps = fresh(R)
+    kernels = collections.Counter(decode_kernel_of(B, reps[0].params[i // R], window_rows > 0) for i in range(start, stop))
     run(reps, 0, start)                        # untimed: the schedule's first steps
     torch.cuda.synchronize()
     split = min(max(start, R), stop)
@@ -309,7 +326,7 @@ def bench_workload(wl, steps, warmup, mode, torch, B, W, fused=True, want_kernel
         "ms_per_step": total_ms / steps, "total_ms": total_ms, "host_wall_ms": wall_ms,
         "kv_tokens_per_s": kv_tokens / (total_ms * 1e-3),
         "generated_tokens_per_s": wl.b * steps / (total_ms * 1e-3),
-        "alg_bytes_per_step": alg_bytes / steps,
+        "alg_bytes_per_step": alg_bytes / steps, "decode_kernels": dict(kernels.most_common()),
         "alg_gbs_whole_step": alg_bytes / (total_ms * 1e-3) / 1e9,
         "prefill_seed_ms": prefill_ms, "quantize_kv_ms": quantize_ms,
         # whole steps (every launch of the step), from the event between the two stretches of the timed region
@@ -543,7 +560,7 @@ STEP_TEXT = {
                  "kept_idx not requested)",
     "fused": "swa_decode_step with SWA_FUSE_COMPACTION (one kernel, token-ordered compaction, kept_idx not "
              "requested)",
-    "shared": "swa_decode_step with SWA_HEAD_SHARED (three launches around the head-summed importance, "
+    "shared": "swa_decode_step with SWA_HEAD_SHARED (two or three launches around the head-summed importance, "
               "hole-filling compaction)",
     "window": "swa_decode_step_window (strict local attention sum over min(w, 64) rows, hole-filling compaction)",
     "split": "swa_decode_step + swa_compact_kv",
@@ -567,7 +584,7 @@ def roofline_of(res, step_mode, kv_int8, wl_name):
     first_frac = first_gbs / HBM_PEAK_GBS if first_gbs else None
     steady_frac = steady_gbs / HBM_PEAK_GBS if steady_gbs else None
     return {
-        "bound": "hbm", "kernel": "swa_decode_kernel",
+        "bound": "hbm", "kernel": next(iter(res["decode_kernels"])), "launches_by_kernel": res["decode_kernels"],
         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
         "traffic": (traffic["fetch_bytes_per_launch"] + traffic["write_bytes_per_launch"]) if traffic else None,
         "traffic_source": ("profiles/pmc_traffic.json: rocprofv3 --pmc FETCH_SIZE and --pmc WRITE_SIZE runs of this "
@@ -589,7 +606,7 @@ def summary_of(res, step_mode, kv_int8, wl_name):
             "decode_kernel_ms_avg": res.get("decode_kernel_ms_avg"),
             "compact_kernel_ms_avg": res.get("compact_kernel_ms_avg"),
             "whole_step_alg_gbs": res["alg_gbs_whole_step"], "prefill_seed_ms": res["prefill_seed_ms"],
-            "roofline": {k: r[k] for k in ("bound", "achieved", "peak", "unit", "frac", "traffic", "alg_bytes_per_launch",
+            "roofline": {k: r[k] for k in ("bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "alg_bytes_per_launch",
                                            "avg_launch_ms", "first_step_frac", "steady_frac")}}
 
 
@@ -618,7 +635,7 @@ def other_workload_in_a_process_of_its_own(name, args):
              "decode_kernel_ms_avg": c["detail"].get("decode_kernel_ms_avg"),
              "compact_kernel_ms_avg": c["detail"].get("compact_kernel_ms_avg"),
              "whole_step_alg_gbs": c["whole_step_alg_gbs"], "prefill_seed_ms": c["detail"].get("prefill_seed_ms"),
-             "roofline": {k: c["roofline"].get(k) for k in ("bound", "achieved", "peak", "unit", "frac", "traffic",
+             "roofline": {k: c["roofline"].get(k) for k in ("bound", "kernel", "achieved", "peak", "unit", "frac", "traffic",
                                                             "alg_bytes_per_launch", "avg_launch_ms", "first_step_frac",
                                                             "steady_frac")},
              "measured_in": "a process of its own"}
