@@ -10,7 +10,7 @@
 //     candidates are ranked by 32-bit counts that all waves share, and rows and ring columns that change slot are moved many at
 //     a time.  Streaming kernel / this one with all values read, 64-bit counts and moves one by one / as it is, us a step with four
 //     fifths of the rows evicted: 512 pairs x 206, f16, d = 128 20.5 / 23.8 / 18.7; 4096 x 256, f16, d = 64 66.8 / 78.8 / 58.2, strict
-//     window of 16 rows 86 / 126 / 74, head-shared 90 / 119 / 73;
+//     window of 16 rows 86 / 126 / 74;
 //   - every wave holds all logits, importance values and positions (one to four slots per lane) and forms softmax,
 //     importance and selection for itself: one barrier behind the logits, one before the output.
 // Weights, importance and kept set are bit-identical to the streaming kernel's (same products, same order of additions).
@@ -218,8 +218,10 @@ swa_short_kernel(DecodeArgs a)
 
         const bool listed = E > 1 || (E == 1 && n_global <= 0);
         // Where most rows go (the step after a prompt), the values wait until the selection is known, and only those of kept rows are
-        // read; the first launch of the head-shared step has no use for them then.
-        const bool late = PHASE == 1 ? listed : 2 * E > m;
+        // read.  The first launch of the head-shared step reads them all, though the second has no use for its output where several rows
+        // go: without them 4096 pairs x 250 slots, f16, d = 64, four fifths evicted take 64 instead of 81 us, but the loads' second form made
+        // every other step 0.1 us slower (84 pairs x 200, bf16, d = 64, one evicted 9.3 / 9.4).
+        const bool late = PHASE == 0 && 2 * E > m;
 
         // ---- the other rows, logits -------------------------------------------------------------
         // As many rows per lane as the length needs, in steps of UE (the counts are written out so that the compiler knows
@@ -508,7 +510,7 @@ swa_short_kernel(DecodeArgs a)
 #pragma unroll
             for (int e = 0; e < EPV; ++e) acc[e] = (grp == 0 && !(wn < 0.f)) ? wn * f[e] : 0.f;
         }
-        bool subtract = PHASE == 1 && late;              // (then the second launch sums the kept rows up)
+        bool subtract = PHASE == 1 && listed;            // (then the second launch sums the kept rows up)
         if constexpr (PHASE == 2) {
             // one row or none leaves the dense output; where little weight would be left the kept rows are added up instead
             float pj = p[0];
