@@ -325,6 +325,29 @@ __device__ __forceinline__ Vec16 load16_stream(const void* p)
 }
 __device__ __forceinline__ void store16(void* p, const Vec16& v) { *reinterpret_cast<Vec16*>(p) = v; }
 
+// One 16-byte load per lane straight to LDS: lane l's chunk lands at dst + 16 l.  off is per lane, the rest
+// uniform.  No register receives anything, so nothing has to be kept alive while it is in flight; the caller counts
+// it (vmcnt) before the barrier that publishes the tile.  (With the compiler's builtin, every third tile waited for
+// all loads: it cannot tell three LDS buffers apart around a loop.)  M0, the destination, is named as overwritten so that
+// the compiler keeps no value of its own there; it warns that it will not preserve a reserved register, which is the point.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <bool STREAM = false>
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t dst)
+{
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+__device__ __forceinline__ uint32_t lds_address(const char* p)
+{
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
 // ---- wave / block reductions -------------------------------------------------
 
 // Cross-lane move on the VALU data-parallel-primitive path (no LDS traffic).

@@ -407,24 +407,6 @@ __device__ __forceinline__ Vec16 lds_read_tr(const char* lo, const char* hi)
     return Vec16{x.x, x.y, y.x, y.y};
 }
 
-// One 16-byte load per lane straight to LDS: lane l's chunk lands at dst + 16 l.  off is per lane, the rest
-// uniform.  No register receives anything, so nothing has to be kept alive while it is in flight; the caller counts
-// it (vmcnt) before the barrier that publishes the tile.  (With the compiler's builtin, every third tile waited for
-// all loads: it cannot tell three LDS buffers apart around a loop.)  M0, the destination, is named as overwritten so that
-// the compiler keeps no value of its own there; it warns that it will not preserve a reserved register, which is the point.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t dst)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-__device__ __forceinline__ uint32_t lds_address(const char* p)
-{
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
-}
-
 // 16-bit formats, prompts of more than 256 rows.  Bound: the matrix cores at the clock the power limit leaves them
 // (1.65-1.8 GHz under this kernel; busy 60 % of the cycles), next to as many clocks of vector work for the
 // softmax.  What it took there, on 1792 pairs of 4096 rows, bf16, d = 128 (before: 8.3-8.4 ms, busy 51 %):

@@ -42,6 +42,7 @@ struct PrefillArgs {
     int32_t bound;        // on the lengths: where the slices are laid (host side)
     bool stated;          // the bound is the caller's, not the capacity (host side)
     int32_t chains;       // statistics: parts of the keys whose sums are still to be merged, kChains or 1
+    int32_t stream;       // column sums: keys do not come from a cache (16-bit formats)
 };
 
 // What one launch does.
@@ -276,6 +277,18 @@ swa_seed_stats_kernel(PrefillArgs a)
     }
 }
 
+// How key tiles reach the operands' layout.  By LDS (16-bit formats): every wave has room for one tile; its rows go there straight from
+// memory as they lie, whole lines by one instruction, and are read back as operands, and the next tile is requested as soon as they
+// are in registers.  Bound: HBM, two reads of the keys at 6.2 TB/s where they are many; before, tiles were loaded in the operands' layout, 32 bytes of
+// a line at a time, and lines were fetched again between their uses.  Whole seed before / now, us: 1792 pairs x 4096 keys, bf16, d =
+// 128, R = 64 640 / 609; 2560 x 1024 f16 219 / 196; 320 x 8000 299 / 234; 512 x 512 24.4 / 21.6; 8192 of 100..500, d = 64, R = 33
+// 155 / 121; 6400 of 17..31 47 / 31; sums after the attention, 1792 x 4096 387 / 308 (differences of whole calls).  Room for two or four
+// tiles leaves fewer workgroups on a CU: no gain, up to 1.6 times as slow.
+// fp32 is bound by its products and keeps the operands' layout (d = 64, R = 33 476 / 508 by LDS), and so do more than 32 rows that are written
+// out, whose stores the wait for a tile would wait for as well (320 x 8000, R = 64 546 / 565; up to 32 rows 512 x 512 23.4 / 21.4).
+template <typename T, int RT, bool WR, int MODE>
+constexpr bool kSeedByLds = Elem<T>::kBytes == 2 && !(WR && RT > 1) && MODE != kSeedStats;
+
 // WR: also write the R rows themselves (the ring of the strict local attention sum).
 template <typename T, int D, int RT, bool WR, int MODE>
 __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
@@ -296,6 +309,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int wave = tid >> 6;
     const int l32 = lane & 31;
     const int hb = lane >> 5;
+    constexpr bool kByLds = kSeedByLds<T, RT, WR, MODE>;
     constexpr bool kStats = MODE == kSeedStats;
     const int row_tiles = kStats ? (a.R + 31) / 32 : 1;
     const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : blockIdx.x / row_tiles;
@@ -348,6 +362,37 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int tile1 = (s < col1 ? s : col1) > col0 ? ((s < col1 ? s : col1) + 31) / 32 : tile0;   // (col0 is a multiple of 32)
     const int t_off = s - R;   // query r sits at position t_off + r and sees keys 0..t_off+r
 
+    // Tiles by way of LDS: chunk c of row r lies at c ^ swizzle(r), chosen by the lane's global address, so that the lanes of an
+    // operand's read spread over the banks.
+    constexpr int TILE = 32 * ROWB;
+    constexpr int CPR = ROWB / 16;                       // 16-byte chunks per row
+    constexpr int RPI = kWave / CPR;                     // rows per load instruction
+    __shared__ __align__(1024) char s_tile[kByLds ? NW : 1][kByLds ? TILE : 16];
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    auto swz = [](int r) { return ROWB == 256 ? (r & 15) : ((r >> 1) & 7); };
+    const char* const my_tile = s_tile[kByLds ? wave_u : 0];
+    auto request = [&](int tile) __attribute__((always_inline)) {
+        const uint32_t at = lds_address(my_tile);
+        const int r_last = s - 1 - tile * 32;            // (rows past the prompt re-read its last one and are masked)
+        const char* base = Kp + (uint32_t)tile * TILE;
+#pragma unroll
+        for (int x = 0; x < TILE / 1024; ++x) {
+            const int j = x * RPI + lane / CPR;
+            const uint32_t off = (uint32_t)(j < r_last ? j : r_last) * ROWB + (uint32_t)(((lane % CPR) ^ swz(j)) * 16);
+            if (MODE == kSeedSums && a.stream) load_to_lds<true>(base, off, at + x * 1024);
+            else load_to_lds<false>(base, off, at + x * 1024);
+        }
+    };
+    auto receive = [&](Vec16(&kv)[NV]) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0): the tile is there
+        asm volatile("" ::: "memory");
+        const char* at = my_tile + l32 * ROWB;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) kv[v] = load16(at + (((2 * v + hb) ^ swz(l32)) << 4));
+        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): it may be overwritten
+        asm volatile("" ::: "memory");
+    };
+
     // Unconditional tile load (rows past the end re-read the last row and are masked later), so
     // that the loads of the next tile can stay in flight while the current one is reduced.
     // Plain loads, not streaming ones: a lane takes 32 bytes of a line per instruction, so the line
@@ -361,6 +406,15 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         for (int v = 0; v < NV; ++v) kv[v] = load16(Kp + at + v * 32);
     };
 
+    auto logits = [](const Vec16(&rows)[NV], const Vec16(&cols)[NV]) __attribute__((always_inline)) {
+        float16_t c;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) c = Mfma<T>::run(rows[v], cols[v], c);
+        return c;
+    };
+
     if constexpr (MODE != kSeedSums) {
     // ------------------------------ pass 1: row statistics ------------------------------
     float M[RT], L[RT];
@@ -372,13 +426,13 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     auto stats_tile = [&](int tile, const Vec16(&kv)[NV]) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
+            const int r = (rt0 + rt) * 32 + l32;
+            const int tmax = (r < R) ? t_off + r : -1;   // last visible key of this lane's query
             float16_t c;
 #pragma unroll
             for (int i = 0; i < 16; ++i) c[i] = 0.f;
 #pragma unroll
             for (int v = 0; v < NV; ++v) c = Mfma<T>::run(kv[v], qv[rt][v], c);   // C[key][query]
-            const int r = (rt0 + rt) * 32 + l32;
-            const int tmax = (r < R) ? t_off + r : -1;   // last visible key of this lane's query
             add_tile_stats(c, tile, hb, tmax, a.scale_log2e, M[rt], L[rt]);
         }
     };
@@ -394,6 +448,23 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
                 load_tile(tile + (u + AHEAD - 1) * NW, kr[(u + AHEAD - 1) % AHEAD]);
                 if (tile + u * NW < tile1) stats_tile(tile + u * NW, kr[u]);
             }
+        }
+    } else if constexpr (kByLds) {
+        const int seen = (t_off + 1) / 32;               // tiles below it: every row sees all keys
+        if (tile0 + wave_u < tile1) request(tile0 + wave_u);
+        for (int tile = tile0 + wave_u; tile < tile1; tile += NW) {
+            Vec16 kv[NV];
+            receive(kv);
+            if (tile + NW < tile1) request(tile + NW);
+            auto stats = [&](auto all_seen) __attribute__((always_inline)) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const int r = rt * 32 + l32;
+                    add_tile_stats_flat<all_seen.value>(logits(kv, qv[rt]), tile, hb, (r < R) ? t_off + r : -1, a.scale_log2e, M[rt], L[rt]);
+                }
+            };
+            if (RT * 32 <= R && tile < seen) stats(std::true_type());
+            else stats(std::false_type());
         }
     } else {
         Vec16 kA[NV], kB[NV];
@@ -459,7 +530,8 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     }
 
     // ------------------------------ pass 2: column sums ---------------------------------
-    auto colsum_tile = [&](int tile, const Vec16(&kv)[NV]) {
+    auto colsum_tile = [&](auto all_seen, int tile, const Vec16(&kv)[NV], auto take) {
+#pragma clang fp contract(off)
         const int key = tile * 32 + l32;
         float colsum = 0.f;
 #pragma unroll
@@ -478,8 +550,8 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int r = r0 + j;
-                    const bool vis = (r < R) && (key <= t_off + r);
-                    const float p = __builtin_amdgcn_exp2f(c[4 * g + j] * a.scale_log2e - Mr[j]) * Ir[j];
+                    const bool vis = all_seen.value || ((r < R) && (key <= t_off + r));
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(c[4 * g + j], a.scale_log2e, -Mr[j])) * Ir[j];
                     colsum += vis ? p : 0.f;
                     if constexpr (WR) {
                         if (r < R && key < s) Rp[(int64_t)r * cap + key] = vis ? p : 0.f;
@@ -488,18 +560,36 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             }
         }
         colsum += __shfl_xor(colsum, 32, kWave);
+        take(key, colsum);
+    };
+    auto put = [&](int key, float colsum) {
         if (Sp && hb == 0 && key < s) Sp[key] = colsum;
     };
-    {
+    if constexpr (kByLds) {
+        const int seen = (t_off + 1) / 32;
+        const int last = tile1 - 1 - wave_u;             // the keys read last by pass 1 are read first here
+        float before = 0.f;                              // a tile's sums are stored ahead of the next request, which the wait is for
+        if (last >= tile0) request(last);
+        for (int tile = last; tile >= tile0; tile -= NW) {
+            Vec16 kv[NV];
+            receive(kv);
+            if (tile != last) put((tile + NW) * 32 + l32, before);
+            if (tile - NW >= tile0) request(tile - NW);
+            auto keep = [&](int, float colsum) { before = colsum; };
+            if (RT * 32 <= R && tile < seen) colsum_tile(std::true_type(), tile, kv, keep);
+            else colsum_tile(std::false_type(), tile, kv, keep);
+        }
+        if (last >= tile0) put((tile0 + (last - tile0) % NW) * 32 + l32, before);
+    } else {
         Vec16 kA[NV], kB[NV];
         // the keys read last by pass 1 are read first here
         const int last = tile1 - 1 - wave;
         load_tile(last, kA);
         for (int tile = last; tile >= tile0; tile -= 2 * NW) {
             load_tile(tile - NW, kB);
-            colsum_tile(tile, kA);
+            colsum_tile(std::false_type(), tile, kA, put);
             load_tile(tile - 2 * NW, kA);
-            if (tile - NW >= tile0) colsum_tile(tile - NW, kB);
+            if (tile - NW >= tile0) colsum_tile(std::false_type(), tile - NW, kB, put);
         }
     }
     const int z0 = s > col0 ? s : col0;
@@ -559,6 +649,10 @@ static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hip
 {
     const int G = seed_slices(pairs, a.bound, a.cap, a.R, a.cols);
     a.G = G;
+    // Keys that the launch before has read are still in the 256 MB Infinity Cache where there are few; loads that pass it by are
+    // faster where there are many: plain / streaming, us, attention and sums, R = 64, 1792 x 4096 bf16 7608 / 7555, 2048 x 1001 f16 899 / 881, 2048 x 513
+    // 357 / 343, 2048 x 300 185 / 184; 128 x 1001 58.1 / 59.2, 128 x 300 19.3 / 20.1; seed in two launches, 32 x 8192 47.7 / 54.0.
+    a.stream = pairs * a.bound * (D * Elem<T>::kBytes) > (128ll << 20);
     const dim3 one((unsigned)pairs), all((unsigned)(pairs * G));
     if (stats_ready) {
         hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
