@@ -12,6 +12,9 @@ __device__ __forceinline__ uint32_t order_key(float f)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// ... and back.
+__device__ __forceinline__ float key_value(uint32_t key) { return u2f((key & 0x80000000u) ? key ^ 0x80000000u : ~key); }
+
 // Sum over the lanes up to and including this one.
 __device__ __forceinline__ int wave_scan(int v)
 {
@@ -33,6 +36,34 @@ __device__ __forceinline__ void min_max_dpp(uint32_t& lo, uint32_t& hi)
     hi = b > hi ? b : hi;
 }
 
+// Largest of a wave's values, none of them negative, in every lane.
+__device__ __forceinline__ int wave_max_int(int v)
+{
+    auto step = [&](int o) { v = o > v ? o : v; };
+    step(__builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true));
+    step(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true));
+    step(__builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true));
+    step(__builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true));
+    step(__builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));     // lane 15 of a row into the next, odd rows
+    step(__builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));     // lane 31 into the upper half
+    return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
+// Smallest and largest of a wave's values, in every lane.
+__device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi)
+{
+    min_max_dpp<0xB1>(lo, hi);
+    min_max_dpp<0x4E>(lo, hi);
+    min_max_dpp<0x141>(lo, hi);
+    min_max_dpp<0x140>(lo, hi);
+#pragma unroll
+    for (int o = 16; o < kWave; o <<= 1) {
+        const uint32_t a = (uint32_t)__shfl_xor((int)lo, o, kWave), b = (uint32_t)__shfl_xor((int)hi, o, kWave);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+}
+
 // LDS of one workgroup's selection.
 template <int NT>
 struct SelectScratch {
@@ -40,21 +71,52 @@ struct SelectScratch {
     uint32_t lo[NT / kWave], hi[NT / kWave];
     int32_t cnt[NT / kWave];
     int32_t sel[3];
-    int32_t listed;                // keys of the bin that holds the threshold, once they are few
-    uint32_t list[kWave];
+    int32_t listed;                // keys of the bin that holds the threshold, once they are few; zero before a selection
+    int32_t rank[kWave];           // ... and how many of them are larger; zero before a selection
+    __align__(16) uint32_t list[kWave];
 };
+
+// Smallest and largest candidate key.  each(f) calls f(key) for every candidate key of the calling thread; every thread of the
+// workgroup takes part.
+template <int NT, typename Each>
+__device__ __forceinline__ void key_range(SelectScratch<NT>& s, Each each, uint32_t& kmin, uint32_t& kmax)
+{
+    constexpr int NW = NT / kWave;
+    kmin = 0xffffffffu;
+    kmax = 0u;
+    each([&](uint32_t key) {
+        kmin = key < kmin ? key : kmin;
+        kmax = key > kmax ? key : kmax;
+    });
+    wave_min_max(kmin, kmax);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        s.lo[threadIdx.x >> 6] = kmin;
+        s.hi[threadIdx.x >> 6] = kmax;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+        kmin = s.lo[v] < kmin ? s.lo[v] : kmin;
+        kmax = s.hi[v] > kmax ? s.hi[v] : kmax;
+    }
+}
 
 // The `want`-th largest (want >= 1, at most the number of candidates) of the candidate keys, as a
 // threshold: keys above thr are kept, and of the n_eq keys equal to thr the first rem (n_eq == rem: all).
-// each(f) calls f(key) for every candidate key of the calling thread; every thread of the workgroup takes part.
+// Every candidate key lies in kmin .. kmax; hist, listed and rank are zero, and a barrier has passed since they were cleared.
 //
 // Histogram select with 2 NT bins over the range the keys really span (a radix select from the top of the word has its
 // first digit, sign and exponent, shared by nearly all keys, and its counters serialise), refined inside the
 // bin that holds the threshold until all of that bin is kept, its keys are equal or there are so few that
 // they can be listed and ranked.  Importance values of a cache are spread enough that this takes one round and
 // the list as a rule, and never more than four rounds.
+//
+// Bound: the instructions that 16 waves on one CU issue, and barriers: the ranks are counted by all waves together (32 pairs x 8192: 5400 ->
+// 3900 clocks for list and ranks).
 template <int NT, typename Each>
-__device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want, Each each, uint32_t& thr, int& rem, int& n_eq)
+__device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want, uint32_t kmin, uint32_t kmax, Each each, uint32_t& thr,
+                                                 int& rem, int& n_eq)
 {
     constexpr int NW = NT / kWave;
     constexpr int LB = NT == 1024 ? 11 : (NT == 512 ? 10 : (NT == 256 ? 9 : 8));
@@ -63,46 +125,27 @@ __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want,
     const int lane = tid & 63;
     const int wave = tid >> 6;
 
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-    each([&](uint32_t key) {
-        kmin = key < kmin ? key : kmin;
-        kmax = key > kmax ? key : kmax;
-    });
-    min_max_dpp<0xB1>(kmin, kmax);
-    min_max_dpp<0x4E>(kmin, kmax);
-    min_max_dpp<0x141>(kmin, kmax);
-    min_max_dpp<0x140>(kmin, kmax);
-#pragma unroll
-    for (int o = 16; o < kWave; o <<= 1) {
-        const uint32_t a = (uint32_t)__shfl_xor((int)kmin, o, kWave), b = (uint32_t)__shfl_xor((int)kmax, o, kWave);
-        kmin = a < kmin ? a : kmin;
-        kmax = b > kmax ? b : kmax;
-    }
-    if (lane == 0) {
-        s.lo[wave] = kmin;
-        s.hi[wave] = kmax;
-    }
-    if (tid == 0) {
-        s.sel[0] = 0;
-        s.sel[1] = s.sel[2] = want;
-        s.listed = 0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < NW; ++v) {
-        kmin = s.lo[v] < kmin ? s.lo[v] : kmin;
-        kmax = s.hi[v] > kmax ? s.hi[v] : kmax;
-    }
     uint32_t lo = kmin;
     uint32_t top = kmax >= kmin ? kmax - kmin : 0u;      // largest offset from lo that still belongs to the range
     int left = want;
-    for (;;) {
+    for (bool whole = true;; whole = false) {
         const int bits = top ? 32 - __builtin_clz(top) : 0;
         const int shift = bits > LB ? bits - LB : 0;
-        each([&](uint32_t key) {
-            const uint32_t off = key - lo;
-            if (key >= lo && off <= top) atomicAdd(&s.hist[off >> shift], 1);
-        });
+        if (whole) {
+            each([&](uint32_t key) {
+                const uint32_t bin = (key - lo) >> shift;
+                atomicAdd(&s.hist[bin < 2 * NT ? bin : 2 * NT - 1], 1);
+            });
+        } else {
+            each([&](uint32_t key) {
+                const uint32_t off = key - lo;
+                if (key >= lo && off <= top) atomicAdd(&s.hist[off >> shift], 1);
+            });
+        }
+        if (tid == 0) {
+            s.sel[0] = 0;
+            s.sel[1] = s.sel[2] = left;
+        }
         __syncthreads();
         const int c0 = s.hist[2 * tid], c1 = s.hist[2 * tid + 1];
         s.hist[2 * tid] = 0;
@@ -131,25 +174,33 @@ __device__ __forceinline__ void select_threshold(SelectScratch<NT>& s, int want,
         n_eq = s.sel[2];
         if (shift == 0 || left == n_eq) break;            // equal keys, or the whole bin is kept
         if (n_eq <= kWave) {
-            // a bin of few keys: listed, and every wave ranks them for itself
+            // a bin of few keys: listed, and their ranks counted by all waves, four keys to compare with each (NW = 16)
             each([&](uint32_t key) {
                 if (key >= lo && key - lo <= top) s.list[atomicAdd(&s.listed, 1)] = key;
             });
             __syncthreads();
-            const uint32_t mine = lane < n_eq ? s.list[lane] : 0u;
-            int larger = 0, equal = 0;
-            for (int j = 0; j < n_eq; ++j) {
-                const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
-                larger += o > mine ? 1 : 0;
-                equal += o == mine ? 1 : 0;
+            const uint32_t mine = s.list[lane];
+            for (int j = 4 * wave; j < n_eq; j += 4 * NW) {
+                const uint4 o = *reinterpret_cast<const uint4*>(&s.list[j]);
+                int larger = o.x > mine ? 1 : 0;
+                larger += (j + 1 < n_eq && o.y > mine) ? 1 : 0;
+                larger += (j + 2 < n_eq && o.z > mine) ? 1 : 0;
+                larger += (j + 3 < n_eq && o.w > mine) ? 1 : 0;
+                if (larger) atomicAdd(&s.rank[lane], larger);
             }
-            const uint64_t at = __ballot(lane < n_eq && larger < left && left <= larger + equal);
-            const int l = __builtin_ctzll(at);
-            lo = (uint32_t)__builtin_amdgcn_readlane((int)mine, l);
-            left -= __builtin_amdgcn_readlane(larger, l);
-            n_eq = __builtin_amdgcn_readlane(equal, l);
+            __syncthreads();
+            // the wanted key: of those with fewer than `left` larger ones the one with most
+            const int larger = s.rank[lane];
+            const bool in = lane < n_eq && larger < left;
+            int most = in ? larger : 0;
+            most = wave_max_int(most);
+            const uint64_t at = __ballot(in && larger == most);
+            lo = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)__builtin_ctzll(at));
+            left -= most;
+            n_eq = (int)__popcll(at);
             break;
         }
+        __syncthreads();                                  // everyone has read the result of this round
     }
     thr = lo;
     rem = left;

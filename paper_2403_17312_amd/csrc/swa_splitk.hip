@@ -7,7 +7,7 @@
 //   2. swa_split_select_kernel   one workgroup per pair: append, softmax over the stored logits,
 //                                importance accumulation, budget and selection (Alg. 1 lines 1-5),
 //                                kept list and the kept tokens' weights to memory;
-//   3. swa_split_gather_kernel   one workgroup per pair and 128 bytes of a row: out = sum p_i v_i / sum p_i
+//   3. swa_split_gather_kernel   one workgroup per pair and 64 or 128 bytes of a row: out = sum p_i v_i / sum p_i
 //                                over the kept list (Alg. 1 lines 6-8), rounded once to the output type.
 // The logits are formed exactly as the one-workgroup kernel forms them (same products, same
 // reduction order), so weights, importance and the kept set are bit-identical to that form; only
@@ -44,7 +44,7 @@ struct SplitArgs {
 
 constexpr int kSelThreads = 1024;    // launch 2: a whole CU's worth of one pair
 constexpr int kGatherThreads = 1024;
-constexpr int kPieceBytes = 128;     // of a value row, per workgroup of launch 3
+constexpr int kNarrowPairs = 64;     // up to so many pairs launch 3 takes 64 bytes of a row per workgroup, else 128
 constexpr int kXcds = 8;             // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
 constexpr int kSelPer = SWA_MAX_CAP / kSelThreads;   // slots per thread of launch 2 at most
 
@@ -116,7 +116,9 @@ __global__ void __launch_bounds__(NT) swa_split_logits_kernel(SplitArgs a)
 // threads share the work.  PER: slots per thread.  Weights are bit-identical to the one-workgroup kernel's: its 512 threads'
 // sums are added up in its order.
 // 32 pairs x 8192 rows, f16, d = 128: 14.6 us (17 with weights and keys in LDS, two rounds of histograms and runs of
-// slots per thread, 33 with the one-workgroup kernel in this place).
+// slots per thread, 33 with the one-workgroup kernel in this place); then 32 400 -> 28 100 clocks with the range of the keys from the old
+// importance (no pass over the new keys and no barrier for it), ranks counted by all waves, and the kept slots placed from lane masks (whole
+// step, with the narrower pieces of launch 3, 8 pairs x 12000 36.8 -> 33.7 us, 32 x 8192 35.2 -> 33.1, 64 x 8192 48.7 -> 46.7).
 template <int PER>
 __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs a)
 {
@@ -151,6 +153,8 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     }
     s_sel.hist[2 * tid] = 0;
     s_sel.hist[2 * tid + 1] = 0;
+    if (tid == 0) s_sel.listed = 0;
+    if (tid < kWave) s_sel.rank[tid] = 0;
     const int len = a.cache_len[s];
     const int n = a.seq_len[s];
     const int m = len + 1;
@@ -181,11 +185,28 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
         }
         if (tid == 0) a.pos[pair * (int64_t)cap + len] = n - 1;
 
+        budget(n, m, a.w, a.sparsity_bp, keep, n_local, n_global, w_eff);
+        const int ncand = m - n_local;
         float mx = -INFINITY;
+        // the old importance of the candidates, as keys: with the largest weight it bounds the new
+        uint32_t kmin = 0xffffffffu, kmax = 0u;
+        const int n0 = anew(keep < m ? ncand : 0);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) mx = fmaxf(mx, z[k]);
+        for (int k = 0; k < PER; ++k) {
+            mx = fmaxf(mx, z[k]);
+            if (k * NT >= n0) continue;
+            const uint32_t old = order_key(sc[k]);
+            const bool cand = tid + k * NT < n0;
+            kmin = cand && old < kmin ? old : kmin;
+            kmax = cand && old > kmax ? old : kmax;
+        }
         mx = wave_max(mx);
-        if (lane == 0) s_red[wave] = mx;
+        wave_min_max(kmin, kmax);
+        if (lane == 0) {
+            s_red[wave] = mx;
+            s_sel.lo[wave] = kmin;
+            s_sel.hi[wave] = kmax;
+        }
         __syncthreads();
         mx = s_red[0];
 #pragma unroll
@@ -216,12 +237,11 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
 #pragma unroll
         for (int v = 0; v < SUMT / kWave; ++v) sum += s_sum[v];
 
-        budget(n, m, a.w, a.sparsity_bp, keep, n_local, n_global, w_eff);
-        const int ncand = m - n_local;
         uint32_t key[PER];
         const int m3 = anew(m);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
+            key[k] = 0u;
             if (k * NT >= m3) continue;
             const int i = tid + k * NT;
             if (i < m3) {
@@ -262,46 +282,65 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
                         if (tid + k * NT < n) f(key[k]);
                     }
                 };
-                select_threshold<NT>(s_sel, n_global, each, thr, rem, n_eq);
+                // Range of the keys: adding a weight, which is at most 1 / sum, to the old importance rounds monotonically, so the range of
+                // the old values and that weight (a little more of it) enclose the new ones; what is not finite is looked at itself.
+#pragma unroll
+                for (int v = 0; v < NW; ++v) {
+                    kmin = s_sel.lo[v] < kmin ? s_sel.lo[v] : kmin;
+                    kmax = s_sel.hi[v] > kmax ? s_sel.hi[v] : kmax;
+                }
+                const float most = key_value(kmax) + 1.0001f / sum;
+                if (kmin > order_key(-INFINITY) && kmax < order_key(INFINITY) && most < INFINITY && sum < INFINITY) kmax = order_key(most);
+                else key_range<NT>(s_sel, each, kmin, kmax);
+                select_threshold<NT>(s_sel, n_global, kmin, kmax, each, thr, rem, n_eq);
             }
             // The kept list: a wave's 64 slots of a register are one run, so ballots place them within it and a scan of the runs' counts
             // (every wave for itself) places the runs.
-            const uint64_t lower = (1ull << lane) - 1ull;
-            uint32_t sure = 0u, tied = 0u;                      // bit k: slot tid + k NT
-            for (int k = PER; k < kSelPer; ++k)
-                if (lane == 0) s_chunk[k * NW + wave] = 0u;
+            auto below = [](uint64_t mask) __attribute__((always_inline)) {       // lanes of it before this one
+                return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            };
+            // which lanes' slots of register k are kept for sure, and which tie with the threshold
+            auto lanes = [&](int k, int m, int n, uint32_t thr, uint64_t& in, uint64_t& eq) __attribute__((always_inline)) {
+                in = __ballot(key[k] > thr);
+                eq = __ballot(key[k] == thr);
+                if ((k + 1) * NT > n) {                         // (not all of them candidates)
+                    const int i = tid + k * NT;
+                    const uint64_t cand = __ballot(i < n);
+                    in = (in & cand) | (__ballot(i < m) & ~cand);
+                    eq &= cand;
+                }
+            };
+            const uint32_t thr_u = (uint32_t)__builtin_amdgcn_readfirstlane((int)thr);
+            int counts = 0;                                     // lane k: register k
             const int m4 = anew(m), n4 = anew(ncand);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                uint32_t c = 0u;
-                if (k * NT < m4) {
-                    const int i = tid + k * NT;
-                    const bool cand = i < n4;
-                    const bool in = i < m4 && (!cand || key[k] > thr), eq = cand && key[k] == thr;
-                    sure |= in ? 1u << k : 0u;
-                    tied |= eq ? 1u << k : 0u;
-                    c = (uint32_t)__popcll(__ballot(in)) | ((uint32_t)__popcll(__ballot(eq)) << 16);
-                }
-                if (lane == 0) s_chunk[k * NW + wave] = c;
+                if (k * NT >= m4) continue;
+                uint64_t in, eq;
+                lanes(k, m4, n4, thr_u, in, eq);
+                counts = lane == k ? (int)__popcll(in) | ((int)__popcll(eq) << 16) : counts;
             }
+            if (lane < kSelPer) s_chunk[lane * NW + wave] = (uint32_t)counts;
             __syncthreads();
             const uint4 c4 = *reinterpret_cast<const uint4*>(&s_chunk[4 * lane]);
             const uint32_t own = c4.x + c4.y + c4.z + c4.w;
             const uint32_t inc = (uint32_t)wave_scan((int)own);
             const int part = wave & 3;                          // chunk k NW + wave: lane (k NW + wave) / 4, its entry `part`
             const uint32_t first = inc - own + (part > 0 ? c4.x : 0u) + (part > 1 ? c4.y : 0u) + (part > 2 ? c4.z : 0u);
-            const int m5 = anew(m);
+            const int m5 = anew(m), n5 = anew(ncand), thr5 = anew((int)thr_u);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 if (k * NT >= m5) continue;
+                uint64_t mask, ties;
+                lanes(k, m5, n5, (uint32_t)thr5, mask, ties);
                 const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)first, k * (NW / 4) + wave / 4);
                 const int eq = (int)(before >> 16);
-                const bool t = (tied >> k) & 1u;
-                const uint64_t tm = __ballot(t);
-                const bool in = ((sure >> k) & 1u) || (t && eq + (int)__popcll(tm & lower) < rem);
-                const uint64_t mask = __ballot(in);
-                if (in) {
-                    const int at = (int)(before & 0xffffu) + (eq < rem ? eq : rem) + (int)__popcll(mask & lower);
+                if (ties) {                                     // the lowest slots of what ties
+                    const bool t = __builtin_amdgcn_inverse_ballot_w64(ties) && eq + below(ties) < rem;
+                    mask |= __ballot(t);
+                }
+                if (__builtin_amdgcn_inverse_ballot_w64(mask)) {
+                    const uint32_t at = (before & 0xffffu) + (uint32_t)(eq < rem ? eq : rem) + (uint32_t)below(mask);
                     kout[at] = tid + k * NT;
                     Wp[at] = z[k];
                 }
@@ -325,26 +364,28 @@ __global__ void __launch_bounds__(kSelThreads) swa_split_select_kernel(SplitArgs
     }
 }
 
-// Launch 3.  Output of one pair from its kept list, 128 bytes of the row per workgroup.
+// Launch 3.  Output of one pair from its kept list, PIECE bytes of the row per workgroup.
 //
 // Bound: what a CU can load (about 100 GB/s with random rows) and the launch's own latency.  Whole rows in slices of the list, or inside
 // launch 2, would need either a fourth launch that adds the slices up or a choice by the number of kept rows, which
 // the host does not know: a compacted cache or a wide window keeps many times the share that the sparsity
-// names.  Channels need no sum across workgroups, whatever is kept.  64-byte pieces are 1 to 5 us faster with few pairs and much
-// kept, but slower from about 96 pairs on (128 pairs x 8192 kept rows, whole step 118 against 102 us).
-// Whole step, f16, d = 128, this form / partial sums and a fourth launch / output in launch 2, in us (launches 1 and 2 have become 3
-// to 6 us faster since, in all three): 32 pairs, 20 of 2048 rows kept 20.6 / 26.3 / 19.4; 410 of 2048 23.2 / 28.8 / 23.1; all of
-// 2048 21.4 / 28.2 / 33.3; 1638 of 8192 40.1 / 45.3 / 46.5; all of 8192 52.8 / 59.2 / 98; 128 pairs, all of 8192 102 / 130 / 136.
-// This form now: 14.7, 14.9, 17.3, 35.1, 49.5 and 97.  Reading the list a round ahead changed nothing, or cost 2 %.
-template <typename T, int D>
+// names.  Channels need no sum across workgroups, whatever is kept.  Pieces of 64 bytes double the workgroups and halve the rounds that each
+// makes over the list, which pays up to 64 pairs, where that leaves a CU to every workgroup; beyond, the halves of a line cost more.
+// Whole step, f16, d = 128, pieces of 128 / 64 bytes, us: 8 pairs x 8192 rows, a fifth kept 28.9 / 27.3, all 43.2 / 37.0; 32 pairs 35.3 /
+// 33.6, 52.6 / 49.0; 64 pairs 48.3 / 47.4, 70.3 / 66.3; 96 pairs 62.7 / 65.1, 85.8 / 107; 128 pairs 72.7 / 75.3, 104 / 123; 32 pairs, bf16, d =
+// 64 31.3 / 28.8, fp32, d = 128 47.7 / 46.7.
+// This form / partial sums and a fourth launch / output in launch 2, when it was chosen (launches 1 and 2 took 3 to 6 us more): 32 pairs, 20 of 2048
+// rows kept 20.6 / 26.3 / 19.4; all of 2048 21.4 / 28.2 / 33.3; 1638 of 8192 40.1 / 45.3 / 46.5; all of 8192 52.8 / 59.2 / 98; 128
+// pairs, all of 8192 102 / 130 / 136.  Reading the list a round ahead changed nothing, or cost 2 %.
+template <typename T, int D, int PIECE>
 __global__ void __launch_bounds__(kGatherThreads) swa_split_gather_kernel(SplitArgs a)
 {
     constexpr int NT = kGatherThreads;
     constexpr int NW = NT / kWave;
     constexpr int EPV = Elem<T>::kPerVec;
     constexpr int ROWB = D * Elem<T>::kBytes;
-    constexpr int LPR = kPieceBytes / 16;         // lanes per piece of a row
-    constexpr int PIECES = ROWB / kPieceBytes;
+    constexpr int LPR = PIECE / 16;         // lanes per piece of a row
+    constexpr int PIECES = ROWB / PIECE;
     constexpr int CH = LPR * EPV;                 // channels of a piece
     constexpr int NG = NT / LPR;
     constexpr int UV = 8;
@@ -362,7 +403,7 @@ __global__ void __launch_bounds__(kGatherThreads) swa_split_gather_kernel(SplitA
     if (pair >= a.pairs || a.ws_ok[pair] == 0) return;          // (a skipped pair: nothing is written for it)
     int keep = a.kept_cnt[(int)(pair / a.h)];
     keep = keep < 0 ? 0 : (keep > a.cap ? a.cap : keep);
-    const char* Vp = a.v_cache + pair * (int64_t)a.cap * ROWB + piece * kPieceBytes + sub * 16;
+    const char* Vp = a.v_cache + pair * (int64_t)a.cap * ROWB + piece * PIECE + sub * 16;
     const float* Wp = a.ws_p + pair * (int64_t)a.cap;
     const int32_t* idx = a.kept_idx + pair * (int64_t)a.cap;
     float acc[EPV];
@@ -394,12 +435,19 @@ __global__ void __launch_bounds__(kGatherThreads) swa_split_gather_kernel(SplitA
             ps += pw[u];
         }
     }
+    // over the wave's row groups
+    auto over_groups = [](float x) __attribute__((always_inline)) {
+        x += dpp_move<0x128>(x);                  // row_ror 8
+        if constexpr (LPR == 4) x += dpp_move<0x124>(x);
+        const uint32_t u = f2u(x);
+        const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        const uint32_t v = f2u(u2f(r16[0]) + u2f(r16[1]));
+        const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return u2f(r32[0]) + u2f(r32[1]);
+    };
 #pragma unroll
-    for (int o = LPR; o < kWave; o <<= 1) {
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
-        ps += __shfl_xor(ps, o, kWave);
-    }
+    for (int e = 0; e < EPV; ++e) acc[e] = over_groups(acc[e]);
+    ps = over_groups(ps);
     if (lane < LPR) {
 #pragma unroll
         for (int e = 0; e < EPV; ++e) s_acc[wave * CH + sub * EPV + e] = acc[e];
@@ -438,8 +486,11 @@ static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
     hipLaunchKernelGGL((swa_split_logits_kernel<T, D, NT>), grid, dim3(NT), 0, stream, a);
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     if (launch_select(a, pairs, stream) != SWA_OK) return SWA_ERR_HIP;
-    const int64_t pieces = (pairs + kXcds - 1) / kXcds * kXcds * (D * Elem<T>::kBytes / kPieceBytes);
-    hipLaunchKernelGGL((swa_split_gather_kernel<T, D>), dim3((unsigned)pieces), dim3(kGatherThreads), 0, stream, a);
+    const int64_t at_most = (pairs + kXcds - 1) / kXcds * kXcds * D * Elem<T>::kBytes;      // bytes of all rows
+    if (pairs <= kNarrowPairs)
+        hipLaunchKernelGGL((swa_split_gather_kernel<T, D, 64>), dim3((unsigned)(at_most / 64)), dim3(kGatherThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((swa_split_gather_kernel<T, D, 128>), dim3((unsigned)(at_most / 128)), dim3(kGatherThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 

@@ -83,3 +83,45 @@ def test_output_whatever_is_kept(dtype, d, w, sparsity, ahead):
                      for x in (vk, vk.abs()))
         # fp32 sums of at most 2500 terms (2^-20 of their magnitude), one rounding to the output type
         assert bool(((st.out[i].double() - want).abs() <= u * want.abs() + 2.0 ** -20 * mag).all()), (n, k)
+
+
+@pytest.mark.parametrize("special", ["inf", "nan", "-nan", "-inf", "huge", "negative", "-0", "tiny"])
+@pytest.mark.parametrize("w,sparsity", [(0, 9000), (64, 5000)])
+def test_importance_of_any_value(special, w, sparsity):
+    """The range of the keys comes from the old importance where that bounds the new, and is looked for where a value is not finite."""
+    import struct
+
+    from paper_2403_17312_amd import binding as B
+    b, h, d, cap = 2, 4, 64, 4200
+    lens = [4199, 2500]
+    g = torch.Generator(device="cuda").manual_seed(29)
+    K, V = (torch.randn((b, h, cap, d), generator=g, device="cuda").half() for _ in range(2))
+    q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").half() for _ in range(3))
+    old = torch.rand((b, h, cap), generator=g, device="cuda") ** 4
+    at = torch.rand((b, h, cap), generator=g, device="cuda") < 0.05
+    if special == "negative":
+        old = torch.where(at, -old, old)
+    elif special == "tiny":
+        old *= 1e-38                                       # (denormals among them)
+    else:
+        bits = {"inf": 0x7f800000, "nan": 0x7fc00000, "-nan": 0xffc00000, "-inf": 0xff800000, "huge": 0x7f7fffff, "-0": 0x80000000}[special]
+        word = struct.unpack("<i", struct.pack("<I", bits))[0]
+        old = torch.where(at, torch.full_like(old, 0).view(torch.int32).fill_(word).view(torch.float32), old)
+    got = []
+    for flags in (0, B.SWA_SPLIT_ROWS):
+        p = B.make_params(b, h, d, cap, w, sparsity, torch.float16, flags=flags)
+        st = B.DecodeState(p, debug_probs=True)
+        st.K.copy_(K)
+        st.V.copy_(V)
+        st.score.copy_(old)
+        st.cache_len.copy_(torch.tensor(lens, dtype=torch.int32))
+        st.seq_len.copy_(torch.tensor([n + 1 for n in lens], dtype=torch.int32))
+        st.decode_step(q, kn, vn)
+        assert st.check_status() == B.SWA_OK
+        got.append(st)
+    one, two = got
+    assert one.kept_cnt.tolist() == two.kept_cnt.tolist()
+    for i, n in enumerate(lens):
+        k = one.kept_cnt[i].item()
+        assert torch.equal(one.score[i, :, :n + 1].view(torch.int32), two.score[i, :, :n + 1].view(torch.int32)), n
+        assert torch.equal(one.kept_idx[i, :, :k], two.kept_idx[i, :, :k]), n
