@@ -115,10 +115,10 @@ int launch_compact(const swa_params& p, void* k_cache, void* v_cache, float* sco
     const int rowb = cache_row_bytes(p);
     constexpr int NT = 256;
     switch (rowb) {
-        case 64: hipLaunchKernelGGL((swa_compact_kernel<64, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
-        case 128: hipLaunchKernelGGL((swa_compact_kernel<128, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
-        case 256: hipLaunchKernelGGL((swa_compact_kernel<256, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
-        case 512: hipLaunchKernelGGL((swa_compact_kernel<512, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
+        case 64: launch_kernel((swa_compact_kernel<64, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
+        case 128: launch_kernel((swa_compact_kernel<128, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
+        case 256: launch_kernel((swa_compact_kernel<256, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
+        case 512: launch_kernel((swa_compact_kernel<512, NT>), dim3((unsigned)pairs), dim3(NT), 0, stream, a); break;
         default: return SWA_ERR_UNSUPPORTED_D;
     }
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;

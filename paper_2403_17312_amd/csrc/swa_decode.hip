@@ -1159,7 +1159,7 @@ static int launch_decode_nt(const DecodeArgs& a, int64_t pairs, size_t lds_bytes
     auto kern = swa_decode_kernel<T, D, NT, RING>;
     int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes);
     if (rc != SWA_OK) return rc;
-    hipLaunchKernelGGL(kern, dim3((unsigned)pairs), dim3(NT), lds_bytes, stream, a);
+    launch_kernel(kern, dim3((unsigned)pairs), dim3(NT), lds_bytes, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 

@@ -684,7 +684,7 @@ int launch_flash_prefill(const swa_params& p, float scale, const void* q, const 
     int64_t wgs = 0;
     if (!flash_grid(a, bound, p.dtype == SWA_F32, wgs)) return SWA_ERR_BAD_SHAPE;
     auto go = [&](auto small, auto large) {
-        hipLaunchKernelGGL(p.d == 64 ? small : large, dim3((unsigned)wgs), dim3(256), 0, stream, a);
+        launch_kernel(p.d == 64 ? small : large, dim3((unsigned)wgs), dim3(256), 0, stream, a);
     };
     if (p.dtype == SWA_F32) go(swa_flash_prefill_kernel<F32, 64>, swa_flash_prefill_kernel<F32, 128>);
     else if (p.dtype == SWA_F16 && direct) go(swa_flash16_kernel<F16, 64>, swa_flash16_kernel<F16, 128>);

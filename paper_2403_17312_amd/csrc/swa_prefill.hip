@@ -655,20 +655,20 @@ static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hip
     a.stream = pairs * a.bound * (D * Elem<T>::kBytes) > (128ll << 20);
     const dim3 one((unsigned)pairs), all((unsigned)(pairs * G));
     if (stats_ready) {
-        hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
+        launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
     } else if (G > 1 && seed_in_two(pairs, a.bound, a.stated, a.R)) {
         if constexpr (D * Elem<T>::kBytes >= 512) {
-            hipLaunchKernelGGL((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
+            launch_kernel((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
         } else if (seed_chains_apart(G, a.cols, a.cap, a.R)) {
             a.chains = kChains;
-            hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, 1>), dim3((unsigned)(pairs * RT * kChains)), dim3(kWave), 0, stream, a);
+            launch_kernel((swa_seed_stats_kernel<T, D, WR, 1>), dim3((unsigned)(pairs * RT * kChains)), dim3(kWave), 0, stream, a);
         } else {
-            hipLaunchKernelGGL((swa_seed_stats_kernel<T, D, WR, kChains>), dim3((unsigned)(pairs * RT)), dim3(kChains * kWave), 0, stream, a);
+            launch_kernel((swa_seed_stats_kernel<T, D, WR, kChains>), dim3((unsigned)(pairs * RT)), dim3(kChains * kWave), 0, stream, a);
         }
         if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
-        hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
+        launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
     } else {
-        hipLaunchKernelGGL((swa_prefill_kernel<T, D, RT, WR, kSeedWhole>), one, dim3(256), 0, stream, a);
+        launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedWhole>), one, dim3(256), 0, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }

@@ -288,11 +288,11 @@ static void launch_longer(const QuantArgs& a, bool stated, hipStream_t stream)
     const dim3 one((unsigned)a.items);
     if constexpr (RESIDENT > 0) {
         if (!stated && a.items > RESIDENT) {
-            hipLaunchKernelGGL((swa_quantize_kernel<D, NT, true>), dim3((unsigned)RESIDENT), dim3(NT), 0, stream, a);
+            launch_kernel((swa_quantize_kernel<D, NT, true>), dim3((unsigned)RESIDENT), dim3(NT), 0, stream, a);
             return;
         }
     }
-    hipLaunchKernelGGL((swa_quantize_kernel<D, NT, false>), one, dim3(NT), 0, stream, a);
+    launch_kernel((swa_quantize_kernel<D, NT, false>), one, dim3(NT), 0, stream, a);
 }
 
 // `stated`: the caller's bound on the lengths, or 0.
@@ -321,7 +321,7 @@ static void launch_quantize_d(QuantArgs a, int stated, hipStream_t stream)
     else a.short_rows = line;
     if (a.short_rows >= 0) {
         const dim3 grid((unsigned)a.units_x, (unsigned)((a.units + a.units_x - 1) / a.units_x));
-        hipLaunchKernelGGL((swa_quantize_short_kernel<D>), grid, dim3(256), 0, stream, a);
+        launch_kernel((swa_quantize_short_kernel<D>), grid, dim3(256), 0, stream, a);
         if (a.short_rows >= a.cap) return;
     }
     if (nt == 256) launch_longer<D, 256, 0>(a, stated > 0, stream);

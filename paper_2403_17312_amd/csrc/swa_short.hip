@@ -57,8 +57,8 @@ struct Launch {
     int go() const
     {
         if constexpr (short_rows<T, D, NT, U>() > 0) {
-            if (a.ring) hipLaunchKernelGGL((swa_short_kernel<T, D, NT, U, true, 0>), dim3((unsigned)pairs), dim3(NT), 0, stream, a);
-            else hipLaunchKernelGGL((swa_short_kernel<T, D, NT, U, false, 0>), dim3((unsigned)pairs), dim3(NT), 0, stream, a);
+            if (a.ring) launch_kernel((swa_short_kernel<T, D, NT, U, true, 0>), dim3((unsigned)pairs), dim3(NT), 0, stream, a);
+            else launch_kernel((swa_short_kernel<T, D, NT, U, false, 0>), dim3((unsigned)pairs), dim3(NT), 0, stream, a);
             return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
         }
         return SWA_ERR_BAD_SHAPE;          // (short_form names no such form)

@@ -14,8 +14,8 @@ struct LaunchShared {
     {
         if constexpr (short_rows<T, D, NT, U>() > 0) {
             const dim3 grid((unsigned)pairs), block(NT);
-            if (a.phase == 1) hipLaunchKernelGGL((swa_short_kernel<T, D, NT, U, false, 1>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((swa_short_kernel<T, D, NT, U, false, 2>), grid, block, 0, stream, a);
+            if (a.phase == 1) launch_kernel((swa_short_kernel<T, D, NT, U, false, 1>), grid, block, 0, stream, a);
+            else launch_kernel((swa_short_kernel<T, D, NT, U, false, 2>), grid, block, 0, stream, a);
             return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
         }
         return SWA_ERR_BAD_SHAPE;          // (short_form names no such form)

@@ -471,10 +471,10 @@ static int launch_select(const SplitArgs& a, int64_t pairs, hipStream_t stream)
 {
     const dim3 grid((unsigned)pairs), block(kSelThreads);
     const int per = (a.lds_slots + kSelThreads - 1) / kSelThreads;
-    if (per <= 3) hipLaunchKernelGGL((swa_split_select_kernel<3>), grid, block, 0, stream, a);
-    else if (per <= 5) hipLaunchKernelGGL((swa_split_select_kernel<5>), grid, block, 0, stream, a);
-    else if (per <= 9) hipLaunchKernelGGL((swa_split_select_kernel<9>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((swa_split_select_kernel<kSelPer>), grid, block, 0, stream, a);
+    if (per <= 3) launch_kernel((swa_split_select_kernel<3>), grid, block, 0, stream, a);
+    else if (per <= 5) launch_kernel((swa_split_select_kernel<5>), grid, block, 0, stream, a);
+    else if (per <= 9) launch_kernel((swa_split_select_kernel<9>), grid, block, 0, stream, a);
+    else launch_kernel((swa_split_select_kernel<kSelPer>), grid, block, 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
@@ -483,14 +483,14 @@ static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
 {
     constexpr int NT = 256;
     const dim3 grid((unsigned)(pairs * a.G));
-    hipLaunchKernelGGL((swa_split_logits_kernel<T, D, NT>), grid, dim3(NT), 0, stream, a);
+    launch_kernel((swa_split_logits_kernel<T, D, NT>), grid, dim3(NT), 0, stream, a);
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     if (launch_select(a, pairs, stream) != SWA_OK) return SWA_ERR_HIP;
     const int64_t at_most = (pairs + kXcds - 1) / kXcds * kXcds * D * Elem<T>::kBytes;      // bytes of all rows
     if (pairs <= kNarrowPairs)
-        hipLaunchKernelGGL((swa_split_gather_kernel<T, D, 64>), dim3((unsigned)(at_most / 64)), dim3(kGatherThreads), 0, stream, a);
+        launch_kernel((swa_split_gather_kernel<T, D, 64>), dim3((unsigned)(at_most / 64)), dim3(kGatherThreads), 0, stream, a);
     else
-        hipLaunchKernelGGL((swa_split_gather_kernel<T, D, 128>), dim3((unsigned)(at_most / 128)), dim3(kGatherThreads), 0, stream, a);
+        launch_kernel((swa_split_gather_kernel<T, D, 128>), dim3((unsigned)(at_most / 128)), dim3(kGatherThreads), 0, stream, a);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
