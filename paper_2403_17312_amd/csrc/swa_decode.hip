@@ -82,6 +82,7 @@ swa_decode_kernel(DecodeArgs a)
     // The 512-thread instantiation (long caches: the step after a prompt) has 128 registers per
     // lane and keeps twice as many rows in flight in the gathered pass and in the row moves.
     constexpr bool kWide = NT >= 512;
+    constexpr int kNarrow = kQ8 ? 128 : 256; // threads of the smallest workgroup
     constexpr int UV = kWide ? 6 : 4;       // value rows in flight per group (gathered pass)
     // Importance values (and positions) prefetched per thread.  They are live through the whole row stream; the 8-bit
     // cache's lanes have no registers for four (with two its streaming pass does not spill: 2560 pairs of about 206 slots
@@ -425,12 +426,22 @@ swa_decode_kernel(DecodeArgs a)
             s_p[i] = e;
             sum += e;
         }
+        // (the order of the additions goes with the length, not with the workgroup that few pairs are given: weights, and with them
+        // the selection, do not depend on the batch)
+        const int ST = NT > kNarrow ? a.sum_threads : NT;
+        if (ST < NT) {
+            __syncthreads();
+            sum = 0.f;
+            if (tid < ST)
+                for (int i = tid; i < m; i += ST) sum += s_p[i];
+        }
         sum = wave_sum(sum);
         if (lane == 0) s_redB[wave] = sum;
         __syncthreads();
         sum = 0.f;
 #pragma unroll
-        for (int v = 0; v < NW; ++v) sum += s_redB[v];
+        for (int v = 0; v < NW; ++v)
+            if (v * kWave < ST) sum += s_redB[v];
 
         // Strict window: the rows of the ring in index order, the current weight standing in for
         // the row this step replaces; a token appended in this step has no earlier rows.
@@ -1163,7 +1174,8 @@ static int launch_decode_nt(const DecodeArgs& a, int64_t pairs, size_t lds_bytes
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
-// Threads per workgroup that decode_block_threads() gives for a cache format: 128 or 256 on the 8-bit cache, else 256 or 512.
+// Threads per workgroup that decode_block_threads() gives for a cache format: 128 or 256 on the 8-bit cache, else 256 or 512 (and 1024 where
+// LDS leaves a CU one workgroup).
 template <typename T>
 constexpr int narrow_threads() { return Elem<T>::kBytes == 1 ? 128 : 256; }
 
@@ -1171,6 +1183,9 @@ template <typename T, int D>
 static int launch_decode_t(const DecodeArgs& a, int64_t pairs, size_t lds_bytes, int nt, hipStream_t stream)
 {
     constexpr int N = narrow_threads<T>();
+    if constexpr (Elem<T>::kBytes > 1) {
+        if (nt == 1024 && !a.ring) return launch_decode_nt<T, D, 1024, false>(a, pairs, lds_bytes, stream);
+    }
     if (a.ring) {
         return nt == N ? launch_decode_nt<T, D, N, true>(a, pairs, lds_bytes, stream)
                        : launch_decode_nt<T, D, 2 * N, true>(a, pairs, lds_bytes, stream);
@@ -1197,6 +1212,8 @@ static int prepare_t()
     if (rc == SWA_OK) rc = prepare_one<T, D, 2 * N, false>();
     if (rc == SWA_OK) rc = prepare_one<T, D, N, true>();
     if (rc == SWA_OK) rc = prepare_one<T, D, 2 * N, true>();
+    if constexpr (Elem<T>::kBytes > 1)
+        if (rc == SWA_OK) rc = prepare_one<T, D, 1024, false>();
     return rc;
 }
 
@@ -1264,7 +1281,9 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
 
     const int64_t pairs = (int64_t)p.b * p.h;
     const int rowb = cache_row_bytes(p);
-    const int nt = decode_block_threads(pairs, bound, (p.flags & SWA_KV_INT8) != 0);
+    const bool stated = p.len_bound > 0;
+    int nt = decode_block_threads(pairs, bound, stated, (p.flags & SWA_KV_INT8) != 0);
+    a.sum_threads = (p.flags & SWA_KV_INT8) ? nt : (bound >= 1024 ? 512 : 256);
     // Without the keys' array only where one more workgroup fits a CU for it (its LDS, next to at most 10 KiB of the kernel's
     // own; 16 waves by registers): forming the keys again for every digit of the selection is not free.
     auto per_cu = [&](int slot_bytes) {
@@ -1280,6 +1299,12 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     a.key_slots = (may_drop && per_cu(16) > per_cu(20)) ? 0 : a.lds_slots;
     const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 16 : 12) : 4) +
                              (size_t)a.key_slots * 4 + (size_t)a.stash_rows * rowb * 2;
+    // Where LDS leaves a CU one workgroup of 512 threads, it gets 1024: twice the loads under way, and the phases behind them shared out
+    // further.  512 / 1024, us, four fifths and one token evicted, f16, d = 128: 32 pairs x 4096 slots 80 / 64, 49.2 / 48.6, x 7000 127 / 94,
+    // 87 / 83; 256 x 4096 152 / 123, 126 / 118; 512 x 4400 272 / 235, 208 / 220; 1280 x 5000 671 / 570, 569 / 562; x 7000 940 / 808, 789 / 767.  Where
+    // two workgroups fit, 1024 threads lose with one token evicted (128 x 1024 35.1 / 33.4, 23.8 / 26.4).  Only under a stated bound: short caches
+    // of a large capacity lose (512 pairs x 100 slots in 5000 18 / 24).
+    if (nt == 512 && stated && !ring && 2 * (lds_bytes + 10 * 1024) > 160 * 1024 && lds_bytes + 14 * 1024 <= 160 * 1024) nt = 1024;
 
     auto launch = [&](const DecodeArgs& args) -> int {
         if (p.flags & SWA_KV_INT8) {

@@ -26,6 +26,7 @@ struct DecodeArgs {
     int32_t h, cap, lds_slots, w, sparsity_bp;
     int32_t key_slots;    // selection keys in LDS: lds_slots, or 0 where they are formed from the new importance instead
     float scale;
+    int32_t sum_threads;  // the softmax sum is formed as by so many threads (at most the workgroup's)
     int32_t fuse_compaction;
     int32_t unordered;    // fused compaction fills holes instead of shifting rows (order by pos only)
     // Head-shared selection runs as two or three launches: phase 1 streams the cache and publishes the

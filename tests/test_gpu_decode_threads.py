@@ -1,0 +1,60 @@
+"""Workgroups of the decode kernel that few pairs and long caches are given: weights, importance, kept set and cache are those of the workgroup
+that a call without a stated bound gets, bit for bit, and the output is right."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+FORMS = ("unordered", "ordered", "two_call", "shared", "window")
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float16, 128), (torch.bfloat16, 64), (torch.float32, 128), (torch.float32, 64)])
+@pytest.mark.parametrize("bound", [257, 300, 1023, 1024, 3700, 4200, 7168])
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("ahead", [1, 5])                              # most of the cache is evicted, one token
+def test_stated_bound_changes_the_workgroup_and_not_the_step(dtype, d, bound, form, ahead):
+    from paper_2403_17312_amd import binding as B
+    lens = [bound - 1, bound - 2, 200, 0] if bound < 4000 else [bound - 1, 70]
+    b, h, cap, w, R = len(lens), 3, bound, 16, 8
+    g = torch.Generator(device="cuda").manual_seed(37)
+    flags = {"unordered": B.SWA_FUSE_COMPACTION | B.SWA_UNORDERED, "ordered": B.SWA_FUSE_COMPACTION, "two_call": 0,
+             "shared": B.SWA_FUSE_COMPACTION | B.SWA_UNORDERED | B.SWA_HEAD_SHARED, "window": B.SWA_FUSE_COMPACTION | B.SWA_UNORDERED}[form]
+    K0, V0 = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    s0 = torch.rand((b, h, cap), generator=g, device="cuda")
+    r0 = torch.rand((b, h, R, cap), generator=g, device="cuda")
+    len0 = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    seq = len0 * ahead + 1 if ahead == 1 else (len0 * 5).clamp(min=1)
+    got = []
+    for stated in (0, bound):
+        p = B.make_params(b, h, d, cap, w, 8000, dtype, len_bound=stated, flags=flags)
+        ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        B.swa_workspace_init(p, ws)
+        x = {"K": K0.clone(), "V": V0.clone(), "score": s0.clone(), "ring": r0.clone(), "cl": len0.clone(), "kc": torch.zeros_like(len0),
+             "pos": torch.arange(cap, dtype=torch.int32, device="cuda").repeat(b, h, 1).contiguous(),
+             "probs": torch.zeros((b, h, cap), device="cuda"), "kept": torch.zeros((b, h, cap), dtype=torch.int32, device="cuda"),
+             "out": torch.zeros((b, h, d), device="cuda", dtype=dtype)}
+        if form == "window":
+            B.swa_decode_step_window(p, q, kn, vn, x["K"], x["V"], x["ring"], R, 3, x["score"], x["pos"], x["cl"], seq, x["kept"], x["kc"],
+                                     x["out"], x["probs"], ws)
+        else:
+            B.swa_decode_step(p, q, kn, vn, x["K"], x["V"], x["score"], x["pos"], x["cl"], seq, x["kept"], x["kc"], x["out"], x["probs"], ws)
+        assert B.swa_check_status(p, ws) == B.SWA_OK
+        got.append(x)
+    one, two = got
+    for a in ("cl", "kc", "probs", "score", "pos", "K", "V", "ring"):
+        assert torch.equal(one[a], two[a]), a
+    # fp32 sums of at most 7168 terms (2^-20 of their magnitude), one rounding to the output type
+    u = {torch.float32: 2.0 ** -20, torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}[dtype]
+    for i, n in enumerate(lens):
+        k = two["kc"][i].item()
+        assert torch.equal(one["kept"][i, :, :k], two["kept"][i, :, :k])
+        at = two["kept"][i, :, :k].long()
+        rows = torch.cat([V0[i, :, :n], vn[i][:, None]], 1).double()
+        pk = torch.gather(two["probs"][i].double(), 1, at)
+        vk = torch.gather(rows, 1, at[..., None].expand(-1, -1, d))
+        want, mag = ((pk[:, None] @ y)[:, 0] / pk.sum(1, keepdim=True) if k else torch.zeros((h, d), device="cuda", dtype=torch.float64)
+                     for y in (vk, vk.abs()))
+        dense = (two["probs"][i, :, :n + 1].double()[:, None] @ rows.abs())[:, 0]
+        # (a few evicted rows are subtracted from the dense sum, whose magnitude then counts, over a kept mass of at least 1/20)
+        assert bool(((two["out"][i].double() - want).abs() <= u * want.abs() + 2.0 ** -20 * (mag + 20 * dense)).all()), (n, k)
