@@ -1300,11 +1300,13 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 16 : 12) : 4) +
                              (size_t)a.key_slots * 4 + (size_t)a.stash_rows * rowb * 2;
     // Where LDS leaves a CU one workgroup of 512 threads, it gets 1024: twice the loads under way, and the phases behind them shared out
-    // further.  512 / 1024, us, four fifths and one token evicted, f16, d = 128: 32 pairs x 4096 slots 80 / 64, 49.2 / 48.6, x 7000 127 / 94,
-    // 87 / 83; 256 x 4096 152 / 123, 126 / 118; 512 x 4400 272 / 235, 208 / 220; 1280 x 5000 671 / 570, 569 / 562; x 7000 940 / 808, 789 / 767.  Where
-    // two workgroups fit, 1024 threads lose with one token evicted (128 x 1024 35.1 / 33.4, 23.8 / 26.4).  Only under a stated bound: short caches
-    // of a large capacity lose (512 pairs x 100 slots in 5000 18 / 24).
-    if (nt == 512 && stated && !ring && 2 * (lds_bytes + 10 * 1024) > 160 * 1024 && lds_bytes + 14 * 1024 <= 160 * 1024) nt = 1024;
+    // further.  512 / 1024, us, four fifths and one token evicted, f16, d = 128: 32 pairs x 5000 slots 95 / 71, 62 / 60, x 7000 127 / 94,
+    // 87 / 83; 256 x 7000 216 / 184, 186 / 179; 1280 x 5000 671 / 570, 569 / 562; x 7000 940 / 808, 789 / 767.  Where
+    // two workgroups fit, 1024 threads lose with one token evicted (128 x 1024 35.1 / 33.4, 23.8 / 26.4).  Whether they would without the keys' array
+    // decides also where few pairs keep it, so that a pair's output (the order of its sum goes with the threads) is the same for any number of
+    // pairs.  Only under a stated bound: short caches of a large capacity lose (512 pairs x 100 slots in 5000 18 / 24).
+    const size_t droppable = (a.unordered && !shared && rowb < 512) ? (size_t)a.key_slots * 4 : 0;
+    if (nt == 512 && stated && !ring && 2 * (lds_bytes - droppable + 10 * 1024) > 160 * 1024 && lds_bytes + 14 * 1024 <= 160 * 1024) nt = 1024;
 
     auto launch = [&](const DecodeArgs& args) -> int {
         if (p.flags & SWA_KV_INT8) {
