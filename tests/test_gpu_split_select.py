@@ -125,3 +125,38 @@ def test_importance_of_any_value(special, w, sparsity):
         k = one.kept_cnt[i].item()
         assert torch.equal(one.score[i, :, :n + 1].view(torch.int32), two.score[i, :, :n + 1].view(torch.int32)), n
         assert torch.equal(one.kept_idx[i, :, :k], two.kept_idx[i, :, :k]), n
+
+
+@pytest.mark.parametrize("dtype,d,b,h,cap", [(torch.float16, 128, 4, 8, 1024), (torch.float32, 64, 4, 3, 1100), (torch.bfloat16, 128, 4, 16, 1536),
+                                             (torch.float32, 128, 4, 5, 2047)])
+@pytest.mark.parametrize("w,sparsity", [(0, 9999), (7, 0), (64, 8000), (900, 9000)])
+def test_caches_below_2048_slots(dtype, d, b, h, cap, w, sparsity):
+    """Few pairs with wide rows are split from 1024 or 1536 slots on: weights, importance and kept set of the one-workgroup kernel."""
+    from paper_2403_17312_amd import binding as B
+    lens = [cap - 1, cap - 2, 700, 0]
+    g = torch.Generator(device="cuda").manual_seed(41)
+    K, V = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    old = torch.floor(torch.rand((b, h, cap), generator=g, device="cuda") * 300) / 300                # (some of them equal)
+    got = []
+    for flags in (0, B.SWA_SPLIT_ROWS):
+        st = B.DecodeState(B.make_params(b, h, d, cap, w, sparsity, dtype, flags=flags), debug_probs=True)
+        st.K.copy_(K)
+        st.V.copy_(V)
+        st.score.copy_(old)
+        st.cache_len.copy_(torch.tensor(lens, dtype=torch.int32))
+        st.seq_len.copy_(torch.tensor([n + 1 for n in lens], dtype=torch.int32))
+        st.decode_step(q, kn, vn)
+        assert st.check_status() == B.SWA_OK
+        got.append(st)
+    one, two = got
+    assert one.cache_len.tolist() == two.cache_len.tolist() and one.kept_cnt.tolist() == two.kept_cnt.tolist()
+    u = {torch.float32: 2.0 ** -20, torch.float16: 2.0 ** -10, torch.bfloat16: 2.0 ** -7}[dtype]
+    for i, n in enumerate(lens):
+        k = one.kept_cnt[i].item()
+        assert torch.equal(one.score[i, :, :n + 1], two.score[i, :, :n + 1]), n
+        assert torch.equal(one.probs[i], two.probs[i]), n
+        assert torch.equal(one.kept_idx[i, :, :k], two.kept_idx[i, :, :k]), n
+        # the same fp32 terms added in another order, rounded once to the output type
+        x, y = one.out[i].double(), two.out[i].double()
+        assert bool(((x - y).abs() <= u * (y.abs() + 1.0)).all()), n
