@@ -85,8 +85,8 @@ int decode_stash_rows(const swa_params& p)
 int decode_block_threads(int64_t pairs, int len_bound, bool stated, bool kv_int8)
 {
     // Measured on MI355X (all five workloads): caches of a thousand slots and more (the first
-    // step after a prompt, low sparsity) want 512 threads per pair, shorter ones 256; the pair
-    // count matters little.
+    // step after a prompt, low sparsity) want 512 threads per pair, shorter ones 256; from a few
+    // hundred pairs on their number matters little.
     // Few pairs do not fill the chip, and a workgroup's own chain of phases is the step: 256 / 512 threads, us, four fifths and one
     // token evicted, f16, d = 128: 4 pairs x 400 slots 19.5 / 16.0, 12.4 / 11.0, x 1000 31.2 / 22.5, 18.5 / 14.9; 84 x 260 17.7 / 16.9, 11.1 /
     // 11.0, x 1000 38.4 / 30.3, 21.6 / 18.5; 128 x 260 18.2 / 17.3, 11.7 / 11.9, x 700 32.3 / 26.8, 18.3 / 17.6; 100 x 700, fp32 71 / 45, 30.4 / 26.2.
