@@ -42,13 +42,13 @@ struct PrefillArgs {
     int32_t bound;        // on the lengths: where the slices are laid (host side)
     bool stated;          // the bound is the caller's, not the capacity (host side)
     int32_t chains;       // statistics: parts of the keys whose sums are still to be merged, kChains or 1
-    int32_t stream;       // column sums: keys do not come from a cache (16-bit formats)
 };
 
 // What one launch does.
 constexpr int kSeedWhole = 0;   // both passes, one workgroup per pair
 constexpr int kSeedStats = 1;   // row statistics of 32 rows of one pair, a copy for every slice
 constexpr int kSeedSums = 2;    // column sums of one slice, from the row statistics of another launch
+constexpr int kSeedSumsFar = 3; // the same, keys read past the caches (16-bit formats)
 constexpr int kChains = 4;      // row statistics: key tile t belongs to chain t % 4, whose sums are merged in ascending order
 
 // Merge two (max, sum-of-exp2) pairs of disjoint key sets.
@@ -284,6 +284,11 @@ swa_seed_stats_kernel(PrefillArgs a)
 // 128, R = 64 640 / 609; 2560 x 1024 f16 219 / 196; 320 x 8000 299 / 234; 512 x 512 24.4 / 21.6; 8192 of 100..500, d = 64, R = 33
 // 155 / 121; 6400 of 17..31 47 / 31; sums after the attention, 1792 x 4096 387 / 308 (differences of whole calls).  Room for two or four
 // tiles leaves fewer workgroups on a CU: no gain, up to 1.6 times as slow.
+// The sums behind the attention find their code cold, so what is fixed in a launch (whether the loads pass the caches, whether there is a
+// score at all, whether a tile can be seen by all rows) is fixed in the code and not asked in the loop, which the compiler
+// copied for every answer: attention and sums before LDS / with copies / without, us: 40 pairs of 69..279 keys, d = 64, R = 33 12.7 /
+// 13.1 / 12.9, d = 128, R = 128 22.8 / 23.4 / 22.7; 128 of 200..256, d = 64, R = 33 14.3 / 14.7 / 14.4; rows, 32 x 1000, R = 16 20.5 / 18.5 /
+// 16.8, R = 64 30.9 / 30.8 / 29.3.  Up to 64 keys with more than 96 rows at d = 128 are 2 to 4 % slower than before LDS (2048 of 17..31 74.5 / 77.1).
 // fp32 is bound by its products and keeps the operands' layout (d = 64, R = 33 476 / 508 by LDS), and so do more than 32 rows that are written
 // out, whose stores the wait for a tile would wait for as well (320 x 8000, R = 64 546 / 565; up to 32 rows 512 x 512 23.4 / 21.4).
 template <typename T, int RT, bool WR, int MODE>
@@ -311,23 +316,24 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int hb = lane >> 5;
     constexpr bool kByLds = kSeedByLds<T, RT, WR, MODE>;
     constexpr bool kStats = MODE == kSeedStats;
+    constexpr bool kSums = MODE == kSeedSums || MODE == kSeedSumsFar;
     const int row_tiles = kStats ? (a.R + 31) / 32 : 1;
-    const int64_t pair = MODE == kSeedSums ? blockIdx.x / a.G : blockIdx.x / row_tiles;
+    const int64_t pair = kSums ? blockIdx.x / a.G : blockIdx.x / row_tiles;
     const int rt0 = kStats ? blockIdx.x % row_tiles : 0;        // first row tile of this workgroup
-    const int g = MODE == kSeedSums ? blockIdx.x % a.G : 0;
+    const int g = kSums ? blockIdx.x % a.G : 0;
     const int cap = a.cap;
     const int R = a.R;
     int s = a.cache_len[pair / a.h];
     s = s > cap ? cap : s;
     // the columns this workgroup owns; it reads the key tiles among them
-    const int col0 = MODE == kSeedSums ? g * a.cols : 0;
-    const int col1 = (MODE != kSeedSums || g == a.G - 1) ? cap : col0 + a.cols;
-    float* Sp = a.score ? a.score + pair * (int64_t)cap : nullptr;
+    const int col0 = kSums ? g * a.cols : 0;
+    const int col1 = (!kSums || g == a.G - 1) ? cap : col0 + a.cols;
+    float* Sp = WR ? nullptr : a.score + pair * (int64_t)cap;      // (either the sums or the rows)
     float* Rp = WR ? a.rows + pair * (int64_t)R * cap : nullptr;
 
     if (s <= 0) {
         if (kStats) return;
-        if (Sp)
+        if (!WR)
             for (int j = col0 + tid; j < col1; j += NT) Sp[j] = 0.f;
         if (Rp)
             for (int r = 0; r < R; ++r)
@@ -379,8 +385,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         for (int x = 0; x < TILE / 1024; ++x) {
             const int j = x * RPI + lane / CPR;
             const uint32_t off = (uint32_t)(j < r_last ? j : r_last) * ROWB + (uint32_t)(((lane % CPR) ^ swz(j)) * 16);
-            if (MODE == kSeedSums && a.stream) load_to_lds<true>(base, off, at + x * 1024);
-            else load_to_lds<false>(base, off, at + x * 1024);
+            load_to_lds<MODE == kSeedSumsFar>(base, off, at + x * 1024);
         }
     };
     auto receive = [&](Vec16(&kv)[NV]) __attribute__((always_inline)) {
@@ -406,16 +411,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         for (int v = 0; v < NV; ++v) kv[v] = load16(Kp + at + v * 32);
     };
 
-    auto logits = [](const Vec16(&rows)[NV], const Vec16(&cols)[NV]) __attribute__((always_inline)) {
-        float16_t c;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) c[i] = 0.f;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) c = Mfma<T>::run(rows[v], cols[v], c);
-        return c;
-    };
-
-    if constexpr (MODE != kSeedSums) {
+    if constexpr (!kSums) {
     // ------------------------------ pass 1: row statistics ------------------------------
     float M[RT], L[RT];
 #pragma unroll
@@ -450,7 +446,15 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             }
         }
     } else if constexpr (kByLds) {
-        const int seen = (t_off + 1) / 32;               // tiles below it: every row sees all keys
+        auto logits = [](const Vec16(&rows)[NV], const Vec16(&cols)[NV]) __attribute__((always_inline)) {
+            float16_t c;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) c = Mfma<T>::run(rows[v], cols[v], c);
+            return c;
+        };
+        const int seen = RT * 32 <= R ? (t_off + 1) / 32 : 0;     // tiles below it: every row sees all keys
         if (tile0 + wave_u < tile1) request(tile0 + wave_u);
         for (int tile = tile0 + wave_u; tile < tile1; tile += NW) {
             Vec16 kv[NV];
@@ -463,7 +467,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
                     add_tile_stats_flat<all_seen.value>(logits(kv, qv[rt]), tile, hb, (r < R) ? t_off + r : -1, a.scale_log2e, M[rt], L[rt]);
                 }
             };
-            if (RT * 32 <= R && tile < seen) stats(std::true_type());
+            if (tile < seen) stats(std::true_type());
             else stats(std::false_type());
         }
     } else {
@@ -508,7 +512,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     if constexpr (kStats) return;
     __syncthreads();
     }
-    if constexpr (MODE == kSeedSums) {
+    if constexpr (kSums) {
         if (tid < RP) {
             const bool row = tid < R && t_off + tid >= 0;
             float Mt = row ? St[tid] : -INFINITY, Lt = row ? St[R + tid] : 0.f;
@@ -563,20 +567,22 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         take(key, colsum);
     };
     auto put = [&](int key, float colsum) {
-        if (Sp && hb == 0 && key < s) Sp[key] = colsum;
+        if (!WR && hb == 0 && key < s) Sp[key] = colsum;
     };
     if constexpr (kByLds) {
-        const int seen = (t_off + 1) / 32;
+        const int seen = RT * 32 <= R ? (t_off + 1) / 32 : 0;
         const int last = tile1 - 1 - wave_u;             // the keys read last by pass 1 are read first here
         float before = 0.f;                              // a tile's sums are stored ahead of the next request, which the wait is for
+        int first = last;                                // (unknown to the compiler, which peels the first round off and doubles the code)
+        asm("" : "+s"(first));
         if (last >= tile0) request(last);
         for (int tile = last; tile >= tile0; tile -= NW) {
             Vec16 kv[NV];
             receive(kv);
-            if (tile != last) put((tile + NW) * 32 + l32, before);
+            if (tile != first) put((tile + NW) * 32 + l32, before);
             if (tile - NW >= tile0) request(tile - NW);
             auto keep = [&](int, float colsum) { before = colsum; };
-            if (RT * 32 <= R && tile < seen) colsum_tile(std::true_type(), tile, kv, keep);
+            if (tile < seen) colsum_tile(std::true_type(), tile, kv, keep);
             else colsum_tile(std::false_type(), tile, kv, keep);
         }
         if (last >= tile0) put((tile0 + (last - tile0) % NW) * 32 + l32, before);
@@ -593,7 +599,7 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
         }
     }
     const int z0 = s > col0 ? s : col0;
-    if (Sp)
+    if (!WR)
         for (int j = z0 + tid; j < col1; j += NT) Sp[j] = 0.f;
     if (Rp)
         for (int r = 0; r < R; ++r)
@@ -652,10 +658,19 @@ static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hip
     // Keys that the launch before has read are still in the 256 MB Infinity Cache where there are few; loads that pass it by are
     // faster where there are many: plain / streaming, us, attention and sums, R = 64, 1792 x 4096 bf16 7608 / 7555, 2048 x 1001 f16 899 / 881, 2048 x 513
     // 357 / 343, 2048 x 300 185 / 184; 128 x 1001 58.1 / 59.2, 128 x 300 19.3 / 20.1; seed in two launches, 32 x 8192 47.7 / 54.0.
-    a.stream = pairs * a.bound * (D * Elem<T>::kBytes) > (128ll << 20);
+    const bool far = pairs * a.bound * (D * Elem<T>::kBytes) > (128ll << 20);
     const dim3 one((unsigned)pairs), all((unsigned)(pairs * G));
-    if (stats_ready) {
+    auto sums = [&]() {
+        if constexpr (kSeedByLds<T, RT, WR, kSeedSums>) {
+            if (far) {
+                launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedSumsFar>), all, dim3(256), 0, stream, a);
+                return;
+            }
+        }
         launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
+    };
+    if (stats_ready) {
+        sums();
     } else if (G > 1 && seed_in_two(pairs, a.bound, a.stated, a.R)) {
         if constexpr (D * Elem<T>::kBytes >= 512) {
             launch_kernel((swa_prefill_kernel<T, D, 1, WR, kSeedStats>), dim3((unsigned)(pairs * RT)), dim3(256), 0, stream, a);
@@ -666,7 +681,7 @@ static int launch_prefill_rt(PrefillArgs a, int64_t pairs, bool stats_ready, hip
             launch_kernel((swa_seed_stats_kernel<T, D, WR, kChains>), dim3((unsigned)(pairs * RT)), dim3(kChains * kWave), 0, stream, a);
         }
         if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
-        launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedSums>), all, dim3(256), 0, stream, a);
+        sums();
     } else {
         launch_kernel((swa_prefill_kernel<T, D, RT, WR, kSeedWhole>), one, dim3(256), 0, stream, a);
     }
