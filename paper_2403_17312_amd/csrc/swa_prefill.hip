@@ -294,6 +294,87 @@ swa_seed_stats_kernel(PrefillArgs a)
 template <typename T, int RT, bool WR, int MODE>
 constexpr bool kSeedByLds = Elem<T>::kBytes == 2 && !(WR && RT > 1) && MODE != kSeedStats;
 
+// Sum of a tile's column over the R rows, for the lane's key: logits again, weights from the rows' statistics.  For tiles loaded in the
+// operands' layout; the kernel has it a second time, with a form that skips the mask, for tiles by way of LDS, in 16 bits (one body for both:
+// fp32's sums of 97 to 128 rows spill 134 registers instead of 97, 512 pairs x 2048 keys 897 / 914 us; this function for both: 16 bits 1 to 3 %
+// slower where prompts are short).
+template <typename T, int RT, bool WR, int NV>
+__device__ __forceinline__ float tile_colsum(const Vec16(&qv)[RT][NV], const Vec16(&kv)[NV], const float* s_M, const float* s_invL, int hb,
+                                             int key, int R, int t_off, float scale_log2e, float* Rp, int cap, int s)
+{
+#pragma clang fp contract(off)
+    float colsum = 0.f;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        float16_t c;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c[i] = 0.f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) c = Mfma<T>::run(qv[rt][v], kv[v], c);   // C[query][key]
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            // the lane's rows 8g + 4hb .. +3 of this query tile: one 16-byte LDS read each
+            const int r0 = rt * 32 + 8 * g + 4 * hb;
+            const float4_t Mr = *reinterpret_cast<const float4_t*>(&s_M[r0]);
+            const float4_t Ir = *reinterpret_cast<const float4_t*>(&s_invL[r0]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = r0 + j;
+                const bool vis = (r < R) && (key <= t_off + r);
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(c[4 * g + j], scale_log2e, -Mr[j])) * Ir[j];
+                colsum += vis ? p : 0.f;
+                if constexpr (WR) {
+                    if (r < R && key < s) Rp[(int64_t)r * cap + key] = vis ? p : 0.f;
+                }
+            }
+        }
+    }
+    return colsum + __shfl_xor(colsum, 32, kWave);
+}
+
+// Tiles by way of LDS: chunk c of row r lies at c ^ swizzle(r), chosen by the lane's global address, so that the lanes of an
+// operand's read spread over the banks.
+template <int ROWB, int NW, bool FAR>
+struct KeyTiles {
+    static constexpr int TILE = 32 * ROWB;
+    static constexpr int CPR = ROWB / 16;                // 16-byte chunks per row
+    static constexpr int RPI = kWave / CPR;              // rows per load instruction
+    static constexpr int NV = CPR / 2;
+    const char* Kp;
+    const char* mine;                                    // this wave's room
+    int s, lane;
+
+    __device__ __forceinline__ KeyTiles(const char* keys, int len, int wave, int lane_) : Kp(keys), s(len), lane(lane_)
+    {
+        __shared__ __align__(1024) char room[NW][TILE];
+        mine = room[wave];
+    }
+    static __device__ __forceinline__ int swz(int r) { return ROWB == 256 ? (r & 15) : ((r >> 1) & 7); }
+    __device__ __forceinline__ void request(int tile) const
+    {
+        const uint32_t at = lds_address(mine);
+        const int r_last = s - 1 - tile * 32;            // (rows past the prompt re-read its last one and are masked)
+        const char* base = Kp + (uint32_t)tile * TILE;
+#pragma unroll
+        for (int x = 0; x < TILE / 1024; ++x) {
+            const int j = x * RPI + lane / CPR;
+            const uint32_t off = (uint32_t)(j < r_last ? j : r_last) * ROWB + (uint32_t)(((lane % CPR) ^ swz(j)) * 16);
+            load_to_lds<FAR>(base, off, at + x * 1024);
+        }
+    }
+    __device__ __forceinline__ void receive(Vec16(&kv)[NV]) const
+    {
+        __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0): the tile is there
+        asm volatile("" ::: "memory");
+        const int l32 = lane & 31, hb = lane >> 5;
+        const char* at = mine + l32 * ROWB;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) kv[v] = load16(at + (((2 * v + hb) ^ swz(l32)) << 4));
+        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): it may be overwritten
+        asm volatile("" ::: "memory");
+    }
+};
+
 // WR: also write the R rows themselves (the ring of the strict local attention sum).
 template <typename T, int D, int RT, bool WR, int MODE>
 __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
@@ -368,36 +449,6 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     const int tile1 = (s < col1 ? s : col1) > col0 ? ((s < col1 ? s : col1) + 31) / 32 : tile0;   // (col0 is a multiple of 32)
     const int t_off = s - R;   // query r sits at position t_off + r and sees keys 0..t_off+r
 
-    // Tiles by way of LDS: chunk c of row r lies at c ^ swizzle(r), chosen by the lane's global address, so that the lanes of an
-    // operand's read spread over the banks.
-    constexpr int TILE = 32 * ROWB;
-    constexpr int CPR = ROWB / 16;                       // 16-byte chunks per row
-    constexpr int RPI = kWave / CPR;                     // rows per load instruction
-    __shared__ __align__(1024) char s_tile[kByLds ? NW : 1][kByLds ? TILE : 16];
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    auto swz = [](int r) { return ROWB == 256 ? (r & 15) : ((r >> 1) & 7); };
-    const char* const my_tile = s_tile[kByLds ? wave_u : 0];
-    auto request = [&](int tile) __attribute__((always_inline)) {
-        const uint32_t at = lds_address(my_tile);
-        const int r_last = s - 1 - tile * 32;            // (rows past the prompt re-read its last one and are masked)
-        const char* base = Kp + (uint32_t)tile * TILE;
-#pragma unroll
-        for (int x = 0; x < TILE / 1024; ++x) {
-            const int j = x * RPI + lane / CPR;
-            const uint32_t off = (uint32_t)(j < r_last ? j : r_last) * ROWB + (uint32_t)(((lane % CPR) ^ swz(j)) * 16);
-            load_to_lds<MODE == kSeedSumsFar>(base, off, at + x * 1024);
-        }
-    };
-    auto receive = [&](Vec16(&kv)[NV]) __attribute__((always_inline)) {
-        __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0): the tile is there
-        asm volatile("" ::: "memory");
-        const char* at = my_tile + l32 * ROWB;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) kv[v] = load16(at + (((2 * v + hb) ^ swz(l32)) << 4));
-        __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): it may be overwritten
-        asm volatile("" ::: "memory");
-    };
-
     // Unconditional tile load (rows past the end re-read the last row and are masked later), so
     // that the loads of the next tile can stay in flight while the current one is reduced.
     // Plain loads, not streaming ones: a lane takes 32 bytes of a line per instruction, so the line
@@ -446,6 +497,8 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             }
         }
     } else if constexpr (kByLds) {
+        const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+        const KeyTiles<ROWB, NW, MODE == kSeedSumsFar> tiles(Kp, s, wave_u, lane);
         auto logits = [](const Vec16(&rows)[NV], const Vec16(&cols)[NV]) __attribute__((always_inline)) {
             float16_t c;
 #pragma unroll
@@ -455,11 +508,11 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
             return c;
         };
         const int seen = RT * 32 <= R ? (t_off + 1) / 32 : 0;     // tiles below it: every row sees all keys
-        if (tile0 + wave_u < tile1) request(tile0 + wave_u);
+        if (tile0 + wave_u < tile1) tiles.request(tile0 + wave_u);
         for (int tile = tile0 + wave_u; tile < tile1; tile += NW) {
             Vec16 kv[NV];
-            receive(kv);
-            if (tile + NW < tile1) request(tile + NW);
+            tiles.receive(kv);
+            if (tile + NW < tile1) tiles.request(tile + NW);
             auto stats = [&](auto all_seen) __attribute__((always_inline)) {
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
@@ -534,68 +587,75 @@ __global__ void __launch_bounds__(256) swa_prefill_kernel(PrefillArgs a)
     }
 
     // ------------------------------ pass 2: column sums ---------------------------------
-    auto colsum_tile = [&](auto all_seen, int tile, const Vec16(&kv)[NV], auto take) {
+    if constexpr (kByLds) {
+        const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+        const KeyTiles<ROWB, NW, MODE == kSeedSumsFar> tiles(Kp, s, wave_u, lane);
+        auto colsum_tile = [&](auto all_seen, int tile, const Vec16(&kv)[NV], auto take) {
 #pragma clang fp contract(off)
-        const int key = tile * 32 + l32;
-        float colsum = 0.f;
+            const int key = tile * 32 + l32;
+            float colsum = 0.f;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            float16_t c;
+            for (int rt = 0; rt < RT; ++rt) {
+                float16_t c;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) c[i] = 0.f;
+                for (int i = 0; i < 16; ++i) c[i] = 0.f;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) c = Mfma<T>::run(qv[rt][v], kv[v], c);   // C[query][key]
+                for (int v = 0; v < NV; ++v) c = Mfma<T>::run(qv[rt][v], kv[v], c);   // C[query][key]
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                // the lane's rows 8g + 4hb .. +3 of this query tile: one 16-byte LDS read each
-                const int r0 = rt * 32 + 8 * g + 4 * hb;
-                const float4_t Mr = *reinterpret_cast<const float4_t*>(&s_M[r0]);
-                const float4_t Ir = *reinterpret_cast<const float4_t*>(&s_invL[r0]);
+                for (int g = 0; g < 4; ++g) {
+                    // the lane's rows 8g + 4hb .. +3 of this query tile: one 16-byte LDS read each
+                    const int r0 = rt * 32 + 8 * g + 4 * hb;
+                    const float4_t Mr = *reinterpret_cast<const float4_t*>(&s_M[r0]);
+                    const float4_t Ir = *reinterpret_cast<const float4_t*>(&s_invL[r0]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = r0 + j;
-                    const bool vis = all_seen.value || ((r < R) && (key <= t_off + r));
-                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(c[4 * g + j], a.scale_log2e, -Mr[j])) * Ir[j];
-                    colsum += vis ? p : 0.f;
-                    if constexpr (WR) {
-                        if (r < R && key < s) Rp[(int64_t)r * cap + key] = vis ? p : 0.f;
+                    for (int j = 0; j < 4; ++j) {
+                        const int r = r0 + j;
+                        const bool vis = all_seen.value || ((r < R) && (key <= t_off + r));
+                        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(c[4 * g + j], a.scale_log2e, -Mr[j])) * Ir[j];
+                        colsum += vis ? p : 0.f;
+                        if constexpr (WR) {
+                            if (r < R && key < s) Rp[(int64_t)r * cap + key] = vis ? p : 0.f;
+                        }
                     }
                 }
             }
-        }
-        colsum += __shfl_xor(colsum, 32, kWave);
-        take(key, colsum);
-    };
-    auto put = [&](int key, float colsum) {
-        if (!WR && hb == 0 && key < s) Sp[key] = colsum;
-    };
-    if constexpr (kByLds) {
+            colsum += __shfl_xor(colsum, 32, kWave);
+            take(key, colsum);
+        };
+        auto put = [&](int key, float colsum) {
+            if (!WR && hb == 0 && key < s) Sp[key] = colsum;
+        };
         const int seen = RT * 32 <= R ? (t_off + 1) / 32 : 0;
         const int last = tile1 - 1 - wave_u;             // the keys read last by pass 1 are read first here
         float before = 0.f;                              // a tile's sums are stored ahead of the next request, which the wait is for
         int first = last;                                // (unknown to the compiler, which peels the first round off and doubles the code)
         asm("" : "+s"(first));
-        if (last >= tile0) request(last);
+        if (last >= tile0) tiles.request(last);
         for (int tile = last; tile >= tile0; tile -= NW) {
             Vec16 kv[NV];
-            receive(kv);
+            tiles.receive(kv);
             if (tile != first) put((tile + NW) * 32 + l32, before);
-            if (tile - NW >= tile0) request(tile - NW);
+            if (tile - NW >= tile0) tiles.request(tile - NW);
             auto keep = [&](int, float colsum) { before = colsum; };
             if (tile < seen) colsum_tile(std::true_type(), tile, kv, keep);
             else colsum_tile(std::false_type(), tile, kv, keep);
         }
         if (last >= tile0) put((tile0 + (last - tile0) % NW) * 32 + l32, before);
     } else {
+        auto colsum_tile = [&](int tile, const Vec16(&kv)[NV]) {
+            const int key = tile * 32 + l32;
+            const float colsum = tile_colsum<T, RT, WR, NV>(qv, kv, s_M, s_invL, hb, key, R, t_off, a.scale_log2e, Rp, cap, s);
+            if (!WR && hb == 0 && key < s) Sp[key] = colsum;
+        };
         Vec16 kA[NV], kB[NV];
         // the keys read last by pass 1 are read first here
         const int last = tile1 - 1 - wave;
         load_tile(last, kA);
         for (int tile = last; tile >= tile0; tile -= 2 * NW) {
             load_tile(tile - NW, kB);
-            colsum_tile(std::false_type(), tile, kA, put);
+            colsum_tile(tile, kA);
             load_tile(tile - 2 * NW, kA);
-            if (tile - NW >= tile0) colsum_tile(std::false_type(), tile - NW, kB, put);
+            if (tile - NW >= tile0) colsum_tile(tile - NW, kB);
         }
     }
     const int z0 = s > col0 ? s : col0;

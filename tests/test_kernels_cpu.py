@@ -75,3 +75,10 @@ def test_column_sums_hold_a_tiles_work_twice_and_no_more(kernels, dtype, d):
     for tiles in (1, 2, 3, 4):
         assert kernels[seed_sums(dtype, d, tiles, False)][0] <= 1.2 * kernels[seed_sums("F32", d, tiles, False)][0], tiles
     assert kernels[seed_sums(dtype, d, 1, True)][0] <= 1.2 * kernels[seed_sums("F32", d, 1, True)][0]
+
+
+def test_fp32_column_sums_of_many_rows_spill_no_more(kernels):
+    """97 to 128 rows at d = 128: 97 registers (376 bytes) do not fit; code that only 16 bits use made it 134 (412 bytes)."""
+    assert kernels[seed_sums("F32", 128, 4, False)][1] <= 376
+    for tiles in (1, 2, 3):
+        assert kernels[seed_sums("F32", 128, tiles, False)][1] == 0, tiles
