@@ -179,10 +179,11 @@ def decode_kernel_of(B, params, ring, rule=[]):
     the sizes and the stated bound (short_form, split_factor)."""
     if not rule:
         L = B.lib()
-        rule += [getattr(L, "_ZN3swa10short_formERK10swa_paramslib"), getattr(L, "_ZN3swa12split_factorElii")]
+        rule += [getattr(L, "_ZN3swa10short_formERK10swa_paramslib"), getattr(L, "_ZN3swa12split_factorElibi")]
         rule[0].restype = ctypes.c_uint64            # {int threads, rows per lane}; no threads: not served
     pairs, bound = params.b * params.h, min(params.len_bound or params.cap, params.cap)
-    if params.flags & B.SWA_SPLIT_ROWS and rule[1](ctypes.c_int64(pairs), bound, params.d * (4 if params.dtype == B.SWA_F32 else 2)) > 1:
+    row = params.d * (4 if params.dtype == B.SWA_F32 else 2)
+    if params.flags & B.SWA_SPLIT_ROWS and rule[1](ctypes.c_int64(pairs), bound, ctypes.c_bool(params.len_bound > 0), row) > 1:
         return "swa_split_logits_kernel"
     form = rule[0](ctypes.byref(params), ctypes.c_int64(pairs), bound, ctypes.c_bool(ring))
     return "swa_short_kernel" if form & 0xffffffff else "swa_decode_kernel"

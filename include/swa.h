@@ -158,8 +158,9 @@ int swa_prepare(void);
  * of the channels per workgroup) and needs the larger workspace that
  * swa_workspace_bytes reports for this flag.  Attention weights, importance and the kept set are
  * bit-identical to the one-workgroup form; the output's partial sums are added in another order.
- * With many pairs or short caches (more than 128 pairs, or a length bound below 2048 rows, for
- * rows of 256 bytes and more 1024 up to 32 pairs and 1536 up to 64: there the extra launches cost more than the slices gain) the call runs the one-workgroup kernel.
+ * With many pairs or short caches the call runs the one-workgroup kernel, because the extra launches cost more
+ * than the slices gain: more than 128 pairs, or fewer than 2048 rows by len_bound (by cap where none is
+ * stated); under a stated bound, with rows of 256 bytes and more, 1024 rows up to 32 pairs and 1536 up to 64.
  */
 #define SWA_SPLIT_ROWS 16
 

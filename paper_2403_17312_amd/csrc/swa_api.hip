@@ -49,16 +49,20 @@ size_t shared_workspace_offset(const swa_params& p)
     return (head + 255) & ~(size_t)255;
 }
 
-int split_factor(int64_t pairs, int len_bound, int row_bytes)
+int split_factor(int64_t pairs, int len_bound, bool stated, int row_bytes)
 {
     // Three launches instead of one pay only when one workgroup per pair leaves most CUs idle for long.  The line
     // was drawn with an earlier form of four launches; with three (f16, d = 128, one workgroup / split in us, a fifth or all of
     // the rows kept): 96 pairs x 2048 rows 37 / 30, 29 / 30; 128 pairs x 2048 39 / 33, 30 / 35; x 4096 64 / 48, 54 / 57;
     // x 8192 115 / 76, 103 / 102.
-    // Below 2048 rows the launches pay for fewer pairs, and not for rows of 128 bytes, whose output launch gains least where all rows
-    // are kept: 8 pairs x 1030 20.6 / 15.4, 14.5 / 13.3; 32 x 1030 20.8 / 16.9, 15.2 / 15.1, x 2000 32.7 / 18.3, 23.9 / 18.5; 64 x 1030 23.0 / 17.5, 16.5 /
-    // 17.5, x 1600 30.9 / 19.3, 22.4 / 20.7; 96 x 1600 31.8 / 22.5, 24.2 / 25.4; bf16, d = 64, 64 x 1600 21.3 / 17.1, 15.0 / 17.0.
-    const int least = row_bytes < 256 ? 2048 : (pairs <= 32 ? 1024 : (pairs <= 64 ? 1536 : 2048));
+    // Below 2048 rows the launches pay for fewer pairs, on a cache that is not compacted between steps, which the flag is for (a fifth kept; in
+    // parentheses all kept, and one token evicted as from a compacted cache): f16, d = 128, 8 pairs x 1030 22.1 / 16.3 (14.5 / 14.1, 15.6 / 16.2);
+    // 32 x 1030 22.4 / 17.6 (15.0 / 16.5, 16.5 / 19.0), x 1600 27.8 / 18.8 (19.0 / 19.7, 20.3 / 21.9), x 2000 31.0 / 19.5 (21.6 / 21.0,
+    // 23.1 / 23.1); 64 x 1540 30.5 / 22.2 (22.4 / 23.5, 24.0 / 25.4); fp32, d = 64, 32 x 1030 20.7 / 17.1 (14.0 / 15.8, 15.5 / 18.3),
+    // d = 128 28.3 / 19.1 (20.1 / 18.9, 21.5 / 21.0).  Not rows of 128 bytes: bf16, d = 64, 64 x 1600 21.3 / 17.1 (15.0 / 17.0).
+    // And only under a stated bound: a capacity says little about lengths, and short caches lose (8 pairs x 100 rows in 1100 slots 12.3 /
+    // 14.6, one token evicted 8.7 / 14.0; 64 x 300 in 2000 16.5 / 17.8, 12.5 / 18.9).
+    const int least = (row_bytes < 256 || !stated) ? 2048 : (pairs <= 32 ? 1024 : (pairs <= 64 ? 1536 : 2048));
     if (pairs > 128 || len_bound < least) return 1;
     // enough workgroups to put about four on every CU, every slice at least 128 rows long
     int64_t g = (1024 + pairs - 1) / pairs;

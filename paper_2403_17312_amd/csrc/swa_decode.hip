@@ -1324,7 +1324,7 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     };
     if (p.flags & SWA_SPLIT_ROWS) {
         // rows of a pair over G workgroups
-        const int G = split_factor(pairs, bound, rowb);
+        const int G = split_factor(pairs, bound, stated, rowb);
         if (G > 1)
             return launch_split(p, scale, G, q, k_new, v_new, k_cache, v_cache, score, pos, cache_len, seq_len, kept_idx,
                                 kept_cnt, out, probs_dbg, workspace, stream);

@@ -77,10 +77,10 @@ bool seed_in_two(int64_t pairs, int bound, bool stated, int R);
 // Whether its row statistics then come from four workgroups per 32 rows, whose sums the column sums merge, or from one.
 bool seed_chains_apart(int G, int cols, int cap, int R);
 
-// SWA_SPLIT_ROWS: workgroups per pair for this many pairs, this bound on the cached length and rows of so many bytes
+// SWA_SPLIT_ROWS: workgroups per pair for this many pairs, this bound on the cached length (stated by the caller, or the capacity) and rows of so many bytes
 // (1 = the one-workgroup kernel serves the call), and the launches of the step.
 constexpr int kMaxSplit = 16;
-int split_factor(int64_t pairs, int len_bound, int row_bytes);
+int split_factor(int64_t pairs, int len_bound, bool stated, int row_bytes);
 int launch_split(const swa_params& p, float scale, int G, const void* q, const void* k_new, const void* v_new, void* k_cache,
                  void* v_cache, float* score, int32_t* pos, int32_t* cache_len, const int32_t* seq_len, int32_t* kept_idx,
                  int32_t* kept_cnt, void* out, float* probs_dbg, void* workspace, hipStream_t stream);

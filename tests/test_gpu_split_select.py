@@ -131,8 +131,13 @@ def test_importance_of_any_value(special, w, sparsity):
                                              (torch.float32, 128, 4, 5, 2047)])
 @pytest.mark.parametrize("w,sparsity", [(0, 9999), (7, 0), (64, 8000), (900, 9000)])
 def test_caches_below_2048_slots(dtype, d, b, h, cap, w, sparsity):
-    """Few pairs with wide rows are split from 1024 or 1536 slots on: weights, importance and kept set of the one-workgroup kernel."""
+    """Few pairs with wide rows are split from 1024 or 1536 slots on, under a stated bound: weights, importance and kept set of the one-workgroup
+    kernel."""
+    import ctypes
+
     from paper_2403_17312_amd import binding as B
+    rule = B.lib()._ZN3swa12split_factorElibi
+    assert rule(ctypes.c_int64(b * h), cap, ctypes.c_bool(True), d * (4 if dtype == torch.float32 else 2)) > 1
     lens = [cap - 1, cap - 2, 700, 0]
     g = torch.Generator(device="cuda").manual_seed(41)
     K, V = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
@@ -140,7 +145,7 @@ def test_caches_below_2048_slots(dtype, d, b, h, cap, w, sparsity):
     old = torch.floor(torch.rand((b, h, cap), generator=g, device="cuda") * 300) / 300                # (some of them equal)
     got = []
     for flags in (0, B.SWA_SPLIT_ROWS):
-        st = B.DecodeState(B.make_params(b, h, d, cap, w, sparsity, dtype, flags=flags), debug_probs=True)
+        st = B.DecodeState(B.make_params(b, h, d, cap, w, sparsity, dtype, len_bound=cap, flags=flags), debug_probs=True)
         st.K.copy_(K)
         st.V.copy_(V)
         st.score.copy_(old)

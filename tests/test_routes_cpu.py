@@ -58,3 +58,14 @@ def test_chains_of_the_statistics_get_workgroups_where_a_slice_can_bring_them_al
     assert rule(G, cols, cap, R) is apart
     for g in range(G.value if apart else 0):          # 8 R floats at the start of every slice, inside it and inside the row
         assert g * cols.value + 8 * R <= (cap if g == G.value - 1 else (g + 1) * cols.value)
+
+
+@pytest.mark.parametrize("pairs,least", [(1, 1024), (32, 1024), (33, 1536), (64, 1536), (65, 2048), (128, 2048)])
+def test_split_rows_where_three_launches_pay(L, pairs, least):
+    rule = L._ZN3swa12split_factorElibi
+    for row in (128, 256, 512):
+        for stated in (False, True):
+            line = least if stated and row >= 256 else 2048
+            assert rule(ctypes.c_int64(pairs), line - 1, ctypes.c_bool(stated), row) == 1, (row, stated)
+            assert rule(ctypes.c_int64(pairs), line, ctypes.c_bool(stated), row) > 1, (row, stated)
+    assert rule(ctypes.c_int64(129), 16384, ctypes.c_bool(True), 512) == 1
