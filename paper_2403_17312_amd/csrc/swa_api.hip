@@ -86,8 +86,44 @@ int decode_stash_rows(const swa_params& p)
     return rows;
 }
 
-int decode_block_threads(int64_t pairs, int len_bound, bool stated, bool kv_int8)
+// Slots from which a pair gets 1024 threads, by form (0: never).  Twice the loads under way, and the phases behind them shared out
+// further, which pays where a CU has one workgroup of 512 threads anyway: LDS has room for one, or pairs are few.
+// 512 / 1024 threads, us, the step after a prompt (four fifths evicted) and a steady one (one token evicted):
+//   unordered (16 bytes a slot, 20 with the selection keys, which rows of 512 bytes always keep): f16, d = 128 4 pairs x 4500 67 / 47, 41.5 /
+//     35.5; 32 x 7100 129 / 94, 84 / 80; 256 x 5200 169 / 146, 138 / 137; 1024 x 7100 822 / 696, 668 / 632; bf16, d = 64 32 x 5200 58 / 47,
+//     35.1 / 32.7; 1024 x 5200 329 / 295, 268 / 262; fp32, d = 64 256 x 6000 ratio 0.92, 0.99; d = 128 32 x 4400 128 / 93, 99 / 101;
+//     1024 x 3600 712 / 648, 636 / 638.  Steady steps within 2 % where they do not gain.  Where two workgroups of 512 threads fit, 1024 lose
+//     (128 x 1024, f16 35.1 / 33.4, 23.8 / 26.4).
+//   head-shared (20 bytes): f16, d = 128 8 x 3620 68 / 50, 44.6 / 38.7; 768 x 3620 355 / 326, 283 / 286; 768 x 6500 612 / 516, 484 / 481; fp32,
+//     d = 128 128 x 4500 184 / 161, 145 / 145.  Rows of 128 bytes leave room for a second workgroup a little longer: 32 x 3620 51 / 41, 36.3 /
+//     31.7, but 768 x 3620 209 / 213, 164 / 172, x 4000 ratio 0.90, 0.99.
+//   token order (16 bytes, and parked rows): up to 256 pairs f16, d = 128 8 x 2100 39 / 32, 62 / 52; 128 x 3000 74 / 64, 145 / 129; 256 x 2100 78 /
+//     74, 132 / 118; bf16, d = 64 128 x 2100 37 / 35, 61 / 54; fp32, d = 128 256 x 2100 128 / 127, 245 / 224.  Below (bf16, d = 64 64 x 1500 22.5 / 23.6),
+//     and for more pairs that two workgroups fit for, 1024 lose (384 x 2100, w = 16 101 / 117, 191 / 195; bf16, d = 64 1536 x 4100 340 / 358);
+//     beyond 4480 slots 768 x 6500 607 / 520, 1082 / 960.  (Whether two fit goes with the parked rows, so with w: one line for all w.)
+//   two calls (8 bytes): up to 128 pairs f16, d = 128 8 x 9100 104 / 72, 81 / 69; 64 x 16000 0.76, 1.00; 128 x 9000 136 / 109, 137 / 133, x 16000
+//     224 / 186, 239 / 252; fp32, d = 128 64 x 12000 0.76, 1.00; 128 x 14000 284 / 244, 390 / 401; more pairs lose (512 x 9100, bf16, d = 64
+//     1.12 in the first step, 512 x 16000, fp32, d = 128 1.02, 1.07).
+// Not the strict window, whose kernel has no such form, and only under a stated bound: short caches of a large capacity lose (512 pairs x
+// 100 slots in 5000 18 / 24).
+static int least_of_1024_threads(const swa_params& p, int64_t pairs, bool ring)
 {
+    if (ring || p.len_bound <= 0 || (p.flags & SWA_KV_INT8)) return 0;
+    if (!(p.flags & SWA_FUSE_COMPACTION)) return pairs <= 128 ? 8961 : 0;
+    if (!(p.flags & SWA_UNORDERED)) return pairs <= 256 ? 2049 : 4481;
+    const int row_bytes = cache_row_bytes(p);
+    if (p.flags & SWA_HEAD_SHARED) return row_bytes < 256 && pairs > 256 ? 3841 : 3585;
+    return row_bytes >= 512 ? 3585 : 4481;
+}
+// (their LDS, next to at most 14 KiB of the kernel's own)
+static_assert(20 * SWA_MAX_UNORDERED_SLOTS + 14 * 1024 <= 160 * 1024 && 16 * SWA_MAX_FUSED_SLOTS + 14 * 1024 <= 160 * 1024 &&
+              8 * SWA_MAX_CAP + 14 * 1024 <= 160 * 1024, "one workgroup of 1024 threads fits a CU");
+
+int decode_block_threads(const swa_params& p, int64_t pairs, int len_bound, bool ring)
+{
+    const bool kv_int8 = (p.flags & SWA_KV_INT8) != 0, stated = p.len_bound > 0;
+    const int least = least_of_1024_threads(p, pairs, ring);
+    if (least && len_bound >= least) return 1024;
     // Measured on MI355X (all five workloads): caches of a thousand slots and more (the first
     // step after a prompt, low sparsity) want 512 threads per pair, shorter ones 256; from a few
     // hundred pairs on their number matters little.

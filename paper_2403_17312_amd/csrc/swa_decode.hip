@@ -1174,8 +1174,8 @@ static int launch_decode_nt(const DecodeArgs& a, int64_t pairs, size_t lds_bytes
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
-// Threads per workgroup that decode_block_threads() gives for a cache format: 128 or 256 on the 8-bit cache, else 256 or 512 (and 1024 where
-// LDS leaves a CU one workgroup).
+// Threads per workgroup that decode_block_threads() gives for a cache format: 128 or 256 on the 8-bit cache, else 256 or 512 (and 1024 for
+// long caches outside the strict window).
 template <typename T>
 constexpr int narrow_threads() { return Elem<T>::kBytes == 1 ? 128 : 256; }
 
@@ -1282,7 +1282,7 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     const int64_t pairs = (int64_t)p.b * p.h;
     const int rowb = cache_row_bytes(p);
     const bool stated = p.len_bound > 0;
-    int nt = decode_block_threads(pairs, bound, stated, (p.flags & SWA_KV_INT8) != 0);
+    const int nt = decode_block_threads(p, pairs, bound, ring != nullptr);
     a.sum_threads = (p.flags & SWA_KV_INT8) ? nt : (bound >= 1024 ? 512 : 256);
     // Without the keys' array only where one more workgroup fits a CU for it (its LDS, next to at most 10 KiB of the kernel's
     // own; 16 waves by registers): forming the keys again for every digit of the selection is not free.
@@ -1299,14 +1299,6 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
     a.key_slots = (may_drop && per_cu(16) > per_cu(20)) ? 0 : a.lds_slots;
     const size_t lds_bytes = (size_t)a.lds_slots * (a.fuse_compaction ? (a.unordered ? 16 : 12) : 4) +
                              (size_t)a.key_slots * 4 + (size_t)a.stash_rows * rowb * 2;
-    // Where LDS leaves a CU one workgroup of 512 threads, it gets 1024: twice the loads under way, and the phases behind them shared out
-    // further.  512 / 1024, us, four fifths and one token evicted, f16, d = 128: 32 pairs x 5000 slots 95 / 71, 62 / 60, x 7000 127 / 94,
-    // 87 / 83; 256 x 7000 216 / 184, 186 / 179; 1280 x 5000 671 / 570, 569 / 562; x 7000 940 / 808, 789 / 767.  Where
-    // two workgroups fit, 1024 threads lose with one token evicted (128 x 1024 35.1 / 33.4, 23.8 / 26.4).  Whether they would without the keys' array
-    // decides also where few pairs keep it, so that a pair's output (the order of its sum goes with the threads) is the same for any number of
-    // pairs.  Only under a stated bound: short caches of a large capacity lose (512 pairs x 100 slots in 5000 18 / 24).
-    const size_t droppable = (a.unordered && !shared && rowb < 512) ? (size_t)a.key_slots * 4 : 0;
-    if (nt == 512 && stated && !ring && 2 * (lds_bytes - droppable + 10 * 1024) > 160 * 1024 && lds_bytes + 14 * 1024 <= 160 * 1024) nt = 1024;
 
     auto launch = [&](const DecodeArgs& args) -> int {
         if (p.flags & SWA_KV_INT8) {

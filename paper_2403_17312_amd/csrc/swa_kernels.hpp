@@ -29,9 +29,9 @@ int raise_dynamic_lds(const void* kernel);
 // Raises that limit for every instantiation of the decode kernel on the current device.
 int prepare_decode();
 
-// Threads per workgroup of the decode kernel for this many (sequence, head) pairs, this bound on the cached length (stated by the
-// caller, or the capacity) and this cache format, unless LDS leaves a CU one workgroup alone (launch_decode).
-int decode_block_threads(int64_t pairs, int len_bound, bool stated, bool kv_int8);
+// Threads per workgroup of the decode kernel for these params (form, cache format, whether the bound is stated), this many (sequence, head)
+// pairs and this bound on the cached length (stated by the caller, or the capacity).
+int decode_block_threads(const swa_params& p, int64_t pairs, int len_bound, bool ring);
 
 // Byte offset, inside the caller's workspace, of the slabs the head-shared step passes from its
 // first launch to its second (present only when SWA_HEAD_SHARED is set).

@@ -1,18 +1,30 @@
 """Workgroups of the decode kernel that few pairs and long caches are given: weights, importance, kept set and cache are those of the workgroup
 that a call without a stated bound gets, bit for bit, and the output is right."""
+import ctypes
+
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
-FORMS = ("unordered", "ordered", "two_call", "shared", "window")
+def threads_of(B, p, ring=False):
+    rule = B.lib()._ZN3swa20decode_block_threadsERK10swa_paramslib
+    bound = min(p.len_bound or p.cap, p.cap)
+    return rule(ctypes.byref(p), ctypes.c_int64(p.b * p.h), bound, ctypes.c_bool(ring))
 
 
-@pytest.mark.parametrize("dtype,d", [(torch.float16, 128), (torch.bfloat16, 64), (torch.float32, 128), (torch.float32, 64)])
-@pytest.mark.parametrize("bound", [257, 300, 1023, 1024, 3700, 4200, 7168])
-@pytest.mark.parametrize("form", FORMS)
+F16, BF16, F32 = torch.float16, torch.bfloat16, torch.float32
+FEW = [(form, dtype, d, bound, 512) for form in ("unordered", "ordered", "two_call", "shared", "window")
+       for dtype, d, bound in ((F16, 128, 257), (F32, 128, 300), (BF16, 64, 1023), (F32, 64, 1023))]
+LONG = [("unordered", F16, 128, 4481, 1024), ("unordered", BF16, 64, 7168, 1024), ("unordered", F32, 64, 4700, 1024), ("unordered", F32, 128, 3585, 1024),
+        ("shared", F16, 128, 3585, 1024), ("shared", BF16, 64, 3841, 1024), ("shared", F32, 128, 7168, 1024),
+        ("ordered", F16, 128, 2049, 1024), ("ordered", BF16, 64, 4481, 1024), ("ordered", F32, 64, 9216, 1024), ("ordered", F32, 128, 9200, 1024),
+        ("two_call", F16, 128, 8961, 1024), ("two_call", BF16, 64, 9024, 1024), ("two_call", F32, 64, 16384, 1024), ("two_call", F32, 128, 16300, 1024)]
+
+
+@pytest.mark.parametrize("form,dtype,d,bound,threads", FEW + LONG)
 @pytest.mark.parametrize("ahead", [1, 5])                              # most of the cache is evicted, one token
-def test_stated_bound_changes_the_workgroup_and_not_the_step(dtype, d, bound, form, ahead):
+def test_stated_bound_changes_the_workgroup_and_not_the_step(form, dtype, d, bound, threads, ahead):
     from paper_2403_17312_amd import binding as B
     lens = [bound - 1, bound - 2, 200, 0] if bound < 4000 else [bound - 1, 70]
     b, h, cap, w, R = len(lens), 3, bound, 16, 8
@@ -28,6 +40,7 @@ def test_stated_bound_changes_the_workgroup_and_not_the_step(dtype, d, bound, fo
     got = []
     for stated in (0, bound):
         p = B.make_params(b, h, d, cap, w, 8000, dtype, len_bound=stated, flags=flags)
+        assert (threads_of(B, p, form == "window") == threads) == (stated > 0)
         ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
         B.swa_workspace_init(p, ws)
         x = {"K": K0.clone(), "V": V0.clone(), "score": s0.clone(), "ring": r0.clone(), "cl": len0.clone(), "kc": torch.zeros_like(len0),
@@ -44,7 +57,7 @@ def test_stated_bound_changes_the_workgroup_and_not_the_step(dtype, d, bound, fo
     one, two = got
     for a in ("cl", "kc", "probs", "score", "pos", "K", "V", "ring"):
         assert torch.equal(one[a], two[a]), a
-    # fp32 sums of at most 7168 terms (2^-20 of their magnitude), one rounding to the output type
+    # fp32 sums of at most 16384 terms (2^-20 of their magnitude), one rounding to the output type
     u = {torch.float32: 2.0 ** -20, torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}[dtype]
     for i, n in enumerate(lens):
         k = two["kc"][i].item()

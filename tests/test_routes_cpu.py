@@ -69,3 +69,34 @@ def test_split_rows_where_three_launches_pay(L, pairs, least):
             assert rule(ctypes.c_int64(pairs), line - 1, ctypes.c_bool(stated), row) == 1, (row, stated)
             assert rule(ctypes.c_int64(pairs), line, ctypes.c_bool(stated), row) > 1, (row, stated)
     assert rule(ctypes.c_int64(129), 16384, ctypes.c_bool(True), 512) == 1
+
+
+UNORDERED, ORDERED, SHARED, TWO_CALL = 1 | 2, 1, 1 | 2 | 4, 0
+
+
+def threads(L, pairs, bound, flags, dtype, d, stated=True, ring=False, cap=16384, w=64):
+    from paper_2403_17312_amd import binding as B
+    assert UNORDERED == B.SWA_FUSE_COMPACTION | B.SWA_UNORDERED and SHARED == UNORDERED | B.SWA_HEAD_SHARED
+    rule = L._ZN3swa20decode_block_threadsERK10swa_paramslib
+    p = B.make_params(pairs, 1, d, cap, w, 8000, dtype, len_bound=bound if stated else 0, flags=flags)
+    return rule(ctypes.byref(p), ctypes.c_int64(pairs), bound, ctypes.c_bool(ring))
+
+
+@pytest.mark.parametrize("flags,dtype,d,pairs,least", [
+    (UNORDERED, "f16", 128, 4, 4481), (UNORDERED, "bf16", 64, 4096, 4481), (UNORDERED, "f32", 64, 300, 4481), (UNORDERED, "f32", 128, 4096, 3585),
+    (SHARED, "f16", 128, 4096, 3585), (SHARED, "f32", 128, 12, 3585), (SHARED, "f32", 64, 12, 3585), (SHARED, "bf16", 64, 256, 3585), (SHARED, "bf16", 64, 512, 3841),
+    (ORDERED, "f16", 128, 256, 2049), (ORDERED, "bf16", 64, 4, 2049), (ORDERED, "f32", 128, 257, 4481), (ORDERED, "bf16", 64, 4096, 4481),
+    (TWO_CALL, "f16", 128, 128, 8961), (TWO_CALL, "f32", 128, 8, 8961), (TWO_CALL, "bf16", 64, 129, 0), (TWO_CALL, "f32", 64, 512, 0)])
+def test_1024_threads_from_one_line_on(L, flags, dtype, d, pairs, least):
+    """Up to the longest cache that a form takes, under a stated bound, whatever the window; no line without a bound or for the strict window."""
+    import torch
+    dt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    top = {UNORDERED: 7168, SHARED: 7168, ORDERED: 9216, TWO_CALL: 16384}[flags]
+    for bound in sorted({257, 600, 1023, 1024, 1025, 2000, 2048, 2049, 3000, 3585, 4480, 4481, top, max(1, least - 1), least or top}):
+        if bound > top:
+            continue
+        for w in (4, 64):
+            assert (threads(L, pairs, bound, flags, dt, d, w=w) == 1024) == (0 < least <= bound), (bound, w)
+        assert threads(L, pairs, bound, flags, dt, d, stated=False, cap=bound) <= 512
+        if flags == UNORDERED:
+            assert threads(L, pairs, bound, flags, dt, d, ring=True) <= 512
