@@ -127,11 +127,20 @@ int decode_block_threads(const swa_params& p, int64_t pairs, int len_bound, bool
     // Measured on MI355X (all five workloads): caches of a thousand slots and more (the first
     // step after a prompt, low sparsity) want 512 threads per pair, shorter ones 256; from a few
     // hundred pairs on their number matters little.
-    // Few pairs do not fill the chip, and a workgroup's own chain of phases is the step: 256 / 512 threads, us, four fifths and one
-    // token evicted, f16, d = 128: 4 pairs x 400 slots 19.5 / 16.0, 12.4 / 11.0, x 1000 31.2 / 22.5, 18.5 / 14.9; 84 x 260 17.7 / 16.9, 11.1 /
-    // 11.0, x 1000 38.4 / 30.3, 21.6 / 18.5; 128 x 260 18.2 / 17.3, 11.7 / 11.9, x 700 32.3 / 26.8, 18.3 / 17.6; 100 x 700, fp32 71 / 45, 30.4 / 26.2.
-    // With 256 pairs steps that evict one token lose (x 300 14.0 / 14.5).  Only under a stated bound: a capacity says little about lengths.
-    if (!kv_int8 && stated && pairs <= 128 && len_bound > 256) return 512;
+    // Few pairs do not fill the chip, and a workgroup's own chain of phases is the step: 256 / 512 threads, us, the step after a prompt (four fifths
+    // evicted) and a steady one (one token evicted), unordered: f16, d = 128 32 x 258 16.7 / 15.1, 10.5 / 10.4, x 1000 32.7 / 24.0, 19.4 /
+    // 15.8; 96 x 258 17.8 / 16.5, 11.2 / 11.1; 128 x 500 23.1 / 19.4, 14.4 / 13.7; fp32, d = 128 128 x 258 24.3 / 19.4, 15.2 / 13.9; in token order f16, d =
+    // 128 64 x 258 17.2 / 16.1, 21.3 / 16.4; strict window 128 x 258 22.3 / 20.0, 15.2 / 14.4.  Steady steps lose up to 384 slots where a row is
+    // 128 bytes, whose loads are over soonest (bf16, d = 64 64 x 300 9.5 / 9.7, 128 x 300 9.9 / 10.3, two calls 10.9 / 11.4, x 385 ratios 0.96 to 1.00),
+    // and with more than 96 pairs of 256-byte rows (f16, d = 128 128 x 300 11.6 / 11.8, two calls 12.4 / 12.8, x 385 0.99, x 450 0.96), outside
+    // token order and the strict window.  With 256 pairs steady steps lose altogether (x 300 14.0 / 14.5).  Only under a stated bound: a capacity
+    // says little about lengths.
+    if (!kv_int8 && stated && pairs <= 128) {
+        const int row_bytes = cache_row_bytes(p);
+        const bool ordered = (p.flags & SWA_FUSE_COMPACTION) && !(p.flags & SWA_UNORDERED);
+        const bool later = !ordered && !ring && (row_bytes < 256 || (row_bytes < 512 && pairs > 96));
+        if (len_bound > (later ? 384 : 256)) return 512;
+    }
     if (!kv_int8) return len_bound >= 1024 ? 512 : 256;
     // 8-bit rows are half as long, so a workgroup has half the lanes' worth of work per row and
     // the fixed phases weigh more: smaller workgroups, more of them in flight.

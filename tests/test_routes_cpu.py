@@ -100,3 +100,26 @@ def test_1024_threads_from_one_line_on(L, flags, dtype, d, pairs, least):
         assert threads(L, pairs, bound, flags, dt, d, stated=False, cap=bound) <= 512
         if flags == UNORDERED:
             assert threads(L, pairs, bound, flags, dt, d, ring=True) <= 512
+
+
+@pytest.mark.parametrize("flags,ring,dtype,d,pairs,least", [
+    (UNORDERED, False, "f16", 128, 96, 257), (UNORDERED, False, "f16", 128, 97, 385), (UNORDERED, False, "f32", 64, 128, 385),
+    (UNORDERED, False, "f32", 128, 128, 257), (UNORDERED, False, "bf16", 64, 4, 385), (SHARED, False, "bf16", 64, 84, 385), (SHARED, False, "f16", 128, 8, 257),
+    (TWO_CALL, False, "bf16", 64, 128, 385), (TWO_CALL, False, "f16", 128, 128, 385), (ORDERED, False, "bf16", 64, 128, 257),
+    (ORDERED, False, "f16", 128, 128, 257), (UNORDERED, True, "bf16", 64, 128, 257), (UNORDERED, True, "f32", 64, 97, 257),
+    (UNORDERED, False, "f32", 128, 129, 1024), (ORDERED, False, "f16", 128, 129, 1024), (UNORDERED, True, "f16", 128, 129, 1024)])
+def test_512_threads_where_few_pairs_gain(L, flags, ring, dtype, d, pairs, least):
+    import torch
+    dt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    for bound in (64, 256, 257, 300, 384, 385, 1023, 1024, 1500):
+        assert threads(L, pairs, bound, flags, dt, d, ring=ring) == (512 if bound >= least else 256), bound
+        assert threads(L, pairs, bound, flags, dt, d, stated=False, ring=ring, cap=bound) == (512 if bound >= 1024 else 256), bound
+
+
+def test_threads_of_the_8_bit_cache_go_with_pairs_and_bound(L):
+    import torch
+    for stated in (False, True):
+        for pairs in (4, 128, 1023, 1024, 4096):
+            for bound in (64, 300, 1023, 1024, 7168):
+                got = threads(L, pairs, bound, UNORDERED | 8, torch.float16, 128, stated=stated, cap=bound)
+                assert got == (128 if pairs >= 1024 and bound < 1024 else 256), (stated, pairs, bound)
