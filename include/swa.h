@@ -231,6 +231,11 @@ int swa_prefill_scores(const swa_params *params, const void *q_tail, int32_t R,
  *   probs_dbg [b,h,cap] float32 or NULL: receives p (0 beyond m) when given.
  * A sequence with cache_len[s] + 1 > cap is skipped (nothing written for it)
  * and the capacity status bit is set.
+ * With 16- and 32-bit caches a pair's weights, importance, kept set and cache are the same bits whatever other pairs
+ * the call has (len_bound being the same: the order of the softmax sum goes with it).  Its output need not be: kernel and
+ * workgroup are chosen from the number of pairs as well, the output's fp32 terms are then added in another order, and the
+ * rounded result may differ in its last bit.  With the 8-bit cache the weights may, too.  (swa_prefill_attention's output
+ * does not depend on the batch.)
  */
 int swa_decode_step(const swa_params *params, const void *q, const void *k_new, const void *v_new,
                     void *k_cache, void *v_cache, float *score, int32_t *pos, int32_t *cache_len,

@@ -426,8 +426,8 @@ swa_decode_kernel(DecodeArgs a)
             s_p[i] = e;
             sum += e;
         }
-        // (the order of the additions goes with the length, not with the workgroup that few pairs are given: weights, and with them
-        // the selection, do not depend on the batch)
+        // (the order of the additions goes with the bound on the length, not with the workgroup that few pairs are given: weights, and with them
+        // the selection, do not depend on the batch; the output's sum, by row group and wave, does)
         const int ST = NT > kNarrow ? a.sum_threads : NT;
         if (ST < NT) {
             __syncthreads();

@@ -71,3 +71,48 @@ def test_stated_bound_changes_the_workgroup_and_not_the_step(form, dtype, d, bou
         dense = (two["probs"][i, :, :n + 1].double()[:, None] @ rows.abs())[:, 0]
         # (a few evicted rows are subtracted from the dense sum, whose magnitude then counts, over a kept mass of at least 1/20)
         assert bool(((two["out"][i].double() - want).abs() <= u * want.abs() + 2.0 ** -20 * (mag + 20 * dense)).all()), (n, k)
+
+
+@pytest.mark.parametrize("dtype,d,bound,few,many,form", [
+    (F16, 128, 500, 126, 129, "unordered"), (F32, 128, 300, 126, 129, "two_call"), (BF16, 64, 1023, 126, 129, "window"), (F16, 128, 300, 96, 99, "unordered"),
+    (F16, 128, 3000, 255, 258, "ordered"), (F16, 128, 250, 510, 513, "unordered"), (F32, 64, 250, 510, 513, "two_call")])
+def test_other_pairs_change_an_output_in_its_last_bits_only(dtype, d, bound, few, many, form):
+    """The same pairs in a call of their own, which gets another workgroup or kernel, and in one with three pairs more."""
+    from paper_2403_17312_amd import binding as B
+    h, cap, R = 3, bound, 8
+    b = many // h
+    g = torch.Generator(device="cuda").manual_seed(43)
+    flags = {"unordered": B.SWA_FUSE_COMPACTION | B.SWA_UNORDERED, "ordered": B.SWA_FUSE_COMPACTION, "two_call": 0,
+             "window": B.SWA_FUSE_COMPACTION | B.SWA_UNORDERED}[form]
+    K0, V0 = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
+    q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(3))
+    s0 = torch.rand((b, h, cap), generator=g, device="cuda")
+    r0 = torch.rand((b, h, R, cap), generator=g, device="cuda")
+    len0 = (bound - 1 - 7 * torch.arange(b, device="cuda") % (bound // 2)).to(torch.int32)
+    got, threads = [], []
+    for n in (few // h, b):
+        p = B.make_params(n, h, d, cap, 16, 8000, dtype, len_bound=bound, flags=flags)
+        threads.append(threads_of(B, p, form == "window"))
+        ws = torch.zeros(B.swa_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        B.swa_workspace_init(p, ws)
+        x = {"K": K0[:n].clone(), "V": V0[:n].clone(), "score": s0[:n].clone(), "ring": r0[:n].clone(), "cl": len0[:n].clone(),
+             "kc": torch.zeros_like(len0[:n]), "pos": torch.arange(cap, dtype=torch.int32, device="cuda").repeat(n, h, 1).contiguous(),
+             "probs": torch.zeros((n, h, cap), device="cuda"), "kept": torch.zeros((n, h, cap), dtype=torch.int32, device="cuda"),
+             "out": torch.zeros((n, h, d), device="cuda", dtype=dtype)}
+        seq, rows = (len0 + 1)[:n].contiguous(), (q[:n].contiguous(), kn[:n].contiguous(), vn[:n].contiguous())
+        if form == "window":
+            B.swa_decode_step_window(p, *rows, x["K"], x["V"], x["ring"], R, 3, x["score"], x["pos"], x["cl"], seq, x["kept"], x["kc"],
+                                     x["out"], x["probs"], ws)
+        else:
+            B.swa_decode_step(p, *rows, x["K"], x["V"], x["score"], x["pos"], x["cl"], seq, x["kept"], x["kc"], x["out"], x["probs"], ws)
+        assert B.swa_check_status(p, ws) == B.SWA_OK
+        got.append(x)
+    assert bound == 250 or threads[0] != threads[1]
+    one, two = got
+    n = few // h
+    for a in ("cl", "kc", "probs", "score", "pos", "K", "V", "ring"):
+        assert torch.equal(one[a], two[a][:n]), a
+    # values of N(0,1) weighted by at most 1: the same fp32 terms in another order (2^-18 of their magnitude), rounded once to the output type
+    u = {F32: 2.0 ** -18, F16: 2.0 ** -10, BF16: 2.0 ** -7}[dtype]
+    x, y = one["out"].double(), two["out"][:n].double()
+    assert bool(((x - y).abs() <= u * (y.abs() + 1.0)).all())
