@@ -81,6 +81,7 @@ bool seed_chains_apart(int G, int cols, int cap, int R);
 // (1 = the one-workgroup kernel serves the call), and the launches of the step.
 constexpr int kMaxSplit = 16;
 int split_factor(int64_t pairs, int len_bound, bool stated, int row_bytes);
+int split_piece_bytes(int64_t pairs);
 int launch_split(const swa_params& p, float scale, int G, const void* q, const void* k_new, const void* v_new, void* k_cache,
                  void* v_cache, float* score, int32_t* pos, int32_t* cache_len, const int32_t* seq_len, int32_t* kept_idx,
                  int32_t* kept_cnt, void* out, float* probs_dbg, void* workspace, hipStream_t stream);

@@ -44,7 +44,6 @@ struct SplitArgs {
 
 constexpr int kSelThreads = 1024;    // launch 2: a whole CU's worth of one pair
 constexpr int kGatherThreads = 1024;
-constexpr int kNarrowPairs = 64;     // up to so many pairs launch 3 takes 64 bytes of a row per workgroup, else 128
 constexpr int kXcds = 8;             // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
 constexpr int kSelPer = SWA_MAX_CAP / kSelThreads;   // slots per thread of launch 2 at most
 
@@ -478,6 +477,9 @@ static int launch_select(const SplitArgs& a, int64_t pairs, hipStream_t stream)
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
+// Bytes of a row per workgroup of launch 3 (both sides of the line measured above).
+int split_piece_bytes(int64_t pairs) { return pairs <= 64 ? 64 : 128; }
+
 template <typename T, int D>
 static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
 {
@@ -487,7 +489,7 @@ static int launch_split_t(const SplitArgs& a, int64_t pairs, hipStream_t stream)
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     if (launch_select(a, pairs, stream) != SWA_OK) return SWA_ERR_HIP;
     const int64_t at_most = (pairs + kXcds - 1) / kXcds * kXcds * D * Elem<T>::kBytes;      // bytes of all rows
-    if (pairs <= kNarrowPairs)
+    if (split_piece_bytes(pairs) == 64)
         launch_kernel((swa_split_gather_kernel<T, D, 64>), dim3((unsigned)(at_most / 64)), dim3(kGatherThreads), 0, stream, a);
     else
         launch_kernel((swa_split_gather_kernel<T, D, 128>), dim3((unsigned)(at_most / 128)), dim3(kGatherThreads), 0, stream, a);

@@ -1,5 +1,7 @@
 """The split-rows step's own selection launch: kept sets and importance against the one-workgroup kernel bit for bit,
 with many equal keys, budgets at the edges, lengths around the threads' runs, and both forms of the output pass."""
+import ctypes
+
 import pytest
 import torch
 
@@ -55,9 +57,22 @@ def test_selection_matches_the_one_workgroup_kernel(dtype, d, cap, w, sparsity, 
 def test_output_whatever_is_kept(dtype, d, w, sparsity, ahead):
     """A cache of a much longer sequence (nearly everything is kept), a wide window, and budgets of a few rows: the launch
     that forms the output, with a number of pairs that is no multiple of the XCDs."""
+    check_output(dtype, d, 5, [2499, 2049], 2500, w, sparsity, ahead)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float16, 64), (torch.float16, 128), (torch.float32, 128)])      # one, two and four pieces a row
+@pytest.mark.parametrize("b,h", [(5, 13), (3, 41), (2, 64)])
+@pytest.mark.parametrize("w,sparsity,ahead", [(64, 8000, 1), (64, 8000, 5), (0, 9999, 1)])
+def test_output_of_more_than_64_pairs(dtype, d, b, h, w, sparsity, ahead):
+    """The launch that forms the output, in pieces of 128 bytes."""
+    check_output(dtype, d, h, [2199, 2049, 2198, 900, 2100][:b], 2200, w, sparsity, ahead)
+
+
+def check_output(dtype, d, h, lens, cap, w, sparsity, ahead):
     from paper_2403_17312_amd import binding as B
-    b, h, cap = 2, 5, 2500
-    lens = [2499, 2049]
+    b = len(lens)
+    pieces = B.lib()._ZN3swa17split_piece_bytesEl
+    assert pieces(ctypes.c_int64(b * h)) == (64 if b * h <= 64 else 128)
     g = torch.Generator(device="cuda").manual_seed(13)
     K, V = (torch.randn((b, h, cap, d), generator=g, device="cuda").to(dtype) for _ in range(2))
     q, kn, vn = (torch.randn((b, h, d), generator=g, device="cuda").to(dtype) for _ in range(3))
@@ -133,8 +148,6 @@ def test_importance_of_any_value(special, w, sparsity):
 def test_caches_below_2048_slots(dtype, d, b, h, cap, w, sparsity):
     """Few pairs with wide rows are split from 1024 or 1536 slots on, under a stated bound: weights, importance and kept set of the one-workgroup
     kernel."""
-    import ctypes
-
     from paper_2403_17312_amd import binding as B
     rule = B.lib()._ZN3swa12split_factorElibi
     assert rule(ctypes.c_int64(b * h), cap, ctypes.c_bool(True), d * (4 if dtype == torch.float32 else 2)) > 1

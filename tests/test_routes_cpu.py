@@ -69,6 +69,7 @@ def test_split_rows_where_three_launches_pay(L, pairs, least):
             assert rule(ctypes.c_int64(pairs), line - 1, ctypes.c_bool(stated), row) == 1, (row, stated)
             assert rule(ctypes.c_int64(pairs), line, ctypes.c_bool(stated), row) > 1, (row, stated)
     assert rule(ctypes.c_int64(129), 16384, ctypes.c_bool(True), 512) == 1
+    assert L._ZN3swa17split_piece_bytesEl(ctypes.c_int64(pairs)) == (64 if pairs <= 64 else 128)
 
 
 UNORDERED, ORDERED, SHARED, TWO_CALL = 1 | 2, 1, 1 | 2 | 4, 0
