@@ -188,8 +188,8 @@ __global__ void swa_fill_zero_kernel(int32_t* p, int64_t n)
 int launch_workspace_init(const swa_params& p, void* workspace, hipStream_t stream)
 {
     const int64_t n = (int64_t)(shared_workspace_offset(p) / 4);   // status word and arrival counters
-    hipLaunchKernelGGL(swa_fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                       static_cast<int32_t*>(workspace), n);
+    launch_kernel(swa_fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
+                  static_cast<int32_t*>(workspace), n);
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 
@@ -320,8 +320,7 @@ int swa_check_status(const swa_params* params, void* workspace, void* stream, in
     if (hipMemcpyAsync(&bits, ws, sizeof(bits), hipMemcpyDeviceToHost, st) != hipSuccess) return SWA_ERR_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) return SWA_ERR_HIP;
     if (bits != 0) {
-        hipLaunchKernelGGL(swa::swa_fill_zero_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<int32_t*>(ws),
-                           (int64_t)1);
+        swa::launch_kernel(swa::swa_fill_zero_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<int32_t*>(ws), 1);
         if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     }
     *status_out = (bits & swa::kStatusCapacityBit)     ? SWA_ERR_CAPACITY
@@ -378,10 +377,9 @@ static int decode_common(const swa_params* params, const void* q, const void* k_
         return SWA_ERR_ALIGNMENT;
     if (zero_arrival_counters) {
         // A fill kernel, not a memset node: callers may capture this call into a graph.
-        hipLaunchKernelGGL(swa::swa_fill_zero_kernel, dim3((unsigned)((params->b + 255) / 256)), dim3(256), 0,
+        swa::launch_kernel(swa::swa_fill_zero_kernel, dim3((unsigned)((params->b + 255) / 256)), dim3(256), 0,
                            static_cast<hipStream_t>(stream),
-                           reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + swa::kWsArriveOffset),
-                           (int64_t)params->b);
+                           reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + swa::kWsArriveOffset), params->b);
         if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     }
     return swa::launch_decode(*params, swa::effective_scale(params), q, k_new, v_new, k_cache, v_cache, score,
@@ -540,9 +538,8 @@ int swa_probe_stream_read(const void* src, size_t bytes, void* sink, void* strea
     const size_t piece = 104 * 1024;                    // bytes per workgroup
     const size_t blocks = bytes / piece;
     if (blocks == 0 || blocks > 0x7fffffffULL) return SWA_ERR_BAD_SHAPE;
-    hipLaunchKernelGGL(swa::swa_stream_read_kernel, dim3((unsigned)blocks), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), static_cast<const swa::Vec16*>(src), piece / 16,
-                       static_cast<uint32_t*>(sink));
+    swa::launch_kernel(swa::swa_stream_read_kernel, dim3((unsigned)blocks), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), static_cast<const swa::Vec16*>(src), piece / 16, static_cast<uint32_t*>(sink));
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
 }
 

@@ -1336,9 +1336,8 @@ int launch_decode(const swa_params& p, float scale, const void* q, const void* k
         a.phase = 2;
         return launch_short_shared(a, p, pairs, form, stream);
     }
-    hipLaunchKernelGGL(swa_headsum_kernel, dim3((unsigned)((bound + kHeadSumThreads - 1) / kHeadSumThreads), (unsigned)p.b),
-                       dim3(kHeadSumThreads), 0, stream,
-                       a.ws_snew, a.cache_len, a.ws_tot, (int)p.h, (int)p.cap);
+    launch_kernel(swa_headsum_kernel, dim3((unsigned)((bound + kHeadSumThreads - 1) / kHeadSumThreads), (unsigned)p.b),
+                  dim3(kHeadSumThreads), 0, stream, a.ws_snew, a.cache_len, a.ws_tot, p.h, p.cap);
     if (hipGetLastError() != hipSuccess) return SWA_ERR_HIP;
     a.phase = 2;
     return form.nt ? launch_short_shared(a, p, pairs, form, stream) : launch(a);

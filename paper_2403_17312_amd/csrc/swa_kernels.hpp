@@ -9,12 +9,14 @@
 
 namespace swa {
 
-// One launch.  The error, if any, is the runtime's last one, as behind <<<>>>, whose compiled form puts the launch's shape on a stack of
-// the runtime's and takes it off again: 2.45 us of host time to issue a launch that way, 2.23 this way.
-template <typename A>
-inline void launch_kernel(void (*kernel)(A), dim3 grid, dim3 block, size_t lds, hipStream_t stream, const A& args)
+// One launch; every launch of the library goes this way.  The error, if any, is the runtime's last one, as behind <<<>>>, whose compiled
+// form puts the launch's shape on a stack of the runtime's and takes it off again: 2.45 us of host time to issue a launch that way, 2.23 this way.
+template <typename T>
+struct Given { typedef T type; };      // (the kernel's parameters say the types, the arguments are converted to them)
+template <typename... A>
+inline void launch_kernel(void (*kernel)(A...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, const typename Given<A>::type&... args)
 {
-    void* arg[] = {const_cast<A*>(&args)};
+    void* arg[] = {const_cast<void*>(static_cast<const void*>(&args))...};
     (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, arg, lds, stream);
 }
 

@@ -262,10 +262,10 @@ int launch_offload(const swa_params& p, const void* k_cache, const void* v_cache
     constexpr int NT = 256;
     const dim3 grid((unsigned)pairs), block(NT);
     switch (rowb) {
-        case 64: hipLaunchKernelGGL((swa_offload_kernel<64, NT>), grid, block, lds, stream, a); break;
-        case 128: hipLaunchKernelGGL((swa_offload_kernel<128, NT>), grid, block, lds, stream, a); break;
-        case 256: hipLaunchKernelGGL((swa_offload_kernel<256, NT>), grid, block, lds, stream, a); break;
-        case 512: hipLaunchKernelGGL((swa_offload_kernel<512, NT>), grid, block, lds, stream, a); break;
+        case 64: launch_kernel((swa_offload_kernel<64, NT>), grid, block, lds, stream, a); break;
+        case 128: launch_kernel((swa_offload_kernel<128, NT>), grid, block, lds, stream, a); break;
+        case 256: launch_kernel((swa_offload_kernel<256, NT>), grid, block, lds, stream, a); break;
+        case 512: launch_kernel((swa_offload_kernel<512, NT>), grid, block, lds, stream, a); break;
         default: return SWA_ERR_UNSUPPORTED_D;
     }
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;
@@ -299,10 +299,10 @@ int launch_reload(const swa_params& p, const swa_host_store& st, const int32_t* 
     constexpr int NT = 256;
     const dim3 grid((unsigned)pairs), block(NT);
     switch (rowb) {
-        case 64: hipLaunchKernelGGL((swa_reload_kernel<64, NT>), grid, block, 0, stream, a); break;
-        case 128: hipLaunchKernelGGL((swa_reload_kernel<128, NT>), grid, block, 0, stream, a); break;
-        case 256: hipLaunchKernelGGL((swa_reload_kernel<256, NT>), grid, block, 0, stream, a); break;
-        case 512: hipLaunchKernelGGL((swa_reload_kernel<512, NT>), grid, block, 0, stream, a); break;
+        case 64: launch_kernel((swa_reload_kernel<64, NT>), grid, block, 0, stream, a); break;
+        case 128: launch_kernel((swa_reload_kernel<128, NT>), grid, block, 0, stream, a); break;
+        case 256: launch_kernel((swa_reload_kernel<256, NT>), grid, block, 0, stream, a); break;
+        case 512: launch_kernel((swa_reload_kernel<512, NT>), grid, block, 0, stream, a); break;
         default: return SWA_ERR_UNSUPPORTED_D;
     }
     return hipGetLastError() == hipSuccess ? SWA_OK : SWA_ERR_HIP;

@@ -28,3 +28,10 @@ def test_a_wave_barrier_stands_between_fences():
             assert re.search(r'__builtin_amdgcn_fence\(__ATOMIC_RELEASE, "wavefront"[^;]*;\s*$', text[:m.start()]), os.path.basename(path)
             assert re.match(r'\s*__builtin_amdgcn_fence\(__ATOMIC_ACQUIRE, "wavefront"', text[m.end():]), os.path.basename(path)
     assert seen
+
+
+def test_kernels_are_launched_in_one_way():
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2403_17312_amd", "csrc", "*.h*"))):
+        text = re.sub(r"//[^\n]*", "", open(path).read())
+        assert "<<<" not in text and "hipLaunchKernelGGL" not in text, os.path.basename(path)
+        assert ("hipLaunchKernel(" in text) == path.endswith("swa_kernels.hpp"), os.path.basename(path)
