@@ -34,7 +34,7 @@ def code_objects(lib):
 
 @pytest.fixture(scope="module")
 def kernels():
-    """Mangled name -> (bytes of code, bytes of scratch per lane)."""
+    """Mangled name -> (bytes of code, bytes of scratch per lane, bytes of LDS beside what a launch asks for)."""
     from paper_2403_17312_amd import binding, build
     if not os.path.exists(binding.LIB_PATH):
         build.build()
@@ -49,17 +49,17 @@ def kernels():
         for kind, link, data in secs:
             if kind != 2:                                 # the symbol table
                 continue
-            code, scratch = {}, {}
+            code, fixed = {}, {}
             for o in range(0, len(data), 24):
                 name, info, _, sec, value, size = struct.unpack_from("<IBBHQQ", data, o)
                 text = secs[link][2]
                 sym = text[name:text.index(b"\0", name)].decode()
-                if sym.endswith(".kd"):                   # kernel descriptor: its second word is the scratch
+                if sym.endswith(".kd"):                   # kernel descriptor: LDS and scratch are its first words
                     _, _, _, addr, off, _ = headers[sec]
-                    scratch[sym[:-3]] = struct.unpack_from("<I", elf, off + value - addr + 4)[0]
+                    fixed[sym[:-3]] = struct.unpack_from("<II", elf, off + value - addr)
                 elif info & 15 == 2:
                     code[sym] = size
-            got.update({k: (code[k], scratch[k]) for k in scratch})
+            got.update({k: (code[k], fixed[k][1], fixed[k][0]) for k in fixed})
     return got
 
 
@@ -82,3 +82,11 @@ def test_fp32_column_sums_of_many_rows_spill_no_more(kernels):
     assert kernels[seed_sums("F32", 128, 4, False)][1] <= 376
     for tiles in (1, 2, 3):
         assert kernels[seed_sums("F32", 128, tiles, False)][1] == 0, tiles
+
+
+def test_1024_threads_leave_room_for_the_longest_caches(kernels):
+    """The rule that gives long caches 1024 threads counts 14 KiB of the kernel's own LDS beside 20 bytes a slot of 7168."""
+    seen = [k for k in kernels if k.startswith("_ZN3swa17swa_decode_kernelI") and "ELi1024ELb0E" in k]
+    assert len(seen) == 6
+    for k in seen:
+        assert kernels[k][2] <= 14 * 1024, k
